@@ -167,6 +167,9 @@ sqap_status launch_decode_attention(const __half *QKV, const int32_t *pos, int H
                                     unsigned int *counter, hipStream_t st);
 sqap_status launch_attention(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V,
                              int64_t ldv, int batch, int Sq, int Sk, int H, int d, __half *O, int64_t ldo, hipStream_t st);
+// head sizes 64 and 128 (attention.hip)
+sqap_status launch_attention_tiles(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
+                                   int batch, int Sq, int Sk, int H, int d, __half *O, int64_t ldo, hipStream_t st);
 sqap_status launch_residual_add(__half *X, int64_t ldx, const __half *Dl, int64_t ldd, int M, int K, hipStream_t st);
 sqap_status launch_quotient_selftest(unsigned long long *mismatches, hipStream_t st);
 // Checks once per device how a launch's workgroups are dealt to the XCDs (see gemm.hip); table_out

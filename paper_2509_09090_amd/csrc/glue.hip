@@ -2,9 +2,8 @@
 // causal softmax attention over a short prefix, residual add.  (RMSNorm and the SwiGLU gate are
 // fused into the activation quantizer, quantize.hip.)  The paper does not restate the decoder;
 // these follow the published architecture (Su et al. 2021 in the half-split pairing used by
-// Llama; Vaswani et al. 2017).  Sequences here are a few hundred tokens (276 before pruning, 148
-// after), so attention is a small fraction of a layer and is written for low latency, not for
-// matrix-core throughput: binary32 FMAs over LDS tiles with an online softmax.
+// Llama; Vaswani et al. 2017).  Attention of head sizes 64 and 128 runs on the matrix cores (attention.hip); the small
+// head sizes take binary32 FMAs over LDS tiles with an online softmax, here.
 #include "common.h"
 #include "quant_math.h"
 #include "decode_attn.h"
@@ -253,221 +252,11 @@ __global__ __launch_bounds__(256) void attention_kernel(const __half *__restrict
     }
 }
 
-// The same attention on the matrix cores, for head sizes 64 and 128: one workgroup of four wavefronts per
-// (head, block of 32 queries, sequence), key tiles of 32.  Everything is kept transposed so that no
-// accumulator ever has to change lanes:
-//   S^T = K Q^T      v_mfma_f32_32x32x8_f16 with A = key rows, B = query rows: lane l holds query l%32,
-//                    register i key 8(i/4) + 4(l/32) + i%4 of the tile;
-//   softmax          over registers and the two lane halves (one cross-lane exchange);
-//   O^T += V^T P^T   registers 4b .. 4b+3 of exp(S^T - m), converted to half, ARE the B operand of key
-//                    block b (keys 8b + 4(l/32) + 0..3); A = V^T is read column-wise (2 bytes at a time)
-//                    from the value tile in LDS.
-// The running maximum, the running sum and the rescaling of O^T are per query, i.e. per lane.  The four
-// wavefronts take the key tiles in turn (tile t belongs to wavefront t % 4), so a sequence of up to 128
-// keys costs one round of loads, and merge their partial (m, l, O^T) through LDS at the end: wavefront w
-// collects column tile w of the output from the other three.  The reduction over the head dimension may
-// visit it in any order as long as A and B agree: MFMA j takes elements 16(j/2) + 8(l/32) + 4(j%2) + 0..3,
-// so that each lane fetches 16 contiguous bytes per pair of MFMAs.
-typedef _Float16 v4h __attribute__((ext_vector_type(4)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-
-constexpr int kAttWaves = 4;
-
-template <int D>
-__global__ __launch_bounds__(64 * kAttWaves) void attention_mfma_kernel(const __half *__restrict__ Q, int64_t ldq,
-                                                            const __half *__restrict__ Kc, int64_t ldk,
-                                                            const __half *__restrict__ V, int64_t ldv, int Sq, int Sk,
-                                                            int H, __half *__restrict__ O, int64_t ldo)
-{
-    constexpr int NP = D / 16;                   // 16-byte pieces of a head row per lane half
-    constexpr int CT = D / 32;                   // 32-column tiles of the head dimension
-    constexpr int VP = D + 8;                    // halves per key row of the value tile in LDS (16-byte aligned, banks staggered)
-    constexpr int NW = kAttWaves;
-    constexpr int VT_BYTES = NW * 32 * VP * 2;
-    constexpr int MERGE_BYTES = CT * NW * 4096 + NW * 64 * 8;      // O^T pieces [ct][wave][16 regs][64 lanes] + (m, l)
-    __shared__ __attribute__((aligned(16))) uint8_t lds[VT_BYTES > MERGE_BYTES ? VT_BYTES : MERGE_BYTES];
-    const int l = threadIdx.x & 63, c = l & 31, h = l >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    __half *vt = reinterpret_cast<__half *>(lds) + wave * (32 * VP);
-    const int head = blockIdx.x, q0 = blockIdx.y * 32;
-    Q += (int64_t)blockIdx.z * Sq * ldq + (int64_t)head * D;
-    O += (int64_t)blockIdx.z * Sq * ldo + (int64_t)head * D;
-    Kc += (int64_t)blockIdx.z * Sk * ldk + (int64_t)head * D;
-    V += (int64_t)blockIdx.z * Sk * ldv + (int64_t)head * D;
-    const int shift = Sk - Sq;
-    const int my_q = q0 + c;
-    const bool q_ok = my_q < Sq;
-    // scores are kept in units of ln 2, so that the exponentials are single v_exp_f32 instructions
-    const float inv_sqrt_d = 1.4426950408889634f / sqrtf((float)D);
-    union Piece { uint4 u; v4h v[2]; };
-
-    Piece qf[NP];
-#pragma unroll
-    for (int m = 0; m < NP; ++m) {
-        qf[m].u = make_uint4(0u, 0u, 0u, 0u);
-        if (q_ok) qf[m].u = *reinterpret_cast<const uint4 *>(Q + (int64_t)my_q * ldq + 16 * m + 8 * h);
-    }
-    v16f ot[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) ot[ct][i] = 0.f;
-    float mrun = -INFINITY, lrun = 0.f;
-    const int last_key = min(Sk - 1, min(q0 + 31, Sq - 1) + shift);
-    const int n_tiles = last_key / 32 + 1;
-
-    Piece kf[NP];
-    auto load_keys = [&](int k0) {
-        const int key = k0 + c;
-#pragma unroll
-        for (int m = 0; m < NP; ++m) {
-            kf[m].u = make_uint4(0u, 0u, 0u, 0u);
-            if (key < Sk) kf[m].u = *reinterpret_cast<const uint4 *>(Kc + (int64_t)key * ldk + 16 * m + 8 * h);
-        }
-    };
-    // keys and values of the next tile are asked for while the current one is worked on: these rows were
-    // just written by another kernel and come from memory, two microseconds away
-    uint4 vraw[D / 16];
-    auto load_values = [&](int k0) {
-#pragma unroll
-        for (int n = 0; n < D / 16; ++n) {
-            const int u = l + 64 * n, key = u / (D / 8), dp = u % (D / 8);
-            vraw[n] = make_uint4(0u, 0u, 0u, 0u);
-            if (k0 + key < Sk) vraw[n] = *reinterpret_cast<const uint4 *>(V + (int64_t)(k0 + key) * ldv + dp * 8);
-        }
-    };
-    if (wave < n_tiles) {
-        load_keys(wave * 32);
-        load_values(wave * 32);
-    }
-    for (int kt = wave; kt < n_tiles; kt += NW) {
-        const int k0 = kt * 32;
-        v16f st;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) st[i] = 0.f;
-#pragma unroll
-        for (int m = 0; m < NP; ++m) {
-            st = __builtin_amdgcn_mfma_f32_32x32x8f16(kf[m].v[0], qf[m].v[0], st, 0, 0, 0);
-            st = __builtin_amdgcn_mfma_f32_32x32x8f16(kf[m].v[1], qf[m].v[1], st, 0, 0, 0);
-        }
-        if (kt + NW < n_tiles) load_keys(k0 + 32 * NW);      // in flight during the softmax and the second product
-        __builtin_amdgcn_wave_barrier();
-        // value tile into LDS as it lies in memory, 16 bytes per lane (the previous tile's readers are this same
-        // wavefront: LDS operations of one wavefront complete in order); the transposition happens on the way
-        // out, below
-#pragma unroll
-        for (int n = 0; n < D / 16; ++n) {
-            const int u = l + 64 * n, key = u / (D / 8), dp = u % (D / 8);
-            *reinterpret_cast<uint4 *>(vt + key * VP + dp * 8) = vraw[n];
-        }
-        if (kt + NW < n_tiles) load_values(k0 + 32 * NW);
-        float tmax = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int key = k0 + 8 * (i >> 2) + 4 * h + (i & 3);
-            const bool seen = q_ok && key < Sk && key <= my_q + shift;
-            st[i] = seen ? st[i] * inv_sqrt_d : -INFINITY;
-            tmax = fmaxf(tmax, st[i]);
-        }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-        const float m_new = fmaxf(mrun, tmax);
-        const float rescale = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mrun - m_new);
-        float tsum = 0.f;
-        v4h pb[4];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float pi = st[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st[i] - m_new);
-            tsum += pi;
-            pb[i >> 2][i & 3] = (_Float16)pi;
-        }
-        tsum += __shfl_xor(tsum, 32);
-        lrun = lrun * rescale + tsum;
-        mrun = m_new;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) ot[ct][i] *= rescale;
-        __builtin_amdgcn_wave_barrier();                     // the value tile is written (same wavefront, in order)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                // A = V^T: this lane's column 32 ct + c of keys 8b + 4h + 0..3: four 2-byte reads, consecutive
-                // lanes on consecutive halves of one key row
-                const _Float16 *col = reinterpret_cast<const _Float16 *>(vt) + (8 * b + 4 * h) * VP + 32 * ct + c;
-                const v4h va = {col[0], col[VP], col[2 * VP], col[3 * VP]};
-                ot[ct] = __builtin_amdgcn_mfma_f32_32x32x8f16(va, pb[b], ot[ct], 0, 0, 0);
-            }
-        __builtin_amdgcn_wave_barrier();
-    }
-    // merge: every wavefront publishes its (m, l) and, for each column tile it does not own, its piece of O^T
-    __syncthreads();                                         // the value tiles are no longer needed
-    float *ml = reinterpret_cast<float *>(lds + CT * NW * 4096);
-    ml[(wave * 64 + l) * 2] = mrun;
-    ml[(wave * 64 + l) * 2 + 1] = lrun;
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-        if (ct != wave) {
-            float *dst = reinterpret_cast<float *>(lds + (ct * NW + wave) * 4096);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) dst[i * 64 + l] = ot[ct][i];
-        }
-    }
-    __syncthreads();
-    if (wave < CT) {
-        float mall = -INFINITY;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) mall = fmaxf(mall, ml[(w * 64 + l) * 2]);
-        float lall = 0.f, f[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const float mw = ml[(w * 64 + l) * 2];
-            f[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - mall);
-            lall += ml[(w * 64 + l) * 2 + 1] * f[w];
-        }
-        v16f acc;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-            if (ct == wave) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[i] = ot[ct][i] * f[ct];         // static indices after unrolling
-            }
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            if (w != wave) {
-                const float *src = reinterpret_cast<const float *>(lds + (wave * NW + w) * 4096);
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[i] = fmaf(src[i * 64 + l], f[w], acc[i]);
-            }
-        }
-        if (q_ok) {
-            const float inv_l = 1.0f / lall;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                union { uint2 u; __half2 p[2]; } out;
-                out.p[0] = __floats2half2_rn(acc[4 * g] * inv_l, acc[4 * g + 1] * inv_l);
-                out.p[1] = __floats2half2_rn(acc[4 * g + 2] * inv_l, acc[4 * g + 3] * inv_l);
-                *reinterpret_cast<uint2 *>(O + (int64_t)my_q * ldo + 32 * wave + 8 * g + 4 * h) = out.u;
-            }
-        }
-    }
-}
-
 sqap_status launch_attention(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V,
                              int64_t ldv, int batch, int Sq, int Sk, int H, int d, __half *O, int64_t ldo, hipStream_t st)
 {
     if (Sq == 0 || batch == 0) return SQAP_OK;
-    if (d == 64 || d == 128) {
-        const dim3 wgrid(H, (Sq + 31) / 32, batch);
-        if (d == 64)
-            hipLaunchKernelGGL(attention_mfma_kernel<64>, wgrid, dim3(64 * kAttWaves), 0, st, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, H, O, ldo);
-        else
-            hipLaunchKernelGGL(attention_mfma_kernel<128>, wgrid, dim3(64 * kAttWaves), 0, st, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, H, O, ldo);
-        SQAP_HIP_CHECK(hipGetLastError());
-        return SQAP_OK;
-    }
+    if (d == 64 || d == 128) return launch_attention_tiles(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, d, O, ldo, st);
     const dim3 grid(H, (Sq + kAttQ - 1) / kAttQ, batch);
 #define SQAP_ATT_CASE(DD)                                                                                          \
     case DD:                                                                                                       \

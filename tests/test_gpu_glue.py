@@ -212,6 +212,31 @@ def test_attention(G, oracle, Sq, Sk, H, d):
     assert G.assert_fp16_close(O.cpu().numpy(), want) >= 0
 
 
+@pytest.mark.parametrize("batch,Sq,Sk,H,d", [(1, 1, 1, 1, 128), (2, 31, 31, 2, 64), (1, 32, 64, 2, 128), (1, 33, 65, 3, 128), (1, 65, 129, 2, 64),
+                                             (1, 20, 191, 2, 128), (1, 20, 192, 2, 128), (2, 70, 193, 2, 128), (1, 3, 640, 1, 128),
+                                             (1, 130, 257, 1, 128), (3, 129, 321, 32, 128), (9, 64, 200, 32, 128)])
+def test_attention_tile_edges(G, oracle, batch, Sq, Sk, H, d):
+    """Tile and group edges of both forms of the matrix-core kernel (one or two query groups, two or four key groups),
+    against binary64.  Bound: the output's rounding to half (2^-11 of it), and for scores up to 40 in units of ln 2
+    probabilities within 40 * 2^-23 of themselves (score, exponential), so 1e-4 for values up to 6 with room to spare."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    g = torch.Generator().manual_seed(Sq * 7 + Sk + H + d)
+    width = H * d
+    q = (2.0 * torch.randn((batch * Sq, width), generator=g)).half()
+    kv = torch.randn((batch * Sk, 2 * width + 8), generator=g).half()          # a pitch of its own
+    qd, kvd = q.cuda(), kv.cuda()
+    O = torch.full((batch * Sq, width), float("nan"), dtype=torch.float16, device="cuda")
+    B.sqap_attention(qd, kvd[:, :width], kvd[:, width:2 * width], H, d, O, batch=batch)
+    q64 = qd.double().view(batch, Sq, H, d).transpose(1, 2)
+    k64 = kvd[:, :width].double().reshape(batch, Sk, H, d).transpose(1, 2)
+    v64 = kvd[:, width:2 * width].double().reshape(batch, Sk, H, d).transpose(1, 2)
+    seen = torch.ones((Sq, Sk), dtype=torch.bool, device="cuda").tril(Sk - Sq)
+    s = (q64 @ k64.transpose(-1, -2).contiguous()) / d ** 0.5
+    want = (torch.softmax(s.masked_fill(~seen, float("-inf")), -1) @ v64).transpose(1, 2).reshape(batch * Sq, width)
+    assert torch.all((O.double() - want).abs() <= 2.0 ** -11 * want.abs() + 1e-4)
+
+
 def test_attention_batch(G, oracle):
     """Sequences stacked as row blocks: each gets what a single call gives."""
     import torch
