@@ -745,11 +745,7 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
                 channel_pair(2 * jo, g2);
                 channel_pair(2 * jo + 1, u2);
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const double gd = (double)g2[e];
-                    const float sl = (float)(gd / (1.0 + exp(-gd)));
-                    y[e] = to_half_value(sl * u2[e]);
-                }
+                for (int e = 0; e < 2; ++e) y[e] = to_half_value(silu_of(g2[e]) * u2[e]);
                 if (n < (P.N >> 1)) store_tagged_pair(a.h + mine, n, y[0], y[1], tag_of(P.layer, kTagH));
             }
         }

@@ -14,6 +14,10 @@ namespace sqap {
 // significand is all ones, which a half-precision scale widened to binary32 never is).
 // Three instructions instead of the ~15 of a full IEEE division per element; every
 // half / half pair is compared against the division operator by sqap_selftest_quotient.
+// It holds for any binary32 v over a half scale: q0 is within two ulps, so the remainder is exact and the corrected sum
+// is off by less than 2^-22 ulp before its one rounding; v / s is never that close to a midpoint of binary32: it is not
+// one (25 odd bits times s would not fit v's 24), and v minus the midpoint times s is a whole number of units, which
+// leaves at least 2^-12 ulp.  (Quotients so small that the remainder underflows are code 0 either way.)
 __device__ __forceinline__ float quotient(float v, float s, float r)
 {
     const float q0 = v * r;
@@ -89,6 +93,33 @@ __device__ __forceinline__ void add_squares8(const float (&v)[8], unsigned long 
         lo += add_lo;
         hi += add_hi + (lo < add_lo ? 1ull : 0ull);
     }
+}
+
+// silu(g) = (float)(g / (1 + exp(-g))) as the definition evaluates it in binary64, for a half value g: the same binary32
+// bits for every one of the 65536 halves (infinities and NaN among them).  exp(-g) = 2^k 2^f, |f| <= 1/2, with
+// 2^f = 1 + f q(f) (q interpolated at Chebyshev nodes), which is exact where |g| is tiny and g / 2 + g^2 / 4 may end on
+// a binary32 tie; the power of two enters the sum 1 + exp(-g) as a factor; the reciprocal by Newton's step.  Some 25
+// instructions where the library's exponential and division took about 70.
+// The power's exponent stops at 2^1000, so a large negative g ends at -0; g = -inf makes f infinite and the result NaN,
+// as -inf / inf is; g = +inf is held at 700 in the exponent only.
+__device__ __forceinline__ float silu_of(float g)
+{
+    const float x = fmaxf(-g, -700.f);
+    const float k = rintf(x * 1.442695040888963f);
+    const double f = fma((double)x, 1.4426950408889634, -(double)k);
+    double q = 0x1.63b2d79741c48p-20;
+    q = fma(q, f, 0x1.00c0e4e154772p-16);
+    q = fma(q, f, 0x1.4308c7183d394p-13);
+    q = fma(q, f, 0x1.5d8775983509fp-10);
+    q = fma(q, f, 0x1.3b2ab70ad2568p-7);
+    q = fma(q, f, 0x1.c6b08da70cce3p-5);
+    q = fma(q, f, 0x1.ebfbdff82a734p-3);
+    q = fma(q, f, 0x1.62e42fef9cc69p-1);
+    const int e = min((int)k, 1000);
+    const double d = fma(fma(q, f, 1.0), __hiloint2double((e + 1023) << 20, 0), 1.0);
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(r, fma(-d, r, 1.0), r);
+    return (float)((double)g * r);
 }
 
 // S / K in binary64.  For a power of two the quotient is S with a smaller exponent (S is zero or at least 2^-48,

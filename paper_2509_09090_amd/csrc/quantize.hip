@@ -15,31 +15,42 @@ namespace sqap {
 //                into a weight), then quantized per row
 enum QuantMode { kPerRow = 0, kChannelwise = 1, kFolded = 2 };
 
-// Reads one row into registers: thread t owns groups t, t+256, ... of 8 consecutive elements.
-template <int GPT>
+// Reads one row into registers: thread t owns groups t, t+T, ... of 8 consecutive elements.
+template <int T, int GPT>
 __device__ __forceinline__ void load_halves(const uint4 *xrow, int K, float (&v)[GPT][8])
 {
     const int t = threadIdx.x;
     const int groups = K >> 3;
+    typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+    v4u raw[GPT];
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
-        const int g = t + gi * 256;
-        if (g < groups) {
-            typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-            union { v4u v; uint4 u; } ld;
-            ld.v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(xrow) + g);   // a row is read once
-            uint4 raw = ld.u;
-            const __half2 *h2 = reinterpret_cast<const __half2 *>(&raw);
+        const int g = t + gi * T;
+        raw[gi] = v4u{0u, 0u, 0u, 0u};
+        if (g < groups) raw[gi] = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(xrow) + g);   // a row is read once
+    }
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                float2 f = __half22float2(h2[p]);
-                v[gi][2 * p] = f.x;
-                v[gi][2 * p + 1] = f.y;
-            }
-        } else {
+    for (int gi = 0; gi < GPT; ++gi) {
+        const __half2 *h2 = reinterpret_cast<const __half2 *>(&raw[gi]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[gi][e] = 0.f;
+        for (int p = 0; p < 4; ++p) {
+            const float2 f = __half22float2(h2[p]);
+            v[gi][2 * p] = f.x;
+            v[gi][2 * p + 1] = f.y;
         }
+    }
+}
+
+// The same groups as they lie in memory (zeros past the end).
+template <int T, int GPT>
+__device__ __forceinline__ void load_raw(const uint4 *from, int K, uint4 (&raw)[GPT])
+{
+    const int groups = K >> 3;
+#pragma unroll
+    for (int gi = 0; gi < GPT; ++gi) {
+        const int g = threadIdx.x + gi * T;
+        raw[gi] = make_uint4(0u, 0u, 0u, 0u);
+        if (g < groups) raw[gi] = from[g];
     }
 }
 
@@ -54,10 +65,10 @@ __device__ __forceinline__ void load_halves(const uint4 *xrow, int K, float (&v)
 __device__ __forceinline__ int rot_at(int i) { return i + ((i >> 6) << 3); }
 constexpr size_t rot_lds_bytes(int K) { return ((size_t)K + (size_t)K / 8) * sizeof(float); }
 
-template <int W>
+template <int T, int W>
 __device__ __forceinline__ void rotate_pass(float *rot, int K, int s)
 {
-    for (int o = threadIdx.x; o < K / W; o += 256) {
+    for (int o = threadIdx.x; o < K / W; o += T) {
         const int base = (o / s) * (W * s) + (o % s);
         float x[W];
 #pragma unroll
@@ -78,7 +89,7 @@ __device__ __forceinline__ void rotate_pass(float *rot, int K, int s)
     }
 }
 
-template <int GPT>
+template <int T, int GPT>
 __device__ __forceinline__ void rotate_row(int K, float (&v)[GPT][8], float *rot)
 {
     const int t = threadIdx.x;
@@ -96,7 +107,7 @@ __device__ __forceinline__ void rotate_row(int K, float (&v)[GPT][8], float *rot
                 }
             }
         }
-        const int g = t + gi * 256;
+        const int g = t + gi * T;
         if (g < groups) {                      // a group of 8 never straddles a padded block of 64
             float4 *dst = reinterpret_cast<float4 *>(rot + rot_at(g * 8));
             dst[0] = make_float4(v[gi][0], v[gi][1], v[gi][2], v[gi][3]);
@@ -108,15 +119,15 @@ __device__ __forceinline__ void rotate_row(int K, float (&v)[GPT][8], float *rot
     // aligned run of B channels, B the largest power of two dividing K (the stages simply stop at B/2)
     const int B = K & -K;
     for (int s = 8; s < B; s <<= 3) {
-        if (s * 8 <= B) rotate_pass<8>(rot, K, s);
-        else if (s * 4 <= B) rotate_pass<4>(rot, K, s);
-        else rotate_pass<2>(rot, K, s);
+        if (s * 8 <= B) rotate_pass<T, 8>(rot, K, s);
+        else if (s * 4 <= B) rotate_pass<T, 4>(rot, K, s);
+        else rotate_pass<T, 2>(rot, K, s);
         __syncthreads();
     }
     const float c = (float)(1.0 / sqrt((double)B));
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
-        const int g = t + gi * 256;
+        const int g = t + gi * T;
         if (g < groups) {
             const float4 *src = reinterpret_cast<const float4 *>(rot + rot_at(g * 8));
             const float4 lo = src[0], hi = src[1];
@@ -126,11 +137,11 @@ __device__ __forceinline__ void rotate_row(int K, float (&v)[GPT][8], float *rot
     }
 }
 
-template <bool ROTATE, int GPT>
+template <bool ROTATE, int T, int GPT>
 __device__ __forceinline__ void load_row(const uint4 *xrow, int K, float (&v)[GPT][8], float *rot)
 {
-    load_halves<GPT>(xrow, K, v);
-    if (ROTATE) rotate_row<GPT>(K, v, rot);
+    load_halves<T, GPT>(xrow, K, v);
+    if (ROTATE) rotate_row<T, GPT>(K, v, rot);
 }
 
 // ---- operations fused in front of the quantizer (the decoder's glue between two linears) ----
@@ -172,19 +183,19 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8])
 // adds its elements into a 128-bit integer, wavefronts and the block add those.  The sum is
 // rounded to binary64 once (top 64 bits with a sticky last bit, then the hardware's u64 -> f64
 // conversion, which rounds to nearest even).  Rows are assumed finite.
-template <int GPT>
-__device__ __forceinline__ void norm_row(float (&v)[GPT][8], int row, int K, const PreArgs &pre,
-                                         unsigned long long *wsum)
+template <int T, int GPT>
+__device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta)[GPT], const uint4 (&gamma)[GPT], int row,
+                                         int K, const PreArgs &pre, unsigned long long *wsum)
 {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, groups = K >> 3;
     unsigned long long hi = 0, lo = 0;
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
-        const int g = t + gi * 256;
+        const int g = t + gi * T;
         if (g < groups) {
             if (pre.delta) {
                 float d[8];
-                unpack8(reinterpret_cast<const uint4 *>(pre.delta + (size_t)row * K)[g], d);
+                unpack8(delta[gi], d);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[gi][e] = round_to_half(v[gi][e] + d[e]);
             }
@@ -201,7 +212,7 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], int row, int K, con
     hi = wsum[0];
     lo = wsum[1];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
+    for (int w = 1; w < T / 64; ++w) {
         const unsigned long long olo = wsum[2 * w + 1];
         lo += olo;
         hi += wsum[2 * w] + (lo < olo ? 1ull : 0ull);
@@ -220,10 +231,10 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], int row, int K, con
     const float r = (float)(1.0 / sqrt(mean_of(Sd, K) + (double)pre.eps));
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
-        const int g = t + gi * 256;
+        const int g = t + gi * T;
         if (g < groups) {
             float gm[8];
-            unpack8(reinterpret_cast<const uint4 *>(pre.gamma)[g], gm);
+            unpack8(gamma[gi], gm);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float xr = v[gi][e] * r;
@@ -237,23 +248,23 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], int row, int K, con
 // SwiGLU (Shazeer 2020; the feed-forward of a Llama decoder): v holds the gate row g, pre.U the
 // up row;  v = half(silu(g) * u),  silu(g) = (float)(g / (1 + exp(-g))) evaluated in binary64.
 // silu is a function of a half value: a GPU test walks all 2^16 of them against the host's.
+// At 2368 x 11008 the vector ALU bounds this form (17.1 thousand instructions per SIMD, 43 per element, 25 of them silu's):
+// 38.7 us against 49.7 with the library's binary64 exponential and division; 117 MB take 23 us.
 // (A per-device table of the 2^16 results was slower than computing: 13 against 10 us at 84 x 11008,
 // 48 scattered 4-byte loads per thread.)
-template <int GPT>
-__device__ __forceinline__ void swiglu_row(float (&v)[GPT][8], int row, int K, const PreArgs &pre)
+template <int T, int GPT>
+__device__ __forceinline__ void swiglu_row(float (&v)[GPT][8], const uint4 (&up)[GPT], int row, int K, const PreArgs &pre)
 {
     const int t = threadIdx.x, groups = K >> 3;
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
-        const int g = t + gi * 256;
+        const int g = t + gi * T;
         if (g < groups) {
             float u[8];
-            unpack8(reinterpret_cast<const uint4 *>(pre.U + (size_t)row * pre.ldu)[g], u);
+            unpack8(up[gi], u);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const double gd = (double)v[gi][e];
-                const float s = (float)(gd / (1.0 + exp(-gd)));
-                v[gi][e] = round_to_half(s * u[e]);
+                v[gi][e] = round_to_half(silu_of(v[gi][e]) * u[e]);
             }
             if (pre.y_out) reinterpret_cast<uint4 *>(pre.y_out + (size_t)row * K)[g] = pack8(v[gi]);
         }
@@ -278,27 +289,35 @@ __device__ __forceinline__ void load_col_scales(const __half *col_scales, int g,
 //   scale = half(max|v| / 7), 2^-24 if that is zero;  code = clamp(rint(v / scale), -8, 7)
 // GPT = groups per thread the instance is compiled for (registers, hence occupancy).
 // PRE selects an operation applied to the row between its read and the quantizer (see above).
-template <bool ROTATE, int GPT, int MODE, int PRE>
-__global__ __launch_bounds__(256) void quantize_rows_kernel(const __half *X, int64_t ldx,      // may alias pre.xsum_out
+template <bool ROTATE, int T, int GPT, int MODE, int PRE>
+__global__ __launch_bounds__(T) void quantize_rows_kernel(const __half *X, int64_t ldx,      // may alias pre.xsum_out
                                                             const int32_t *__restrict__ rows, int K,
                                                             const __half *__restrict__ col_scales,
                                                             uint8_t *__restrict__ Xq,
                                                             __half *__restrict__ scale_out, const PreArgs pre)
 {
     extern __shared__ __attribute__((aligned(16))) float rot[];       // the padded row when ROTATE
-    __shared__ float wave_max[4];
-    __shared__ unsigned long long wave_sum[8];
+    __shared__ float wave_max[T / 64];
+    __shared__ unsigned long long wave_sum[T / 32];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int row = blockIdx.x;
     const int64_t src = rows ? (int64_t)rows[row] : (int64_t)row;
     const uint4 *xrow = reinterpret_cast<const uint4 *>(X + src * ldx);
     const int groups = K >> 3;
 
+    // everything the row needs is asked for before any of it is worked on (2368 rows: SwiGLU of 11008 38.7 us against 40.0
+    // with the up row fetched group by group, norm of 4096 16.2 against 17.6)
     float v[GPT][8];
-    load_halves<GPT>(xrow, K, v);
-    if (PRE == kPreNorm) norm_row<GPT>(v, row, K, pre, wave_sum);
-    if (PRE == kPreSwiglu) swiglu_row<GPT>(v, row, K, pre);
-    if (ROTATE) rotate_row<GPT>(K, v, rot);
+    uint4 second[GPT], third[GPT];
+    (void)second;
+    (void)third;
+    if (PRE == kPreSwiglu || (PRE == kPreNorm && pre.delta))
+        load_raw<T, GPT>(reinterpret_cast<const uint4 *>(PRE == kPreSwiglu ? pre.U + (int64_t)row * pre.ldu : pre.delta + (int64_t)row * K), K, second);
+    if (PRE == kPreNorm) load_raw<T, GPT>(reinterpret_cast<const uint4 *>(pre.gamma), K, third);
+    load_halves<T, GPT>(xrow, K, v);
+    if (PRE == kPreNorm) norm_row<T, GPT>(v, second, third, row, K, pre, wave_sum);
+    if (PRE == kPreSwiglu) swiglu_row<T, GPT>(v, second, row, K, pre);
+    if (ROTATE) rotate_row<T, GPT>(K, v, rot);
     if (!Xq) return;                     // the caller wanted the half-precision result only (uniform)
     uint32_t *qrow = reinterpret_cast<uint32_t *>(Xq + (size_t)row * (K >> 1));
 
@@ -306,7 +325,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const __half *X, int
         if (t == 0) scale_out[row] = __ushort_as_half((unsigned short)0x3c00);      // 1.0
 #pragma unroll
         for (int gi = 0; gi < GPT; ++gi) {
-            const int g = t + gi * 256;
+            const int g = t + gi * T;
             if (g < groups) {
                 float c[8];
                 load_col_scales(col_scales, g, c);
@@ -323,7 +342,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const __half *X, int
     if (MODE == kFolded) {
 #pragma unroll
         for (int gi = 0; gi < GPT; ++gi) {
-            const int g = t + gi * 256;
+            const int g = t + gi * T;
             if (g < groups) {
                 float c[8];
                 load_col_scales(col_scales, g, c);
@@ -341,23 +360,25 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const __half *X, int
     amax = wavefront_max(amax);
     if (lane == 0) wave_max[wave] = amax;
     __syncthreads();
-    amax = fmaxf(fmaxf(wave_max[0], wave_max[1]), fmaxf(wave_max[2], wave_max[3]));
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) amax = fmaxf(amax, wave_max[w]);
 
     const __half sh = row_scale(amax);
     const float sf = __half2float(sh);
     if (t == 0) scale_out[row] = sh;
 
-    // Inputs that were neither rotated nor multiplied by channel scales are half values, for
-    // which the fast quotient is verified exhaustively; the others take the division operator.
+    // The fast quotient is correctly rounded for every finite half scale (quant_math.h).  A rotated row can exceed what a
+    // half scale reaches: then the scale is infinite and the division operator says what that gives.
     const float rcp = 1.0f / sf;
+    const bool divide = (ROTATE || MODE == kFolded) && !(sf <= 65504.f);
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
-        const int g = t + gi * 256;
+        const int g = t + gi * T;
         if (g < groups) {
             uint32_t packed = 0;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                packed |= code4((ROTATE || MODE == kFolded) ? v[gi][e] / sf : quotient(v[gi][e], sf, rcp)) << (4 * e);
+                packed |= code4(divide ? v[gi][e] / sf : quotient(v[gi][e], sf, rcp)) << (4 * e);
             }
             qrow[g] = packed;
         }
@@ -452,7 +473,7 @@ __global__ __launch_bounds__(256) void channel_absmax_kernel(const __half *__res
     for (int row = blockIdx.x; row < M; row += gridDim.x) {
         const int64_t src = rows ? (int64_t)rows[row] : (int64_t)row;
         float v[GPT][8];
-        load_row<ROTATE, GPT>(reinterpret_cast<const uint4 *>(X + src * ldx), K, v, rot);
+        load_row<ROTATE, 256, GPT>(reinterpret_cast<const uint4 *>(X + src * ldx), K, v, rot);
 #pragma unroll
         for (int gi = 0; gi < GPT; ++gi)
 #pragma unroll
@@ -488,27 +509,6 @@ __global__ __launch_bounds__(256) void channel_scales_kernel(const float *__rest
     }
 }
 
-template <bool ROTATE, int GPT, int MODE, int PRE>
-static void launch_quantize_inst(const __half *X, int64_t ldx, const int32_t *rows, int M, int K, size_t lds,
-                                 const __half *col_scales, uint8_t *Xq, __half *sx, const PreArgs &pre,
-                                 hipStream_t st)
-{
-    hipLaunchKernelGGL((quantize_rows_kernel<ROTATE, GPT, MODE, PRE>), dim3(M), dim3(256), lds, st, X, ldx, rows, K,
-                       col_scales, Xq, sx, pre);
-}
-
-template <bool ROTATE, int MODE, int PRE>
-static void launch_quantize_gpt(int gpt, const __half *X, int64_t ldx, const int32_t *rows, int M, int K,
-                                size_t lds, const __half *col_scales, uint8_t *Xq, __half *sx, const PreArgs &pre,
-                                hipStream_t st)
-{
-    if (gpt <= 1) launch_quantize_inst<ROTATE, 1, MODE, PRE>(X, ldx, rows, M, K, lds, col_scales, Xq, sx, pre, st);
-    else if (gpt <= 2) launch_quantize_inst<ROTATE, 2, MODE, PRE>(X, ldx, rows, M, K, lds, col_scales, Xq, sx, pre, st);
-    else if (gpt <= 4) launch_quantize_inst<ROTATE, 4, MODE, PRE>(X, ldx, rows, M, K, lds, col_scales, Xq, sx, pre, st);
-    else if (gpt <= 6) launch_quantize_inst<ROTATE, 6, MODE, PRE>(X, ldx, rows, M, K, lds, col_scales, Xq, sx, pre, st);
-    else launch_quantize_inst<ROTATE, 8, MODE, PRE>(X, ldx, rows, M, K, lds, col_scales, Xq, sx, pre, st);
-}
-
 // Rotation keeps the row in LDS: K floats plus padding, above the 64 KiB default for the widest rows.
 template <class Kern>
 static sqap_status allow_rotation_lds(Kern kernel, size_t lds)
@@ -517,6 +517,41 @@ static sqap_status allow_rotation_lds(Kern kernel, size_t lds)
         SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)rot_lds_bytes(16384)));
     return SQAP_OK;
+}
+
+template <bool ROTATE, int T, int GPT, int MODE, int PRE>
+static sqap_status launch_quantize_inst(const __half *X, int64_t ldx, const int32_t *rows, int M, int K,
+                                        const __half *col_scales, uint8_t *Xq, __half *sx, const PreArgs &pre, hipStream_t st)
+{
+    const size_t lds = ROTATE ? rot_lds_bytes(K) : 0;
+    if (ROTATE) {
+        sqap_status s = allow_rotation_lds(&quantize_rows_kernel<ROTATE, T, GPT, MODE, PRE>, lds);
+        if (s != SQAP_OK) return s;
+    }
+    hipLaunchKernelGGL((quantize_rows_kernel<ROTATE, T, GPT, MODE, PRE>), dim3(M), dim3(T), lds, st, X, ldx, rows, K,
+                       col_scales, Xq, sx, pre);
+    return SQAP_OK;
+}
+
+// Threads per row: a row of more than 512 groups of 8 keeps 512 threads busy (2368 x 11008, SwiGLU: 38.9 us with 512
+// threads, 40.6 with 256, 49.4 with 128); with at most two rows per compute unit the longest rows take 1024 (84 x 11008,
+// SwiGLU 6.1 us against 7.1 and 8.8; plain 3.4 against 3.7 and 5.0).  Up to 512 groups, 256 threads are better as soon as
+// rows share compute units, since every wavefront repeats the norm's scalar part (2368 x 4096 norm 17.2 us against 19.8
+// with 512; 84 x 4096 4.5 against 4.1).
+template <bool ROTATE, int MODE, int PRE>
+static sqap_status launch_quantize_gpt(const __half *X, int64_t ldx, const int32_t *rows, int M, int K,
+                                       const __half *col_scales, uint8_t *Xq, __half *sx, const PreArgs &pre, hipStream_t st)
+{
+    const int groups = K / 8, cus = device_cu_count();
+#define SQAP_Q(T, G) launch_quantize_inst<ROTATE, T, G, MODE, PRE>(X, ldx, rows, M, K, col_scales, Xq, sx, pre, st)
+    if (groups > 1024) {
+        if (M <= 2 * cus) return SQAP_Q(1024, 2);
+        return groups <= 1536 ? SQAP_Q(512, 3) : SQAP_Q(512, 4);
+    }
+    if (groups > 512) return SQAP_Q(512, 2);
+    if (groups > 256) return M <= cus ? SQAP_Q(512, 1) : SQAP_Q(256, 2);
+    return SQAP_Q(256, 1);
+#undef SQAP_Q
 }
 
 constexpr int kPairsMinRows = 1024;      // from here on the plain quantizer takes two rows per block
@@ -531,10 +566,8 @@ static sqap_status launch_quantize_mode(const __half *X, int64_t ldx, const int3
         if constexpr (PRE == kPreSwiglu) {
             return fail(SQAP_EUNSUPPORTED, "rotation is not available behind the SwiGLU gate");
         } else {
-            const size_t lds = rot_lds_bytes(K);
-            sqap_status s = allow_rotation_lds(&quantize_rows_kernel<true, 8, MODE, PRE>, lds);
+            sqap_status s = launch_quantize_gpt<true, MODE, PRE>(X, ldx, rows, M, K, col_scales, Xq, sx, pre, st);
             if (s != SQAP_OK) return s;
-            launch_quantize_gpt<true, MODE, PRE>(gpt, X, ldx, rows, M, K, lds, col_scales, Xq, sx, pre, st);
         }
     } else if (MODE == kPerRow && PRE == kPreNone && Xq && M >= kPairsMinRows) {
         const dim3 grid((M + 1) / 2), block(256);
@@ -544,7 +577,8 @@ static sqap_status launch_quantize_mode(const __half *X, int64_t ldx, const int3
         else if (gpt <= 6) hipLaunchKernelGGL(quantize_row_pairs_kernel<6>, grid, block, 0, st, X, ldx, rows, M, K, Xq, sx);
         else hipLaunchKernelGGL(quantize_row_pairs_kernel<8>, grid, block, 0, st, X, ldx, rows, M, K, Xq, sx);
     } else {
-        launch_quantize_gpt<false, MODE, PRE>(gpt, X, ldx, rows, M, K, 0, col_scales, Xq, sx, pre, st);
+        sqap_status s = launch_quantize_gpt<false, MODE, PRE>(X, ldx, rows, M, K, col_scales, Xq, sx, pre, st);
+        if (s != SQAP_OK) return s;
     }
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;

@@ -114,6 +114,59 @@ def test_silu_of_every_half_value(G, oracle):
     assert np.array_equal(got.view(np.uint16), h_o.view(np.uint16)), int(np.count_nonzero(got.view(np.uint16) != h_o.view(np.uint16)))
 
 
+def test_silu_against_many_factors_and_at_the_infinities(G, oracle):
+    """The product with u is rounded to half, which hides the last bits of silu: 64 factors that move the boundary about."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    g = np.arange(65536, dtype=np.uint16).view(np.float16)
+    g = g[np.isfinite(g)].reshape(62, 1024)
+    u = (np.random.default_rng(5).random(64) + 1.0).astype(np.float16)
+    Gm, Um = np.concatenate([g] * 64), np.repeat(u, 62)[:, None] * np.ones((1, 1024), np.float16)
+    h = torch.zeros(Gm.shape, dtype=torch.float16, device="cuda")
+    B.sqap_swiglu_quantize_act(G.to_dev(Gm), G.to_dev(Um), None, None, h_out=h)
+    torch.cuda.synchronize()
+    assert np.array_equal(h.cpu().numpy().view(np.uint16), oracle.swiglu(Gm, Um).view(np.uint16))
+    e = torch.tensor([[float("inf"), float("-inf"), float("nan"), -0.0, -65504.0, 65504.0, 0.0, -1.0]], dtype=torch.float16, device="cuda")
+    o = torch.zeros((1, 8), dtype=torch.float16, device="cuda")
+    B.sqap_swiglu_quantize_act(e, torch.ones_like(e), None, None, h_out=o)
+    o = o.cpu().numpy()[0]
+    assert o[0] == np.inf and np.isnan(o[1]) and np.isnan(o[2]) and o[5] == 65504.0
+    assert [np.signbit(x) for x in o[3:7]] == [True, True, False, False] and o[3] == 0 and o[4] == 0
+
+
+@pytest.mark.parametrize("M", [1, 256, 257, 512, 513])
+@pytest.mark.parametrize("K", [2048, 2064, 4096, 4112, 8192, 8208, 12288, 12304, 16384])
+def test_threads_per_row(G, oracle, M, K):
+    """Both sides of every line of the rule that picks the threads of a row: plain, rotated, norm and SwiGLU rows.
+    Row 0 overflows its scale once rotated."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    rng = np.random.default_rng(M + K)
+    few = np.unique(np.linspace(0, M - 1, 6).astype(int))      # the rows the oracle works out
+    X = rng.standard_normal((M, K)).astype(np.float16)
+    X[:, ::97] *= 30
+    X[0] = 65504.0
+    U = rng.standard_normal((M, K)).astype(np.float16)
+    gamma = (1 + 0.1 * rng.standard_normal(K)).astype(np.float16)
+    xd, ud, gd = G.to_dev(X), G.to_dev(U), G.to_dev(gamma)
+    q = torch.zeros((M, K // 2), dtype=torch.uint8, device="cuda")
+    s = torch.zeros((M,), dtype=torch.float16, device="cuda")
+
+    def same(want):
+        torch.cuda.synchronize()
+        assert np.array_equal(q.cpu().numpy()[few], want[0]) and np.array_equal(s.cpu().numpy()[few].view(np.uint16), np.asarray(want[1]).view(np.uint16))
+        q.zero_()
+
+    B.sqap_quantize_act(xd, None, q, s)
+    same(oracle.quantize_rows(X[few]))
+    B.sqap_quantize_act(xd, None, q, s, flags=B.ROTATE_HADAMARD)
+    same(oracle.quantize_rows(X[few], rotate=True))
+    B.sqap_rmsnorm_quantize_act(ud, None, gd, 1e-5, q, s, delta=ud)
+    same(oracle.quantize_rows(oracle.rmsnorm_rows(U[few], gamma, 1e-5, delta=U[few])[1]))
+    B.sqap_swiglu_quantize_act(ud, ud, q, s)
+    same(oracle.quantize_rows(oracle.swiglu(U[few], U[few])))
+
+
 @pytest.mark.parametrize("M,F,channelwise,sliced", [(148, 11008, False, True), (7, 64, False, False), (33, 2056, True, False),
                                                      (8, 11008, False, True)])
 def test_swiglu_quantize(G, oracle, M, F, channelwise, sliced):
