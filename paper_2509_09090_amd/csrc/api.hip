@@ -350,6 +350,7 @@ sqap_status sqap_attention(const sqap_f16 *Q, int64_t ldq, const sqap_f16 *K, in
     if (!Q || !K || !V || !O) return fail(SQAP_EINVAL, "sqap_attention: null pointer");
     if (((ldq | ldk | ldv | ldo) & 7) || !aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O))
         return fail(SQAP_EUNSUPPORTED, "sqap_attention: operands and pitches must be 16-byte aligned");
+    const DeviceOfCall device;
     return launch_attention(reinterpret_cast<const __half *>(Q), ldq, reinterpret_cast<const __half *>(K), ldk,
                             reinterpret_cast<const __half *>(V), ldv, batch, Sq, Sk, H, d, reinterpret_cast<__half *>(O), ldo,
                             as_stream(stream));
@@ -586,6 +587,7 @@ sqap_status sqap_w4a4_linear(const uint8_t *Xq, const sqap_f16 *sx, int32_t M,
     if (M == 0) return SQAP_OK;
     if (!Xq || !sx || !Y) return fail(SQAP_EINVAL, "sqap_w4a4_linear: null pointer");
     if (!aligned16(Xq)) return fail(SQAP_EUNSUPPORTED, "sqap_w4a4_linear: Xq must be 16-byte aligned");
+    const DeviceOfCall device;
     size_t need = linear_workspace_bytes(M, w->N, w->K);
     if (need > 0) {
         if (!workspace || workspace_bytes < need)
@@ -742,6 +744,7 @@ sqap_status sqap_group_run(const sqap_group *g, void *stream)
 {
     const Group *gg = reinterpret_cast<const Group *>(g);
     if (!gg || gg->magic != kGroupMagic) return fail(SQAP_EINVAL, "sqap_group_run: not a group handle");
+    const DeviceOfCall device;
     SkinnyArgs a = {};
     a.table = gg->table;
     a.count = gg->count;

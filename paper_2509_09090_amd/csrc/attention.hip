@@ -326,14 +326,16 @@ template <int D, int NQ, int NK>
 static sqap_status launch_tiles(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
                                 int batch, int Sq, int Sk, int H, __half *O, int64_t ldo, hipStream_t st)
 {
-    static std::atomic<int> allowed[kMaxDeviceSlots];
     constexpr int bytes = attention_lds_bytes<D, NQ, NK>();
     static_assert(bytes <= 160 * 1024, "LDS of a compute unit");
-    const int slot = device_slot();
-    if (bytes > 48 * 1024 && !allowed[slot].load(std::memory_order_relaxed)) {
-        SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&attention_tiles_kernel<D, NQ, NK>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-        allowed[slot].store(1, std::memory_order_relaxed);
+    if constexpr (bytes > 48 * 1024) {
+        static std::atomic<bool> allowed[kMaxDeviceSlots];
+        const int slot = device_slot();
+        if (!allowed[slot].load(std::memory_order_acquire)) {
+            SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&attention_tiles_kernel<D, NQ, NK>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+            allowed[slot].store(true, std::memory_order_release);
+        }
     }
     hipLaunchKernelGGL((attention_tiles_kernel<D, NQ, NK>), dim3(H, (Sq + 32 * NQ - 1) / (32 * NQ), batch),
                        dim3(64 * NQ * NK), bytes, st, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, O, ldo);

@@ -75,12 +75,24 @@ static inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream
 // Launcher state that belongs to a device (function attributes set, CU count): one slot per device
 // ordinal, atomics so that host threads may race to initialise it (every racer writes the same value).
 constexpr int kMaxDeviceSlots = 64;
-static inline int device_slot()
+static inline int current_device()
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0) dev = 0;
-    return dev % kMaxDeviceSlots;
+    return dev;
 }
+// The runtime takes 0.8 us to name the current device, and a launch path asks up to four times.  An entry point that
+// launches puts one of these on its stack: the device is looked up once, for this call on this thread.
+struct DeviceOfCall {
+    DeviceOfCall() : outer(known) { if (outer < 0) known = current_device(); }
+    ~DeviceOfCall() { known = outer; }
+    DeviceOfCall(const DeviceOfCall &) = delete;
+    DeviceOfCall &operator=(const DeviceOfCall &) = delete;
+    static inline thread_local int known = -1;
+    const int outer;
+};
+static inline int device_ordinal() { return DeviceOfCall::known >= 0 ? DeviceOfCall::known : current_device(); }
+static inline int device_slot() { return device_ordinal() % kMaxDeviceSlots; }
 static inline int device_cu_count()
 {
     static std::atomic<int> cus[kMaxDeviceSlots];

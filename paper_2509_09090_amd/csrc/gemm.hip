@@ -1072,8 +1072,8 @@ static bool persistent_allowed()
     }();
     const int sw = g_persistent_switch.load(std::memory_order_relaxed);
     if (sw == 0 || (sw < 0 && disabled)) return false;
-    int dev = 0;
-    return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices && g_dealing[dev].load() == 1;
+    const int dev = device_ordinal();
+    return dev < kMaxDevices && g_dealing[dev].load() == 1;
 }
 
 static int persistent_blocks()
