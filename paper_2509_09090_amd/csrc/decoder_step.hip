@@ -740,12 +740,17 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
                     }
                 }
             } else {
-                // h = half(silu(g) * u), silu(g) = (float)(g / (1 + exp(-g))) in binary64
+                // h = half(silu(g) * u), silu(g) = (float)(g / (1 + exp(-g))) in binary64 (silu_of gives the same bits with
+                // fewer instructions, but two values per lane are latency: 1330 us per token of the 7B shape against 1321)
                 float g2[2], u2[2];
                 channel_pair(2 * jo, g2);
                 channel_pair(2 * jo + 1, u2);
 #pragma unroll
-                for (int e = 0; e < 2; ++e) y[e] = to_half_value(silu_of(g2[e]) * u2[e]);
+                for (int e = 0; e < 2; ++e) {
+                    const double gd = (double)g2[e];
+                    const float sl = (float)(gd / (1.0 + exp(-gd)));
+                    y[e] = to_half_value(sl * u2[e]);
+                }
                 if (n < (P.N >> 1)) store_tagged_pair(a.h + mine, n, y[0], y[1], tag_of(P.layer, kTagH));
             }
         }
