@@ -273,6 +273,55 @@ sqap_status launch_attention(const __half *Q, int64_t ldq, const __half *Kc, int
     return SQAP_OK;
 }
 
+// The workgroup (of T threads) that arrives last, of n_groups, quantizes the whole output row, as quantize_rows_kernel does.
+// row_lds: width halves of LDS, wave_max: T / 64 floats.
+template <int T>
+__device__ __forceinline__ void quantize_by_the_last(float *row_lds, float *wave_max, int *last_flag, const __half *O, int width,
+                                                     int n_groups, uint8_t *Xq, __half *sx, unsigned int *counter)
+{
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (wave * 64 < kDecMaxD) __threadfence();         // this head's outputs before the arrival (these wavefronts stored them)
+    __syncthreads();
+    if (t == 0) {
+        const unsigned int before = atomicAdd(counter, 1u);
+        *last_flag = before == (unsigned int)(n_groups - 1);
+    }
+    __syncthreads();
+    if (!*last_flag) return;
+    __threadfence();                                   // the other heads' outputs after the arrival
+    __half *row = reinterpret_cast<__half *>(row_lds);
+    const int groups = width >> 3;
+    float amax = 0.f;
+    for (int g = t; g < groups; g += T) {
+        const uint4 raw = reinterpret_cast<const uint4 *>(O)[g];
+        reinterpret_cast<uint4 *>(row)[g] = raw;
+        float f[8];
+        unpack_halves(raw, f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(f[e]));
+    }
+    amax = wavefront_max(amax);
+    if (lane == 0) wave_max[wave] = amax;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) amax = fmaxf(amax, wave_max[w]);
+    const __half sh = row_scale(amax);
+    const float sf = __half2float(sh);
+    const float rcp = 1.0f / sf;
+    if (t == 0) {
+        sx[0] = sh;
+        atomicExch(counter, 0u);                       // the next call starts from zero again
+    }
+    for (int g = t; g < groups; g += T) {
+        float f[8];
+        unpack_halves(reinterpret_cast<const uint4 *>(row)[g], f);
+        uint32_t packed = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) packed |= code4(quotient(f[e], sf, rcp)) << (4 * e);
+        reinterpret_cast<uint32_t *>(Xq)[g] = packed;
+    }
+}
+
 // One decode step's attention in a single launch: the new token's query and key are rotated (same
 // arithmetic as rope_kernel), the rotated key and the value go into row `past` of the cache, and the
 // query attends to cache rows 0 .. past.  One workgroup per head.  At one token each of the three
@@ -294,60 +343,237 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(const __half *__r
 {
     __shared__ DecodeAttnLds lds;
     __shared__ int last_flag;
-    float *ored = lds.ored, *wred = lds.wred;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int width = H * d;
     decode_attention_head<false>(lds, blockIdx.x, QKV, pos[0], H, d, base, KV, ldkv, past, O, nullptr, freq);
     if (!Xq) return;
 
-    // the workgroup that arrives last quantizes the whole row (as quantize_rows_kernel does)
-    __threadfence();                                   // this head's outputs before the arrival
-    __syncthreads();
-    if (t == 0) {
-        const unsigned int before = atomicAdd(counter, 1u);
-        last_flag = before == (unsigned int)(H - 1);
+    quantize_by_the_last<256>(lds.ored, lds.wred, &last_flag, O, H * d, H, Xq, sx, counter);
+}
+
+// The same for a long cache.  decode_attention_head walks the chunks one after the other with four wavefronts, one per
+// SIMD, and waits for its own instructions (2.6 us per chunk of 192 keys; with the rows of three chunks in flight no less).
+// Its arithmetic leaves more freedom than that: every score is a sum of its own, every column of every key group a chain
+// of its own, and the chunks' running maxima follow from the scores.  Eight wavefronts work out all scores (32 keys at
+// a time), then maxima, probabilities and group sums of all chunks side by side, then the output, two key groups
+// per wavefront and four columns per lane.  The same operations in the same order per value: the same bits.
+// What bounds it: a compute unit takes in about 65 GB/s, 7.4 ns per position (512 bytes), and there is one per head (more
+// would have to meet in memory that the call does not have); rows in flight beyond these gave nothing.
+// Measured (32 heads of 128, us without the quantizer, the other kernel in brackets): 192 positions 7.8 (7.5), 400 9.4
+// (9.8), 800 12.8 (15.9), 1500 16.9 (23.4), 3000 28.1 (43.6): used from two chunks on.
+// Scores wait in LDS, 4 bytes per position: up to kDecLongMax of them (with the rest 52 KiB).
+constexpr int kDecLongMin = 2 * kDecChunk;
+constexpr int kDecLongT = 512, kDecLongMax = 42 * kDecChunk, kDecLongChunks = kDecLongMax / kDecChunk;
+constexpr int kDecLongKeys = 6;            // key rows per lane on their way during the scores: a chunk
+typedef unsigned int sqap_v2u __attribute__((ext_vector_type(2)));
+constexpr int kDecLongAhead = 2;           // chunks whose value rows are on their way during the output
+
+__global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const __half *__restrict__ QKV,
+                                                                          const int32_t *__restrict__ pos, int H, int d,
+                                                                          double base, __half *KV, int64_t ldkv, int past,
+                                                                          __half *O, uint8_t *__restrict__ Xq,
+                                                                          __half *__restrict__ sx, unsigned int *counter,
+                                                                          const RopeFreq freq)
+{
+    extern __shared__ __attribute__((aligned(16))) float sc[];        // scores, then probabilities; whole chunks
+    __shared__ __attribute__((aligned(16))) float qf[kDecMaxD];
+    __shared__ __attribute__((aligned(16))) __half knew[kDecMaxD], vnew[kDecMaxD];
+    __shared__ __attribute__((aligned(16))) float ored[kDecRedFloats];
+    __shared__ float cmax[kDecLongChunks], mrun[kDecLongChunks], resc[kDecLongChunks], psg[kDecLongChunks * 16], lw[4], wave_max[kDecLongT / 64];
+    __shared__ int last_flag;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, h = blockIdx.x;
+    const int half_d = d >> 1, width = H * d, Sk = past + 1, n_chunks = (Sk + kDecChunk - 1) / kDecChunk;
+    const __half *q = QKV + (int64_t)h * d, *k = q + width, *v = k + width;
+    __half fresh[6] = {};
+    if (t < half_d) {
+        fresh[0] = q[t];
+        fresh[1] = q[t + half_d];
+        fresh[2] = k[t];
+        fresh[3] = k[t + half_d];
+        fresh[4] = v[t];
+        fresh[5] = v[t + half_d];
     }
-    __syncthreads();
-    if (!last_flag) return;
-    __threadfence();                                   // the other heads' outputs after the arrival
-    __half *row = reinterpret_cast<__half *>(ored);
-    const int groups = width >> 3;
-    float amax = 0.f;
-    for (int g = t; g < groups; g += 256) {
-        const uint4 raw = reinterpret_cast<const uint4 *>(O)[g];
-        reinterpret_cast<uint4 *>(row)[g] = raw;
-        float f[8];
-        unpack_halves(raw, f);
+    const int kg = t >> 4, c = t & 15;
+    const bool col_ok = c * 8 < d;
+    // a uniform base and a 32-bit lane offset per load; past the last cached row that row again (its score is not used)
+    constexpr int KSTEP = kDecLongT / 16;
+    const uint32_t pitch = (uint32_t)ldkv * 2u, k_limit = (uint32_t)(past - 1) * pitch + (col_ok ? c * 16 : 0);
+    const char *kbase = reinterpret_cast<const char *>(KV + (int64_t)h * d);
+    uint32_t k_at = (uint32_t)kg * pitch + (col_ok ? c * 16 : 0);
+    auto next_key_row = [&] {
+        const sqap_v4u raw = *reinterpret_cast<const sqap_v4u *>(kbase + min(k_at, k_limit));
+        k_at += KSTEP * pitch;
+        return raw;
+    };
+    sqap_v4u kraw[kDecLongKeys];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(f[e]));
+    for (int u = 0; u < kDecLongKeys; ++u) kraw[u] = next_key_row();
+
+    // rotation of this head's query and key; the value is copied (as in decode_attention_head)
+    if (t < half_d) {
+        double sn, cs;
+        sincos(rope_angle(freq, pos[0], t, d, base), &sn, &cs);
+        __half *krow = KV + (int64_t)past * ldkv + (int64_t)h * d, *vrow = krow + width;
+        double lo = (double)__half2float(fresh[0]), hi = (double)__half2float(fresh[1]);
+        qf[t] = __half2float(__float2half_rn((float)(lo * cs - hi * sn)));
+        qf[t + half_d] = __half2float(__float2half_rn((float)(hi * cs + lo * sn)));
+        lo = (double)__half2float(fresh[2]);
+        hi = (double)__half2float(fresh[3]);
+        const __half k0 = __float2half_rn((float)(lo * cs - hi * sn)), k1 = __float2half_rn((float)(hi * cs + lo * sn));
+        knew[t] = k0;
+        knew[t + half_d] = k1;
+        global_store_half(krow + t, k0);
+        global_store_half(krow + t + half_d, k1);
+        vnew[t] = fresh[4];
+        vnew[t + half_d] = fresh[5];
+        global_store_half(vrow + t, fresh[4]);
+        global_store_half(vrow + t + half_d, fresh[5]);
     }
-    amax = wavefront_max(amax);
-    if (lane == 0) wred[wave] = amax;
-    __syncthreads();
-    amax = fmaxf(fmaxf(wred[0], wred[1]), fmaxf(wred[2], wred[3]));
-    const __half sh = row_scale(amax);
-    const float sf = __half2float(sh);
-    const float rcp = 1.0f / sf;
-    if (t == 0) {
-        sx[0] = sh;
-        atomicExch(counter, 0u);                       // the next call starts from zero again
-    }
-    for (int g = t; g < groups; g += 256) {
-        float f[8];
-        unpack_halves(reinterpret_cast<const uint4 *>(row)[g], f);
-        uint32_t packed = 0;
+    lds_barrier();
+
+    // scores
+    float q8[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) packed |= code4(quotient(f[e], sf, rcp)) << (4 * e);
-        reinterpret_cast<uint32_t *>(Xq)[g] = packed;
+    for (int e = 0; e < 8; ++e) q8[e] = col_ok ? qf[c * 8 + e] : 0.f;
+    const float inv_sqrt_d = 1.0f / sqrtf((float)d);
+    auto score = [&](const uint4 raw) {
+        float kf[8];
+        unpack_halves(raw, kf);
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s = fmaf(q8[e], kf[e], s);
+        s = col_ok ? s : 0.f;                             // (a lane past the head's columns read some other ones)
+        s += dpp_move_f<kDppXor1>(s);
+        s += dpp_move_f<kDppXor2>(s);
+        s += dpp_move_f<kDppHalfMirror>(s);
+        s += dpp_move_f<kDppMirror>(s);
+        return s * inv_sqrt_d;
+    };
+    static_assert(kDecChunk == KSTEP * kDecLongKeys, "a round of the scores is a chunk");
+    float *mine = sc + kg;
+    for (int i = 0; i < n_chunks; ++i, mine += kDecChunk) {
+#pragma unroll
+        for (int u = 0; u < kDecLongKeys; ++u) {
+            const float s = score(make_uint4(kraw[u].x, kraw[u].y, kraw[u].z, kraw[u].w));
+            kraw[u] = next_key_row();
+            if (c == 0) mine[KSTEP * u] = s;
+        }
     }
+    const float s_new = score(lds_load16(knew + (col_ok ? c * 8 : 0)));
+    // the first value rows, on their way during the softmax (a wavefront: two key groups, 4 columns per lane)
+    const int vg = 2 * wave + (lane >> 5), vc = (lane & 31) * 4;
+    const bool v_ok = vc < d;
+    const uint32_t v_limit = (uint32_t)(past - 1) * pitch + (v_ok ? vc * 2 : 0);
+    const char *vbase = reinterpret_cast<const char *>(KV + width + (int64_t)h * d);
+    uint32_t v_at = (uint32_t)vg * pitch + (v_ok ? vc * 2 : 0);
+    auto next_value_row = [&] {
+        const sqap_v2u raw = *reinterpret_cast<const sqap_v2u *>(vbase + min(v_at, v_limit));
+        v_at += 16 * pitch;
+        return raw;
+    };
+    sqap_v2u vraw[kDecLongAhead][kDecKeys];
+#pragma unroll
+    for (int a = 0; a < kDecLongAhead; ++a)
+#pragma unroll
+        for (int j = 0; j < kDecKeys; ++j) vraw[a][j] = next_value_row();
+    lds_barrier();
+    for (int key = past + t; key < n_chunks * kDecChunk; key += kDecLongT) sc[key] = key == past ? s_new : -INFINITY;     // (t = 0: the new token)
+    lds_barrier();
+
+    // chunk maxima, running maxima, rescaling factors
+    for (int i = wave; i < n_chunks; i += kDecLongT / 64) {
+        float m = fmaxf(fmaxf(sc[i * kDecChunk + lane], sc[i * kDecChunk + 64 + lane]), sc[i * kDecChunk + 128 + lane]);
+        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+        if (lane == 0) cmax[i] = m;
+    }
+    lds_barrier();
+    if (t < n_chunks) {
+        float before = -INFINITY, m = -INFINITY;
+        for (int i = 0; i <= t; ++i) {
+            before = m;
+            m = fmaxf(m, cmax[i]);
+        }
+        mrun[t] = m;
+        resc[t] = expf(before - m);
+    }
+    lds_barrier();
+    for (int key = t; key < n_chunks * kDecChunk; key += kDecLongT) {
+        const float s = sc[key];
+        sc[key] = s == -INFINITY ? 0.f : expf(s - mrun[key / kDecChunk]);
+    }
+    lds_barrier();
+    for (int i = t; i < n_chunks * 16; i += kDecLongT) {
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < kDecKeys; ++j) sum += sc[(i >> 4) * kDecChunk + 16 * j + (i & 15)];
+        psg[i] = sum;
+    }
+    lds_barrier();
+
+    if (wave == kDecLongT / 64 - 1 && lane < 4) {         // the running sums of the four sets of key groups
+        float l = 0.f;
+        for (int i = 0; i < n_chunks; ++i) {
+            const float *p = psg + i * 16 + lane * 4;
+            l = l * resc[i] + ((p[0] + p[1]) + (p[2] + p[3]));
+        }
+        lw[lane] = l;
+    }
+    float o[4] = {0.f, 0.f, 0.f, 0.f};
+    auto value_chunk = [&](sqap_v2u (&rows)[kDecKeys], int i, auto last_c) {
+        constexpr bool LAST = decltype(last_c)::value;
+        const float f = resc[i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] *= f;
+#pragma unroll
+        for (int j = 0; j < kDecKeys; ++j) {
+            const int key = i * kDecChunk + 16 * j + vg;
+            union { sqap_v2u v; __half2 h2[2]; } raw;
+            raw.v = rows[j];
+            if (LAST) {                                   // the new token's row, and zeros past it
+                if (key >= past) raw.v = key == past && v_ok ? *reinterpret_cast<const sqap_v2u *>(vnew + vc) : sqap_v2u{0u, 0u};
+            } else {
+                rows[j] = next_value_row();
+            }
+            const float p = sc[key];
+            const float2 lo = __half22float2(raw.h2[0]), hi = __half22float2(raw.h2[1]);
+            o[0] = fmaf(p, lo.x, o[0]);
+            o[1] = fmaf(p, lo.y, o[1]);
+            o[2] = fmaf(p, hi.x, o[2]);
+            o[3] = fmaf(p, hi.y, o[3]);
+        }
+    };
+    for (int i0 = 0; i0 < n_chunks; i0 += kDecLongAhead) {
+#pragma unroll
+        for (int a = 0; a < kDecLongAhead; ++a) {
+            if (i0 + a < n_chunks - 1) value_chunk(vraw[a], i0 + a, std::false_type{});
+            else if (i0 + a == n_chunks - 1) value_chunk(vraw[a], i0 + a, std::true_type{});
+        }
+    }
+    if (v_ok) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ored[vg * kDecMaxD + vc + e] = o[e];
+    }
+    lds_barrier();
+    if (t < d) {
+        float acc = 0.f;
+#pragma unroll
+        for (int g = 0; g < 16; ++g) acc += ored[g * kDecMaxD + t];
+        const float l = (lw[0] + lw[1]) + (lw[2] + lw[3]);
+        O[(int64_t)h * d + t] = __float2half_rn(acc * (1.0f / l));
+    }
+    if (Xq) quantize_by_the_last<kDecLongT>(ored, wave_max, &last_flag, O, width, H, Xq, sx, counter);
 }
 
 sqap_status launch_decode_attention(const __half *QKV, const int32_t *pos, int H, int d, double base, __half *KV,
                                     int64_t ldkv, int past, __half *O, uint8_t *Xq, __half *sx,
                                     unsigned int *counter, hipStream_t st)
 {
-    hipLaunchKernelGGL(decode_attention_kernel, dim3(H), dim3(256), 0, st, QKV, pos, H, d, base, KV, ldkv, past, O, Xq,
-                       sx, counter, rope_frequencies(d, base));
+    if (past >= kDecLongMin && past < kDecLongMax && (int64_t)(past + 1024) * ldkv * 2 < (int64_t)1 << 31) {
+        const size_t lds = (size_t)(past / kDecChunk + 1) * kDecChunk * sizeof(float);
+        hipLaunchKernelGGL(decode_attention_long_kernel, dim3(H), dim3(kDecLongT), lds, st, QKV, pos, H, d, base, KV, ldkv, past,
+                           O, Xq, sx, counter, rope_frequencies(d, base));
+    } else {
+        hipLaunchKernelGGL(decode_attention_kernel, dim3(H), dim3(256), 0, st, QKV, pos, H, d, base, KV, ldkv, past, O, Xq,
+                           sx, counter, rope_frequencies(d, base));
+    }
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }

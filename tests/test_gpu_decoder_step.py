@@ -78,6 +78,7 @@ def _wide_token(rng, K):
                                                          (256, 4, 64, 512, 2, 1000, 9, True),         # tokens of wide dynamic range
                                                          (1024, 8, 128, 2816, 2, 5008, 40, False),   # several groups per workgroup, ragged shares
                                                          (512, 4, 128, 1408, 2, 3008, 300, False),   # a cache longer than one attention chunk
+                                                         (256, 4, 64, 512, 1, 1000, 390, False),     # the chain's attention in its form for long caches
                                                          (4096, 32, 128, 11008, 1, 32000, 148, False)])   # the 7B layer shape and head
 def test_decoder_step_matches_the_oracle_and_the_launch_chain(G, oracle, hidden, H, d, F, L, vocab, S, wide):
     import torch
