@@ -261,9 +261,16 @@ sqap_status launch_prune_rows(const float *scores, int batch, int n, int keep_k,
 
 // ---------------------------------------------------------------------------
 // Full selection rule of Section 3.2: K_attn (Eq. 1) + K_ring (Eq. 2-4) + K_fps
-// (Eq. 5).  One wavefront per observation; lane l owns tokens l, l + 64, ...
-// (at most 1024 tokens, 16 per lane).  Everything after the projection is
+// (Eq. 5).  Lane l owns tokens l, l + 64, ... (at most 1024 tokens, 16 per lane).  Four wavefronts per
+// observation hold the same tokens: the distances to the set the sampling starts from, one member at a time,
+// are shared out by lane number mod 4; then the first wavefront samples alone (a pick depends on the one before, and a
+// barrier per pick would cost more than the arithmetic it shares out).  Everything after the projection is
 // integer work, so the result is exact.
+// A serial chain bounds it: a pick is about 5 instructions per 64 tokens, a wavefront maximum and the
+// decoding of the winner.  A token's state is one word, squared distance * 2048 + inverted index: the largest word is the
+// next pick, a member's distance is zero, which keeps it out without further tests, and (u, v) are packed halves whose
+// squared distance is one subtraction and one dot product.  Measured per call, 16 observations, us (one wavefront, masks
+// and coordinates apart, in brackets): 16 x 16 tokens, 128 kept 15.6 (26.6); 32 x 32, 512 kept 91 (214).
 constexpr int kSelectCamera = 26;          // doubles per observation: K (9), [R|t] (12), point (3), patch w, h
 constexpr uint32_t kFarAway = 1u << 20;    // above any squared distance on a grid of <= 1024 tokens
 
@@ -305,35 +312,43 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+typedef short v2s __attribute__((ext_vector_type(2)));
+constexpr int kSelectWaves = 4;
+
+__device__ __forceinline__ uint32_t squared_distance(uint32_t a, uint32_t b)        // of packed (u, v)
+{
+    const v2s d = __builtin_bit_cast(v2s, a) - __builtin_bit_cast(v2s, b);
+    return (uint32_t)__builtin_amdgcn_sdot2(d, d, 0, false);
+}
+
 template <int PL>     // tokens per lane: at most 64 * PL tokens
-__global__ __launch_bounds__(64) void prune_select_kernel(const float *__restrict__ scores, int gw, int gh,
+__global__ __launch_bounds__(64 * kSelectWaves) void prune_select_kernel(const float *__restrict__ scores, int gw, int gh,
                                                           int k_attn, int keep_total,
                                                           const double *__restrict__ camera, int radius,
                                                           int32_t *__restrict__ idx_out, int cap,
                                                           int32_t *__restrict__ count_out)
 {
-    const int lane = threadIdx.x, b = blockIdx.x;
+    __shared__ uint32_t part[kSelectWaves][64 * PL];
+    const int lane = threadIdx.x & 63, b = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = gw * gh;
     const float *s = scores + (size_t)b * n;
     const unsigned long long below = (1ull << lane) - 1ull;      // lanes with a lower number
 
-    int cu = 0, cv = 0;
-    bool have_ring = false;
-    if (camera) have_ring = project_token(camera + (size_t)b * kSelectCamera, cu, cv);
-
     // own tokens: lane + 64 r.  Tokens 64 r .. 64 r + 63 sit in lane order, so "lower index
     // first" is "lower row first, then lower lane".
     bool valid[PL], kept[PL];
-    uint32_t key[PL];
-    int tu[PL], tv[PL];
+    uint32_t key[PL], uv[PL];
 #pragma unroll
     for (int r = 0; r < PL; ++r) {
         const int i = lane + 64 * r;
         valid[r] = i < n;
         key[r] = valid[r] ? score_key(s[i]) : 0u;
-        tu[r] = valid[r] ? i % gw : 0;
-        tv[r] = valid[r] ? i / gw : 0;
+        uv[r] = valid[r] ? (uint32_t)(i % gw) | ((uint32_t)(i / gw) << 16) : 0u;
     }
+    int cu = 0, cv = 0;
+    bool have_ring = false;
+    if (camera) have_ring = project_token(camera + (size_t)b * kSelectCamera, cu, cv);
 
     // Eq. 1: the k_attn-th largest key T, found bit by bit from the top (T is the largest value
     // that at least k_attn keys reach), then keys above T and the first tokens equal to T.
@@ -358,7 +373,7 @@ __global__ __launch_bounds__(64) void prune_select_kernel(const float *__restric
         eq_seen += __popcll(mk);
         // Eq. 4 by the distance itself
         if (have_ring && valid[r]) {
-            const int du = abs(tu[r] - cu), dv = abs(tv[r] - cv);
+            const int du = abs((int)(uv[r] & 0xffffu) - cu), dv = abs((int)(uv[r] >> 16) - cv);
             keep = keep || (du > dv ? du : dv) <= radius;
         }
         kept[r] = keep;
@@ -369,51 +384,49 @@ __global__ __launch_bounds__(64) void prune_select_kernel(const float *__restric
 
     // Eq. 5: distance of every candidate to the set kept so far, then one pick per step
     const int m = keep_total > count ? keep_total - count : 0;
-    uint32_t mind[PL];
+    if (m > 0) {                                             // (the same in all four wavefronts)
+        uint32_t mind[PL];
 #pragma unroll
-    for (int r = 0; r < PL; ++r) mind[r] = kFarAway;
-    if (m > 0) {
+        for (int r = 0; r < PL; ++r) mind[r] = valid[r] ? kFarAway : 0u;
 #pragma unroll
         for (int rr = 0; rr < PL; ++rr) {
-            unsigned long long mk = __ballot(kept[rr]);     // kept tokens 64 rr .. 64 rr + 63, one at a time
+            unsigned long long mk = __ballot(kept[rr]) & (0x1111111111111111ull << wave);      // this wavefront's members
             while (mk) {
                 const int src = __builtin_ctzll(mk);
                 mk &= mk - 1;
-                const int ju = __builtin_amdgcn_readlane(tu[rr], src), jv = __builtin_amdgcn_readlane(tv[rr], src);
+                const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)uv[rr], src);
 #pragma unroll
-                for (int r = 0; r < PL; ++r) {
-                    const int du = tu[r] - ju, dv = tv[r] - jv;
-                    const uint32_t d = (uint32_t)(du * du + dv * dv);
-                    mind[r] = d < mind[r] ? d : mind[r];
-                }
+                for (int r = 0; r < PL; ++r) mind[r] = min(mind[r], squared_distance(uv[r], at));
             }
         }
-    }
-    for (int step = 0; step < m; ++step) {
-        // largest distance, lowest index among equals: the index enters the key inverted
-        uint32_t best = 0;
+#pragma unroll
+        for (int r = 0; r < PL; ++r) part[wave][lane + 64 * r] = mind[r];
+        __syncthreads();
+        if (wave != 0) return;
+        uint32_t state[PL];
 #pragma unroll
         for (int r = 0; r < PL; ++r) {
-            const uint32_t k2 = (valid[r] && !kept[r]) ? (mind[r] << 11) + (uint32_t)(2047 - (lane + 64 * r)) : 0u;
-            best = k2 > best ? k2 : best;
+            const int i = lane + 64 * r;
+            const uint32_t d = min(min(part[0][i], part[1][i]), min(part[2][i], part[3][i]));
+            state[r] = (d << 11) + (uint32_t)(2047 - i);
         }
-        best = wave_max_u32(best);
-        const int w = 2047 - (int)(best & 2047u);
-        const int wl = w & 63, wr = w >> 6;
-        int wu = 0, wv = 0;
+        const uint32_t inv_gw = (1u << 20) / (uint32_t)gw + 1u;      // w / gw = (w * inv_gw) >> 20: w * gw < 2^20
+        for (int step = 0; step < m; ++step) {
+            // largest distance, lowest index among equals: the index is in the state inverted
+            uint32_t best = state[0];
 #pragma unroll
-        for (int r = 0; r < PL; ++r)
-            if (r == wr) {                                   // uniform
-                wu = __builtin_amdgcn_readlane(tu[r], wl);
-                wv = __builtin_amdgcn_readlane(tv[r], wl);
-            }
+            for (int r = 1; r < PL; ++r) best = max(best, state[r]);
+            best = wave_max_u32(best);
+            const uint32_t w = 2047u - (best & 2047u);
+            const uint32_t v = (w * inv_gw) >> 20, at = (w - v * (uint32_t)gw) | (v << 16);
 #pragma unroll
-        for (int r = 0; r < PL; ++r) {
-            if (lane + 64 * r == w) kept[r] = true;
-            const int du = tu[r] - wu, dv = tv[r] - wv;
-            const uint32_t d = (uint32_t)(du * du + dv * dv);
-            mind[r] = d < mind[r] ? d : mind[r];
+            for (int r = 0; r < PL; ++r)
+                state[r] = min(state[r], (squared_distance(uv[r], at) << 11) + (uint32_t)(2047 - (lane + 64 * r)));
         }
+#pragma unroll
+        for (int r = 0; r < PL; ++r) kept[r] = kept[r] || (valid[r] && (state[r] >> 11) == 0u);
+    } else if (wave != 0) {
+        return;
     }
 
     // ascending output
@@ -435,28 +448,43 @@ sqap_status launch_prune_select(const float *scores, int batch, int gw, int gh, 
 {
     const int n = gw * gh;
     if (n <= 256)
-        hipLaunchKernelGGL(prune_select_kernel<4>, dim3(batch), dim3(64), 0, st, scores, gw, gh, k_attn, keep_total,
+        hipLaunchKernelGGL(prune_select_kernel<4>, dim3(batch), dim3(64 * kSelectWaves), 0, st, scores, gw, gh, k_attn, keep_total,
                            camera, radius, idx, cap, count);
     else if (n <= 512)
-        hipLaunchKernelGGL(prune_select_kernel<8>, dim3(batch), dim3(64), 0, st, scores, gw, gh, k_attn, keep_total,
+        hipLaunchKernelGGL(prune_select_kernel<8>, dim3(batch), dim3(64 * kSelectWaves), 0, st, scores, gw, gh, k_attn, keep_total,
                            camera, radius, idx, cap, count);
     else
-        hipLaunchKernelGGL(prune_select_kernel<16>, dim3(batch), dim3(64), 0, st, scores, gw, gh, k_attn,
+        hipLaunchKernelGGL(prune_select_kernel<16>, dim3(batch), dim3(64 * kSelectWaves), 0, st, scores, gw, gh, k_attn,
                            keep_total, camera, radius, idx, cap, count);
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }
 
 // One block per observation: walks the sequence in order, keeps every token
-// outside the visual span and the visual tokens listed (ascending) in idx.
+// outside the visual span and the visual tokens listed (ascending) in idx.  The list is read once, into one flag
+// per visual token; spans that do not fit the flags search the list, whose dependent reads took most of the
+// kernel's time (16 x 256 tokens: 3.4 us, with flags 2.6; 16 x 1024: 6.8 and 3.4).
+constexpr int kRowFlags = 8192;
 __global__ __launch_bounds__(256) void kept_rows_kernel(const int32_t *__restrict__ idx, int keep_k,
                                                         int seq_len, int vis_begin, int n_vis,
                                                         int32_t *__restrict__ rows)
 {
     __shared__ int wave_sums[4];
+    __shared__ uint32_t flag_words[kRowFlags / 4];
+    uint8_t *flags = reinterpret_cast<uint8_t *>(flag_words);
     const int b = blockIdx.x, t = threadIdx.x;
     const int32_t *my = idx + (size_t)b * keep_k;
     int32_t *out = rows + (size_t)b * (seq_len - n_vis + keep_k);
+    const bool flagged = n_vis <= kRowFlags;
+    if (flagged) {
+        for (int i = t; i < (n_vis + 3) / 4; i += 256) flag_words[i] = 0u;
+        __syncthreads();
+        for (int i = t; i < keep_k; i += 256) {
+            const int v = my[i];
+            if (v >= 0 && v < n_vis) flags[v] = 1;
+        }
+        __syncthreads();
+    }
     int base = 0;
     for (int c = 0; c < seq_len; c += 256) {
         const int s = c + t;
@@ -465,6 +493,8 @@ __global__ __launch_bounds__(256) void kept_rows_kernel(const int32_t *__restric
             const int v = s - vis_begin;
             if (v < 0 || v >= n_vis) {
                 keep = true;
+            } else if (flagged) {
+                keep = flags[v] != 0;
             } else {                     // binary search in the ascending list
                 int lo = 0, hi = keep_k;
                 while (lo < hi) {
@@ -611,6 +641,7 @@ __device__ __forceinline__ float block_reduce_256(float v, bool take_max, float 
                     : (scratch4[0] + scratch4[1]) + (scratch4[2] + scratch4[3]);
 }
 
+template <int kRowsInFlight>                      // key rows a lane group loads before it reduces any
 __global__ __launch_bounds__(256) void attn_head_kernel(const __half *__restrict__ q, const __half *__restrict__ k,
                                                         int S, int H, int d, int vis_begin, int n_vis,
                                                         float *__restrict__ scores, unsigned int *heads_done,
@@ -638,18 +669,17 @@ __global__ __launch_bounds__(256) void attn_head_kernel(const __half *__restrict
         }
     }
     const float inv_sqrt_d = 1.0f / sqrtf((float)d);
-    constexpr int kRowsInFlight = 8;              // key rows a lane group loads before it reduces any
     for (int s0 = 0; s0 < S; s0 += groups * kRowsInFlight) {
         uint4 raw[kRowsInFlight];
 #pragma unroll
         for (int r = 0; r < kRowsInFlight; ++r) {
             const int s = s0 + r * groups + grp;
-            raw[r] = make_uint4(0u, 0u, 0u, 0u);
             if (s < S) raw[r] = *reinterpret_cast<const uint4 *>(k + ((size_t)s * H + h) * d + sub * 8);
         }
 #pragma unroll
         for (int r = 0; r < kRowsInFlight; ++r) {
             const int s = s0 + r * groups + grp;
+            if (s0 + r * groups >= S) break;      // (uniform)
             const __half2 *h2 = reinterpret_cast<const __half2 *>(&raw[r]);
             float acc = 0.f;
 #pragma unroll
@@ -658,7 +688,21 @@ __global__ __launch_bounds__(256) void attn_head_kernel(const __half *__restrict
                 acc = fmaf(qf[2 * i], f.x, acc);
                 acc = fmaf(qf[2 * i + 1], f.y, acc);
             }
-            for (int o = lp >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+            // the lane group's sum in every lane, partners 8, 4, 2, 1 apart, without LDS permutes: once the step by 8 has made
+            // the lanes of a row repeat every 8, 4 back is 4 across, and so on; in groups of 8 the partner 4 across is the
+            // mirror image's mirror image within its quad
+            if (lp == 16) {
+                acc += dpp_move_f<0x128>(acc);
+                acc += dpp_move_f<0x124>(acc);
+                acc += dpp_move_f<0x122>(acc);
+                acc += dpp_move_f<0x121>(acc);
+            } else if (lp == 8) {
+                acc += dpp_move_f<0x1B>(dpp_move_f<kDppHalfMirror>(acc));
+                acc += dpp_move_f<kDppXor2>(acc);
+                acc += dpp_move_f<kDppXor1>(acc);
+            } else {
+                for (int o = lp >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+            }
             if (s < S && sub == 0) logits[s] = acc * inv_sqrt_d;
         }
     }
@@ -713,6 +757,20 @@ size_t attn_scores_workspace_bytes(int batch, int H, int n_vis)
     return score_counter_bytes(batch) + (size_t)batch * H * n_vis * sizeof(float);
 }
 
+// A round of loads is a trip to memory that everything else waits for: 18 rows per lane group take the 276 keys of an
+// observation with heads of 128 in one round (16 observations x 32 heads: 11.6 us; 8 rows, three rounds: 15.6; one observation
+// 8.0 and 12.4), 9 where that is enough (8 x 8 tokens, heads of 64: 5.2 and 6.5).
+static void launch_attn_head(const __half *q, const __half *k, int batch, int S, int H, int d, int vis_begin, int n_vis,
+                             float *scores, unsigned int *counters, float *weights, hipStream_t st)
+{
+    if (S <= 9 * (2048 / d))
+        hipLaunchKernelGGL(attn_head_kernel<9>, dim3(H, batch), dim3(256), 0, st, q, k, S, H, d, vis_begin, n_vis, scores,
+                           counters, weights);
+    else
+        hipLaunchKernelGGL(attn_head_kernel<18>, dim3(H, batch), dim3(256), 0, st, q, k, S, H, d, vis_begin, n_vis, scores,
+                           counters, weights);
+}
+
 sqap_status launch_attn_scores(const __half *q, const __half *k, int batch, int S, int H, int d,
                                int vis_begin, int n_vis, float *scores, void *workspace, size_t workspace_bytes,
                                hipStream_t st)
@@ -720,8 +778,7 @@ sqap_status launch_attn_scores(const __half *q, const __half *k, int batch, int 
     if (score_fast_path(q, k, S, d) && workspace && workspace_bytes >= attn_scores_workspace_bytes(batch, H, n_vis)) {
         unsigned int *counters = reinterpret_cast<unsigned int *>(workspace);
         float *weights = reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(workspace) + score_counter_bytes(batch));
-        hipLaunchKernelGGL(attn_head_kernel, dim3(H, batch), dim3(256), 0, st, q, k, S, H, d, vis_begin, n_vis, scores,
-                           counters, weights);
+        launch_attn_head(q, k, batch, S, H, d, vis_begin, n_vis, scores, counters, weights, st);
     } else {
         for (int b = 0; b < batch; ++b)
             hipLaunchKernelGGL(attn_scores_kernel, dim3(1), dim3(64 * kScoreWaves), n_vis * sizeof(float), st,
@@ -781,8 +838,7 @@ sqap_status launch_attn_scores_noalloc(const __half *q, const __half *k, int bat
     // counter lines of THIS call's batch, which all lie inside the kNoAllocMaxBatch lines that are kept zero.
     unsigned int *counters = reinterpret_cast<unsigned int *>(ptr);
     float *weights = reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(ptr) + kNoAllocCounterBytes);
-    hipLaunchKernelGGL(attn_head_kernel, dim3(H, batch), dim3(256), 0, st, q, k, S, H, d, vis_begin, n_vis, scores,
-                       counters, weights);
+    launch_attn_head(q, k, batch, S, H, d, vis_begin, n_vis, scores, counters, weights, st);
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }

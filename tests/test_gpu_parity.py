@@ -202,6 +202,17 @@ def test_prune_select(G, oracle, gw, gh, batch, k_attn, total, radius, with_cam)
         assert np.all(idx[b, cnt[b]:] == -1)
 
 
+@pytest.mark.parametrize("gw,gh,k_attn,total", [(1024, 1, 0, 1024), (1, 1024, 3, 700), (33, 31, 0, 1000), (7, 9, 0, 63), (257, 3, 100, 700),
+                                                (64, 1, 64, 64), (5, 13, 64, 65), (32, 32, 1000, 1001)])
+def test_prune_select_thin_grids_and_full_sets(G, oracle, gw, gh, k_attn, total):
+    """The longest distances a grid of 1024 tokens has, sampling from an empty set up to every token, one pick to make."""
+    s = wl.scores(3, gw * gh, wl.rng_for(99, gw * 1000 + gh, wl.T_SCORES, extra=k_attn))
+    idx, cnt = _gpu_select(G, s, gw, gh, k_attn, total, None, 0)
+    want = _oracle_select(oracle, s, gw, gh, k_attn, total, None, 0)
+    for b in range(3):
+        assert cnt[b] == len(want[b]) and np.array_equal(idx[b, : cnt[b]], want[b]), b
+
+
 def test_prune_select_projection_edge_cases(G, oracle):
     """Points on patch borders, outside the image, behind the camera: the token is decided in binary64
     on both sides, so the sets agree exactly."""
