@@ -4,6 +4,8 @@
 // these follow the published architecture (Su et al. 2021 in the half-split pairing used by
 // Llama; Vaswani et al. 2017).  Attention of head sizes 64 and 128 runs on the matrix cores (attention.hip); the small
 // head sizes take binary32 FMAs over LDS tiles with an online softmax, here.
+#include <algorithm>
+
 #include "common.h"
 #include "quant_math.h"
 #include "decode_attn.h"
@@ -67,18 +69,99 @@ __global__ __launch_bounds__(256) void rope_append_kernel(__half *__restrict__ Q
     dst[i + half_d] = r1;
 }
 
+// The same in 16-byte pieces, for head sizes that are a power of two from 16 to 256 and rows that lie 16 bytes aligned: a
+// workgroup takes one token (or a share of its heads, where tokens are few), evaluates the d/2 angles of its position
+// once and shares sines and cosines through LDS; a thread keeps the eight pairs of its piece in registers and rotates that
+// piece of head after head, two 16-byte loads and stores each, the first head's asked for before the angles.
+// APPEND: slots 0 .. H-1 queries, H .. 2H-1 keys (into the cache), 2H .. 3H-1 values (copied).
+// What bounds it: memory with many tokens (77 MB at 2368 tokens x 64 heads of 128, 15 us at the rate of a copy), the sine
+// and cosine with few.  Measured (us): 2368 tokens 15.1 (one pair per thread and step: 26.2), 148 with append 3.4 (5.9).
+// Below kRopePiecesFrom pairs a thread per pair is quicker (8 tokens, 32 heads of 128, append: 2.4 against 2.7).
+template <bool APPEND>
+__global__ __launch_bounds__(256) void rope_pieces_kernel(__half *__restrict__ X, int64_t ld, const int32_t *__restrict__ pos, int H,
+                                                          int d, double base, __half *__restrict__ KV, int64_t ldkv,
+                                                          const RopeFreq freq)
+{
+    __shared__ double cs[kRopeTableMax], sn[kRopeTableMax];
+    const int half_d = d >> 1, s = blockIdx.x, t = threadIdx.x;
+    const int pieces = half_d >> 3, piece = t & (pieces - 1);         // (a power of two)
+    const int slots = APPEND ? 3 * H : H, step = 256 / pieces * gridDim.y;
+    int slot = t / pieces + 256 / pieces * blockIdx.y;
+    __half *row = X + (int64_t)s * ld + piece * 8;
+    union Piece { sqap_v4u v; __half2 h[4]; };
+    Piece lo, hi;
+    lo.v = hi.v = sqap_v4u{0u, 0u, 0u, 0u};
+    auto fetch = [&] {
+        lo.v = *reinterpret_cast<const sqap_v4u *>(row + (int64_t)slot * d);
+        hi.v = *reinterpret_cast<const sqap_v4u *>(row + (int64_t)slot * d + half_d);
+    };
+    if (slot < slots) fetch();
+    if (t < half_d) {
+        double sv, cv;
+        sincos(rope_angle(freq, pos[s], t, d, base), &sv, &cv);
+        sn[t] = sv;
+        cs[t] = cv;
+    }
+    __syncthreads();
+    double c8[8], s8[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        c8[e] = cs[piece * 8 + e];
+        s8[e] = sn[piece * 8 + e];
+    }
+    while (slot < slots) {
+        __half *to = !APPEND || slot < H ? row + (int64_t)slot * d : KV + (int64_t)s * ldkv + (int64_t)(slot - H) * d + piece * 8;
+        if (!APPEND || slot < 2 * H) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const float2 a = __half22float2(lo.h[p]), b = __half22float2(hi.h[p]);
+                const double a0 = (double)a.x, a1 = (double)a.y, b0 = (double)b.x, b1 = (double)b.y;
+                lo.h[p] = __halves2half2(__float2half_rn((float)(a0 * c8[2 * p] - b0 * s8[2 * p])),
+                                         __float2half_rn((float)(a1 * c8[2 * p + 1] - b1 * s8[2 * p + 1])));
+                hi.h[p] = __halves2half2(__float2half_rn((float)(b0 * c8[2 * p] + a0 * s8[2 * p])),
+                                         __float2half_rn((float)(b1 * c8[2 * p + 1] + a1 * s8[2 * p + 1])));
+            }
+        }
+        *reinterpret_cast<sqap_v4u *>(to) = lo.v;
+        *reinterpret_cast<sqap_v4u *>(to + half_d) = hi.v;
+        slot += step;
+        if (slot < slots) fetch();
+    }
+}
+
+constexpr int kRopePiecesFrom = 1 << 17;
+
+template <bool APPEND>
+static bool launch_rope_pieces(__half *X, int64_t ld, const int32_t *pos, int S, int H, int d, double base, __half *KV,
+                               int64_t ldkv, hipStream_t st)
+{
+    if (d < 16 || d > 2 * kRopeTableMax || (d & (d - 1)) != 0 || (ld & 7) != 0 || (reinterpret_cast<uintptr_t>(X) & 15u) != 0) return false;
+    if (APPEND && ((ldkv & 7) != 0 || (reinterpret_cast<uintptr_t>(KV) & 15u) != 0)) return false;
+    if ((int64_t)S * (APPEND ? 3 * H : H) * (d / 2) < kRopePiecesFrom) return false;
+    // few tokens: a token's heads are dealt to as many workgroups as they fill, up to four per compute unit in all
+    const int rounds = ((APPEND ? 3 * H : H) * (d / 16) + 255) / 256;
+    const int shares = S >= 1024 ? 1 : std::min(rounds, std::min(64, 1024 / S + 1));
+    hipLaunchKernelGGL(rope_pieces_kernel<APPEND>, dim3(S, shares), dim3(256), 0, st, X, ld, pos, H, d, base, KV, ldkv,
+                       rope_frequencies(d, base));
+    return true;
+}
+
 sqap_status launch_rope_append(__half *QKV, int64_t ld, const int32_t *pos, int S, int H, int d, double base,
                                __half *KV, int64_t ldkv, hipStream_t st)
 {
     const int64_t total = (int64_t)S * 3 * H * (d / 2);
     if (total == 0) return SQAP_OK;
+    if (launch_rope_pieces<true>(QKV, ld, pos, S, H, d, base, KV, ldkv, st)) {
+        SQAP_HIP_CHECK(hipGetLastError());
+        return SQAP_OK;
+    }
     hipLaunchKernelGGL(rope_append_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, QKV, ld, pos, S, H, d,
                        base, KV, ldkv, rope_frequencies(d, base));
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }
 
-// The same for many tokens: one workgroup per token evaluates the d/2 angles of its position once (the
+// Any other head size or alignment, many tokens: one workgroup per token evaluates the d/2 angles of its position once (the
 // binary64 power, sine and cosine are a few hundred instructions per pair) and shares them between the
 // heads through LDS.  With few tokens the per-pair kernel is faster (more threads in flight: 6.7 against
 // 8.8 us at 84 tokens); at 2368 tokens this one takes a tenth of its time.
@@ -113,6 +196,10 @@ sqap_status launch_rope(__half *X, int64_t ld, const int32_t *pos, int S, int H,
 {
     const int64_t total = (int64_t)S * H * (d / 2);
     if (total == 0) return SQAP_OK;
+    if (launch_rope_pieces<false>(X, ld, pos, S, H, d, base, nullptr, 0, st)) {
+        SQAP_HIP_CHECK(hipGetLastError());
+        return SQAP_OK;
+    }
     if (S >= kRopeTokenKernelFrom && d / 2 <= kRopeMaxHalfD) {
         hipLaunchKernelGGL(rope_token_kernel, dim3(S), dim3(256), 0, st, X, ld, pos, H, d, base, rope_frequencies(d, base));
         SQAP_HIP_CHECK(hipGetLastError());
