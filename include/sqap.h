@@ -461,8 +461,9 @@ sqap_status sqap_selftest_dispatch(uint32_t *xcc_of_block_out, void *stream);
 sqap_status sqap_set_persistent_kernels(int32_t enabled);
 
 /*
- * Which kernel sqap_w4a4_linear uses for 8 < M < 512 with K a multiple of 256 (and at least 1024): 1, the
- * default, the kernel in which every workgroup owns complete outputs and nothing passes between
+ * Which kernel sqap_w4a4_linear uses for M > 8 where the outputs are few enough for every workgroup to own complete
+ * ones (any K; M up to 2560 rows, fewer the more channels there are): 1, the
+ * default, the kernel that does so, in which nothing passes between
  * workgroups (it needs no workspace); 0 the tile kernels that split K between workgroups and exchange
  * partial sums through the workspace (which other shapes always use).  Same results bit for bit; process
  * wide; for tests and measurement.  sqap_workspace_bytes reports what the second kind needs either way.

@@ -165,10 +165,10 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
                                __half *Y, int64_t ldy, int32_t *acc_out, void *workspace,
                                hipStream_t st);
 
-// Few hundred token rows, K a multiple of 256: every workgroup owns complete outputs (gemm_rows.hip)
+// Few outputs per compute unit: every workgroup owns complete ones (gemm_rows.hip)
 bool rows_kernel_applies(int M, int N, int K);
 sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, const Weight &w, __half *Y, int64_t ldy,
-                               int32_t *acc_out, hipStream_t st);
+                               int32_t *acc_out, unsigned long long *error_word, hipStream_t st);
 void set_mid_m_kernel(int which);        // 0: tiles split along K between workgroups, 1: whole outputs per workgroup
 
 sqap_status launch_rope(__half *X, int64_t ld, const int32_t *pos, int S, int H, int d, double base, hipStream_t st);

@@ -1456,9 +1456,10 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
     p.n_groups = w.n_groups;
     p.chunks = w.chunks;
     p.y_vec_ok = (reinterpret_cast<uintptr_t>(Y) & 15u) == 0 && (ldy & 7) == 0;
-    // A few hundred token rows: whole outputs per workgroup, nothing exchanged between workgroups
-    if (M < kStreamKMinM && g_mid_m_kernel.load(std::memory_order_relaxed) == 1 && rows_kernel_applies(M, w.N, w.K))
-        return launch_rows_linear(Xq, sx, M, w, Y, ldy, acc_out, st);
+    // Few enough outputs per compute unit: whole outputs per workgroup, nothing exchanged between workgroups
+    if (g_mid_m_kernel.load(std::memory_order_relaxed) == 1 && rows_kernel_applies(M, w.N, w.K))
+        return launch_rows_linear(Xq, sx, M, w, Y, ldy, acc_out,
+                                  w.K % kBK == 0 && workspace ? reinterpret_cast<unsigned long long *>(workspace) + kErrWord : nullptr, st);
     if (w.K % kBK == 0 && persistent_allowed()) {
         if (M >= kStreamKMinM) return launch_streamk<CfgBig, false>(p, workspace, st);
         // Narrow tiles.  With few tiles, each is shared by many workgroups (256 / tiles of them) and

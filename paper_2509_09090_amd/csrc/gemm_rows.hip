@@ -1,4 +1,4 @@
-// W4A4 linear for a few hundred token rows (8 < M <= 640): every workgroup owns complete outputs.
+// W4A4 linear for a few hundred token rows (and for more where the channels are few): every workgroup owns complete outputs.
 //
 // At these sizes the output is too small to fill the machine with whole 256 x 256 tiles, and splitting K
 // between workgroups costs a chain of global round trips (partial store, flag, reduction) that is longer
@@ -49,9 +49,10 @@ struct RowsParams {
     int64_t ldy;
     int M, N, K, chunks;
     int c16;               // 16-channel groups: ceil(N / 16)
-    int tblocks;           // blocks of token rows (1, 2 or 4)
+    int tblocks;           // blocks of token rows (1, 2, 4, 8 or 16)
     int rows_per_block;    // multiple of 16, at most 16 * kRowsMaxA
     int per_xcd;           // workgroups of an XCD that share its channel groups, per token block
+    unsigned long long *error_word;        // of the caller's workspace, nullable: cleared (no wait can fail here)
 };
 
 __device__ __forceinline__ void widen16(const v4i p, v4i &lo, v4i &hi)
@@ -81,7 +82,9 @@ __device__ __forceinline__ uint32_t dequant_pair(int acc0, int acc1, float sx_ov
 // (with loads under run-time conditions it waits for all of them, i.e. for a full memory round trip per
 // token group).  Token groups are taken two at a time so that consecutive products go to different
 // accumulators, and the next pair's operands are read from LDS before the current pair is multiplied.
-template <int AH, int B>
+// RAGGED: K is any multiple of 32.  The last step then ends inside its 256 codes: token pieces past K are put into the slab as
+// zeros (and weight pieces past K are any others), and a wavefront may have no step at all.
+template <int AH, int B, bool RAGGED>
 __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, int row0, int row_end, int c0)
 {
     static_assert(AH >= 1 && AH <= kRowsMaxAH && B >= 1 && B <= kRowsMaxB, "tile shape");
@@ -90,12 +93,12 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int kq = wave & 3, th = wave >> 2;
     const int Kh = p.K >> 1;
-    const int steps = p.K / kRowsStepCodes;
+    const int steps = RAGGED ? (p.K + kRowsStepCodes - 1) / kRowsStepCodes : p.K / kRowsStepCodes;
     const int s_begin = steps * kq / 4, s_end = steps * (kq + 1) / 4;
     // The wavefront takes its steps in rotated order, starting at a step that depends on the workgroup: all
     // workgroups of an XCD read the same token rows, and walking K in step they would all ask the same one
     // or two L2 channels for the same lines at the same time.
-    const int nst = s_end - s_begin, rot = (int)(blockIdx.x >> 3) % nst;
+    const int own = s_end - s_begin, nst = RAGGED ? max(own, 1) : own, rot = (int)(blockIdx.x >> 3) % nst;
     auto step_of = [&](int i) {                                     // i-th step of this wavefront (i past the end: the last)
         int v = min(i, nst - 1) + rot;
         if (v >= nst) v -= nst;
@@ -108,13 +111,16 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
     // offset of this lane's piece in load i: (wrow0 + 8 i + lane / 8) * Kh + 16 * (lane % 8); rows past M - 1
     // re-read row M - 1 (never stored): one addition and one minimum per load instead of a pointer per load.
     const int lr = lane >> 3, piece = lane & 7;
-    const uint32_t xoff0 = (uint32_t)(wrow0 + lr) * (uint32_t)Kh + piece * 16;
-    const uint32_t xlimit = (uint32_t)(p.M - 1) * (uint32_t)Kh + piece * 16;
+    const uint32_t xoff0 = (uint32_t)(wrow0 + lr) * (uint32_t)Kh + (RAGGED ? 0 : piece * 16);
+    const uint32_t xlimit = (uint32_t)(p.M - 1) * (uint32_t)Kh + (RAGGED ? 0 : piece * 16);
     const uint8_t *xbase = p.Xq;
     auto x_ptr = [&](int i, int step) {           // uniform base + 32-bit lane offset: no 64-bit lane arithmetic
         const uint32_t off = min(xoff0 + (uint32_t)(i * 8) * (uint32_t)Kh, xlimit);
+        if (RAGGED) return reinterpret_cast<const v4i *>(xbase + (off + (uint32_t)min(step * 8 + piece, p.chunks - 1) * 16));
         return reinterpret_cast<const v4i *>(xbase + (size_t)step * 128 + off);
     };
+    // what goes into the slab of a row piece loaded for `step`
+    auto slab_piece = [&](const v4i v, int step) { return !RAGGED || step * 8 + piece < p.chunks ? v : v4i{0, 0, 0, 0}; };
     const int xdst = lr * kRowsPitch + piece * 16;                 // + i * 8 * pitch
     // operand order: lane l reads token l % 16, piece l / 16 (+ 4 for the second K-block of a step)
     const int xfrag = (lane & 15) * kRowsPitch + (lane >> 4) * 16;
@@ -146,7 +152,8 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
         constexpr int set = decltype(set_c)::value, q = decltype(q_c)::value;
 #pragma unroll
         for (int j = 0; j < B; ++j)
-            wr[set][q][j] = *reinterpret_cast<const v4i *>(wbase[j] + (size_t)(step * 8 + q * 4) * 512 + woff);
+            wr[set][q][j] = RAGGED ? *reinterpret_cast<const v4i *>(wbase[j] + (uint32_t)min(step * 8 + q * 4 + (lane >> 4), p.chunks - 1) * 512 + (lane & 15) * 16)
+                                   : *reinterpret_cast<const v4i *>(wbase[j] + (size_t)(step * 8 + q * 4) * 512 + woff);
     };
     auto read_pair = [&](int ip, int q, v4i (&dst)[2]) {
 #pragma unroll
@@ -164,7 +171,7 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
     load_w(step_of(1), c1_, c0_);
     load_w(step_of(1), c1_, c1_);
 #pragma unroll
-    for (int i = 0; i < 2 * AH; ++i) *reinterpret_cast<v4i *>(slab + i * 8 * kRowsPitch + xdst) = xr[i];
+    for (int i = 0; i < 2 * AH; ++i) *reinterpret_cast<v4i *>(slab + i * 8 * kRowsPitch + xdst) = slab_piece(xr[i], step_of(0));
     load_x(step_of(1));
     read_pair(0, 0, xf);
 
@@ -172,7 +179,8 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
     auto step_body = [&](int i, auto par_c) {
         constexpr int PAR = decltype(par_c)::value;
         constexpr std::integral_constant<int, PAR> cur{};
-        const int s2 = step_of(i + 2);
+        const int s1 = step_of(i + 1), s2 = step_of(i + 2);
+        (void)s1;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             v4i wl[B], wh[B];
@@ -208,7 +216,7 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
                         if (4 * ip + r < 2 * AH) {
-                            *reinterpret_cast<v4i *>(slab + (4 * ip + r) * 8 * kRowsPitch + xdst) = xr[4 * ip + r];
+                            *reinterpret_cast<v4i *>(slab + (4 * ip + r) * 8 * kRowsPitch + xdst) = slab_piece(xr[4 * ip + r], s1);
                             xr[4 * ip + r] = *x_ptr(4 * ip + r, s2);
                         }
                 }
@@ -221,11 +229,11 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
         read_pair(0, 0, xf);                         // the next step's first pair (its rows were stored above)
     };
     int i = 0;
-    for (; i + 1 < nst; i += 2) {
+    for (; i + 1 < own; i += 2) {
         step_body(i, c0_);
         step_body(i + 1, c1_);
     }
-    if (i < nst) step_body(i, c0_);
+    if (i < own) step_body(i, c0_);
 
     // add the accumulators of the four wavefronts that share a token half through LDS; wavefront (kq, th)
     // finishes tiles kq, kq + 4, ... of its half
@@ -285,10 +293,11 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
 // contiguous runs, and inside an XCD to `per_xcd` workgroups per token block, so that the workgroups that
 // read the same weights (one per token block) sit behind one L2.  AH = 16-token groups per wavefront: a
 // block has 2 AH of them (rows past the block re-read other rows and are never stored).
-template <int AH>
+template <int AH, bool RAGGED>
 __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const RowsParams p)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && p.error_word) *p.error_word = 0ull;
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     const int tb = j % p.tblocks, slot = j / p.tblocks;
     if (slot >= p.per_xcd) return;
@@ -301,9 +310,9 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const Row
     const int n = g_end - g_begin, tiles = (n + kRowsMaxB - 1) / kRowsMaxB;
     for (int k = 0; k < tiles; ++k) {
         const int c0 = g_begin + n * k / tiles, b = g_begin + n * (k + 1) / tiles - c0;
-        if (b == 3) rows_tile<AH, 3>(p, smem, row0, row_end, c0);
-        else if (b == 2) rows_tile<AH, 2>(p, smem, row0, row_end, c0);
-        else rows_tile<AH, 1>(p, smem, row0, row_end, c0);
+        if (b == 3) rows_tile<AH, 3, RAGGED>(p, smem, row0, row_end, c0);
+        else if (b == 2) rows_tile<AH, 2, RAGGED>(p, smem, row0, row_end, c0);
+        else rows_tile<AH, 1, RAGGED>(p, smem, row0, row_end, c0);
     }
 }
 
@@ -311,17 +320,23 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const Row
 // of its own (each workgroup then reads fewer token rows, and the weights are read once per block, the
 // second time from the L2).  Cost of a workgroup in clock cycles: what its compute unit loads at 64 bytes
 // per cycle against what its matrix cores multiply (a 16 x 16 x 64 product takes 16 cycles on one of four SIMDs).
-// Only plans in which a workgroup's channel groups fit ONE tile are taken: a second tile reads the token
-// rows again and pays the start-up of the load pipeline again, and measured slower than the tile kernels
-// that split K between workgroups (N = 22016 at M = 148: 28.6 against 28.3 us; N = 32000: 42 against 30 us),
-// while single-tile shapes measured 25-45 % faster (N = 4096: 9.1 against 15.0 us, N = 12288: 15.7 against
-// 20.8 us, K = 11008: 15.2 against 22.1 us, all at M = 148).
+// Plans in which a workgroup's channel groups fit ONE tile are always taken: 25-45 % faster than the tile kernels
+// that split K between workgroups at a few hundred rows (M = 148: N = 4096 9.1 against 15.0 us, N = 12288 15.7 against
+// 20.8, K = 11008 15.2 against 22.1), more where those have few tiles or a K that is no multiple of 128 (us, M x N x K:
+// 522 x 1024 x 2816 8.2 against 25.4; 2000 x 700 x 5504 19.2 against 46.4; 148 x 2048 x 5504 10.2 against 16.5;
+// 32 x 512 x 512 3.5 against 7.8; 450 x 300 x 4160 9.1 against 57).  A second tile reads the token rows again and pays the
+// start-up of the load pipeline again: worth it up to 64 rows (64 x 22016 x 4096 17.5 against 19.7, 16 rows 12.9 against
+// 18.3; 84 rows 21.6 against 20.9), where the 256 x 256 tiles are few (four groups: 600 x 4096 x 4096 23.4 against 31.2,
+// 2368 x 1024 x 4096 25.1 against 31.3), and against the tiles with a guarded K (six groups, M > 160: 300 x 12288 x 4160 33.9
+// against 50.7, 1200 x 3000 x 4160 33.1 against 50.6; eight at K = 1088: 600 x 8000 25.4 against 17.8); not at
+// 160 < M < 512 otherwise (276 x 8192 x 4096 23.0 against 19.7) nor with K below 1024 (600 x 4096 x 512 12.4 against 11.0).
 static bool rows_plan(int M, int N, int K, int cus, RowsParams *p)
 {
-    if (M <= kSkinnyMaxM || K % kRowsStepCodes != 0 || K / kRowsStepCodes < 4 || N < 16) return false;
+    if (M <= kSkinnyMaxM || K % 32 != 0 || N < 16) return false;
     const int c16 = (N + 15) / 16;
+    const int max_groups = K < 1024 ? kRowsMaxB : K % 128 != 0 && M > 160 && K >= 2048 ? 6 : M <= 64 ? 6 : M >= 512 ? 4 : kRowsMaxB;
     double best = 0.0;
-    for (int tb = 1; tb <= 4; tb *= 2) {
+    for (int tb = 1; tb <= 16; tb *= 2) {
         const int rows = ((M + tb - 1) / tb + 15) / 16 * 16;
         if (rows > 16 * kRowsMaxA) continue;
         const int a = (rows / 16 + 1) & ~1;                     // two wavefront halves of equal size
@@ -329,7 +344,7 @@ static bool rows_plan(int M, int N, int K, int cus, RowsParams *p)
         if (per_xcd < 1) per_xcd = 1;
         const int W = 8 * per_xcd;
         const int n = (c16 + W - 1) / W;
-        if (n > kRowsMaxB) continue;                            // more than one tile per workgroup
+        if (n > max_groups) continue;
         const double bytes = (a * 16.0 + 2 * 16.0 * n) * (K / 2);
         const double mfma = (double)a * n * (K / 128) * 2 * 16 / 4;
         const double cost = std::max(bytes / 64.0, mfma / 0.7);
@@ -350,31 +365,37 @@ static int rows_cus()
     return cus > 256 ? 256 : cus < 8 ? 8 : cus;
 }
 
-// Shapes this kernel takes: K a multiple of 256 with at least one step per wavefront, up to four blocks of 160
-// token rows, and few enough channels that every workgroup has a single tile.
+// Shapes this kernel takes: up to sixteen blocks of 160 token rows, and few enough channels per workgroup.
 bool rows_kernel_applies(int M, int N, int K)
 {
     RowsParams p = {};
     return rows_plan(M, N, K, rows_cus(), &p);
 }
 
-template <int AH>
-static sqap_status launch_rows_a(const RowsParams &p, int blocks, hipStream_t st)
+template <int AH, bool RAGGED>
+static sqap_status launch_rows_k(const RowsParams &p, int blocks, hipStream_t st)
 {
     static std::atomic<bool> configured[kMaxDeviceSlots];
     const int dslot = device_slot();
     if (!configured[dslot].load(std::memory_order_acquire)) {
-        SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_rows_kernel<AH>),
+        SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_rows_kernel<AH, RAGGED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLdsBytes));
         configured[dslot].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((gemm_rows_kernel<AH>), dim3(blocks), dim3(64 * kRowsWaves), kRowsLdsBytes, st, p);
+    hipLaunchKernelGGL((gemm_rows_kernel<AH, RAGGED>), dim3(blocks), dim3(64 * kRowsWaves), kRowsLdsBytes, st, p);
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }
 
+template <int AH>
+static sqap_status launch_rows_a(const RowsParams &p, int blocks, hipStream_t st)
+{
+    if (p.K % kRowsStepCodes == 0 && p.K / kRowsStepCodes >= 4) return launch_rows_k<AH, false>(p, blocks, st);
+    return launch_rows_k<AH, true>(p, blocks, st);
+}
+
 sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, const Weight &w, __half *Y, int64_t ldy,
-                               int32_t *acc_out, hipStream_t st)
+                               int32_t *acc_out, unsigned long long *error_word, hipStream_t st)
 {
     RowsParams p = {};
     p.Xq = Xq;
@@ -388,6 +409,7 @@ sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, const
     p.N = w.N;
     p.K = w.K;
     p.chunks = w.chunks;
+    p.error_word = error_word;
     if (!rows_plan(M, w.N, w.K, rows_cus(), &p))
         return fail(SQAP_EUNSUPPORTED, "sqap_w4a4_linear: M = %d, N = %d, K = %d outside the row kernel's range", M, w.N, w.K);
     const int blocks = 8 * p.per_xcd * p.tblocks;

@@ -256,6 +256,23 @@ def test_whole_output_kernel_edge_shapes(G, oracle, M, N, K):
     assert G.assert_fp16_close(Y, Yo) == 0
 
 
+# K that ends inside a step of 256 codes or is shorter than the four wavefronts' shares (some get no step), up to sixteen
+# blocks of token rows, several tiles per workgroup; the shapes on both sides of every line of the rule.
+@pytest.mark.parametrize("M,N,K", [(9, 16, 32), (20, 100, 64), (33, 48, 96), (17, 256, 256), (32, 512, 512), (70, 77, 736), (148, 512, 1408),
+                                   (161, 300, 1056), (100, 512, 5504), (300, 33, 4160), (641, 100, 1280), (1300, 64, 288), (2560, 16, 544),
+                                   (2561, 16, 256), (64, 12800, 1024), (65, 12800, 1024), (600, 3100, 1024), (512, 3100, 992), (170, 9000, 2080)])
+def test_whole_output_kernel_any_k(G, oracle, M, N, K):
+    rng = np.random.default_rng(M + N * 3 + K)
+    Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
+    sx = (rng.random(M) * 2 + 0.01).astype(np.float16)
+    sw = (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
+    Y, acc, err = _linear_with_error_word(G, Xq, sx, Wq, sw, pitch_extra=0 if N % 8 else 24)
+    Yo, acco = oracle.w4a4_linear(Xq, sx, Wq, sw)
+    assert err == 0                       # cleared by whichever kernel ran
+    assert np.array_equal(acc, acco)
+    assert G.assert_fp16_close(Y, Yo) == 0
+
+
 @pytest.mark.parametrize("M", [1, 8])
 def test_config4_decode_headline_launch(G, oracle, M):
     """The launch bench.py times for configuration 4: ONE group launch over the seven 7B-shaped linears of 16
