@@ -461,11 +461,11 @@ sqap_status sqap_selftest_dispatch(uint32_t *xcc_of_block_out, void *stream);
 sqap_status sqap_set_persistent_kernels(int32_t enabled);
 
 /*
- * Which kernel sqap_w4a4_linear uses for M > 8 where the outputs are few enough for every workgroup to own complete
- * ones (any K; M up to 2560 rows, fewer the more channels there are): 1, the
- * default, the kernel that does so, in which nothing passes between
+ * Which kernel sqap_w4a4_linear uses where the outputs are few enough for every workgroup to own complete
+ * ones (any K; M up to 2560 rows, fewer the more channels there are), for M <= 8 too, and for sqap_group_run of up to four
+ * problems that share their input: 1, the default, the kernel that does so, in which nothing passes between
  * workgroups (it needs no workspace); 0 the tile kernels that split K between workgroups and exchange
- * partial sums through the workspace (which other shapes always use).  Same results bit for bit; process
+ * partial sums through the workspace, or for M <= 8 the weight-streaming kernel (which other shapes always use).  Same results bit for bit; process
  * wide; for tests and measurement.  sqap_workspace_bytes reports what the second kind needs either way.
  * Always SQAP_OK.
  */
@@ -533,7 +533,8 @@ sqap_status sqap_group_create(const sqap_linear_desc *descs, int32_t count, sqap
 sqap_status sqap_group_run(const sqap_group *g, void *stream);
 
 /*
- * How sqap_group_run will launch a group (host arithmetic only; no GPU work): the number of problems and of
+ * How sqap_group_run launches a group with the weight-streaming kernel (all groups but those of up to four
+ * problems with one input, see sqap_set_mid_m_kernel; host arithmetic only; no GPU work): the number of problems and of
  * row groups (32 output channels each) in it, and the form of the small-M kernel the launch takes on a
  * device with `compute_units` compute units (0: the current device): wavefronts that share one row
  * group along K (1, 2, 4 or 8), wavefronts per workgroup (8, or 16 for launches in which every wavefront

@@ -596,7 +596,7 @@ sqap_status sqap_w4a4_linear(const uint8_t *Xq, const sqap_f16 *sx, int32_t M,
         if (reinterpret_cast<uintptr_t>(workspace) & 255u)
             return fail(SQAP_EINVAL, "sqap_w4a4_linear: workspace must be 256-byte aligned");
     }
-    if (M <= kSkinnyMaxM && w->K % 64 == 0) {
+    if (M <= kSkinnyMaxM && w->K % 64 == 0 && !(rows_kernel_wanted() && rows_kernel_applies(M, (w->N + 15) / 16, w->K))) {
         SkinnyArgs a = {};
         a.table = nullptr;
         a.count = 1;
@@ -721,6 +721,19 @@ sqap_status sqap_group_create(const sqap_linear_desc *descs, int32_t count, sqap
         return fail(SQAP_ENOMEM, "sqap_group_create: host allocation failed");
     }
     g->magic = kGroupMagic;
+    if (count <= kRowsMaxWeights) {                  // problems that share their input can be one product over all their channels
+        g->rows_count = count;
+        g->rows_Xq = host[0].Xq;
+        g->rows_sx = host[0].sx;
+        g->rows_M = host[0].M;
+        g->rows_K = host[0].chunks * 32;
+        for (int i = 0; i < count; ++i) {
+            const SkinnyEntry &e = host[i];
+            g->rows[i] = {e.Wd, e.sw, e.Y, e.acc_out, e.ldy, e.N, 0};
+            g->rows_groups += (e.N + 15) / 16;
+            if (e.Xq != host[0].Xq || e.sx != host[0].sx || e.M != host[0].M || e.chunks != host[0].chunks) g->rows_count = 0;
+        }
+    }
     g->count = count;
     g->total_items = total;
     g->max_chunks = max_chunks;
@@ -745,6 +758,8 @@ sqap_status sqap_group_run(const sqap_group *g, void *stream)
     const Group *gg = reinterpret_cast<const Group *>(g);
     if (!gg || gg->magic != kGroupMagic) return fail(SQAP_EINVAL, "sqap_group_run: not a group handle");
     const DeviceOfCall device;
+    if (gg->rows_count > 0 && rows_kernel_wanted() && rows_kernel_applies(gg->rows_M, gg->rows_groups, gg->rows_K))
+        return launch_rows_linear(gg->rows_Xq, gg->rows_sx, gg->rows_M, gg->rows_K, gg->rows, gg->rows_count, nullptr, as_stream(stream));
     SkinnyArgs a = {};
     a.table = gg->table;
     a.count = gg->count;

@@ -60,9 +60,25 @@ struct SkinnyArgs {
 };
 constexpr int kSkinnyMaxM = 8;
 
+// One weight of a launch of gemm_rows.hip: up to four share the input rows.
+struct RowsWeight {
+    const uint8_t *Wd;     // streaming layout
+    const __half *sw;      // padded to whole row groups
+    __half *Y;
+    int32_t *acc_out;      // nullable
+    int64_t ldy;
+    int N, g_begin;        // g_begin: first of its 16-channel groups in the launch-wide numbering (set by the launch)
+};
+constexpr int kRowsMaxWeights = 4;
+
 // Device-resident table of small-M problems, run by one launch.
 struct Group {
     uint32_t magic;
+    int rows_count;                        // problems, if they share one input and gemm_rows.hip may run them; 0 otherwise
+    const uint8_t *rows_Xq;
+    const __half *rows_sx;
+    int rows_M, rows_K, rows_groups;
+    RowsWeight rows[kRowsMaxWeights];
     int count, total_items, max_chunks;
     long long total_cost;
     SkinnyEntry *table;   // device
@@ -166,9 +182,10 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
                                hipStream_t st);
 
 // Few outputs per compute unit: every workgroup owns complete ones (gemm_rows.hip)
-bool rows_kernel_applies(int M, int N, int K);
-sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, const Weight &w, __half *Y, int64_t ldy,
-                               int32_t *acc_out, unsigned long long *error_word, hipStream_t st);
+bool rows_kernel_applies(int M, int channel_groups, int K);        // (of 16 channels)
+sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
+                               unsigned long long *error_word, hipStream_t st);
+bool rows_kernel_wanted();
 void set_mid_m_kernel(int which);        // 0: tiles split along K between workgroups, 1: whole outputs per workgroup
 
 sqap_status launch_rope(__half *X, int64_t ld, const int32_t *pos, int S, int H, int d, double base, hipStream_t st);

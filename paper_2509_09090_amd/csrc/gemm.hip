@@ -1057,6 +1057,8 @@ sqap_status probe_dispatch(int device, hipStream_t st, uint32_t *table_out)
 
 static std::atomic<int> g_mid_m_kernel{1};            // 1: gemm_rows_kernel where it applies, 0: the split-K tile kernels
 
+bool rows_kernel_wanted() { return g_mid_m_kernel.load(std::memory_order_relaxed) == 1; }
+
 void set_mid_m_kernel(int which) { g_mid_m_kernel.store(which ? 1 : 0); }
 
 static std::atomic<int> g_persistent_switch{-1};      // -1: follow the environment, 0: off, 1: on
@@ -1456,10 +1458,13 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
     p.n_groups = w.n_groups;
     p.chunks = w.chunks;
     p.y_vec_ok = (reinterpret_cast<uintptr_t>(Y) & 15u) == 0 && (ldy & 7) == 0;
-    // Few enough outputs per compute unit: whole outputs per workgroup, nothing exchanged between workgroups
-    if (g_mid_m_kernel.load(std::memory_order_relaxed) == 1 && rows_kernel_applies(M, w.N, w.K))
-        return launch_rows_linear(Xq, sx, M, w, Y, ldy, acc_out,
-                                  w.K % kBK == 0 && workspace ? reinterpret_cast<unsigned long long *>(workspace) + kErrWord : nullptr, st);
+    // Few enough outputs per compute unit: whole outputs per workgroup, nothing exchanged between workgroups.  (The
+    // error word is only there where the entry point asked for a workspace.)
+    if (rows_kernel_wanted() && rows_kernel_applies(M, (w.N + 15) / 16, w.K)) {
+        const RowsWeight rw = {w.data, w.scales, Y, acc_out, ldy, w.N, 0};
+        const bool has_word = linear_workspace_bytes(M, w.N, w.K) > 0;
+        return launch_rows_linear(Xq, sx, M, w.K, &rw, 1, has_word ? reinterpret_cast<unsigned long long *>(workspace) + kErrWord : nullptr, st);
+    }
     if (w.K % kBK == 0 && persistent_allowed()) {
         if (M >= kStreamKMinM) return launch_streamk<CfgBig, false>(p, workspace, st);
         // Narrow tiles.  With few tiles, each is shared by many workgroups (256 / tiles of them) and

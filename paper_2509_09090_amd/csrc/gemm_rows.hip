@@ -32,6 +32,8 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 constexpr int kRowsMaxAH = 5;          // 16-token groups per wavefront (a block of token rows has twice as many)
 constexpr int kRowsMaxA = 2 * kRowsMaxAH;
 constexpr int kRowsMaxB = 3;           // 16-channel groups per tile
+constexpr int kRowsMaxBFew = 6;        // the same where a wavefront has one token group (AH = 1)
+constexpr int rows_max_b(int ah) { return ah == 1 ? kRowsMaxBFew : kRowsMaxB; }
 constexpr int kRowsWaves = 8;
 constexpr int kRowsStepCodes = 256;    // codes of K per main-loop step of a wavefront (two MFMA K-blocks of 128)
 constexpr int kRowsPitch = 144;        // bytes per slab row: 128 of codes + 16 of padding
@@ -42,18 +44,27 @@ constexpr int kRowsLdsBytes = kRowsReduceBytes > kRowsWaves * kRowsSlabBytes ? k
 struct RowsParams {
     const uint8_t *Xq;     // [M, K/2] canonical
     const __half *sx;      // [M]
-    const uint8_t *Wd;     // streaming layout (see common.h)
-    const __half *sw;      // padded to whole row groups
-    __half *Y;
-    int32_t *acc_out;      // nullable
-    int64_t ldy;
-    int M, N, K, chunks;
-    int c16;               // 16-channel groups: ceil(N / 16)
+    int M, K, chunks;
+    int count;             // weights the input is multiplied with (q, k and v, say): their channel groups follow one another
+    RowsWeight w[kRowsMaxWeights];
+    int c16;               // 16-channel groups in all
     int tblocks;           // blocks of token rows (1, 2, 4, 8 or 16)
     int rows_per_block;    // multiple of 16, at most 16 * kRowsMaxA
     int per_xcd;           // workgroups of an XCD that share its channel groups, per token block
     unsigned long long *error_word;        // of the caller's workspace, nullable: cleared (no wait can fail here)
 };
+
+// the weight that channel group g (of all of them) belongs to.  A single one sits at a fixed place among the kernel's
+// arguments; finding one of several costs a dependent scalar load, 0.5 us at the start of a launch.
+template <bool MULTI>
+__device__ __forceinline__ const RowsWeight &rows_weight(const RowsParams &p, int g)
+{
+    if (!MULTI) return p.w[0];
+    int k = 0;
+#pragma unroll
+    for (int i = 1; i < kRowsMaxWeights; ++i) k = i < p.count && g >= p.w[i].g_begin ? i : k;
+    return p.w[k];
+}
 
 __device__ __forceinline__ void widen16(const v4i p, v4i &lo, v4i &hi)
 {
@@ -84,10 +95,10 @@ __device__ __forceinline__ uint32_t dequant_pair(int acc0, int acc1, float sx_ov
 // accumulators, and the next pair's operands are read from LDS before the current pair is multiplied.
 // RAGGED: K is any multiple of 32.  The last step then ends inside its 256 codes: token pieces past K are put into the slab as
 // zeros (and weight pieces past K are any others), and a wavefront may have no step at all.
-template <int AH, int B, bool RAGGED>
+template <int AH, int B, bool RAGGED, bool MULTI>
 __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, int row0, int row_end, int c0)
 {
-    static_assert(AH >= 1 && AH <= kRowsMaxAH && B >= 1 && B <= kRowsMaxB, "tile shape");
+    static_assert(AH >= 1 && AH <= kRowsMaxAH && B >= 1 && B <= rows_max_b(AH), "tile shape");
     constexpr int PAIRS = (AH + 1) / 2;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -129,8 +140,9 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
     const uint8_t *wbase[B];
 #pragma unroll
     for (int j = 0; j < B; ++j) {
-        const int g = c0 + j;
-        wbase[j] = p.Wd + (size_t)(g >> 1) * p.chunks * 512 + (g & 1) * 256;
+        const RowsWeight &w = rows_weight<MULTI>(p, c0 + j);
+        const int g = c0 + j - w.g_begin;
+        wbase[j] = w.Wd + (size_t)(g >> 1) * p.chunks * 512 + (g & 1) * 256;
     }
     const uint32_t woff = (uint32_t)(lane >> 4) * 512 + (lane & 15) * 16;
 
@@ -246,41 +258,42 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
             *reinterpret_cast<v4i *>(red + ((wave * AH * B + i * B + j) * 64 + lane) * 4) = acc[i][j];
     __syncthreads();
     const int tok_in = lane & 15, ch4 = (lane >> 4) * 4;
-    const bool y_vec = (p.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(p.Y) & 7u) == 0;
-    const bool a_vec = (p.N & 3) == 0 && p.acc_out && (reinterpret_cast<uintptr_t>(p.acc_out) & 15u) == 0;
     for (int tt = kq; tt < AH * B; tt += 4) {
         const int i = tt / B, j = tt - i * B;
         v4i sum = {0, 0, 0, 0};
 #pragma unroll
         for (int w = 0; w < 4; ++w)
             sum += *reinterpret_cast<const v4i *>(red + (((th * 4 + w) * AH * B + tt) * 64 + lane) * 4);
-        const int row = wrow0 + i * 16 + tok_in, col = (c0 + j) * 16 + ch4;
-        if (row < row_end && col < p.N) {
+        const RowsWeight &w = rows_weight<MULTI>(p, c0 + j);
+        const bool y_vec = (w.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(w.Y) & 7u) == 0;
+        const bool a_vec = (w.N & 3) == 0 && w.acc_out && (reinterpret_cast<uintptr_t>(w.acc_out) & 15u) == 0;
+        const int row = wrow0 + i * 16 + tok_in, col = (c0 + j - w.g_begin) * 16 + ch4;
+        if (row < row_end && col < w.N) {
             const float sxf = __half2float(p.sx[row]) * 0.00390625f;
-            const uint2 swr = *reinterpret_cast<const uint2 *>(p.sw + col);            // zero padded past N
+            const uint2 swr = *reinterpret_cast<const uint2 *>(w.sw + col);            // zero padded past N
             const __half2 *sw2 = reinterpret_cast<const __half2 *>(&swr);
             const float2 s01 = __half22float2(sw2[0]), s23 = __half22float2(sw2[1]);
             uint2 pk;
             pk.x = dequant_pair(sum.x, sum.y, sxf, s01.x, s01.y);
             pk.y = dequant_pair(sum.z, sum.w, sxf, s23.x, s23.y);
-            __half *dst = p.Y + (size_t)row * p.ldy + col;
-            if (y_vec && col + 4 <= p.N) {
+            __half *dst = w.Y + (size_t)row * w.ldy + col;
+            if (y_vec && col + 4 <= w.N) {
                 *reinterpret_cast<uint2 *>(dst) = pk;
             } else {
                 const __half *h = reinterpret_cast<const __half *>(&pk);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (col + e < p.N) dst[e] = h[e];
+                    if (col + e < w.N) dst[e] = h[e];
             }
-            if (p.acc_out) {
-                int32_t *ad = p.acc_out + (size_t)row * p.N + col;
+            if (w.acc_out) {
+                int32_t *ad = w.acc_out + (size_t)row * w.N + col;
                 const v4i v = {sum.x >> 8, sum.y >> 8, sum.z >> 8, sum.w >> 8};
-                if (a_vec && col + 4 <= p.N) {
+                if (a_vec && col + 4 <= w.N) {
                     *reinterpret_cast<v4i *>(ad) = v;
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (col + e < p.N) ad[e] = v[e];
+                        if (col + e < w.N) ad[e] = v[e];
                 }
             }
         }
@@ -293,7 +306,7 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
 // contiguous runs, and inside an XCD to `per_xcd` workgroups per token block, so that the workgroups that
 // read the same weights (one per token block) sit behind one L2.  AH = 16-token groups per wavefront: a
 // block has 2 AH of them (rows past the block re-read other rows and are never stored).
-template <int AH, bool RAGGED>
+template <int AH, bool RAGGED, bool MULTI>
 __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const RowsParams p)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -306,13 +319,20 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const Row
     const int row0 = tb * p.rows_per_block;
     if (row0 >= p.M) return;
     const int row_end = min(p.M, row0 + p.rows_per_block);      // rows past it belong to the next block (or to nobody)
-    // tiles of at most kRowsMaxB groups, as even as possible (5 -> 3 + 2, 4 -> 2 + 2)
-    const int n = g_end - g_begin, tiles = (n + kRowsMaxB - 1) / kRowsMaxB;
+    // tiles of at most MAXB groups, as even as possible (5 -> 3 + 2, 4 -> 2 + 2)
+    constexpr int MAXB = rows_max_b(AH);
+    const int n = g_end - g_begin, tiles = (n + MAXB - 1) / MAXB;
     for (int k = 0; k < tiles; ++k) {
         const int c0 = g_begin + n * k / tiles, b = g_begin + n * (k + 1) / tiles - c0;
-        if (b == 3) rows_tile<AH, 3, RAGGED>(p, smem, row0, row_end, c0);
-        else if (b == 2) rows_tile<AH, 2, RAGGED>(p, smem, row0, row_end, c0);
-        else rows_tile<AH, 1, RAGGED>(p, smem, row0, row_end, c0);
+        if constexpr (MAXB > kRowsMaxB) {
+            if (b == 6) rows_tile<AH, 6, RAGGED, MULTI>(p, smem, row0, row_end, c0);
+            else if (b == 5) rows_tile<AH, 5, RAGGED, MULTI>(p, smem, row0, row_end, c0);
+            else if (b == 4) rows_tile<AH, 4, RAGGED, MULTI>(p, smem, row0, row_end, c0);
+        }
+        if (b > 3) continue;
+        if (b == 3) rows_tile<AH, 3, RAGGED, MULTI>(p, smem, row0, row_end, c0);
+        else if (b == 2) rows_tile<AH, 2, RAGGED, MULTI>(p, smem, row0, row_end, c0);
+        else rows_tile<AH, 1, RAGGED, MULTI>(p, smem, row0, row_end, c0);
     }
 }
 
@@ -330,11 +350,15 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const Row
 // 2368 x 1024 x 4096 25.1 against 31.3), and against the tiles with a guarded K (six groups, M > 160: 300 x 12288 x 4160 33.9
 // against 50.7, 1200 x 3000 x 4160 33.1 against 50.6; eight at K = 1088: 600 x 8000 25.4 against 17.8); not at
 // 160 < M < 512 otherwise (276 x 8192 x 4096 23.0 against 19.7) nor with K below 1024 (600 x 4096 x 512 12.4 against 11.0).
-static bool rows_plan(int M, int N, int K, int cus, RowsParams *p)
+// Up to 32 rows a tile takes six groups and two tiles are taken.  That includes decode sizes: one launch per linear (or per
+// group of linears with one input: q, k and v are a product over 12288 channels) has no stream long enough for the
+// streaming kernel's pipeline, and here its start-up is shorter (M = 1 / 8, us, the streaming kernel in brackets: 4096 x 4096 5.7 / 5.8 (8.2 /
+// 8.6), 12288 x 4096 8.9 (11.9 / 13.2), 22016 x 4096 13.8 / 14.0 (15.9 / 16.5), K = 11008 8.0 / 8.2 (12.8 / 13.5), 32000 x 4096
+// 17.6 / 17.5 (19.3 / 19.4), 512 x 512 3.5 / 3.8 (6.9 / 7.0)).  Launches of many problems stay with that kernel.
+static bool rows_plan(int M, int c16, int K, int cus, RowsParams *p)
 {
-    if (M <= kSkinnyMaxM || K % 32 != 0 || N < 16) return false;
-    const int c16 = (N + 15) / 16;
-    const int max_groups = K < 1024 ? kRowsMaxB : K % 128 != 0 && M > 160 && K >= 2048 ? 6 : M <= 64 ? 6 : M >= 512 ? 4 : kRowsMaxB;
+    if (K % 32 != 0 || c16 < 1) return false;
+    const int max_groups = M <= 32 ? (M <= kSkinnyMaxM || K >= 1024 ? 2 * kRowsMaxBFew : kRowsMaxB) : K < 1024 ? kRowsMaxB : K % 128 != 0 && M > 160 && K >= 2048 ? 6 : M <= 64 ? 6 : M >= 512 ? 4 : kRowsMaxB;
     double best = 0.0;
     for (int tb = 1; tb <= 16; tb *= 2) {
         const int rows = ((M + tb - 1) / tb + 15) / 16 * 16;
@@ -366,23 +390,23 @@ static int rows_cus()
 }
 
 // Shapes this kernel takes: up to sixteen blocks of 160 token rows, and few enough channels per workgroup.
-bool rows_kernel_applies(int M, int N, int K)
+bool rows_kernel_applies(int M, int channel_groups, int K)
 {
     RowsParams p = {};
-    return rows_plan(M, N, K, rows_cus(), &p);
+    return rows_plan(M, channel_groups, K, rows_cus(), &p);
 }
 
-template <int AH, bool RAGGED>
+template <int AH, bool RAGGED, bool MULTI>
 static sqap_status launch_rows_k(const RowsParams &p, int blocks, hipStream_t st)
 {
     static std::atomic<bool> configured[kMaxDeviceSlots];
     const int dslot = device_slot();
     if (!configured[dslot].load(std::memory_order_acquire)) {
-        SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_rows_kernel<AH, RAGGED>),
+        SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_rows_kernel<AH, RAGGED, MULTI>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLdsBytes));
         configured[dslot].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((gemm_rows_kernel<AH, RAGGED>), dim3(blocks), dim3(64 * kRowsWaves), kRowsLdsBytes, st, p);
+    hipLaunchKernelGGL((gemm_rows_kernel<AH, RAGGED, MULTI>), dim3(blocks), dim3(64 * kRowsWaves), kRowsLdsBytes, st, p);
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }
@@ -390,28 +414,32 @@ static sqap_status launch_rows_k(const RowsParams &p, int blocks, hipStream_t st
 template <int AH>
 static sqap_status launch_rows_a(const RowsParams &p, int blocks, hipStream_t st)
 {
-    if (p.K % kRowsStepCodes == 0 && p.K / kRowsStepCodes >= 4) return launch_rows_k<AH, false>(p, blocks, st);
-    return launch_rows_k<AH, true>(p, blocks, st);
+    const bool ragged = p.K % kRowsStepCodes != 0 || p.K / kRowsStepCodes < 4;
+    if constexpr (AH == 1) {                     // several weights: decode sizes only (sqap_group_run)
+        if (p.count > 1) return ragged ? launch_rows_k<AH, true, true>(p, blocks, st) : launch_rows_k<AH, false, true>(p, blocks, st);
+    }
+    return ragged ? launch_rows_k<AH, true, false>(p, blocks, st) : launch_rows_k<AH, false, false>(p, blocks, st);
 }
 
-sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, const Weight &w, __half *Y, int64_t ldy,
-                               int32_t *acc_out, unsigned long long *error_word, hipStream_t st)
+sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
+                               unsigned long long *error_word, hipStream_t st)
 {
     RowsParams p = {};
     p.Xq = Xq;
     p.sx = sx;
-    p.Wd = w.data;
-    p.sw = w.scales;
-    p.Y = Y;
-    p.acc_out = acc_out;
-    p.ldy = ldy;
     p.M = M;
-    p.N = w.N;
-    p.K = w.K;
-    p.chunks = w.chunks;
+    p.K = K;
+    p.chunks = K / 32;
     p.error_word = error_word;
-    if (!rows_plan(M, w.N, w.K, rows_cus(), &p))
-        return fail(SQAP_EUNSUPPORTED, "sqap_w4a4_linear: M = %d, N = %d, K = %d outside the row kernel's range", M, w.N, w.K);
+    p.count = count;
+    int groups = 0;
+    for (int i = 0; i < count; ++i) {
+        p.w[i] = weights[i];
+        p.w[i].g_begin = groups;
+        groups += (weights[i].N + 15) / 16;
+    }
+    if (!rows_plan(M, groups, K, rows_cus(), &p))
+        return fail(SQAP_EUNSUPPORTED, "sqap_w4a4_linear: M = %d, %d channels, K = %d outside the row kernel's range", M, groups * 16, K);
     const int blocks = 8 * p.per_xcd * p.tblocks;
     const int ah = (p.rows_per_block / 16 + 1) / 2;             // token groups per wavefront
     switch (ah) {

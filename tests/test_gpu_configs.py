@@ -273,6 +273,41 @@ def test_whole_output_kernel_any_k(G, oracle, M, N, K):
     assert G.assert_fp16_close(Y, Yo) == 0
 
 
+@pytest.mark.parametrize("M,K,Ns", [(1, 64, (5,)), (3, 512, (16, 48)), (8, 1408, (1000, 33, 7)), (4, 4096, (512, 512, 512, 100)), (8, 4096, (24576, 24576)),
+                                    (2, 4096, (24576, 24577)), (7, 704, (50, 60, 70, 80, 90))])
+def test_groups_with_one_input(G, oracle, M, K, Ns):
+    """Groups whose problems share their input are one product over all their channels (up to four problems, up to twelve
+    channel groups per compute unit: the last two are past that), each with its own pitch and accumulators: against the oracle, and
+    against the weight-streaming kernel."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    rng = np.random.default_rng(M + K + len(Ns))
+    Xq = _random_packed(rng, M, K)
+    sx = (rng.random(M) * 2 + 0.01).astype(np.float16)
+    xd, sd = G.to_dev(Xq), G.to_dev(sx)
+    probs, want = [], []
+    for i, N in enumerate(Ns):
+        Wq = _random_packed(rng, N, K)
+        sw = (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
+        Y = torch.full((M, N + 3 * i), float("nan"), dtype=torch.float16, device="cuda")
+        acc = torch.zeros((M, N), dtype=torch.int32, device="cuda") if i % 2 == 0 else None
+        probs.append((xd, sd, B.sqap_weight_pack(G.to_dev(Wq), G.to_dev(sw)), Y[:, :N], acc))
+        rows = np.arange(N) if N < 2000 else np.unique(np.r_[0:40, N - 40:N])
+        want.append((rows,) + oracle.w4a4_linear(Xq, sx, Wq[rows], sw[rows]))
+    group = B.sqap_group_create(probs)
+    try:
+        for which in (1, 0):
+            B.sqap_set_mid_m_kernel(which)
+            group.run()
+            torch.cuda.synchronize()
+            for (_, _, _, Y, acc), (rows, Yo, acco) in zip(probs, want):
+                assert G.assert_fp16_close(Y.cpu().numpy()[:, rows], Yo) == 0, which
+                assert acc is None or np.array_equal(acc.cpu().numpy()[:, rows], acco), which
+                Y.fill_(float("nan"))
+    finally:
+        B.sqap_set_mid_m_kernel(1)
+
+
 @pytest.mark.parametrize("M", [1, 8])
 def test_config4_decode_headline_launch(G, oracle, M):
     """The launch bench.py times for configuration 4: ONE group launch over the seven 7B-shaped linears of 16
