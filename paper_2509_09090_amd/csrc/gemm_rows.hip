@@ -358,6 +358,7 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const Row
 static bool rows_plan(int M, int c16, int K, int cus, RowsParams *p)
 {
     if (K % 32 != 0 || c16 < 1) return false;
+    if (M <= kSkinnyMaxM && K % 64 == 0 && K > 32768) return false;         // the streaming kernel's, which says what it refuses
     const int max_groups = M <= 32 ? (M <= kSkinnyMaxM || K >= 1024 ? 2 * kRowsMaxBFew : kRowsMaxB) : K < 1024 ? kRowsMaxB : K % 128 != 0 && M > 160 && K >= 2048 ? 6 : M <= 64 ? 6 : M >= 512 ? 4 : kRowsMaxB;
     double best = 0.0;
     for (int tb = 1; tb <= 16; tb *= 2) {
