@@ -249,7 +249,7 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta
 // up row;  v = half(silu(g) * u),  silu(g) = (float)(g / (1 + exp(-g))) evaluated in binary64.
 // silu is a function of a half value: a GPU test walks all 2^16 of them against the host's.
 // At 2368 x 11008 the vector ALU bounds this form (17.1 thousand instructions per SIMD, 43 per element, 25 of them silu's):
-// 38.7 us against 49.7 with the library's binary64 exponential and division; 117 MB take 23 us.
+// 40 us against 49.7 with the library's binary64 exponential and division; 117 MB take 23 us.
 // (A per-device table of the 2^16 results was slower than computing: 13 against 10 us at 84 x 11008,
 // 48 scattered 4-byte loads per thread.)
 template <int T, int GPT>
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(T) void quantize_rows_kernel(const __half *X, int64
     const uint4 *xrow = reinterpret_cast<const uint4 *>(X + src * ldx);
     const int groups = K >> 3;
 
-    // everything the row needs is asked for before any of it is worked on (2368 rows: SwiGLU of 11008 38.7 us against 40.0
+    // everything the row needs is asked for before any of it is worked on (2368 rows, 512 threads: SwiGLU of 11008 38.7 us against 40.0
     // with the up row fetched group by group, norm of 4096 16.2 against 17.6)
     float v[GPT][8];
     uint4 second[GPT], third[GPT];
@@ -533,9 +533,11 @@ static sqap_status launch_quantize_inst(const __half *X, int64_t ldx, const int3
     return SQAP_OK;
 }
 
-// Threads per row: a row of more than 512 groups of 8 keeps 512 threads busy (2368 x 11008, SwiGLU: 38.9 us with 512
-// threads, 40.6 with 256, 49.4 with 128); with at most two rows per compute unit the longest rows take 1024 (84 x 11008,
-// SwiGLU 6.1 us against 7.1 and 8.8; plain 3.4 against 3.7 and 5.0).  Up to 512 groups, 256 threads are better as soon as
+// Threads per row.  With at most two rows per compute unit the longest rows take 1024 (84 x 11008, SwiGLU 6.1 us against 7.1
+// with 512 and 8.8 with 256; plain 3.4 against 3.7 and 5.0).  With more rows 256 are better although the kernel alone is not
+// (2368 x 11008, SwiGLU: 40.6 us, 38.9 with 512, 49.4 with 128): norm, gate|up, SwiGLU and down in a row take 295 us, 315 with
+// 512 and 300 with 128: the linears around it run faster.  Rows of 513 to 1024 groups keep 512 (norm to down at 1100 x 5504
+// 76.6 us, 77.2 with 256).  Up to 512 groups, 256 threads are better as soon as
 // rows share compute units, since every wavefront repeats the norm's scalar part (2368 x 4096 norm 17.2 us against 19.8
 // with 512; 84 x 4096 4.5 against 4.1).
 template <bool ROTATE, int MODE, int PRE>
@@ -546,7 +548,7 @@ static sqap_status launch_quantize_gpt(const __half *X, int64_t ldx, const int32
 #define SQAP_Q(T, G) launch_quantize_inst<ROTATE, T, G, MODE, PRE>(X, ldx, rows, M, K, col_scales, Xq, sx, pre, st)
     if (groups > 1024) {
         if (M <= 2 * cus) return SQAP_Q(1024, 2);
-        return groups <= 1536 ? SQAP_Q(512, 3) : SQAP_Q(512, 4);
+        return groups <= 1536 ? SQAP_Q(256, 6) : SQAP_Q(256, 8);
     }
     if (groups > 512) return SQAP_Q(512, 2);
     if (groups > 256) return M <= cus ? SQAP_Q(512, 1) : SQAP_Q(256, 2);
