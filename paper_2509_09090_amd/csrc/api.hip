@@ -596,7 +596,9 @@ sqap_status sqap_w4a4_linear(const uint8_t *Xq, const sqap_f16 *sx, int32_t M,
         if (reinterpret_cast<uintptr_t>(workspace) & 255u)
             return fail(SQAP_EINVAL, "sqap_w4a4_linear: workspace must be 256-byte aligned");
     }
-    if (M <= kSkinnyMaxM && w->K % 64 == 0 && !(rows_kernel_wanted() && rows_kernel_applies(M, (w->N + 15) / 16, w->K))) {
+    // (decided once: another thread may turn the switch meanwhile, and what M <= 8 would fall through to asks for a workspace)
+    const bool whole_outputs = rows_kernel_wanted() && rows_kernel_applies(M, (w->N + 15) / 16, w->K);
+    if (M <= kSkinnyMaxM && w->K % 64 == 0 && !whole_outputs) {
         SkinnyArgs a = {};
         a.table = nullptr;
         a.count = 1;
@@ -618,7 +620,7 @@ sqap_status sqap_w4a4_linear(const uint8_t *Xq, const sqap_f16 *sx, int32_t M,
         return launch_skinny(a, w->chunks, as_stream(stream));
     }
     return launch_w4a4_linear(Xq, reinterpret_cast<const __half *>(sx), M, *w,
-                              reinterpret_cast<__half *>(Y), ldy, acc_out, workspace,
+                              reinterpret_cast<__half *>(Y), ldy, acc_out, workspace, whole_outputs,
                               as_stream(stream));
 }
 

@@ -179,7 +179,7 @@ sqap_status launch_weight_pack(const uint8_t *Wq, const __half *sw, const Weight
 size_t linear_workspace_bytes(int M, int N, int K);
 sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const Weight &w,
                                __half *Y, int64_t ldy, int32_t *acc_out, void *workspace,
-                               hipStream_t st);
+                               bool whole_outputs, hipStream_t st);
 
 // Few outputs per compute unit: every workgroup owns complete ones (gemm_rows.hip)
 bool rows_kernel_applies(int M, int channel_groups, int K);        // (of 16 channels)

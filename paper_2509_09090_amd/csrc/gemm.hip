@@ -1441,7 +1441,7 @@ sqap_status plan_linear_shares(int M, int N, int K, int blocks_per_xcd, uint32_t
 }
 
 sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const Weight &w,
-                               __half *Y, int64_t ldy, int32_t *acc_out, void *workspace, hipStream_t st)
+                               __half *Y, int64_t ldy, int32_t *acc_out, void *workspace, bool whole_outputs, hipStream_t st)
 {
     if (w.K > kMaxK) return fail(SQAP_EUNSUPPORTED, "sqap_w4a4_linear: K = %d above %d", w.K, kMaxK);
     GemmParams p = {};
@@ -1460,7 +1460,7 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
     p.y_vec_ok = (reinterpret_cast<uintptr_t>(Y) & 15u) == 0 && (ldy & 7) == 0;
     // Few enough outputs per compute unit: whole outputs per workgroup, nothing exchanged between workgroups.  (The
     // error word is only there where the entry point asked for a workspace.)
-    if (rows_kernel_wanted() && rows_kernel_applies(M, (w.N + 15) / 16, w.K)) {
+    if (whole_outputs) {
         const RowsWeight rw = {w.data, w.scales, Y, acc_out, ldy, w.N, 0};
         const bool has_word = linear_workspace_bytes(M, w.N, w.K) > 0;
         return launch_rows_linear(Xq, sx, M, w.K, &rw, 1, has_word ? reinterpret_cast<unsigned long long *>(workspace) + kErrWord : nullptr, st);

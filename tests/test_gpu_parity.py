@@ -593,3 +593,41 @@ def test_group_of_small_m_linears(G, oracle):
     g.free()
     for pr in problems:
         pr[2].free()
+
+
+def test_small_m_linear_while_another_thread_turns_the_switch(G, oracle):
+    """A call decides once which kernel it takes: the launches of M <= 8 need no workspace whatever the switch does meanwhile."""
+    import threading
+    import torch
+    from paper_2509_09090_amd import binding as B
+    rng = np.random.default_rng(31)
+    M, N, K = 4, 512, 512
+    assert B.sqap_workspace_bytes(M, N, K) == 0
+    Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
+    sx = (rng.random(M) * 2 + 0.01).astype(np.float16)
+    sw = (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
+    Yo, acco = oracle.w4a4_linear(Xq, sx, Wq, sw)
+    xq, sxd, W = G.to_dev(Xq), G.to_dev(sx), B.sqap_weight_pack(G.to_dev(Wq), G.to_dev(sw))
+    Y = torch.full((200, M, N), float("nan"), dtype=torch.float16, device="cuda")
+    acc = torch.full((200, M, N), -1, dtype=torch.int32, device="cuda")
+    stop = threading.Event()
+
+    def turn():
+        which = 0
+        while not stop.is_set():
+            B.sqap_set_mid_m_kernel(which)
+            which ^= 1
+
+    t = threading.Thread(target=turn)
+    t.start()
+    try:
+        for i in range(200):
+            B.sqap_w4a4_linear(xq, sxd, W, Y[i], acc[i], None)
+    finally:
+        stop.set()
+        t.join()
+        B.sqap_set_mid_m_kernel(1)
+    torch.cuda.synchronize()
+    assert np.array_equal(acc.cpu().numpy(), np.broadcast_to(acco, (200, M, N)))
+    assert G.assert_fp16_close(Y.cpu().numpy(), np.broadcast_to(Yo, (200, M, N))) == 0
+    W.free()
