@@ -42,16 +42,18 @@ constexpr int kRowsReduceBytes = kRowsWaves * kRowsMaxAH * kRowsMaxB * 1024;    
 constexpr int kRowsLdsBytes = kRowsReduceBytes > kRowsWaves * kRowsSlabBytes ? kRowsReduceBytes : kRowsWaves * kRowsSlabBytes;
 
 struct RowsParams {
+    // An argument whose line of 64 bytes is cold is a trip to memory in front of the first load of codes: what a launch
+    // with one weight needs lies in the first two lines (spread over three, a launch of 4 to 10 us took 0.1 to 0.3 us longer)
     const uint8_t *Xq;     // [M, K/2] canonical
     const __half *sx;      // [M]
+    unsigned long long *error_word;        // of the caller's workspace, nullable: cleared (no wait can fail here)
     int M, K, chunks;
-    int count;             // weights the input is multiplied with (q, k and v, say): their channel groups follow one another
-    RowsWeight w[kRowsMaxWeights];
     int c16;               // 16-channel groups in all
     int tblocks;           // blocks of token rows (1, 2, 4, 8 or 16)
     int rows_per_block;    // multiple of 16, at most 16 * kRowsMaxA
     int per_xcd;           // workgroups of an XCD that share its channel groups, per token block
-    unsigned long long *error_word;        // of the caller's workspace, nullable: cleared (no wait can fail here)
+    int count;             // weights the input is multiplied with (q, k and v, say): their channel groups follow one another
+    RowsWeight w[kRowsMaxWeights];
 };
 
 // the weight that channel group g (of all of them) belongs to.  A single one sits at a fixed place among the kernel's
