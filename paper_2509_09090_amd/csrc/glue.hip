@@ -76,7 +76,10 @@ __global__ __launch_bounds__(256) void rope_append_kernel(__half *__restrict__ Q
 // APPEND: slots 0 .. H-1 queries, H .. 2H-1 keys (into the cache), 2H .. 3H-1 values (copied).
 // What bounds it: memory with many tokens (77 MB at 2368 tokens x 64 heads of 128, 15 us at the rate of a copy), the sine
 // and cosine with few.  Measured (us): 2368 tokens 15.1 (one pair per thread and step: 26.2), 148 with append 3.4 (5.9).
-// Below kRopePiecesFrom pairs a thread per pair is quicker (8 tokens, 32 heads of 128, append: 2.4 against 2.7).
+// Where a thread per pair, or from kRopeTokenKernelFrom tokens on rope_token_kernel, is quicker: few pairs (append, 8 tokens of 64
+// heads of 256 2.42 against 2.66, 64 of 32 heads of 64 2.42 against 2.55, 512 of 8 heads of 32 2.48 against 2.58; the other way
+// round 130 of 8 heads of 128 2.52 against 2.68), and tokens that fill less than half a wavefront, of which the workgroup has
+// four (2400 tokens, 4 heads of 64: 3.90 against 4.60, 8 heads 4.45 against 4.41; append, 1 head of 64: 2.93 against 4.65).
 template <bool APPEND>
 __global__ __launch_bounds__(256) void rope_pieces_kernel(__half *__restrict__ X, int64_t ld, const int32_t *__restrict__ pos, int H,
                                                           int d, double base, __half *__restrict__ KV, int64_t ldkv,
@@ -129,7 +132,8 @@ __global__ __launch_bounds__(256) void rope_pieces_kernel(__half *__restrict__ X
     }
 }
 
-constexpr int kRopePiecesFrom = 1 << 17;
+constexpr int kRopeTokenKernelFrom = 512;        // tokens
+constexpr int kRopePiecesMinThreads = 32;        // with work, of a workgroup
 
 template <bool APPEND>
 static bool launch_rope_pieces(__half *X, int64_t ld, const int32_t *pos, int S, int H, int d, double base, __half *KV,
@@ -137,7 +141,9 @@ static bool launch_rope_pieces(__half *X, int64_t ld, const int32_t *pos, int S,
 {
     if (d < 16 || d > 2 * kRopeTableMax || (d & (d - 1)) != 0 || (ld & 7) != 0 || (reinterpret_cast<uintptr_t>(X) & 15u) != 0) return false;
     if (APPEND && ((ldkv & 7) != 0 || (reinterpret_cast<uintptr_t>(KV) & 15u) != 0)) return false;
-    if ((int64_t)S * (APPEND ? 3 * H : H) * (d / 2) < kRopePiecesFrom) return false;
+    const int64_t threads = (int64_t)(APPEND ? 3 * H : H) * (d / 16);         // that a token has work for
+    const int from = !APPEND && S >= kRopeTokenKernelFrom ? 1 << 17 : S < 128 ? 1 << 18 : (3 << 16) + 1;        // pairs
+    if (threads < kRopePiecesMinThreads || S * threads * 8 < from) return false;
     // few tokens: a token's heads are dealt to as many workgroups as they fill, up to four per compute unit in all
     const int rounds = ((APPEND ? 3 * H : H) * (d / 16) + 255) / 256;
     const int shares = S >= 1024 ? 1 : std::min(rounds, std::min(64, 1024 / S + 1));
@@ -161,12 +167,11 @@ sqap_status launch_rope_append(__half *QKV, int64_t ld, const int32_t *pos, int 
     return SQAP_OK;
 }
 
-// Any other head size or alignment, many tokens: one workgroup per token evaluates the d/2 angles of its position once (the
+// What the pieces leave, many tokens: one workgroup per token evaluates the d/2 angles of its position once (the
 // binary64 power, sine and cosine are a few hundred instructions per pair) and shares them between the
 // heads through LDS.  With few tokens the per-pair kernel is faster (more threads in flight: 6.7 against
 // 8.8 us at 84 tokens); at 2368 tokens this one takes a tenth of its time.
 constexpr int kRopeMaxHalfD = 256;
-constexpr int kRopeTokenKernelFrom = 512;        // tokens
 
 __global__ __launch_bounds__(256) void rope_token_kernel(__half *__restrict__ X, int64_t ld,
                                                          const int32_t *__restrict__ pos, int H, int d, double base,

@@ -197,7 +197,9 @@ def test_swiglu_quantize(G, oracle, M, F, channelwise, sliced):
     assert np.array_equal(Xq.cpu().numpy(), q_o)
 
 
-@pytest.mark.parametrize("S,H,d", [(276, 32, 128), (5, 3, 16), (148, 4, 64), (700, 6, 64), (1100, 5, 48), (1030, 16, 16), (90, 9, 256), (410, 5, 128)])
+@pytest.mark.parametrize("S,H,d", [(276, 32, 128), (5, 3, 16), (148, 4, 64), (700, 6, 64), (1100, 5, 48), (1030, 16, 16), (90, 9, 256), (410, 5, 128),
+                                   # both sides of the rule that hands a rotation to pieces of 16 bytes
+                                   (1030, 33, 16), (520, 31, 16), (520, 64, 16), (127, 32, 128), (128, 24, 128), (128, 25, 128)])
 def test_rope(G, oracle, S, H, d):
     import torch
     from paper_2509_09090_amd import binding as B
