@@ -641,7 +641,9 @@ __device__ __forceinline__ float block_reduce_256(float v, bool take_max, float 
                     : (scratch4[0] + scratch4[1]) + (scratch4[2] + scratch4[3]);
 }
 
-template <int kRowsInFlight>                      // key rows a lane group loads before it reduces any
+// kRowsInFlight: key rows a lane group loads before it reduces any.  LP: lanes per key row, 16 or 8 (then the sum takes no LDS
+// permutes), 0 for any other.
+template <int kRowsInFlight, int LP>
 __global__ __launch_bounds__(256) void attn_head_kernel(const __half *__restrict__ q, const __half *__restrict__ k,
                                                         int S, int H, int d, int vis_begin, int n_vis,
                                                         float *__restrict__ scores, unsigned int *heads_done,
@@ -655,7 +657,7 @@ __global__ __launch_bounds__(256) void attn_head_kernel(const __half *__restrict
     k += (size_t)b * S * H * d;
     scores += (size_t)b * n_vis;
     float *head_weights = all_head_weights + (size_t)b * H * n_vis;
-    const int lp = d >> 3;                        // lanes per key row: a power of two, 1 .. 32
+    const int lp = LP ? LP : d >> 3;              // lanes per key row: a power of two, 1 .. 32
     const int sub = t & (lp - 1), grp = t / lp, groups = 256 / lp;
     float qf[8];
     {
@@ -674,12 +676,13 @@ __global__ __launch_bounds__(256) void attn_head_kernel(const __half *__restrict
 #pragma unroll
         for (int r = 0; r < kRowsInFlight; ++r) {
             const int s = s0 + r * groups + grp;
+            if (LP == 0) raw[r] = make_uint4(0u, 0u, 0u, 0u);
             if (s < S) raw[r] = *reinterpret_cast<const uint4 *>(k + ((size_t)s * H + h) * d + sub * 8);
         }
 #pragma unroll
         for (int r = 0; r < kRowsInFlight; ++r) {
             const int s = s0 + r * groups + grp;
-            if (s0 + r * groups >= S) break;      // (uniform)
+            if (LP != 0 && s0 + r * groups >= S) break;      // (uniform; with LDS permutes it would keep them from overlapping)
             const __half2 *h2 = reinterpret_cast<const __half2 *>(&raw[r]);
             float acc = 0.f;
 #pragma unroll
@@ -691,12 +694,12 @@ __global__ __launch_bounds__(256) void attn_head_kernel(const __half *__restrict
             // the lane group's sum in every lane, partners 8, 4, 2, 1 apart, without LDS permutes: once the step by 8 has made
             // the lanes of a row repeat every 8, 4 back is 4 across, and so on; in groups of 8 the partner 4 across is the
             // mirror image's mirror image within its quad
-            if (lp == 16) {
+            if (LP == 16) {
                 acc += dpp_move_f<0x128>(acc);
                 acc += dpp_move_f<0x124>(acc);
                 acc += dpp_move_f<0x122>(acc);
                 acc += dpp_move_f<0x121>(acc);
-            } else if (lp == 8) {
+            } else if (LP == 8) {
                 acc += dpp_move_f<0x1B>(dpp_move_f<kDppHalfMirror>(acc));
                 acc += dpp_move_f<kDppXor2>(acc);
                 acc += dpp_move_f<kDppXor1>(acc);
@@ -759,16 +762,19 @@ size_t attn_scores_workspace_bytes(int batch, int H, int n_vis)
 
 // A round of loads is a trip to memory that everything else waits for: 18 rows per lane group take the 276 keys of an
 // observation with heads of 128 in one round (16 observations x 32 heads: 11.6 us; 8 rows, three rounds: 15.6; one observation
-// 8.0 and 12.4), 9 where that is enough (8 x 8 tokens, heads of 64: 5.2 and 6.5).
+// 8.0 and 12.4), 9 where that is enough (8 x 8 tokens, heads of 64: 5.2 and 6.5).  Other head sizes add their lanes with LDS
+// permutes, whose latency bounds a round: eight rows side by side (us, observations x keys x heads x head size: 6 x 2524 x 32 x 16
+// 25.9, 3 x 1455 x 32 x 32 15.5, 3 x 2867 x 32 x 256 160; 18 rows with a stop at the last key 27.9, 17.2 and 185).
 static void launch_attn_head(const __half *q, const __half *k, int batch, int S, int H, int d, int vis_begin, int n_vis,
                              float *scores, unsigned int *counters, float *weights, hipStream_t st)
 {
-    if (S <= 9 * (2048 / d))
-        hipLaunchKernelGGL(attn_head_kernel<9>, dim3(H, batch), dim3(256), 0, st, q, k, S, H, d, vis_begin, n_vis, scores,
-                           counters, weights);
-    else
-        hipLaunchKernelGGL(attn_head_kernel<18>, dim3(H, batch), dim3(256), 0, st, q, k, S, H, d, vis_begin, n_vis, scores,
-                           counters, weights);
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(H, batch), dim3(256), 0, st, q, k, S, H, d, vis_begin, n_vis, scores, counters, weights);
+    };
+    const bool one_round_of_nine = S <= 9 * (2048 / d);
+    if (d == 128) launch(one_round_of_nine ? attn_head_kernel<9, 16> : attn_head_kernel<18, 16>);
+    else if (d == 64) launch(one_round_of_nine ? attn_head_kernel<9, 8> : attn_head_kernel<18, 8>);
+    else launch(attn_head_kernel<8, 0>);
 }
 
 sqap_status launch_attn_scores(const __half *q, const __half *k, int batch, int S, int H, int d,
