@@ -533,13 +533,14 @@ sqap_status sqap_group_create(const sqap_linear_desc *descs, int32_t count, sqap
 sqap_status sqap_group_run(const sqap_group *g, void *stream);
 
 /*
- * How sqap_group_run launches a group with the weight-streaming kernel (all groups but those of up to four
- * problems with one input, see sqap_set_mid_m_kernel; host arithmetic only; no GPU work): the number of problems and of
- * row groups (32 output channels each) in it, and the form of the small-M kernel the launch takes on a
+ * How sqap_group_run will launch a group (host arithmetic only; no GPU work): the number of problems and of
+ * row groups (32 output channels each) in it, and the form of the kernel the launch takes on a
  * device with `compute_units` compute units (0: the current device): wavefronts that share one row
  * group along K (1, 2, 4 or 8), wavefronts per workgroup (8, or 16 for launches in which every wavefront
  * streams four or more row groups: outputs then wait in LDS slots, output_slots_out per wavefront, 0
- * otherwise).  Any out pointer may be NULL.  EINVAL: not a group handle, compute_units < 0.
+ * otherwise).  Up to four problems with one input that run as one product (see sqap_set_mid_m_kernel, whose
+ * setting at the time of the call counts): 4, 8 and 0.  Any out pointer may be NULL.  EINVAL: not a group
+ * handle, compute_units < 0.
  */
 sqap_status sqap_group_info(const sqap_group *g, int32_t compute_units, int32_t *problems_out,
                             int32_t *row_groups_out, int32_t *wavefronts_per_row_group_out,

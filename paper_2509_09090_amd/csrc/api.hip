@@ -597,7 +597,7 @@ sqap_status sqap_w4a4_linear(const uint8_t *Xq, const sqap_f16 *sx, int32_t M,
             return fail(SQAP_EINVAL, "sqap_w4a4_linear: workspace must be 256-byte aligned");
     }
     // (decided once: another thread may turn the switch meanwhile, and what M <= 8 would fall through to asks for a workspace)
-    const bool whole_outputs = rows_kernel_wanted() && rows_kernel_applies(M, (w->N + 15) / 16, w->K);
+    const bool whole_outputs = rows_kernel_wanted() && rows_kernel_applies(M, (w->N + 15) / 16, w->K, device_cu_count());
     if (M <= kSkinnyMaxM && w->K % 64 == 0 && !whole_outputs) {
         SkinnyArgs a = {};
         a.table = nullptr;
@@ -755,12 +755,18 @@ sqap_status sqap_group_create(const sqap_linear_desc *descs, int32_t count, sqap
     return SQAP_OK;
 }
 
+// problems with one input as one product over all their channels, every workgroup with complete outputs
+static bool group_has_whole_outputs(const Group *g, int compute_units)
+{
+    return g->rows_count > 0 && rows_kernel_wanted() && rows_kernel_applies(g->rows_M, g->rows_groups, g->rows_K, compute_units);
+}
+
 sqap_status sqap_group_run(const sqap_group *g, void *stream)
 {
     const Group *gg = reinterpret_cast<const Group *>(g);
     if (!gg || gg->magic != kGroupMagic) return fail(SQAP_EINVAL, "sqap_group_run: not a group handle");
     const DeviceOfCall device;
-    if (gg->rows_count > 0 && rows_kernel_wanted() && rows_kernel_applies(gg->rows_M, gg->rows_groups, gg->rows_K))
+    if (group_has_whole_outputs(gg, device_cu_count()))
         return launch_rows_linear(gg->rows_Xq, gg->rows_sx, gg->rows_M, gg->rows_K, gg->rows, gg->rows_count, nullptr, as_stream(stream));
     SkinnyArgs a = {};
     a.table = gg->table;
@@ -777,8 +783,9 @@ sqap_status sqap_group_info(const sqap_group *g, int32_t compute_units, int32_t 
     const Group *gg = reinterpret_cast<const Group *>(g);
     if (!gg || gg->magic != kGroupMagic) return fail(SQAP_EINVAL, "sqap_group_info: not a group handle");
     if (compute_units < 0) return fail(SQAP_EINVAL, "sqap_group_info: compute_units = %d", compute_units);
-    int S, W, cap;
-    skinny_plan(gg->total_items, gg->max_chunks, compute_units > 0 ? compute_units : device_cu_count(), &S, &W, &cap);
+    const int cus = compute_units > 0 ? compute_units : device_cu_count();
+    int S = kRowsKShares, W = kRowsWaves, cap = 0;
+    if (!group_has_whole_outputs(gg, cus)) skinny_plan(gg->total_items, gg->max_chunks, cus, &S, &W, &cap);
     if (problems_out) *problems_out = gg->count;
     if (row_groups_out) *row_groups_out = gg->total_items;
     if (wavefronts_per_row_group_out) *wavefronts_per_row_group_out = S;

@@ -182,7 +182,8 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
                                bool whole_outputs, hipStream_t st);
 
 // Few outputs per compute unit: every workgroup owns complete ones (gemm_rows.hip)
-bool rows_kernel_applies(int M, int channel_groups, int K);        // (of 16 channels)
+constexpr int kRowsWaves = 8, kRowsKShares = 4;                    // wavefronts per workgroup; of them, along K
+bool rows_kernel_applies(int M, int channel_groups, int K, int compute_units);        // (groups of 16 channels)
 sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
                                unsigned long long *error_word, hipStream_t st);
 bool rows_kernel_wanted();

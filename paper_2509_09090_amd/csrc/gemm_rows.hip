@@ -34,7 +34,6 @@ constexpr int kRowsMaxA = 2 * kRowsMaxAH;
 constexpr int kRowsMaxB = 3;           // 16-channel groups per tile
 constexpr int kRowsMaxBFew = 6;        // the same where a wavefront has one token group (AH = 1)
 constexpr int rows_max_b(int ah) { return ah == 1 ? kRowsMaxBFew : kRowsMaxB; }
-constexpr int kRowsWaves = 8;
 constexpr int kRowsStepCodes = 256;    // codes of K per main-loop step of a wavefront (two MFMA K-blocks of 128)
 constexpr int kRowsPitch = 144;        // bytes per slab row: 128 of codes + 16 of padding
 constexpr int kRowsSlabBytes = kRowsMaxAH * 16 * kRowsPitch;                           // 11520 per wavefront
@@ -386,17 +385,13 @@ static bool rows_plan(int M, int c16, int K, int cus, RowsParams *p)
     return best > 0.0;
 }
 
-static int rows_cus()
-{
-    int cus = device_cu_count();
-    return cus > 256 ? 256 : cus < 8 ? 8 : cus;
-}
+static int rows_cus(int cus) { return cus > 256 ? 256 : cus < 8 ? 8 : cus; }
 
 // Shapes this kernel takes: up to sixteen blocks of 160 token rows, and few enough channels per workgroup.
-bool rows_kernel_applies(int M, int channel_groups, int K)
+bool rows_kernel_applies(int M, int channel_groups, int K, int compute_units)
 {
     RowsParams p = {};
-    return rows_plan(M, channel_groups, K, rows_cus(), &p);
+    return rows_plan(M, channel_groups, K, rows_cus(compute_units), &p);
 }
 
 template <int AH, bool RAGGED, bool MULTI>
@@ -441,7 +436,7 @@ sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, int K
         p.w[i].g_begin = groups;
         groups += (weights[i].N + 15) / 16;
     }
-    if (!rows_plan(M, groups, K, rows_cus(), &p))
+    if (!rows_plan(M, groups, K, rows_cus(device_cu_count()), &p))
         return fail(SQAP_EUNSUPPORTED, "sqap_w4a4_linear: M = %d, %d channels, K = %d outside the row kernel's range", M, groups * 16, K);
     const int blocks = 8 * p.per_xcd * p.tblocks;
     const int ah = (p.rows_per_block / 16 + 1) / 2;             // token groups per wavefront

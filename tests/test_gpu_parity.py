@@ -631,3 +631,29 @@ def test_small_m_linear_while_another_thread_turns_the_switch(G, oracle):
     assert np.array_equal(acc.cpu().numpy(), np.broadcast_to(acco, (200, M, N)))
     assert G.assert_fp16_close(Y.cpu().numpy(), np.broadcast_to(Yo, (200, M, N))) == 0
     W.free()
+
+
+def test_group_info_describes_the_launch(G):
+    """Problems that share their input run as one product of workgroups of eight wavefronts, four along K; with that kernel off,
+    with another input, or with too many channels for the device, the weight-streaming kernel is described."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    M, N, K = 4, 544, 512
+    xq, sx = torch.zeros((2, M, K // 2), dtype=torch.uint8, device="cuda"), torch.ones((M,), dtype=torch.float16, device="cuda")
+    W = B.sqap_weight_pack(torch.zeros((N, K // 2), dtype=torch.uint8, device="cuda"), torch.ones((N,), dtype=torch.float16, device="cuda"))
+    Y = torch.zeros((2, M, N), dtype=torch.float16, device="cuda")
+    same = B.sqap_group_create([(xq[0], sx, W, Y[0]), (xq[0], sx, W, Y[1])])
+    other = B.sqap_group_create([(xq[0], sx, W, Y[0]), (xq[1], sx, W, Y[1])])
+    streaming = other.info(256)
+    assert streaming[:2] == (2, 34) and streaming[2:] != (4, 8, 0)
+    assert same.info(256) == (2, 34, 4, 8, 0)
+    few = same.info(8), other.info(8)                # 68 groups of 16 channels over 8 workgroups: nine each, within the limit of twelve
+    assert few[0] == (2, 34, 4, 8, 0)
+    B.sqap_set_mid_m_kernel(0)
+    try:
+        assert same.info(256) == streaming and same.info(8) == few[1]
+    finally:
+        B.sqap_set_mid_m_kernel(1)
+    same.free()
+    other.free()
+    W.free()
