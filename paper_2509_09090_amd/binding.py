@@ -128,11 +128,17 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# the raw handle: a torch.cuda.Stream object built only to be asked for it costs 2.4 us a call.  (Not part of torch's public
+# interface: without it the object is asked.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is not None:
         return ctypes.c_void_p(int(stream))
-    # the raw handle: a torch.cuda.Stream object built only to be asked for it costs 2.4 us a call
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def sqap_init(stream=None):

@@ -371,3 +371,14 @@ def test_planned_shares_random_shapes():
             assert sorted(published) == sorted(waited), (M, N, K, nb)
             assert len({j for j, _ in published}) == len(published), (M, N, K, nb)
         assert max(planned) <= max(even) + 1e-9, (M, N, K, nb)
+
+
+@pytest.mark.parametrize("raw", [True, False])
+def test_current_stream_with_and_without_the_raw_handle(monkeypatch, raw):
+    """torch's raw stream handle is not public: a torch without it still gives its current stream."""
+    from types import SimpleNamespace
+    monkeypatch.setattr(B.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(B, "_raw_stream", (lambda device: 100 + device) if raw else None)
+    assert B._stream(None) == (103 if raw else 77)
+    assert B._stream(5).value == 5
