@@ -441,6 +441,13 @@ sqap_status sqap_residual_add(sqap_f16 *X, int64_t ldx, const sqap_f16 *delta, i
 sqap_status sqap_selftest_quotient(uint64_t *mismatches_out, void *stream);
 
 /*
+ * The same for the silu of sqap_swiglu_quantize_act, which is evaluated with an exponential and a
+ * reciprocal of the library's own: counts the half values g, all 65536 of them, for which its binary32
+ * bits differ from those of (float)(g / (1 + exp(-g))) in binary64 (NaN is NaN).  Expected result: 0.
+ */
+sqap_status sqap_selftest_silu(uint64_t *mismatches_out, void *stream);
+
+/*
  * Self-test of the dispatch order the persistent GEMM kernels rely on.  They
  * pass partial sums between workgroups b and b' of one launch with
  * b % 8 == b' % 8 through ordinary stores, which requires both to run behind

@@ -20,7 +20,7 @@ EXPORTS = (
     "sqap_last_error", "sqap_version", "sqap_attn_scores", "sqap_attn_scores_batch", "sqap_prune_topk", "sqap_kept_rows",
     "sqap_gather_rows", "sqap_quantize_act", "sqap_quantize_weight", "sqap_weight_pack",
     "sqap_weight_free", "sqap_weight_info", "sqap_workspace_bytes", "sqap_w4a4_linear",
-    "sqap_group_create", "sqap_group_run", "sqap_group_free", "sqap_selftest_quotient", "sqap_selftest_dispatch",
+    "sqap_group_create", "sqap_group_run", "sqap_group_free", "sqap_selftest_quotient", "sqap_selftest_silu", "sqap_selftest_dispatch",
     "sqap_prune_rows", "sqap_prune_select", "sqap_channel_scales", "sqap_quantize_act_channelwise",
     "sqap_quantize_weight_folded", "sqap_rmsnorm_quantize_act", "sqap_swiglu_quantize_act", "sqap_rope",
     "sqap_attention", "sqap_residual_add", "sqap_rope_append", "sqap_plan_linear_shares", "sqap_decode_attention", "sqap_group_info", "sqap_init",
@@ -104,6 +104,7 @@ def lib():
         L.sqap_decoder_set_wait_limit.argtypes = [vp, i64]
         L.sqap_group_info.argtypes = [vp, i32] + [ctypes.POINTER(i32)] * 5
         L.sqap_selftest_quotient.argtypes = [vp, vp]
+        L.sqap_selftest_silu.argtypes = [vp, vp]
         L.sqap_init.argtypes = [vp]
         L.sqap_set_persistent_kernels.argtypes = [i32]
         L.sqap_set_mid_m_kernel.argtypes = [i32]
@@ -344,6 +345,11 @@ def sqap_residual_add(X, delta, stream=None):
 def sqap_selftest_quotient(counter, stream=None):
     """counter: zeroed int64 device tensor of one element; receives the number of mismatches."""
     _check(lib().sqap_selftest_quotient(_ptr(counter), _stream(stream)))
+
+
+def sqap_selftest_silu(counter, stream=None):
+    """counter: zeroed int64 device tensor of one element; receives the number of mismatches."""
+    _check(lib().sqap_selftest_silu(_ptr(counter), _stream(stream)))
 
 
 def sqap_selftest_dispatch(stream=None):

@@ -570,6 +570,12 @@ sqap_status sqap_selftest_quotient(uint64_t *mismatches_out, void *stream)
     return launch_quotient_selftest(reinterpret_cast<unsigned long long *>(mismatches_out), as_stream(stream));
 }
 
+sqap_status sqap_selftest_silu(uint64_t *mismatches_out, void *stream)
+{
+    if (!mismatches_out) return fail(SQAP_EINVAL, "sqap_selftest_silu: null pointer");
+    return launch_silu_selftest(reinterpret_cast<unsigned long long *>(mismatches_out), as_stream(stream));
+}
+
 size_t sqap_workspace_bytes(int32_t M, int32_t N, int32_t K)
 {
     if (M <= 0 || N <= 0 || K <= 0) return 0;

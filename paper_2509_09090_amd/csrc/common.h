@@ -202,6 +202,7 @@ sqap_status launch_attention_tiles(const __half *Q, int64_t ldq, const __half *K
                                    int batch, int Sq, int Sk, int H, int d, __half *O, int64_t ldo, hipStream_t st);
 sqap_status launch_residual_add(__half *X, int64_t ldx, const __half *Dl, int64_t ldd, int M, int K, hipStream_t st);
 sqap_status launch_quotient_selftest(unsigned long long *mismatches, hipStream_t st);
+sqap_status launch_silu_selftest(unsigned long long *mismatches, hipStream_t st);
 // Checks once per device how a launch's workgroups are dealt to the XCDs (see gemm.hip); table_out
 // (host, 256 words, nullable) receives the XCC id of every workgroup and forces a fresh probe.
 sqap_status probe_dispatch(int device, hipStream_t st, uint32_t *table_out);

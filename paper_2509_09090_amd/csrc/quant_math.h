@@ -98,8 +98,11 @@ __device__ __forceinline__ void add_squares8(const float (&v)[8], unsigned long 
 // silu(g) = (float)(g / (1 + exp(-g))) as the definition evaluates it in binary64, for a half value g: the same binary32
 // bits for every one of the 65536 halves (infinities and NaN among them).  exp(-g) = 2^k 2^f, |f| <= 1/2, with
 // 2^f = 1 + f q(f) (q interpolated at Chebyshev nodes), which is exact where |g| is tiny and g / 2 + g^2 / 4 may end on
-// a binary32 tie; the power of two enters the sum 1 + exp(-g) as a factor; the reciprocal by Newton's step.  Some 25
-// instructions where the library's exponential and division took about 70.
+// a binary32 tie; the power of two enters the sum 1 + exp(-g) as a factor; the reciprocal by one Newton step on the
+// hardware's estimate.  Some 25 instructions where the library's exponential and division took about 70.
+// The binary64 value is off by up to 2e-12 relative (a polynomial of nine terms, an estimate's error squared), so that its
+// rounding agrees everywhere is a matter of no half value ending that close to a tie, and near g = 0, where some do, of what
+// v_rcp_f64 returns for arguments near 2: sqap_selftest_silu compares all of them on the device.
 // The power's exponent stops at 2^1000, so a large negative g ends at -0; g = -inf makes f infinite and the result NaN,
 // as -inf / inf is; g = +inf is held at 700 in the exponent only.
 __device__ __forceinline__ float silu_of(float g)

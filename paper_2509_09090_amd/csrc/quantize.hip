@@ -686,6 +686,22 @@ sqap_status launch_quotient_selftest(unsigned long long *mismatches, hipStream_t
     return SQAP_OK;
 }
 
+// The same for silu_of, over all 65536 half values, against the definition with the library's exponential and division.
+__global__ __launch_bounds__(256) void silu_selftest_kernel(unsigned long long *mismatches)
+{
+    const float g = __half2float(__ushort_as_half((unsigned short)(blockIdx.x * 256 + threadIdx.x)));
+    const double gd = (double)g;
+    const float want = (float)(gd / (1.0 + exp(-gd))), got = silu_of(g);
+    if (__float_as_uint(want) != __float_as_uint(got) && !(want != want && got != got)) atomicAdd(mismatches, 1ull);
+}
+
+sqap_status launch_silu_selftest(unsigned long long *mismatches, hipStream_t st)
+{
+    hipLaunchKernelGGL(silu_selftest_kernel, dim3(256), dim3(256), 0, st, mismatches);
+    SQAP_HIP_CHECK(hipGetLastError());
+    return SQAP_OK;
+}
+
 // canonical [N, K/2] -> streaming layout (see Weight in common.h); one 16-byte
 // piece per thread; rows past N and their scales are written as zero.
 __global__ __launch_bounds__(256) void weight_pack_kernel(const uint8_t *__restrict__ Wq,

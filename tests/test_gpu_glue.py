@@ -114,6 +114,24 @@ def test_silu_of_every_half_value(G, oracle):
     assert np.array_equal(got.view(np.uint16), h_o.view(np.uint16)), int(np.count_nonzero(got.view(np.uint16) != h_o.view(np.uint16)))
 
 
+def test_silu_bits_of_every_half_value(G, oracle):
+    """In front of the product, in binary32: the same bits as the definition with the device library's exponential, which the decode step
+    kernel evaluates; and, where a factor of 3 shows a last bit near a tie (silu(g) = g / 2 + g^2 / 4 there), as the oracle's."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    c = torch.zeros((1,), dtype=torch.int64, device="cuda")
+    B.sqap_selftest_silu(c)
+    torch.cuda.synchronize()
+    assert int(c.item()) == 0
+    g = -np.arange(1, 2049, dtype=np.uint16).view(np.float16)
+    Gm = np.concatenate([g, g]).reshape(2, 2048)
+    Um = np.array([[3.0], [5.0]], np.float16) * np.ones((2, 2048), np.float16)
+    h = torch.zeros(Gm.shape, dtype=torch.float16, device="cuda")
+    B.sqap_swiglu_quantize_act(G.to_dev(Gm), G.to_dev(Um), None, None, h_out=h)
+    torch.cuda.synchronize()
+    assert np.array_equal(h.cpu().numpy().view(np.uint16), oracle.swiglu(Gm, Um).view(np.uint16))
+
+
 def test_silu_against_many_factors_and_at_the_infinities(G, oracle):
     """The product with u is rounded to half, which hides the last bits of silu: 64 factors that move the boundary about."""
     import torch
