@@ -1,4 +1,6 @@
 """Helpers for the GPU parity tests: numpy in, HIP library, numpy out."""
+import contextlib
+
 import numpy as np
 import torch
 
@@ -66,6 +68,17 @@ def gpu_linear(Xq, sx, Wq, sw, want_acc=True):
     torch.cuda.synchronize()
     W.free()
     return Y.cpu().numpy(), (acc.cpu().numpy() if want_acc else None)
+
+
+@contextlib.contextmanager
+def whole_outputs(on):
+    """With on = 0 the linears and groups that the kernel with whole outputs per workgroup would take by default go to the
+    kernels that serve the other shapes (tiles, stream-K, weight streaming)."""
+    B.sqap_set_mid_m_kernel(1 if on else 0)
+    try:
+        yield
+    finally:
+        B.sqap_set_mid_m_kernel(1)
 
 
 def assert_fp16_close(got, ref):

@@ -63,7 +63,10 @@ def test_topk_zero_sizes(G):
 
 @pytest.mark.parametrize("batch,S,v0,nv,k", [(1, 276, 0, 256, 128), (16, 276, 0, 256, 128),
                                              (3, 30, 4, 16, 5), (2, 700, 100, 500, 123),
-                                             (2, 20, 0, 20, 0), (2, 20, 3, 0, 0), (1, 64, 0, 64, 32)])
+                                             (2, 20, 0, 20, 0), (2, 20, 3, 0, 0), (1, 64, 0, 64, 32),
+                                             # one flag per visual token up to 8192 of them, a search of the list beyond
+                                             (2, 8300, 50, 8192, 4000), (2, 8300, 50, 8193, 4000), (1, 8200, 3, 8190, 8189),
+                                             (1, 9100, 17, 9000, 1)])
 def test_kept_rows_and_gather(G, oracle, batch, S, v0, nv, k):
     s = wl.scores(batch, max(nv, 1), wl.rng_for(91, S, wl.T_SCORES, k))[:, :nv]
     idx = oracle.prune_topk(s, k) if nv else np.zeros((batch, 0), np.int32)
@@ -316,17 +319,24 @@ def _random_packed(rng, R, K):
                                    (148, 1024, 11008), (513, 544, 640),
                                    # ragged last tile row of the 256-row tiles: 2, 3, 5 and 7 of its 8 row groups hold tokens
                                    (576, 1280, 4096), (608, 512, 2048), (672, 768, 1024), (736, 512, 512),
-                                   (2368, 512, 4096)])
+                                   (2368, 512, 4096),
+                                   # too many channels for whole outputs per workgroup: the other kernels by default, ragged last tile
+                                   # row (3, 5, 7 row groups), narrow tiles of 96 and 160 rows, the same with a guarded K, weight streaming
+                                   (608, 4160, 1024), (672, 4160, 1024), (736, 4160, 1024), (84, 12320, 256), (148, 12320, 256),
+                                   (84, 12320, 288), (148, 12320, 288), (300, 12320, 160), (8, 49184, 64)])
 def test_linear_random_codes(G, oracle, M, N, K):
-    """Uniform random codes (including -8) exercise every tile edge and the exact int32 sum."""
+    """Uniform random codes (including -8) exercise every tile edge and the exact int32 sum, in the kernel with whole outputs
+    per workgroup, where that is the default, and in the one that it stands in for."""
     rng = np.random.default_rng(M * 7 + N * 3 + K)
     Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
     sx = (rng.random(M) * 2 + 0.01).astype(np.float16)
     sw = (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
-    Y, acc = G.gpu_linear(Xq, sx, Wq, sw)
     Yo, acco = oracle.w4a4_linear(Xq, sx, Wq, sw)
-    assert np.array_equal(acc, acco)
-    assert G.assert_fp16_close(Y, Yo) == 0
+    for which in (1, 0):
+        with G.whole_outputs(which):
+            Y, acc = G.gpu_linear(Xq, sx, Wq, sw)
+        assert np.array_equal(acc, acco), which
+        assert G.assert_fp16_close(Y, Yo) == 0, which
 
 
 def test_dispatch_order_selftest(G):
@@ -338,18 +348,20 @@ def test_dispatch_order_selftest(G):
 
 @pytest.mark.parametrize("M,N,K", [(600, 768, 1024), (148, 1024, 2048), (84, 512, 1024)])
 def test_linear_fallback_kernels(G, oracle, M, N, K):
-    """With the persistent kernels switched off the one-tile-per-workgroup kernels give the same bits."""
+    """With the persistent kernels switched off the one-tile-per-workgroup kernels give the same bits (both apart from the kernel
+    with whole outputs per workgroup, which would take all three shapes)."""
     rng = np.random.default_rng(M + N + K)
     Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
     sx = (rng.random(M) * 2 + 0.01).astype(np.float16)
     sw = (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
-    Y1, acc1 = G.gpu_linear(Xq, sx, Wq, sw)
     from paper_2509_09090_amd import binding as B
-    B.sqap_set_persistent_kernels(False)
-    try:
-        Y2, acc2 = G.gpu_linear(Xq, sx, Wq, sw)
-    finally:
-        B.sqap_set_persistent_kernels(True)
+    with G.whole_outputs(0):
+        Y1, acc1 = G.gpu_linear(Xq, sx, Wq, sw)
+        B.sqap_set_persistent_kernels(False)
+        try:
+            Y2, acc2 = G.gpu_linear(Xq, sx, Wq, sw)
+        finally:
+            B.sqap_set_persistent_kernels(True)
     _, acco = oracle.w4a4_linear(Xq, sx, Wq, sw)
     assert np.array_equal(acc1, acco) and np.array_equal(acc2, acco)
     assert np.array_equal(Y1.view(np.uint16), Y2.view(np.uint16))
@@ -458,13 +470,21 @@ def test_attn_scores_batch(G, oracle):
             assert np.allclose(out[b].cpu().numpy(), one.cpu().numpy(), rtol=1e-6, atol=1e-9), (nb, S, H, d, b)
 
 
-@pytest.mark.parametrize("M,N,K", [(600, 768, 1024),     # 3 x 3 tiles of 256 x 256 over 256 workgroups: every tile is shared
-                                   (148, 1024, 2048),    # narrow tiles, finished together by their contributors
-                                   (84, 512, 11008)])
-def test_linear_replayed_from_a_graph(G, oracle, M, N, K):
+@pytest.mark.parametrize("which,M,N,K", [(0, 600, 768, 1024),     # 3 x 3 tiles of 256 x 256 over 256 workgroups: every tile is shared
+                                         (0, 148, 1024, 2048),    # narrow tiles, finished together by their contributors
+                                         (0, 84, 512, 11008),
+                                         (1, 600, 4352, 1024),    # stream-K tiles, narrow tiles by default: too many channels for
+                                         (1, 148, 12320, 1024),   # whole outputs per workgroup
+                                         (1, 148, 1024, 2048), (1, 4, 512, 1024)])      # whole outputs per workgroup
+def test_linear_replayed_from_a_graph(G, oracle, which, M, N, K):
     """A captured launch of the split (persistent) kernels carries the launch epoch it was captured with:
     every replay, with new operands and eager launches on the same workspace in between, must still
-    give the exact result."""
+    give the exact result.  (which = 0: without the kernel that needs no split.)"""
+    with G.whole_outputs(which):
+        _replay_linear(G, oracle, M, N, K)
+
+
+def _replay_linear(G, oracle, M, N, K):
     import torch
     from paper_2509_09090_amd import binding as B
     rng = np.random.default_rng(4242 + M)
@@ -475,7 +495,7 @@ def test_linear_replayed_from_a_graph(G, oracle, M, N, K):
     sxd = torch.zeros((M,), dtype=torch.float16, device="cuda")
     Y = torch.zeros((M, N), dtype=torch.float16, device="cuda")
     acc = torch.zeros((M, N), dtype=torch.int32, device="cuda")
-    ws = torch.empty((B.sqap_workspace_bytes(M, N, K),), dtype=torch.uint8, device="cuda")
+    ws = torch.empty((max(B.sqap_workspace_bytes(M, N, K), 256),), dtype=torch.uint8, device="cuda")
     ws.random_(0, 256)                  # the workspace needs no initialisation
     side = torch.cuda.Stream()          # default priority
     side.wait_stream(torch.cuda.current_stream())
@@ -513,14 +533,17 @@ def test_linear_replayed_from_a_graph(G, oracle, M, N, K):
                                    # few row groups with long rows: every wavefront walks its ring two or three times
                                    (1, 8192, 8192), (3, 2048, 16384), (2, 96, 8320), (8, 4096, 11008)])
 def test_small_m_linear(G, oracle, M, N, K):
+    """Whole outputs per workgroup, the default for all of these, and the weight-streaming kernel."""
     rng = np.random.default_rng(M * 11 + N * 5 + K)
     Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
     sx = (rng.random(M) * 2 + 0.01).astype(np.float16)
     sw = (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
-    Y, acc = G.gpu_linear(Xq, sx, Wq, sw)
     Yo, acco = oracle.w4a4_linear(Xq, sx, Wq, sw)
-    assert np.array_equal(acc, acco)
-    assert G.assert_fp16_close(Y, Yo) == 0
+    for which in (1, 0):
+        with G.whole_outputs(which):
+            Y, acc = G.gpu_linear(Xq, sx, Wq, sw)
+        assert np.array_equal(acc, acco), which
+        assert G.assert_fp16_close(Y, Yo) == 0, which
 
 
 def test_group_with_many_row_groups_per_wavefront(G, oracle):
