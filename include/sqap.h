@@ -393,7 +393,8 @@ sqap_status sqap_swiglu_quantize_act(const sqap_f16 *G, int64_t ldg, const sqap_
  * sqap_attention: causal softmax attention.  Query i (of Sq) sits at position
  * Sk - Sq + i of the key sequence and sees keys 0 .. Sk - Sq + i:
  *   o[i,h,:] = sum_t softmax_t((q[i,h,:] . k[t,h,:]) / sqrt(d)) v[t,h,:]
- * in binary32 (online softmax over tiles of 64 keys), rounded to half.
+ * in binary32 (online softmax; with d = 64 or 128 a probability enters its product as the sum of two
+ * halves, 22 bits), rounded to half.
  * Q [Sq, H*d], K, V [Sk, H*d], O [Sq, H*d] with row pitches in elements; a
  * batch of independent sequences is a stack of such row blocks (sequence b
  * owns rows b*Sq .. of Q and O and rows b*Sk .. of K and V).

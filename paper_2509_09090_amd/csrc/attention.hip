@@ -20,8 +20,9 @@ namespace sqap {
 // off (2-norm, 1024 queries x 2048 keys), with two 2.07e-4, which is the rounding of the output; the second set of
 // products costs 10 % at that size.  That also makes the running maximum free to lag: it is only raised when
 // a score exceeds it by more than 2^6 (scores are in units of ln 2), so O^T (64 registers) is seldom rescaled.
-// What bounds it: not the loads (three or four buffers instead of two: no faster) nor any one unit (matrix cores busy
-// 40 % of the time at 1024 x 2048), but the chain key reads -> products -> softmax -> products of a wavefront with two
+// What bounds it: not the loads (three or four buffers instead of two: no faster) nor any one unit (at 1024 x 2048 the
+// matrix cores are busy in 45 % of the cycles in which a compute unit has work, the vector ALU in 45 %, LDS in 16 %; no bank conflicts), but
+// the chain key reads -> products -> softmax -> products of a wavefront with two
 // wavefronts per SIMD to fill it; having all LDS reads of a step in flight at once gave 12 %, addresses as a uniform base
 // and a lane offset 15 %.  Slower: 64 keys per wavefront and step (the same at two waves per SIMD, worse with fewer),
 // four or eight query groups on one tile, half of the key groups running half a step behind the others.
@@ -350,7 +351,9 @@ static sqap_status launch_tiles(const __half *Q, int64_t ldq, const __half *Kc, 
 //   1x84x1000, 32 heads 19.7 / 14.7;  1x1024x1024, 8 heads 19.2 / 14.3;  1x64x384, 32 heads 9.6 / 7.7;
 //   1x1x149, 32 heads 6.0 / 5.8;  1x148x148, 32 heads 6.3 / 6.5;  1x400x400, 32 heads 10.5 / 12.4;
 //   16x148x148, 32 heads 22.2 / 49.3;  1x1024x2048, 32 heads 48.5 / 71.3.
-// (The second form needs four column tiles to share out: heads of 64 stay with the first.)
+// The second form needs four column tiles to share out: heads of 64 stay with the first, few queries over many keys among them
+// (us, with four wavefronts along the keys and no sharing in brackets: 1x10x1341, 1 head 16.1 (17.6); 2x2x2917, 8 heads 32.9 (34.4);
+// 1x7x2506, 32 heads 29.0 (30.6); 1x25x554, 8 heads 8.6 (10.0)).
 sqap_status launch_attention_tiles(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
                                    int batch, int Sq, int Sk, int H, int d, __half *O, int64_t ldo, hipStream_t st)
 {

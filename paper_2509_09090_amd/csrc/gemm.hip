@@ -1106,7 +1106,7 @@ static bool narrow_tile_is_mid(int M)
 size_t linear_workspace_bytes(int M, int, int K)
 {
     if (K % kBK != 0 || M <= kSkinnyMaxM) return 0;
-    // one tile-sized int32 slot per workgroup; the narrow shapes need two (see gemm_splitk_kernel)
+    // one tile-sized int32 slot per workgroup; the narrow shapes need two for the joint finish (see gemm_splitk_kernel)
     if (M >= kStreamKMinM) return kFlagBytes + (size_t)kMaxPersistentBlocks * CfgBig::BM * CfgBig::BN * sizeof(int32_t);
     const size_t slot = narrow_tile_is_mid(M) ? (size_t)CfgMid::BM * CfgMid::BN : (size_t)CfgLow::BM * CfgLow::BN;
     return kFlagBytes + 2 * (size_t)kMaxPersistentBlocks * slot * sizeof(int32_t);
@@ -1471,6 +1471,8 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
         // the contributors finish it together; with many tiles a single finisher has only two or
         // three partials to add, which measured faster than the joint finish (23.6 vs 28.6 us at
         // M = 148, N = 11008, K = 4096; the other way round, 21.6 vs 15.2 us, at N = 4096).
+        // The joint finish is for devices with fewer than 256 compute units (a partition) and for sqap_set_mid_m_kernel(0): with all
+        // of them, every shape of so few tiles goes to the kernel with whole outputs above (4096 there: 9.1 us).
         const bool mid = narrow_tile_is_mid(M);
         const int64_t tiles = (int64_t)((M + (mid ? CfgMid::BM : CfgLow::BM) - 1) / (mid ? CfgMid::BM : CfgLow::BM)) *
                               ((w.N + CfgMid::BN - 1) / CfgMid::BN);

@@ -22,7 +22,8 @@
 // int4 -> int8 as in the large-M kernel: (x << 4) & 0xF0F0F0F0 and x & 0xF0F0F0F0 give 16 * code for the even
 // and the odd codes; both operands are split the same way, so the accumulator is 256 * sum(x * w).
 // The price is that every workgroup reads all its token rows for the whole K (they come from the L2,
-// which the 32 workgroups of an XCD share).
+// which the 32 workgroups of an XCD share).  And with 16 rows or fewer, decode sizes among them, the second half has no token
+// group of its own: wavefronts 4 .. 7 read the last row and all weights once more and store nothing.
 #include "common.h"
 
 namespace sqap {
@@ -341,26 +342,43 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const Row
 // of its own (each workgroup then reads fewer token rows, and the weights are read once per block, the
 // second time from the L2).  Cost of a workgroup in clock cycles: what its compute unit loads at 64 bytes
 // per cycle against what its matrix cores multiply (a 16 x 16 x 64 product takes 16 cycles on one of four SIMDs).
-// Plans in which a workgroup's channel groups fit ONE tile are always taken: 25-45 % faster than the tile kernels
-// that split K between workgroups at a few hundred rows (M = 148: N = 4096 9.1 against 15.0 us, N = 12288 15.7 against
-// 20.8, K = 11008 15.2 against 22.1), more where those have few tiles or a K that is no multiple of 128 (us, M x N x K:
-// 522 x 1024 x 2816 8.2 against 25.4; 2000 x 700 x 5504 19.2 against 46.4; 148 x 2048 x 5504 10.2 against 16.5;
-// 32 x 512 x 512 3.5 against 7.8; 450 x 300 x 4160 9.1 against 57).  A second tile reads the token rows again and pays the
-// start-up of the load pipeline again: worth it up to 64 rows (64 x 22016 x 4096 17.5 against 19.7, 16 rows 12.9 against
-// 18.3; 84 rows 21.6 against 20.9), where the 256 x 256 tiles are few (four groups: 600 x 4096 x 4096 23.4 against 31.2,
-// 2368 x 1024 x 4096 25.1 against 31.3), and against the tiles with a guarded K (six groups, M > 160: 300 x 12288 x 4160 33.9
-// against 50.7, 1200 x 3000 x 4160 33.1 against 50.6; eight at K = 1088: 600 x 8000 25.4 against 17.8); not at
-// 160 < M < 512 otherwise (276 x 8192 x 4096 23.0 against 19.7) nor with K below 1024 (600 x 4096 x 512 12.4 against 11.0).
-// Up to 32 rows a tile takes six groups and two tiles are taken.  That includes decode sizes: one launch per linear (or per
-// group of linears with one input: q, k and v are a product over 12288 channels) has no stream long enough for the
-// streaming kernel's pipeline, and here its start-up is shorter (M = 1 / 8, us, the streaming kernel in brackets: 4096 x 4096 5.7 / 5.8 (8.2 /
-// 8.6), 12288 x 4096 8.9 (11.9 / 13.2), 22016 x 4096 13.8 / 14.0 (15.9 / 16.5), K = 11008 8.0 / 8.2 (12.8 / 13.5), 32000 x 4096
-// 17.6 / 17.5 (19.3 / 19.4), 512 x 512 3.5 / 3.8 (6.9 / 7.0)).  Launches of many problems stay with that kernel.
+// The plan with the lowest cost is taken, if a workgroup then has no more channel groups than rows_max_groups allows.
+//
+// How many groups of 16 channels a workgroup may have for this kernel to be the faster one (us, M x N x K, the other kernel behind
+// "against").
+// One tile (three groups; six up to 32 rows): always.  148 rows: N = 4096 9.1 against 15.0, N = 12288 15.7 against 20.8, K = 11008
+// 15.2 against 22.1; where the 256 x 256 tiles are few or K is no multiple of 128, more: 522 x 1024 x 2816 8.2 against 25.4;
+// 2000 x 700 x 5504 19.2 against 46.4; 148 x 2048 x 5504 10.2 against 16.5; 32 x 512 x 512 3.5 against 7.8; 450 x 300 x 4160 9.1
+// against 57.
+// A second tile reads the token rows again and pays the start-up of the load pipeline again.  Worth it
+//   up to 64 rows: 64 x 22016 x 4096 17.5 against 19.7, 16 rows 12.9 against 18.3 (84 rows 21.6 against 20.9: not);
+//   against the tiles with a guarded K: 300 x 12288 x 4160 33.9 against 50.7, 1200 x 3000 x 4160 33.1 against 50.6 (not with eight
+//   groups at K = 1088: 600 x 8000 25.4 against 17.8);
+//   four groups from 512 rows on: 600 x 4096 x 4096 23.4 against 31.2, 2368 x 1024 x 4096 25.1 against 31.3;
+// not between otherwise (276 x 8192 x 4096 23.0 against 19.7), nor with a K too short to make up for a start-up (600 x 4096 x 512
+// 12.4 against 11.0).
+// Decode sizes are in: one launch per linear (or per group of linears with one input: q, k and v are a product over 12288
+// channels) has no stream long enough for the streaming kernel's pipeline, and here its start-up is shorter (M = 1 / 8, the streaming
+// kernel in brackets: 4096 x 4096 5.7 / 5.8 (8.2 / 8.6), 12288 x 4096 8.9 (11.9 / 13.2), 22016 x 4096 13.8 / 14.0 (15.9 / 16.5),
+// K = 11008 8.0 / 8.2 (12.8 / 13.5), 32000 x 4096 17.6 / 17.5 (19.3 / 19.4), 512 x 512 3.5 / 3.8 (6.9 / 7.0)).  Launches of many
+// problems stay with that kernel.
+// Both sides compared on 800 drawn shapes (1 to 2600 rows, 16 to 60000 channels, K of 32 to 16384) and 120 groups: fifteen shapes more
+// than 2 % slower with this rule than with the kernels they had before it, by up to 0.3 us at 3 to 8 us (5 % at one), 447 more than
+// 2 % faster.
+static int rows_max_groups(int M, int K)
+{
+    if (M <= 32) return M <= kSkinnyMaxM || K >= 1024 ? 2 * kRowsMaxBFew : kRowsMaxB;
+    if (K < 1024) return kRowsMaxB;
+    if (M <= 64) return 2 * kRowsMaxB;
+    if (M > 160 && K % 128 != 0 && K >= 2048) return 2 * kRowsMaxB;
+    return M >= 512 ? 4 : kRowsMaxB;
+}
+
 static bool rows_plan(int M, int c16, int K, int cus, RowsParams *p)
 {
     if (K % 32 != 0 || c16 < 1) return false;
     if (M <= kSkinnyMaxM && K % 64 == 0 && K > 32768) return false;         // the streaming kernel's, which says what it refuses
-    const int max_groups = M <= 32 ? (M <= kSkinnyMaxM || K >= 1024 ? 2 * kRowsMaxBFew : kRowsMaxB) : K < 1024 ? kRowsMaxB : K % 128 != 0 && M > 160 && K >= 2048 ? 6 : M <= 64 ? 6 : M >= 512 ? 4 : kRowsMaxB;
+    const int max_groups = rows_max_groups(M, K);
     double best = 0.0;
     for (int tb = 1; tb <= 16; tb *= 2) {
         const int rows = ((M + tb - 1) / tb + 15) / 16 * 16;

@@ -447,8 +447,9 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(const __half *__r
 // of its own, and the chunks' running maxima follow from the scores.  Eight wavefronts work out all scores (32 keys at
 // a time), then maxima, probabilities and group sums of all chunks side by side, then the output, two key groups
 // per wavefront and four columns per lane.  The same operations in the same order per value: the same bits.
-// What bounds it: a compute unit takes in about 65 GB/s, 7.4 ns per position (512 bytes), and there is one per head (more
-// would have to meet in memory that the call does not have); rows in flight beyond these gave nothing.
+// What bounds it: a compute unit takes in about 65 GB/s (7.4 ns more per position of 512 bytes, from 1500 to 3000 of them), and
+// there is one per head; rows in flight beyond these gave nothing.  (The value columns are independent chains: workgroups that
+// each take all scores and a share of the columns would not have to meet.  Not tried.)
 // Measured (32 heads of 128, us without the quantizer, the other kernel in brackets): 192 positions 7.8 (7.5), 400 9.4
 // (9.8), 800 12.8 (15.9), 1500 16.9 (23.4), 3000 28.1 (43.6): used from two chunks on.
 // Scores wait in LDS, 4 bytes per position: up to kDecLongMax of them (with the rest 52 KiB).

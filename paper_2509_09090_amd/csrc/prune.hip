@@ -266,11 +266,12 @@ sqap_status launch_prune_rows(const float *scores, int batch, int n, int keep_k,
 // are shared out by lane number mod 4; then the first wavefront samples alone (a pick depends on the one before, and a
 // barrier per pick would cost more than the arithmetic it shares out).  Everything after the projection is
 // integer work, so the result is exact.
-// A serial chain bounds it: a pick is about 5 instructions per 64 tokens, a wavefront maximum and the
-// decoding of the winner.  A token's state is one word, squared distance * 2048 + inverted index: the largest word is the
-// next pick, a member's distance is zero, which keeps it out without further tests, and (u, v) are packed halves whose
-// squared distance is one subtraction and one dot product.  Measured per call, 16 observations, us (one wavefront, masks
-// and coordinates apart, in brackets): 16 x 16 tokens, 128 kept 15.6 (26.6); 32 x 32, 512 kept 91 (214).
+// A serial chain bounds it: 32 ballot rounds of the top-k search, one per bit of the key, then the picks; a pick is about
+// 5 instructions per 64 tokens, a wavefront maximum and the decoding of the winner.  A token's state is one word, squared
+// distance * 2048 + inverted index: the largest word is the next pick, a member's distance is zero, which keeps it out without
+// further tests, and (u, v) are packed halves whose squared distance is one subtraction and one dot product.  Measured per
+// call, 16 observations, us (one wavefront, masks and coordinates apart, in brackets): 16 x 16 tokens, 128 kept 15.6 (26.6);
+// 32 x 32, 512 kept 91 (214).
 constexpr int kSelectCamera = 26;          // doubles per observation: K (9), [R|t] (12), point (3), patch w, h
 constexpr uint32_t kFarAway = 1u << 20;    // above any squared distance on a grid of <= 1024 tokens
 

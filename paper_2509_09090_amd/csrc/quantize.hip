@@ -248,8 +248,8 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta
 // SwiGLU (Shazeer 2020; the feed-forward of a Llama decoder): v holds the gate row g, pre.U the
 // up row;  v = half(silu(g) * u),  silu(g) = (float)(g / (1 + exp(-g))) evaluated in binary64.
 // silu is a function of a half value: a GPU test walks all 2^16 of them against the host's.
-// At 2368 x 11008 the vector ALU bounds this form (17.1 thousand instructions per SIMD, 43 per element, 25 of them silu's):
-// 40 us against 49.7 with the library's binary64 exponential and division; 117 MB take 23 us.
+// At 2368 x 11008 the vector ALU bounds this form (16.5 thousand instructions per SIMD, 42 per element, 25 of them silu's, and issuing
+// in 98 % of the cycles): 40 us against 49.7 with the library's binary64 exponential and division; 117 MB take 23 us.
 // (A per-device table of the 2^16 results was slower than computing: 13 against 10 us at 84 x 11008,
 // 48 scattered 4-byte loads per thread.)
 template <int T, int GPT>

@@ -259,7 +259,7 @@ def test_whole_output_kernel_edge_shapes(G, oracle, M, N, K):
 # blocks of token rows, several tiles per workgroup; the shapes on both sides of every line of the rule.
 @pytest.mark.parametrize("M,N,K", [(9, 16, 32), (20, 100, 64), (33, 48, 96), (17, 256, 256), (32, 512, 512), (70, 77, 736), (148, 512, 1408),
                                    (161, 300, 1056), (100, 512, 5504), (300, 33, 4160), (641, 100, 1280), (1300, 64, 288), (2560, 16, 544),
-                                   (2561, 16, 256), (64, 12800, 1024), (65, 12800, 1024), (600, 3100, 1024), (512, 3100, 992), (170, 9000, 2080)])
+                                   (2561, 16, 256), (64, 12800, 1024), (65, 12800, 1024), (600, 3100, 1024), (512, 3100, 992), (170, 9000, 2080), (125, 12000, 288)])
 def test_whole_output_kernel_any_k(G, oracle, M, N, K):
     rng = np.random.default_rng(M + N * 3 + K)
     Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
