@@ -26,8 +26,11 @@ namespace sqap {
 // wavefronts per SIMD to fill it; having all LDS reads of a step in flight at once gave 12 %, addresses as a uniform base
 // and a lane offset 15 %.  Slower: 64 keys per wavefront and step (the same at two waves per SIMD, worse with fewer),
 // four or eight query groups on one tile, half of the key groups running half a step behind the others.
+// Finding out whether outputs are finite and agreeing on it takes 0.1 to 0.2 us of a workgroup (16 x 148 x 148 22.7 without, 23.6 with,
+// 1024 x 2048 50.7 and 51.0; a second time through the keys doubles a workgroup's time).  Heads of 64 are held to the 128 registers that
+// four wavefronts per SIMD leave, which the second time through would pass (16 x 274 x 274, 32 heads 26.6, with 137 registers 28.0).
 // Measured (us; the kernel before, one key tile per wavefront and 2-byte transposing reads, in brackets; heads of 128):
-// 16 x 148 x 148, 32 heads 22.2 (62.8); 1024 x 2048, 32 heads 48.5 (126); 148 x 148, 32 heads 6.3 (8.2); 84 x 84 5.3 (6.2).
+// 16 x 148 x 148, 32 heads 23.2 (62.8); 1024 x 2048, 32 heads 48.8 (126); 148 x 148, 32 heads 6.5 (8.2); 84 x 84 5.5 (6.2).
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -54,13 +57,22 @@ __device__ __forceinline__ int swizzle(int r)
 }
 
 // two buffers of NK * 32 key rows and value rows; the merge reuses them for a (maximum, sum) pair per lane and the
-// column tiles that a wavefront does not own
+// column tiles that a wavefront does not own, and a word behind these
+template <int D, int NQ, int NK>
+constexpr int merge_bytes() { return NQ * NK * 512 + NQ * NK * (NK - 1) * (D / 32 / NK) * 4096; }
+
 template <int D, int NQ, int NK>
 constexpr int attention_lds_bytes()
 {
-    const int tiles = 2 * NK * 32 * 2 * (2 * D);
-    const int merge = NK == 1 ? 0 : NQ * NK * 512 + NQ * NK * (NK - 1) * (D / 32 / NK) * 4096;
+    const int tiles = 2 * NK * 32 * 2 * (2 * D), merge = merge_bytes<D, NQ, NK>() + 16;
     return tiles > merge ? tiles : merge;
+}
+
+// two halves: those of b where a's are not finite
+__device__ __forceinline__ unsigned where_not_finite(unsigned a, unsigned b)
+{
+    const unsigned lo = (a & 0x7c00u) == 0x7c00u ? b : a, hi = (a & 0x7c000000u) == 0x7c000000u ? b : a;
+    return (lo & 0xffffu) | (hi & 0xffff0000u);
 }
 
 // The A operands of 32 keys: per 16 keys and column tile two transposing reads (keys +0..3 and +8..11 of this lane half).
@@ -98,28 +110,29 @@ __device__ __forceinline__ void read_values(unsigned at, const unsigned (&lane_v
         for (int ct = 0; ct < D / 32; ++ct) va[n][ct] = r[n][ct].v;
 }
 
-template <int D, int NQ, int NK>
-__global__ __launch_bounds__(64 * NQ * NK, 2) void attention_tiles_kernel(const __half *__restrict__ Q, int64_t ldq,
-                                                              const __half *__restrict__ Kc, int64_t ldk,
-                                                              const __half *__restrict__ V, int64_t ldv, int Sq, int Sk,
-                                                              __half *__restrict__ O, int64_t ldo)
+// The queries of a workgroup over all their keys: this wavefront's column tiles (OWN of them), as pairs of halves.
+// FIRST: the fast way, with two assumptions.  Values are finite: an infinite one times the low half of a probability, which is
+// zero or negative as often as not, is NaN where the probability times the value is infinite.  And scores are below 2^24 in
+// units of ln 2: the maximum is a rounded product, the scores it is taken from are not, and beyond that the difference, which
+// should be zero at the largest, is off by more than 1: the sum of the probabilities, at least 1 otherwise, is then below 1/2, or
+// a probability overflows.  Where an assumption fails outputs are not finite, and the result is true (for a lane of them).  Not FIRST:
+// one half per probability, rounded products, and zeros for the values past the last key, for which neither matters; no
+// probability of a key that is seen, and no factor, is zero there, so that an infinite value stays one however small its weight
+// (probabilities are 2^9 times as large: the smallest half adds 2^-33 of the largest).
+template <int D, int NQ, int NK, bool FIRST>
+__device__ __forceinline__ bool attend(uint8_t *lds, int l, int wave, int qblock, const __half *__restrict__ Q, int64_t ldq,
+                                        const __half *__restrict__ Kc, int64_t ldk, const __half *__restrict__ V, int64_t ldv,
+                                        int Sq, int Sk, unsigned (&w)[D / 32 / NK][8])
 {
     constexpr int NP = D / 16, CT = D / 32, TK = 32, TILE = NK * TK, ROW = 2 * D, PIECES = D / 8;
     constexpr int BUF = TILE * 2 * ROW;                               // keys, then values
     constexpr int RPI = 1024 / ROW;                                   // rows per wavefront load
     constexpr int WAVES = NQ * NK, LOADS_PER_WAVE = 2 * TILE / RPI / WAVES;
     static_assert(WAVES % 4 == 0 && (TILE / RPI) % WAVES == 0, "every wavefront asks for the same number of pieces");
-    static_assert(NK == 1 || CT % NK == 0, "the key groups share the output's column tiles");
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-    const int l = threadIdx.x & 63, c = l & 31, h = l >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int kg = NK == 1 ? 0 : wave / NQ, qg = NK == 1 ? wave : wave % NQ;
-    const int qblock = gridDim.y - 1 - blockIdx.y;                    // the longest rows first
+    static_assert(NK > 1 && CT % NK == 0, "the key groups share the output's column tiles");
+    const int c = l & 31, h = l >> 5;
+    const int kg = wave / NQ, qg = wave % NQ;
     const int q0 = (qblock * NQ + qg) * 32;
-    Q += (int64_t)blockIdx.z * Sq * ldq + (int64_t)blockIdx.x * D;
-    O += (int64_t)blockIdx.z * Sq * ldo + (int64_t)blockIdx.x * D;
-    Kc += (int64_t)blockIdx.z * Sk * ldk + (int64_t)blockIdx.x * D;
-    V += (int64_t)blockIdx.z * Sk * ldv + (int64_t)blockIdx.x * D;
     const int shift = Sk - Sq, my_q = q0 + c;
     const int block_last = min(Sk - 1, min((qblock + 1) * NQ * 32 - 1, Sq - 1) + shift);
     const int last_key = q0 < Sq ? min(q0 + 31, Sq - 1) + shift : -1; // of this wavefront
@@ -184,6 +197,15 @@ __global__ __launch_bounds__(64 * NQ * NK, 2) void attention_tiles_kernel(const 
 #pragma unroll
     for (int m = 0; m < NP; ++m) lane_k[m] = c * ROW + (((2 * m + h) ^ swizzle<D>(c)) << 4);
 
+    auto factor = [](float x) __attribute__((always_inline)) {
+        const float f = __builtin_amdgcn_exp2f(x);
+        return !FIRST && f < 0x1p-100f ? 0x1p-100f : f;               // (NaN stays)
+    };
+    auto probability = [&](float s, float m) __attribute__((always_inline)) {
+        if (FIRST) return __builtin_amdgcn_exp2f(fmaf(s, scale, -m));
+        const float p = __builtin_amdgcn_exp2f((s * scale - m) + 9.f);
+        return p < 0x1p-24f && s > -INFINITY ? 0x1p-24f : p;
+    };
     v16f st;
     auto scores = [&](int it) {
         const int key_tile = (it & 1) * BUF + kg * TK * ROW;
@@ -213,7 +235,7 @@ __global__ __launch_bounds__(64 * NQ * NK, 2) void attention_tiles_kernel(const 
         tmax = fmaxf(__uint_as_float(other[0]), __uint_as_float(other[1])) * scale;
         if (__any(tmax > mrun + kRaiseBy)) {
             const float m_new = fmaxf(mrun, tmax);
-            const float f = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mrun - m_new);
+            const float f = m_new == -INFINITY ? 1.f : factor(mrun - m_new);
             mrun = m_new;
             lrun *= f;
 #pragma unroll
@@ -225,8 +247,7 @@ __global__ __launch_bounds__(64 * NQ * NK, 2) void attention_tiles_kernel(const 
         v8h ph[2], pl[2];
 #pragma unroll
         for (int i = 0; i < 16; i += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(st[i], scale, -m_sub));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(st[i + 1], scale, -m_sub));
+            const float p0 = probability(st[i], m_sub), p1 = probability(st[i + 1], m_sub);
             lrun += p0 + p1;
             const v2h pk = {(_Float16)p0, (_Float16)p1};
             const v2h pr = {(_Float16)remainder_of<0>(pk, p0), (_Float16)remainder_of<1>(pk, p1)};
@@ -240,13 +261,18 @@ __global__ __launch_bounds__(64 * NQ * NK, 2) void attention_tiles_kernel(const 
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
                 ot[ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[n][ct], ph[n], ot[ct], 0, 0, 0);
-                ot[ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[n][ct], pl[n], ot[ct], 0, 0, 0);
+                if (FIRST) ot[ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[n][ct], pl[n], ot[ct], 0, 0, 0);
             }
     };
 
     for (int it = 0; it < n_iter; ++it) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this wavefront's part of tile `it` has landed
         lds_barrier();                                                // everybody's has; the other buffer is free
+        if (!FIRST && (it + 1) * TILE > Sk) {                         // zeros instead of the last value row's repetitions
+            for (int r = Sk - it * TILE + threadIdx.x / PIECES; r < TILE; r += 64 * WAVES / PIECES)
+                *reinterpret_cast<uint4 *>(lds + (it & 1) * BUF + (TILE + r) * ROW + 16 * (threadIdx.x % PIECES)) = make_uint4(0u, 0u, 0u, 0u);
+            lds_barrier();
+        }
         issue(it + 1);
         if (it * TILE + kg * TK <= last_key) {
             scores(it);
@@ -258,67 +284,100 @@ __global__ __launch_bounds__(64 * NQ * NK, 2) void attention_tiles_kernel(const 
 
     // merge of the key groups: group g collects column tiles g * CT / NK .. from the others
     constexpr int OWN = CT / NK;
-    if constexpr (NK > 1) {
-        float *ml = reinterpret_cast<float *>(lds);                   // [wave][64] pairs (maximum, sum)
-        float *pieces = ml + WAVES * 128;
-        __syncthreads();                                              // the tiles are no longer needed
-        ml[(wave * 64 + l) * 2] = mrun;
-        ml[(wave * 64 + l) * 2 + 1] = lrun;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            const int owner = ct / OWN;
-            if (owner != kg) {
-                float *dst = pieces + (((qg * NK + owner) * (NK - 1) + (kg < owner ? kg : kg - 1)) * OWN + ct % OWN) * 1024;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) dst[i * 64 + l] = ot[ct][i];
-            }
-        }
-        __syncthreads();
-        float mall = -INFINITY, f[NK];
-#pragma unroll
-        for (int g = 0; g < NK; ++g) mall = fmaxf(mall, ml[((g * NQ + qg) * 64 + l) * 2]);
-        float lall = 0.f;
-#pragma unroll
-        for (int g = 0; g < NK; ++g) {
-            const float mg = ml[((g * NQ + qg) * 64 + l) * 2];
-            f[g] = mg == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mg - mall);
-            lall += ml[((g * NQ + qg) * 64 + l) * 2 + 1] * f[g];
-        }
-        const float f_own = mrun == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun - mall);
-        lrun = lall;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            if (ct / OWN == kg) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) ot[ct][i] *= f_own;
-#pragma unroll
-                for (int g = 0; g < NK; ++g)
-                    if (g != kg) {
-                        const float *src = pieces + (((qg * NK + kg) * (NK - 1) + (g < kg ? g : g - 1)) * OWN + ct % OWN) * 1024;
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) ot[ct][i] = fmaf(src[i * 64 + l], f[g], ot[ct][i]);
-                    }
-            }
-        }
-    }
-    const float inv_l = 1.0f / lrun;
+    float *ml = reinterpret_cast<float *>(lds);                       // [wave][64] pairs (maximum, sum)
+    float *pieces = ml + WAVES * 128;
+    __syncthreads();                                                  // the tiles are no longer needed
+    ml[(wave * 64 + l) * 2] = mrun;
+    ml[(wave * 64 + l) * 2 + 1] = lrun;
+    if (threadIdx.x == 0) *reinterpret_cast<int *>(lds + merge_bytes<D, NQ, NK>()) = 0;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-        if (NK > 1 && ct / OWN != kg) continue;
-        // four consecutive columns per register quad; two quads make 16 bytes once the lane halves have exchanged
-        unsigned w[8];
+        const int owner = ct / OWN;
+        if (owner != kg) {
+            float *dst = pieces + (((qg * NK + owner) * (NK - 1) + (kg < owner ? kg : kg - 1)) * OWN + ct % OWN) * 1024;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) dst[i * 64 + l] = ot[ct][i];
+        }
+    }
+    __syncthreads();
+    float mall = -INFINITY, f[NK];
+#pragma unroll
+    for (int g = 0; g < NK; ++g) mall = fmaxf(mall, ml[((g * NQ + qg) * 64 + l) * 2]);
+    float lall = 0.f;
+#pragma unroll
+    for (int g = 0; g < NK; ++g) {
+        const float mg = ml[((g * NQ + qg) * 64 + l) * 2];
+        f[g] = mg == -INFINITY ? 0.f : factor(mg - mall);
+        lall += ml[((g * NQ + qg) * 64 + l) * 2 + 1] * f[g];
+    }
+    const float f_own = mrun == -INFINITY ? 0.f : factor(mrun - mall);
+    const float inv_l = !FIRST || lall >= 0.5f ? 1.0f / lall : NAN;
+    float zero[4] = {};                                               // NaN with the first output that is not finite
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+        if (ct / OWN != kg) continue;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) ot[ct][i] *= f_own;
+#pragma unroll
+        for (int g = 0; g < NK; ++g)
+            if (g != kg) {
+                const float *src = pieces + (((qg * NK + kg) * (NK - 1) + (g < kg ? g : g - 1)) * OWN + ct % OWN) * 1024;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) ot[ct][i] = fmaf(src[i * 64 + l], f[g], ot[ct][i]);
+            }
 #pragma unroll
         for (int i = 0; i < 16; i += 2) {
             union { __half2 v; unsigned u; } pk;
             pk.v = __floats2half2_rn(ot[ct][i] * inv_l, ot[ct][i + 1] * inv_l);
-            w[i >> 1] = pk.u;
+            w[ct % OWN][i >> 1] = pk.u;
+            zero[(i >> 1) & 3] = __builtin_amdgcn_fdot2(__builtin_bit_cast(v2h, pk.u), v2h{0, 0}, zero[(i >> 1) & 3], false);
         }
+    }
+    return my_q < Sq && (zero[0] + zero[1]) + (zero[2] + zero[3]) != 0.f;
+}
+
+template <int D, int NQ, int NK>
+__global__ __launch_bounds__(64 * NQ * NK, D == 64 ? 4 : 2) void attention_tiles_kernel(const __half *__restrict__ Q, int64_t ldq,
+                                                              const __half *__restrict__ Kc, int64_t ldk,
+                                                              const __half *__restrict__ V, int64_t ldv, int Sq, int Sk,
+                                                              __half *__restrict__ O, int64_t ldo)
+{
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    constexpr int OWN = D / 32 / NK;
+    const int l = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int qblock = gridDim.y - 1 - blockIdx.y;                    // the longest rows first
+    Q += (int64_t)blockIdx.z * Sq * ldq + (int64_t)blockIdx.x * D;
+    Kc += (int64_t)blockIdx.z * Sk * ldk + (int64_t)blockIdx.x * D;
+    V += (int64_t)blockIdx.z * Sk * ldv + (int64_t)blockIdx.x * D;
+    unsigned w[OWN][8];
+    const bool bad = attend<D, NQ, NK, true>(lds, l, wave, qblock, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, w);
+    // If any wavefront has outputs that are not finite, the workgroup goes through its keys again and takes those from there.  (Nothing
+    // has been stored yet: the queries may lie where the output goes.)
+    int *again = reinterpret_cast<int *>(lds + merge_bytes<D, NQ, NK>());
+    if (__any(bad) && l == 0) *again = 1;
+    lds_barrier();
+    if (*again != 0) {
+        int l1 = l;
+        asm volatile("" : "+v"(l1));                                  // (nothing of the first time is kept in registers for this)
+        lds_barrier();                                                // everybody has read it: the tiles come back
+        unsigned w1[OWN][8];
+        attend<D, NQ, NK, false>(lds, l1, wave, qblock, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, w1);
+#pragma unroll
+        for (int t = 0; t < OWN; ++t)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) w[t][i] = where_not_finite(w[t][i], w1[t][i]);
+    }
+    const int h = l >> 5, my_q = (qblock * NQ + wave % NQ) * 32 + (l & 31);
+    O += (int64_t)blockIdx.z * Sq * ldo + (int64_t)blockIdx.x * D + (int64_t)my_q * ldo + 32 * (wave / NQ) * OWN;
+#pragma unroll
+    for (int t = 0; t < OWN; ++t) {
+        // four consecutive columns per register quad; two quads make 16 bytes once the lane halves have exchanged
 #pragma unroll
         for (int g = 0; g < 4; g += 2) {
-            const auto a = __builtin_amdgcn_permlane32_swap(w[2 * g], w[2 * g + 2], false, false);
-            const auto b = __builtin_amdgcn_permlane32_swap(w[2 * g + 1], w[2 * g + 3], false, false);
-            if (my_q < Sq)
-                *reinterpret_cast<uint4 *>(O + (int64_t)my_q * ldo + 32 * ct + 8 * g + 8 * h) = make_uint4(a[0], b[0], a[1], b[1]);
+            const auto a = __builtin_amdgcn_permlane32_swap(w[t][2 * g], w[t][2 * g + 2], false, false);
+            const auto b = __builtin_amdgcn_permlane32_swap(w[t][2 * g + 1], w[t][2 * g + 3], false, false);
+            if (my_q < Sq) *reinterpret_cast<uint4 *>(O + 32 * t + 8 * g + 8 * h) = make_uint4(a[0], b[0], a[1], b[1]);
         }
     }
 }

@@ -310,6 +310,61 @@ def test_attention_tile_edges(G, oracle, batch, Sq, Sk, H, d):
     assert torch.all((O.double() - want).abs() <= 2.0 ** -11 * want.abs() + 1e-4)
 
 
+@pytest.mark.parametrize("spread", [0.5, 30.0])
+@pytest.mark.parametrize("batch,Sq,Sk,H,d", [(1, 40, 40, 2, 128), (2, 33, 65, 3, 64), (1, 20, 700, 2, 128), (9, 64, 200, 32, 128), (1, 1, 1, 1, 64)])
+def test_attention_of_infinite_values(G, batch, Sq, Sk, H, d, spread):
+    """A query that sees an infinite value gets that infinity, however little weight it has (and NaN from infinities of both signs);
+    the columns without one come out as ever."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    g = torch.Generator().manual_seed(Sq + Sk + d)
+    width = H * d
+    q = (spread * torch.randn((batch * Sq, width), generator=g)).half().cuda()
+    k = torch.randn((batch * Sk, width), generator=g).half().cuda()
+    v = torch.randn((batch * Sk, width), generator=g).half()
+    clean = v.clone().cuda()
+    at, cols = (0, Sk // 2 - (Sq - 1), Sk - Sq), (3, d - 1, width - 7)                    # keys that every query sees, columns of theirs
+    at = [max(0, a) for a in at]
+    for b in range(batch):
+        v[b * Sk + at[0], cols[0]] = float("inf")
+        v[b * Sk + at[1], cols[1]] = float("-inf")
+        v[b * Sk + at[0], cols[2]], v[b * Sk + at[2], cols[2]] = float("inf"), float("-inf")
+    if at[0] == at[2]:
+        for b in range(batch):
+            v[b * Sk, cols[2]] = float("nan")
+    out, ref = (torch.full((batch * Sq, width), 5.0, dtype=torch.float16, device="cuda") for _ in range(2))
+    B.sqap_attention(q, k, v.cuda(), H, d, out, batch=batch)
+    B.sqap_attention(q, k, clean, H, d, ref, batch=batch)
+    torch.cuda.synchronize()
+    assert torch.all(out[:, cols[0]] == float("inf")) and torch.all(out[:, cols[1]] == float("-inf")) and torch.all(out[:, cols[2]].isnan())
+    rest = [c for c in range(width) if c not in cols]
+    assert torch.equal(out[:, rest], ref[:, rest])
+    same = q.clone()                                            # the output over the queries
+    B.sqap_attention(same, k, v.cuda(), H, d, same, batch=batch)
+    assert torch.equal(same.view(torch.int16), out.view(torch.int16))
+
+
+@pytest.mark.parametrize("batch,Sq,Sk,H,d", [(1, 40, 40, 2, 128), (2, 33, 65, 3, 64), (1, 20, 700, 2, 128), (9, 64, 200, 32, 128)])
+def test_attention_of_huge_scores(G, batch, Sq, Sk, H, d):
+    """Scores of 10^8 and more, whose last bits are worth more than a whole exponent: the largest score takes all (they are whole
+    numbers times 2^14 / sqrt(d), exact in binary32, so that no two lie close together without being equal)."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    g = torch.Generator().manual_seed(Sq * 3 + Sk + d)
+    width = H * d
+    q, k = (128.0 * torch.randint(-128, 129, (n, width), generator=g) * scale for n, scale in ((batch * Sq, 1), (batch * Sk, 1)))
+    q, k = q.half().cuda(), k.half().cuda()
+    v = torch.randn((batch * Sk, width), generator=g).half().cuda()
+    O = torch.full((batch * Sq, width), float("nan"), dtype=torch.float16, device="cuda")
+    B.sqap_attention(q, k, v, H, d, O, batch=batch)
+    q64, k64, v64 = (t.double().view(batch, -1, H, d).transpose(1, 2) for t in (q, k, v))
+    s = torch.matmul(q64, k64.transpose(-1, -2).contiguous()) / d ** 0.5
+    seen = torch.ones((Sq, Sk), dtype=torch.bool, device="cuda").tril(Sk - Sq)
+    want = torch.matmul(torch.softmax(s.masked_fill(~seen, float("-inf")), -1), v64).transpose(1, 2).reshape(batch * Sq, width)
+    # one half per probability: 2^-11 of the result, and its rounding
+    assert torch.all((O.double() - want).abs() <= 2.0 ** -10 * want.abs() + 1e-4)
+
+
 def test_attention_batch(G, oracle):
     """Sequences stacked as row blocks: each gets what a single call gives."""
     import torch
