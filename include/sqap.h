@@ -547,7 +547,8 @@ sqap_status sqap_group_run(const sqap_group *g, void *stream);
  * group along K (1, 2, 4 or 8), wavefronts per workgroup (8, or 16 for launches in which every wavefront
  * streams four or more row groups: outputs then wait in LDS slots, output_slots_out per wavefront, 0
  * otherwise).  Up to four problems with one input that run as one product (see sqap_set_mid_m_kernel, whose
- * setting at the time of the call counts): 4, 8 and 0.  Any out pointer may be NULL.  EINVAL: not a group
+ * setting at the time of the call counts): as many wavefronts along K as it has whole or begun blocks of 128 codes, rounded down to
+ * 1, 2, 4 or 8; 8 and 0.  Any out pointer may be NULL.  EINVAL: not a group
  * handle, compute_units < 0.
  */
 sqap_status sqap_group_info(const sqap_group *g, int32_t compute_units, int32_t *problems_out,

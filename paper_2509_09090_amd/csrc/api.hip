@@ -472,7 +472,8 @@ sqap_status sqap_weight_pack(const uint8_t *Wq, const sqap_f16 *sw, int32_t N, i
     w->data = nullptr;
     w->scales = nullptr;
     hipError_t e = hipGetDevice(&w->device);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&w->data), data_bytes);
+    // (gemm_few.hip reads K in blocks of four chunks: up to three past the end)
+    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&w->data), data_bytes + 3 * 512);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&w->scales), scale_bytes);
     if (e != hipSuccess) {
         if (w->data) (void)hipFree(w->data);
@@ -603,7 +604,7 @@ sqap_status sqap_w4a4_linear(const uint8_t *Xq, const sqap_f16 *sx, int32_t M,
             return fail(SQAP_EINVAL, "sqap_w4a4_linear: workspace must be 256-byte aligned");
     }
     // (decided once: another thread may turn the switch meanwhile, and what M <= 8 would fall through to asks for a workspace)
-    const bool whole_outputs = rows_kernel_wanted() && rows_kernel_applies(M, (w->N + 15) / 16, w->K, device_cu_count());
+    const bool whole_outputs = rows_kernel_wanted() && rows_kernel_applies(M, (w->N + 15) / 16, w->K, device_cu_count(), 1);
     if (M <= kSkinnyMaxM && w->K % 64 == 0 && !whole_outputs) {
         SkinnyArgs a = {};
         a.table = nullptr;
@@ -764,7 +765,7 @@ sqap_status sqap_group_create(const sqap_linear_desc *descs, int32_t count, sqap
 // problems with one input as one product over all their channels, every workgroup with complete outputs
 static bool group_has_whole_outputs(const Group *g, int compute_units)
 {
-    return g->rows_count > 0 && rows_kernel_wanted() && rows_kernel_applies(g->rows_M, g->rows_groups, g->rows_K, compute_units);
+    return g->rows_count > 0 && rows_kernel_wanted() && rows_kernel_applies(g->rows_M, g->rows_groups, g->rows_K, compute_units, g->rows_count);
 }
 
 sqap_status sqap_group_run(const sqap_group *g, void *stream)
@@ -790,7 +791,7 @@ sqap_status sqap_group_info(const sqap_group *g, int32_t compute_units, int32_t 
     if (!gg || gg->magic != kGroupMagic) return fail(SQAP_EINVAL, "sqap_group_info: not a group handle");
     if (compute_units < 0) return fail(SQAP_EINVAL, "sqap_group_info: compute_units = %d", compute_units);
     const int cus = compute_units > 0 ? compute_units : device_cu_count();
-    int S = kRowsKShares, W = kRowsWaves, cap = 0;
+    int S = few_k_shares(gg->rows_K), W = kRowsWaves, cap = 0;
     if (!group_has_whole_outputs(gg, cus)) skinny_plan(gg->total_items, gg->max_chunks, cus, &S, &W, &cap);
     if (problems_out) *problems_out = gg->count;
     if (row_groups_out) *row_groups_out = gg->total_items;

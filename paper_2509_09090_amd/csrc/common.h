@@ -60,7 +60,7 @@ struct SkinnyArgs {
 };
 constexpr int kSkinnyMaxM = 8;
 
-// One weight of a launch of gemm_rows.hip: up to four share the input rows.
+// One weight of a launch of gemm_rows.hip or gemm_few.hip (there up to four share the input rows).
 struct RowsWeight {
     const uint8_t *Wd;     // streaming layout
     const __half *sw;      // padded to whole row groups
@@ -183,9 +183,14 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
 
 // Few outputs per compute unit: every workgroup owns complete ones (gemm_rows.hip)
 constexpr int kRowsWaves = 8, kRowsKShares = 4;                    // wavefronts per workgroup; of them, along K
-bool rows_kernel_applies(int M, int channel_groups, int K, int compute_units);        // (groups of 16 channels)
+bool rows_kernel_applies(int M, int channel_groups, int K, int compute_units, int weights);        // (groups of 16 channels)
 sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
                                unsigned long long *error_word, hipStream_t st);
+// the same for up to 16 rows, also of several weights with one input (gemm_few.hip)
+bool few_kernel_applies(int M, int channel_groups, int K, int compute_units);
+int few_k_shares(int K);                                           // wavefronts of a workgroup along K
+sqap_status launch_few_linear(const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
+                              unsigned long long *error_word, hipStream_t st);
 bool rows_kernel_wanted();
 void set_mid_m_kernel(int which);        // 0: tiles split along K between workgroups, 1: whole outputs per workgroup
 

@@ -22,8 +22,7 @@
 // int4 -> int8 as in the large-M kernel: (x << 4) & 0xF0F0F0F0 and x & 0xF0F0F0F0 give 16 * code for the even
 // and the odd codes; both operands are split the same way, so the accumulator is 256 * sum(x * w).
 // The price is that every workgroup reads all its token rows for the whole K (they come from the L2,
-// which the 32 workgroups of an XCD share).  And with 16 rows or fewer, decode sizes among them, the second half has no token
-// group of its own: wavefronts 4 .. 7 read the last row and all weights once more and store nothing.
+// which the 32 workgroups of an XCD share).  Up to 16 rows are gemm_few.hip's.
 #include "common.h"
 
 namespace sqap {
@@ -52,21 +51,8 @@ struct RowsParams {
     int tblocks;           // blocks of token rows (1, 2, 4, 8 or 16)
     int rows_per_block;    // multiple of 16, at most 16 * kRowsMaxA
     int per_xcd;           // workgroups of an XCD that share its channel groups, per token block
-    int count;             // weights the input is multiplied with (q, k and v, say): their channel groups follow one another
-    RowsWeight w[kRowsMaxWeights];
+    RowsWeight w;
 };
-
-// the weight that channel group g (of all of them) belongs to.  A single one sits at a fixed place among the kernel's
-// arguments; finding one of several costs a dependent scalar load, 0.5 us at the start of a launch.
-template <bool MULTI>
-__device__ __forceinline__ const RowsWeight &rows_weight(const RowsParams &p, int g)
-{
-    if (!MULTI) return p.w[0];
-    int k = 0;
-#pragma unroll
-    for (int i = 1; i < kRowsMaxWeights; ++i) k = i < p.count && g >= p.w[i].g_begin ? i : k;
-    return p.w[k];
-}
 
 __device__ __forceinline__ void widen16(const v4i p, v4i &lo, v4i &hi)
 {
@@ -97,7 +83,7 @@ __device__ __forceinline__ uint32_t dequant_pair(int acc0, int acc1, float sx_ov
 // accumulators, and the next pair's operands are read from LDS before the current pair is multiplied.
 // RAGGED: K is any multiple of 32.  The last step then ends inside its 256 codes: token pieces past K are put into the slab as
 // zeros (and weight pieces past K are any others), and a wavefront may have no step at all.
-template <int AH, int B, bool RAGGED, bool MULTI>
+template <int AH, int B, bool RAGGED>
 __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, int row0, int row_end, int c0)
 {
     static_assert(AH >= 1 && AH <= kRowsMaxAH && B >= 1 && B <= rows_max_b(AH), "tile shape");
@@ -142,8 +128,8 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
     const uint8_t *wbase[B];
 #pragma unroll
     for (int j = 0; j < B; ++j) {
-        const RowsWeight &w = rows_weight<MULTI>(p, c0 + j);
-        const int g = c0 + j - w.g_begin;
+        const RowsWeight &w = p.w;
+        const int g = c0 + j;
         wbase[j] = w.Wd + (size_t)(g >> 1) * p.chunks * 512 + (g & 1) * 256;
     }
     const uint32_t woff = (uint32_t)(lane >> 4) * 512 + (lane & 15) * 16;
@@ -266,10 +252,10 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
 #pragma unroll
         for (int w = 0; w < 4; ++w)
             sum += *reinterpret_cast<const v4i *>(red + (((th * 4 + w) * AH * B + tt) * 64 + lane) * 4);
-        const RowsWeight &w = rows_weight<MULTI>(p, c0 + j);
+        const RowsWeight &w = p.w;
         const bool y_vec = (w.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(w.Y) & 7u) == 0;
         const bool a_vec = (w.N & 3) == 0 && w.acc_out && (reinterpret_cast<uintptr_t>(w.acc_out) & 15u) == 0;
-        const int row = wrow0 + i * 16 + tok_in, col = (c0 + j - w.g_begin) * 16 + ch4;
+        const int row = wrow0 + i * 16 + tok_in, col = (c0 + j) * 16 + ch4;
         if (row < row_end && col < w.N) {
             const float sxf = __half2float(p.sx[row]) * 0.00390625f;
             const uint2 swr = *reinterpret_cast<const uint2 *>(w.sw + col);            // zero padded past N
@@ -308,7 +294,7 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
 // contiguous runs, and inside an XCD to `per_xcd` workgroups per token block, so that the workgroups that
 // read the same weights (one per token block) sit behind one L2.  AH = 16-token groups per wavefront: a
 // block has 2 AH of them (rows past the block re-read other rows and are never stored).
-template <int AH, bool RAGGED, bool MULTI>
+template <int AH, bool RAGGED>
 __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const RowsParams p)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -327,14 +313,14 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const Row
     for (int k = 0; k < tiles; ++k) {
         const int c0 = g_begin + n * k / tiles, b = g_begin + n * (k + 1) / tiles - c0;
         if constexpr (MAXB > kRowsMaxB) {
-            if (b == 6) rows_tile<AH, 6, RAGGED, MULTI>(p, smem, row0, row_end, c0);
-            else if (b == 5) rows_tile<AH, 5, RAGGED, MULTI>(p, smem, row0, row_end, c0);
-            else if (b == 4) rows_tile<AH, 4, RAGGED, MULTI>(p, smem, row0, row_end, c0);
+            if (b == 6) rows_tile<AH, 6, RAGGED>(p, smem, row0, row_end, c0);
+            else if (b == 5) rows_tile<AH, 5, RAGGED>(p, smem, row0, row_end, c0);
+            else if (b == 4) rows_tile<AH, 4, RAGGED>(p, smem, row0, row_end, c0);
         }
         if (b > 3) continue;
-        if (b == 3) rows_tile<AH, 3, RAGGED, MULTI>(p, smem, row0, row_end, c0);
-        else if (b == 2) rows_tile<AH, 2, RAGGED, MULTI>(p, smem, row0, row_end, c0);
-        else rows_tile<AH, 1, RAGGED, MULTI>(p, smem, row0, row_end, c0);
+        if (b == 3) rows_tile<AH, 3, RAGGED>(p, smem, row0, row_end, c0);
+        else if (b == 2) rows_tile<AH, 2, RAGGED>(p, smem, row0, row_end, c0);
+        else rows_tile<AH, 1, RAGGED>(p, smem, row0, row_end, c0);
     }
 }
 
@@ -357,11 +343,6 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gemm_rows_kernel(const Row
 //   four groups from 512 rows on: 600 x 4096 x 4096 23.4 against 31.2, 2368 x 1024 x 4096 25.1 against 31.3;
 // not between otherwise (276 x 8192 x 4096 23.0 against 19.7), nor with a K too short to make up for a start-up (600 x 4096 x 512
 // 12.4 against 11.0).
-// Decode sizes are in: one launch per linear (or per group of linears with one input: q, k and v are a product over 12288
-// channels) has no stream long enough for the streaming kernel's pipeline, and here its start-up is shorter (M = 1 / 8, the streaming
-// kernel in brackets: 4096 x 4096 5.7 / 5.8 (8.2 / 8.6), 12288 x 4096 8.9 (11.9 / 13.2), 22016 x 4096 13.8 / 14.0 (15.9 / 16.5),
-// K = 11008 8.0 / 8.2 (12.8 / 13.5), 32000 x 4096 17.6 / 17.5 (19.3 / 19.4), 512 x 512 3.5 / 3.8 (6.9 / 7.0)).  Launches of many
-// problems stay with that kernel.
 // Both sides compared on 800 drawn shapes (1 to 2600 rows, 16 to 60000 channels, K of 32 to 16384) and 120 groups: fifteen shapes more
 // than 2 % slower with this rule than with the kernels they had before it, by up to 0.3 us at 3 to 8 us (5 % at one), 447 more than
 // 2 % faster.
@@ -377,7 +358,6 @@ static int rows_max_groups(int M, int K)
 static bool rows_plan(int M, int c16, int K, int cus, RowsParams *p)
 {
     if (K % 32 != 0 || c16 < 1) return false;
-    if (M <= kSkinnyMaxM && K % 64 == 0 && K > 32768) return false;         // the streaming kernel's, which says what it refuses
     const int max_groups = rows_max_groups(M, K);
     double best = 0.0;
     for (int tb = 1; tb <= 16; tb *= 2) {
@@ -405,24 +385,27 @@ static bool rows_plan(int M, int c16, int K, int cus, RowsParams *p)
 
 static int rows_cus(int cus) { return cus > 256 ? 256 : cus < 8 ? 8 : cus; }
 
-// Shapes this kernel takes: up to sixteen blocks of 160 token rows, and few enough channels per workgroup.
-bool rows_kernel_applies(int M, int channel_groups, int K, int compute_units)
+// Shapes that this kernel or the one for few rows takes: up to sixteen blocks of 160 token rows, and few enough channels per
+// workgroup.  (Several weights with one input: few rows only.)
+bool rows_kernel_applies(int M, int channel_groups, int K, int compute_units, int weights)
 {
+    if (M <= kSkinnyMaxM && K % 64 == 0 && K > 32768) return false;         // the streaming kernel's, which says what it refuses
+    if (few_kernel_applies(M, channel_groups, K, compute_units)) return true;
     RowsParams p = {};
-    return rows_plan(M, channel_groups, K, rows_cus(compute_units), &p);
+    return weights == 1 && rows_plan(M, channel_groups, K, rows_cus(compute_units), &p);
 }
 
-template <int AH, bool RAGGED, bool MULTI>
+template <int AH, bool RAGGED>
 static sqap_status launch_rows_k(const RowsParams &p, int blocks, hipStream_t st)
 {
     static std::atomic<bool> configured[kMaxDeviceSlots];
     const int dslot = device_slot();
     if (!configured[dslot].load(std::memory_order_acquire)) {
-        SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_rows_kernel<AH, RAGGED, MULTI>),
+        SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_rows_kernel<AH, RAGGED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLdsBytes));
         configured[dslot].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((gemm_rows_kernel<AH, RAGGED, MULTI>), dim3(blocks), dim3(64 * kRowsWaves), kRowsLdsBytes, st, p);
+    hipLaunchKernelGGL((gemm_rows_kernel<AH, RAGGED>), dim3(blocks), dim3(64 * kRowsWaves), kRowsLdsBytes, st, p);
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }
@@ -431,15 +414,15 @@ template <int AH>
 static sqap_status launch_rows_a(const RowsParams &p, int blocks, hipStream_t st)
 {
     const bool ragged = p.K % kRowsStepCodes != 0 || p.K / kRowsStepCodes < 4;
-    if constexpr (AH == 1) {                     // several weights: decode sizes only (sqap_group_run)
-        if (p.count > 1) return ragged ? launch_rows_k<AH, true, true>(p, blocks, st) : launch_rows_k<AH, false, true>(p, blocks, st);
-    }
-    return ragged ? launch_rows_k<AH, true, false>(p, blocks, st) : launch_rows_k<AH, false, false>(p, blocks, st);
+    return ragged ? launch_rows_k<AH, true>(p, blocks, st) : launch_rows_k<AH, false>(p, blocks, st);
 }
 
 sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
                                unsigned long long *error_word, hipStream_t st)
 {
+    int groups = 0;
+    for (int i = 0; i < count; ++i) groups += (weights[i].N + 15) / 16;
+    if (few_kernel_applies(M, groups, K, device_cu_count())) return launch_few_linear(Xq, sx, M, K, weights, count, error_word, st);
     RowsParams p = {};
     p.Xq = Xq;
     p.sx = sx;
@@ -447,13 +430,7 @@ sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, int K
     p.K = K;
     p.chunks = K / 32;
     p.error_word = error_word;
-    p.count = count;
-    int groups = 0;
-    for (int i = 0; i < count; ++i) {
-        p.w[i] = weights[i];
-        p.w[i].g_begin = groups;
-        groups += (weights[i].N + 15) / 16;
-    }
+    p.w = weights[0];
     if (!rows_plan(M, groups, K, rows_cus(device_cu_count()), &p))
         return fail(SQAP_EUNSUPPORTED, "sqap_w4a4_linear: M = %d, %d channels, K = %d outside the row kernel's range", M, groups * 16, K);
     const int blocks = 8 * p.per_xcd * p.tblocks;

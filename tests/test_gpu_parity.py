@@ -546,6 +546,43 @@ def test_small_m_linear(G, oracle, M, N, K):
         assert G.assert_fp16_close(Y, Yo) == 0, which
 
 
+# one block of K, fewer blocks than wavefronts, blocks that do not come out even, a last block of one chunk; 8 | 9 and 16 | 17 rows;
+# one and many 16-channel groups per workgroup, the last one of a single channel; more token loads than are staged at once
+@pytest.mark.parametrize("M,N,K", [(1, 1, 32), (8, 17, 96), (9, 16, 128), (16, 4097, 160), (17, 4097, 160), (5, 12305, 416), (12, 530, 1056),
+                                   (16, 40, 11008), (16, 48, 16416), (7, 31, 32736), (13, 65537, 64)])
+def test_few_rows_linear_edges(G, oracle, M, N, K):
+    rng = np.random.default_rng(M * 131 + N + K)
+    Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
+    sx = (rng.random(M) * 2 + 0.01).astype(np.float16)
+    sw = (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
+    Yo, acco = oracle.w4a4_linear(Xq, sx, Wq, sw)
+    Y, acc = G.gpu_linear(Xq, sx, Wq, sw)
+    assert np.array_equal(acc, acco)
+    assert G.assert_fp16_close(Y, Yo) == 0
+
+
+@pytest.mark.parametrize("M,K,Ns", [(1, 64, (1, 1, 1, 1)), (8, 448, (33, 500, 16, 4100)), (4, 4096, (512, 512, 512)), (3, 2112, (9000, 24))])
+def test_group_with_one_input_runs_as_one_product(G, oracle, M, K, Ns):
+    import torch
+    from paper_2509_09090_amd import binding as B
+    rng = np.random.default_rng(M + K)
+    Xq, sx = _random_packed(rng, M, K), (rng.random(M) * 2 + 0.01).astype(np.float16)
+    xq, sxd, problems, refs = G.to_dev(Xq), G.to_dev(sx), [], []
+    for i, N in enumerate(Ns):
+        Wq, sw = _random_packed(rng, N, K), (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
+        Y = torch.full((M, N + i), float("nan"), dtype=torch.float16, device="cuda")[:, :N]          # rows of any alignment
+        acc = torch.full((M, N), -1, dtype=torch.int32, device="cuda")
+        problems.append((xq, sxd, B.sqap_weight_pack(G.to_dev(Wq), G.to_dev(sw)), Y, acc))
+        refs.append(oracle.w4a4_linear(Xq, sx, Wq, sw))
+    g = B.sqap_group_create(problems)
+    g.run()
+    torch.cuda.synchronize()
+    for (_, _, _, Y, acc), (Yo, acco) in zip(problems, refs):
+        assert np.array_equal(acc.cpu().numpy(), acco)
+        assert G.assert_fp16_close(Y.cpu().numpy(), Yo) == 0
+    g.free()
+
+
 def test_group_with_many_row_groups_per_wavefront(G, oracle):
     """A launch long enough for the form of the kernel that parks outputs in LDS (every wavefront gets
     more row groups than it has slots, so the slots are also emptied mid-run), with problems of different
