@@ -604,7 +604,8 @@ sqap_status sqap_w4a4_linear(const uint8_t *Xq, const sqap_f16 *sx, int32_t M,
             return fail(SQAP_EINVAL, "sqap_w4a4_linear: workspace must be 256-byte aligned");
     }
     // (decided once: another thread may turn the switch meanwhile, and what M <= 8 would fall through to asks for a workspace)
-    const bool whole_outputs = rows_kernel_wanted() && rows_kernel_applies(M, (w->N + 15) / 16, w->K, device_cu_count(), 1);
+    WholePlan plan;
+    const bool whole_outputs = rows_kernel_wanted() && whole_output_plan(M, (w->N + 15) / 16, w->K, device_cu_count(), 1, &plan);
     if (M <= kSkinnyMaxM && w->K % 64 == 0 && !whole_outputs) {
         SkinnyArgs a = {};
         a.table = nullptr;
@@ -627,7 +628,7 @@ sqap_status sqap_w4a4_linear(const uint8_t *Xq, const sqap_f16 *sx, int32_t M,
         return launch_skinny(a, w->chunks, as_stream(stream));
     }
     return launch_w4a4_linear(Xq, reinterpret_cast<const __half *>(sx), M, *w,
-                              reinterpret_cast<__half *>(Y), ldy, acc_out, workspace, whole_outputs,
+                              reinterpret_cast<__half *>(Y), ldy, acc_out, workspace, whole_outputs ? &plan : nullptr,
                               as_stream(stream));
 }
 
@@ -763,9 +764,9 @@ sqap_status sqap_group_create(const sqap_linear_desc *descs, int32_t count, sqap
 }
 
 // problems with one input as one product over all their channels, every workgroup with complete outputs
-static bool group_has_whole_outputs(const Group *g, int compute_units)
+static bool group_has_whole_outputs(const Group *g, int compute_units, WholePlan *plan)
 {
-    return g->rows_count > 0 && rows_kernel_wanted() && rows_kernel_applies(g->rows_M, g->rows_groups, g->rows_K, compute_units, g->rows_count);
+    return g->rows_count > 0 && rows_kernel_wanted() && whole_output_plan(g->rows_M, g->rows_groups, g->rows_K, compute_units, g->rows_count, plan);
 }
 
 sqap_status sqap_group_run(const sqap_group *g, void *stream)
@@ -773,8 +774,9 @@ sqap_status sqap_group_run(const sqap_group *g, void *stream)
     const Group *gg = reinterpret_cast<const Group *>(g);
     if (!gg || gg->magic != kGroupMagic) return fail(SQAP_EINVAL, "sqap_group_run: not a group handle");
     const DeviceOfCall device;
-    if (group_has_whole_outputs(gg, device_cu_count()))
-        return launch_rows_linear(gg->rows_Xq, gg->rows_sx, gg->rows_M, gg->rows_K, gg->rows, gg->rows_count, nullptr, as_stream(stream));
+    WholePlan plan;
+    if (group_has_whole_outputs(gg, device_cu_count(), &plan))
+        return launch_whole_outputs(plan, gg->rows_Xq, gg->rows_sx, gg->rows_M, gg->rows_K, gg->rows, gg->rows_count, nullptr, as_stream(stream));
     SkinnyArgs a = {};
     a.table = gg->table;
     a.count = gg->count;
@@ -792,7 +794,8 @@ sqap_status sqap_group_info(const sqap_group *g, int32_t compute_units, int32_t 
     if (compute_units < 0) return fail(SQAP_EINVAL, "sqap_group_info: compute_units = %d", compute_units);
     const int cus = compute_units > 0 ? compute_units : device_cu_count();
     int S = few_k_shares(gg->rows_K), W = kRowsWaves, cap = 0;
-    if (!group_has_whole_outputs(gg, cus)) skinny_plan(gg->total_items, gg->max_chunks, cus, &S, &W, &cap);
+    WholePlan plan;
+    if (!group_has_whole_outputs(gg, cus, &plan)) skinny_plan(gg->total_items, gg->max_chunks, cus, &S, &W, &cap);
     if (problems_out) *problems_out = gg->count;
     if (row_groups_out) *row_groups_out = gg->total_items;
     if (wavefronts_per_row_group_out) *wavefronts_per_row_group_out = S;

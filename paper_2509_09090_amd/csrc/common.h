@@ -177,16 +177,22 @@ sqap_status launch_channel_scales(const __half *X, int64_t ldx, const int32_t *r
 sqap_status launch_weight_pack(const uint8_t *Wq, const __half *sw, const Weight &w,
                                hipStream_t st);
 size_t linear_workspace_bytes(int M, int N, int K);
+struct WholePlan;
 sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const Weight &w,
                                __half *Y, int64_t ldy, int32_t *acc_out, void *workspace,
-                               bool whole_outputs, hipStream_t st);
+                               const WholePlan *whole_outputs, hipStream_t st);
 
-// Few outputs per compute unit: every workgroup owns complete ones (gemm_rows.hip)
-constexpr int kRowsWaves = 8, kRowsKShares = 4;                    // wavefronts per workgroup; of them, along K
-bool rows_kernel_applies(int M, int channel_groups, int K, int compute_units, int weights);        // (groups of 16 channels)
-sqap_status launch_rows_linear(const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
-                               unsigned long long *error_word, hipStream_t st);
-// the same for up to 16 rows, also of several weights with one input (gemm_few.hip)
+// Few outputs per compute unit: every workgroup owns complete ones.  Up to 16 rows, also of several weights with one input:
+// gemm_few.hip; more: gemm_rows.hip.  The plan is made once per call: it says whether a shape is taken, and how.
+constexpr int kRowsWaves = 8;                                      // wavefronts per workgroup
+struct WholePlan {
+    bool few;                                                      // of gemm_few.hip (the rest is gemm_rows.hip's)
+    int tblocks, rows_per_block, per_xcd;                          // token blocks, rows of each, workgroups per XCD and block
+    int token_groups, channel_groups, k_shares;                    // of a workgroup (16 rows), of a wavefront (16 channels); shares of K
+};
+bool whole_output_plan(int M, int channel_groups, int K, int compute_units, int weights, WholePlan *plan);
+sqap_status launch_whole_outputs(const WholePlan &plan, const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
+                                 unsigned long long *error_word, hipStream_t st);
 bool few_kernel_applies(int M, int channel_groups, int K, int compute_units);
 int few_k_shares(int K);                                           // wavefronts of a workgroup along K
 sqap_status launch_few_linear(const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,

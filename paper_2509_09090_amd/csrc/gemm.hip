@@ -1441,7 +1441,8 @@ sqap_status plan_linear_shares(int M, int N, int K, int blocks_per_xcd, uint32_t
 }
 
 sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const Weight &w,
-                               __half *Y, int64_t ldy, int32_t *acc_out, void *workspace, bool whole_outputs, hipStream_t st)
+                               __half *Y, int64_t ldy, int32_t *acc_out, void *workspace, const WholePlan *whole_outputs,
+                               hipStream_t st)
 {
     if (w.K > kMaxK) return fail(SQAP_EUNSUPPORTED, "sqap_w4a4_linear: K = %d above %d", w.K, kMaxK);
     GemmParams p = {};
@@ -1463,7 +1464,7 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
     if (whole_outputs) {
         const RowsWeight rw = {w.data, w.scales, Y, acc_out, ldy, w.N, 0};
         const bool has_word = linear_workspace_bytes(M, w.N, w.K) > 0;
-        return launch_rows_linear(Xq, sx, M, w.K, &rw, 1, has_word ? reinterpret_cast<unsigned long long *>(workspace) + kErrWord : nullptr, st);
+        return launch_whole_outputs(*whole_outputs, Xq, sx, M, w.K, &rw, 1, has_word ? reinterpret_cast<unsigned long long *>(workspace) + kErrWord : nullptr, st);
     }
     if (w.K % kBK == 0 && persistent_allowed()) {
         if (M >= kStreamKMinM) return launch_streamk<CfgBig, false>(p, workspace, st);
@@ -1472,7 +1473,7 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
         // three partials to add, which measured faster than the joint finish (23.6 vs 28.6 us at
         // M = 148, N = 11008, K = 4096; the other way round, 21.6 vs 15.2 us, at N = 4096).
         // The joint finish is for devices with fewer than 256 compute units (a partition) and for sqap_set_mid_m_kernel(0): with all
-        // of them, every shape of so few tiles goes to the kernel with whole outputs above (4096 there: 9.1 us).
+        // of them, every shape of so few tiles goes to the kernel with whole outputs above (4096 there: 8.0 us).
         const bool mid = narrow_tile_is_mid(M);
         const int64_t tiles = (int64_t)((M + (mid ? CfgMid::BM : CfgLow::BM) - 1) / (mid ? CfgMid::BM : CfgLow::BM)) *
                               ((w.N + CfgMid::BN - 1) / CfgMid::BN);

@@ -561,6 +561,23 @@ def test_few_rows_linear_edges(G, oracle, M, N, K):
     assert G.assert_fp16_close(Y, Yo) == 0
 
 
+# one row more than the kernel for few rows; one to six token groups; one to three channel groups (K in eighths) and four to six (in
+# quarters, an odd one out); two and three tiles per workgroup; several token blocks, the last one short; one, two, three and more steps,
+# whole and begun ones
+@pytest.mark.parametrize("M,N,K", [(17, 16, 32), (33, 4097, 1024), (48, 8200, 2048), (90, 12305, 160), (96, 16400, 1024), (65, 20481, 1536),
+                                   (40, 24593, 1536), (20, 49169, 544), (161, 700, 3072), (97, 33, 4128), (500, 1000, 2080), (2560, 300, 1056),
+                                   (16, 13000, 512), (11, 64, 8224), (1, 16, 65568)])
+def test_whole_output_linear_edges(G, oracle, M, N, K):
+    rng = np.random.default_rng(M * 17 + N + K)
+    Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
+    sx = (rng.random(M) * 2 + 0.01).astype(np.float16)
+    sw = (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
+    Yo, acco = oracle.w4a4_linear(Xq, sx, Wq, sw)
+    Y, acc = G.gpu_linear(Xq, sx, Wq, sw)
+    assert np.array_equal(acc, acco)
+    assert G.assert_fp16_close(Y, Yo) == 0
+
+
 @pytest.mark.parametrize("M,K,Ns", [(1, 64, (1, 1, 1, 1)), (8, 448, (33, 500, 16, 4100)), (4, 4096, (512, 512, 512)), (3, 2112, (9000, 24))])
 def test_group_with_one_input_runs_as_one_product(G, oracle, M, K, Ns):
     import torch
