@@ -97,6 +97,16 @@ __device__ __forceinline__ void lds_store16(void *p, const uint4 v)
 // step and layer wrote the word).
 __device__ __forceinline__ __half untag(unsigned w) { return __ushort_as_half((unsigned short)(w & 0xffffu)); }
 
+// Output column t of a head by thread t < d, two columns per 32-bit store past the caches (d is even): the workgroup that quantizes the
+// whole row may sit behind another L2.
+__device__ __forceinline__ void store_head_output(__half *O, int d, float v)
+{
+    const int t = threadIdx.x;
+    const unsigned mine = __half_as_ushort(__float2half_rn(v)), next = __shfl_down(mine, 1);
+    if (t < d && (t & 1) == 0)
+        __hip_atomic_store(reinterpret_cast<unsigned *>(O + t), mine | (next << 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Rotation of head h's query and key of the new token (same arithmetic as rope_kernel), cache append (rotated
 // key | value into row `past` of KV), attention of the query over cache rows 0 .. past, output into
 // O[h * d .. h * d + d) (and into trace, when given).  Called by EVERY thread of the workgroup (it contains
@@ -307,9 +317,9 @@ __device__ __forceinline__ void decode_attention_head(DecodeAttnLds &lds, int h,
             for (int g = 0; g < 16; ++g) acc += ored[g * kDecMaxD + t];
         }
         const float l = (wred[8] + wred[9]) + (wred[10] + wred[11]);
-        const __half r = __float2half_rn(acc * (1.0f / l));
+        [[maybe_unused]] const __half r = __float2half_rn(acc * (1.0f / l));
         if constexpr (!TAGGED) {
-            if (t < d) reinterpret_cast<__half *>(O)[(int64_t)h * d + t] = r;
+            store_head_output(reinterpret_cast<__half *>(O) + (int64_t)h * d, d, acc * (1.0f / l));
         } else {
             // two tagged words per 64-bit agent-scope store (d is even, so a pair never leaves the head)
             const unsigned mine = __half_as_ushort(r), next = __shfl_down(mine, 1);

@@ -365,30 +365,31 @@ sqap_status launch_attention(const __half *Q, int64_t ldq, const __half *Kc, int
     return SQAP_OK;
 }
 
-// The workgroup (of T threads) that arrives last, of n_groups, quantizes the whole output row, as quantize_rows_kernel does.
+// The workgroup (of T threads) that arrives last, of n_groups, quantizes the whole output row, as quantize_rows_kernel does.  The outputs
+// were stored past the caches (agent scope), are complete once the vector-memory counter has drained, and are read past the caches
+// here: no fence, which would write back and invalidate a whole L2 per workgroup.
 // row_lds: width halves of LDS, wave_max: T / 64 floats.
 template <int T>
 __device__ __forceinline__ void quantize_by_the_last(float *row_lds, float *wave_max, int *last_flag, const __half *O, int width,
                                                      int n_groups, uint8_t *Xq, __half *sx, unsigned int *counter)
 {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    if (wave * 64 < kDecMaxD) __threadfence();         // this head's outputs before the arrival (these wavefronts stored them)
-    __syncthreads();
-    if (t == 0) {
-        const unsigned int before = atomicAdd(counter, 1u);
-        *last_flag = before == (unsigned int)(n_groups - 1);
-    }
-    __syncthreads();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's outputs have arrived before the workgroup does
+    lds_barrier();
+    if (t == 0) *last_flag = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned int)(n_groups - 1);
+    lds_barrier();
     if (!*last_flag) return;
-    __threadfence();                                   // the other heads' outputs after the arrival
     __half *row = reinterpret_cast<__half *>(row_lds);
     const int groups = width >> 3;
     float amax = 0.f;
     for (int g = t; g < groups; g += T) {
-        const uint4 raw = reinterpret_cast<const uint4 *>(O)[g];
-        reinterpret_cast<uint4 *>(row)[g] = raw;
+        union { unsigned long long u[2]; uint4 v; } raw;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            raw.u[i] = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(O) + 2 * g + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        reinterpret_cast<uint4 *>(row)[g] = raw.v;
         float f[8];
-        unpack_halves(raw, f);
+        unpack_halves(raw.v, f);
 #pragma unroll
         for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(f[e]));
     }
@@ -402,7 +403,7 @@ __device__ __forceinline__ void quantize_by_the_last(float *row_lds, float *wave
     const float rcp = 1.0f / sf;
     if (t == 0) {
         sx[0] = sh;
-        atomicExch(counter, 0u);                       // the next call starts from zero again
+        __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // the next call starts from zero again
     }
     for (int g = t; g < groups; g += T) {
         float f[8];
@@ -445,20 +446,25 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(const __half *__r
 // SIMD, and waits for its own instructions (2.6 us per chunk of 192 keys; with the rows of three chunks in flight no less).
 // Its arithmetic leaves more freedom than that: every score is a sum of its own, every column of every key group a chain
 // of its own, and the chunks' running maxima follow from the scores.  Eight wavefronts work out all scores (32 keys at
-// a time), then maxima, probabilities and group sums of all chunks side by side, then the output, two key groups
-// per wavefront and four columns per lane.  The same operations in the same order per value: the same bits.
-// What bounds it: a compute unit takes in about 65 GB/s (7.4 ns more per position of 512 bytes, from 1500 to 3000 of them), and
-// there is one per head; rows in flight beyond these gave nothing.  (The value columns are independent chains: workgroups that
-// each take all scores and a share of the columns would not have to meet.  Not tried.)
-// Measured (32 heads of 128, us without the quantizer, the other kernel in brackets): 192 positions 7.8 (7.5), 400 9.4
-// (9.8), 800 12.8 (15.9), 1500 16.9 (23.4), 3000 28.1 (43.6): used from two chunks on.
+// a time, the sums over lanes for eight of them together), then maxima, probabilities and group sums of all chunks side by side, then
+// the output, two key groups per wavefront and four columns per lane.  The same operations in the same order per value: the same bits.
+// SHARES: workgroups of a head.  Each works out all scores and takes a share of the value columns, so they need not meet; the first
+// one appends to the cache.
+// What bounds it: a compute unit takes in a cache line of 128 bytes every four cycles or so (65 GB/s, however many rows are on their way:
+// 16 or 24 per lane instead of 8 in the scores gave nothing), and a head's rows go through one unit: with two, keys and half of the values
+// (32 heads of 128, from 1500 to 3000 positions 7.4 ns per position, 8.2 with one).
+// Measured with the quantizer folded in (32 heads of 128, us; one workgroup per head; the form before, which also summed key by key and
+// fenced a whole L2 before it arrived): 400 positions 9.5 (10.6; 13.9), 800 11.4 (13.1; 16.5), 1500 13.5 (16.5; 20.7), 3000 24.6 (28.8; 32.3);
+// 64, in the kernel above, 7.5 (8.7).  Without the quantizer the kernel above took 7.5 at 192 positions, 15.9 at 800: this one from two chunks on.
+// Two shares where a share of a value row still is whole lines and the heads leave the units for it.
 // Scores wait in LDS, 4 bytes per position: up to kDecLongMax of them (with the rest 52 KiB).
 constexpr int kDecLongMin = 2 * kDecChunk;
 constexpr int kDecLongT = 512, kDecLongMax = 42 * kDecChunk, kDecLongChunks = kDecLongMax / kDecChunk;
-constexpr int kDecLongKeys = 6;            // key rows per lane on their way during the scores: a chunk
+constexpr int kDecLongKeys = 8;            // keys per lane that are summed together, and rows on their way
 typedef unsigned int sqap_v2u __attribute__((ext_vector_type(2)));
 constexpr int kDecLongAhead = 2;           // chunks whose value rows are on their way during the output
 
+template <int SHARES>
 __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const __half *__restrict__ QKV,
                                                                           const int32_t *__restrict__ pos, int H, int d,
                                                                           double base, __half *KV, int64_t ldkv, int past,
@@ -472,7 +478,7 @@ __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const 
     __shared__ __attribute__((aligned(16))) float ored[kDecRedFloats];
     __shared__ float cmax[kDecLongChunks], mrun[kDecLongChunks], resc[kDecLongChunks], psg[kDecLongChunks * 16], lw[4], wave_max[kDecLongT / 64];
     __shared__ int last_flag;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, h = blockIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, h = blockIdx.x, share = SHARES == 1 ? 0 : blockIdx.y;
     const int half_d = d >> 1, width = H * d, Sk = past + 1, n_chunks = (Sk + kDecChunk - 1) / kDecChunk;
     const __half *q = QKV + (int64_t)h * d, *k = q + width, *v = k + width;
     __half fresh[6] = {};
@@ -513,12 +519,14 @@ __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const 
         const __half k0 = __float2half_rn((float)(lo * cs - hi * sn)), k1 = __float2half_rn((float)(hi * cs + lo * sn));
         knew[t] = k0;
         knew[t + half_d] = k1;
-        global_store_half(krow + t, k0);
-        global_store_half(krow + t + half_d, k1);
         vnew[t] = fresh[4];
         vnew[t + half_d] = fresh[5];
-        global_store_half(vrow + t, fresh[4]);
-        global_store_half(vrow + t + half_d, fresh[5]);
+        if (share == 0) {
+            global_store_half(krow + t, k0);
+            global_store_half(krow + t + half_d, k1);
+            global_store_half(vrow + t, fresh[4]);
+            global_store_half(vrow + t + half_d, fresh[5]);
+        }
     }
     lds_barrier();
 
@@ -527,48 +535,73 @@ __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const 
 #pragma unroll
     for (int e = 0; e < 8; ++e) q8[e] = col_ok ? qf[c * 8 + e] : 0.f;
     const float inv_sqrt_d = 1.0f / sqrtf((float)d);
-    auto score = [&](const uint4 raw) {
+    // where a key's score goes: the twelve keys of a chunk that a key group has lie side by side
+    auto place_of = [](int key) {
+        const int chunk = key / kDecChunk, r = key - chunk * kDecChunk;
+        return chunk * kDecChunk + (r & 15) * kDecKeys + (r >> 4);
+    };
+    auto dot = [&](const uint4 raw) {
         float kf[8];
         unpack_halves(raw, kf);
         float s = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) s = fmaf(q8[e], kf[e], s);
-        s = col_ok ? s : 0.f;                             // (a lane past the head's columns read some other ones)
+        return col_ok ? s : 0.f;                          // (a lane past the head's columns read some other ones)
+    };
+    auto score = [&](const uint4 raw) {
+        float s = dot(raw);
         s += dpp_move_f<kDppXor1>(s);
         s += dpp_move_f<kDppXor2>(s);
         s += dpp_move_f<kDppHalfMirror>(s);
         s += dpp_move_f<kDppMirror>(s);
         return s * inv_sqrt_d;
     };
-    static_assert(kDecChunk == KSTEP * kDecLongKeys, "a round of the scores is a chunk");
-    float *mine = sc + kg;
-    for (int i = 0; i < n_chunks; ++i, mine += kDecChunk) {
+    // Eight keys at a time: at each of the first three steps of the sums over 16 lanes a lane goes on with half of the keys, so that
+    // lane c ends with the sum of key c % 8: 26 instructions for eight sums instead of 40, one product and one store instead of
+    // eight.  The pairs added are those of score(), so are the bits.
+    const bool odd1 = c & 1, odd2 = c & 2, odd4 = c & 4;
+    auto xor4 = [](float v) {                             // lane c ^ 4's
+        const int w = (int)__float_as_uint(v);
+        const int up = __builtin_amdgcn_update_dpp(0, w, 0x104, 0xf, 0x5, false);         // row_shl:4 into lanes 0-3 and 8-11
+        return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(up, w, 0x114, 0xf, 0xa, false));      // row_shr:4 into the others
+    };
+    for (int k0 = 0; k0 < past; k0 += KSTEP * kDecLongKeys) {
+        float s[kDecLongKeys];
 #pragma unroll
         for (int u = 0; u < kDecLongKeys; ++u) {
-            const float s = score(make_uint4(kraw[u].x, kraw[u].y, kraw[u].z, kraw[u].w));
+            s[u] = dot(make_uint4(kraw[u].x, kraw[u].y, kraw[u].z, kraw[u].w));
             kraw[u] = next_key_row();
-            if (c == 0) mine[KSTEP * u] = s;
         }
+#pragma unroll
+        for (int u = 0; u < 8; u += 2) s[u] = (odd1 ? s[u + 1] : s[u]) + dpp_move_f<kDppXor1>(odd1 ? s[u] : s[u + 1]);
+#pragma unroll
+        for (int u = 0; u < 8; u += 4) s[u] = (odd2 ? s[u + 2] : s[u]) + dpp_move_f<kDppXor2>(odd2 ? s[u] : s[u + 2]);
+        s[0] = (odd4 ? s[4] : s[0]) + xor4(odd4 ? s[0] : s[4]);
+        s[0] += dpp_move_f<0x128>(s[0]);                  // row_ror:8
+        const int key = k0 + (c & 7) * KSTEP + kg;
+        if (c < 8 && key < past) sc[place_of(key)] = s[0] * inv_sqrt_d;
     }
     const float s_new = score(lds_load16(knew + (col_ok ? c * 8 : 0)));
-    // the first value rows, on their way during the softmax (a wavefront: two key groups, 4 columns per lane)
-    const int vg = 2 * wave + (lane >> 5), vc = (lane & 31) * 4;
+    // the first value rows, on their way during the softmax (a wavefront: two key groups, C columns per lane)
+    constexpr int C = 4 / SHARES;
+    typedef typename std::conditional<SHARES == 1, sqap_v2u, unsigned>::type piece_t;
+    const int vg = 2 * wave + (lane >> 5), vc = share * (kDecMaxD / SHARES) + (lane & 31) * C;
     const bool v_ok = vc < d;
-    const uint32_t v_limit = (uint32_t)(past - 1) * pitch + (v_ok ? vc * 2 : 0);
     const char *vbase = reinterpret_cast<const char *>(KV + width + (int64_t)h * d);
-    uint32_t v_at = (uint32_t)vg * pitch + (v_ok ? vc * 2 : 0);
-    auto next_value_row = [&] {
-        const sqap_v2u raw = *reinterpret_cast<const sqap_v2u *>(vbase + min(v_at, v_limit));
-        v_at += 16 * pitch;
-        return raw;
+    const uint32_t v_col = v_ok ? vc * 2 : 0, v_first = (uint32_t)vg * pitch + v_col;
+    // a chunk's value rows: a uniform base, lane offsets that stop at the last cached row
+    auto load_values = [&](piece_t (&rows)[kDecKeys], int i) {
+        const int first = min(min(i, n_chunks - 1) * kDecChunk, past - 1);
+        const char *from = vbase + (int64_t)first * pitch;
+        const uint32_t limit = (uint32_t)(past - 1 - first) * pitch + v_col;
+#pragma unroll
+        for (int j = 0; j < kDecKeys; ++j) rows[j] = *reinterpret_cast<const piece_t *>(from + min(v_first + (uint32_t)j * 16u * pitch, limit));
     };
-    sqap_v2u vraw[kDecLongAhead][kDecKeys];
+    piece_t vraw[kDecLongAhead][kDecKeys];
 #pragma unroll
-    for (int a = 0; a < kDecLongAhead; ++a)
-#pragma unroll
-        for (int j = 0; j < kDecKeys; ++j) vraw[a][j] = next_value_row();
+    for (int a = 0; a < kDecLongAhead; ++a) load_values(vraw[a], a);
     lds_barrier();
-    for (int key = past + t; key < n_chunks * kDecChunk; key += kDecLongT) sc[key] = key == past ? s_new : -INFINITY;     // (t = 0: the new token)
+    for (int key = past + t; key < n_chunks * kDecChunk; key += kDecLongT) sc[place_of(key)] = key == past ? s_new : -INFINITY;     // (t = 0: the new token)
     lds_barrier();
 
     // chunk maxima, running maxima, rescaling factors
@@ -596,7 +629,7 @@ __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const 
     for (int i = t; i < n_chunks * 16; i += kDecLongT) {
         float sum = 0.f;
 #pragma unroll
-        for (int j = 0; j < kDecKeys; ++j) sum += sc[(i >> 4) * kDecChunk + 16 * j + (i & 15)];
+        for (int j = 0; j < kDecKeys; ++j) sum += sc[i * kDecKeys + j];
         psg[i] = sum;
     }
     lds_barrier();
@@ -609,29 +642,36 @@ __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const 
         }
         lw[lane] = l;
     }
-    float o[4] = {0.f, 0.f, 0.f, 0.f};
-    auto value_chunk = [&](sqap_v2u (&rows)[kDecKeys], int i, auto last_c) {
+    float o[C] = {};
+    auto value_chunk = [&](piece_t (&rows)[kDecKeys], int i, auto last_c) {
         constexpr bool LAST = decltype(last_c)::value;
         const float f = resc[i];
+        float p[kDecKeys];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] *= f;
+        for (int j = 0; j < kDecKeys; j += 4) {
+            const float4 four = *reinterpret_cast<const float4 *>(sc + (i * 16 + vg) * kDecKeys + j);
+            p[j] = four.x;
+            p[j + 1] = four.y;
+            p[j + 2] = four.z;
+            p[j + 3] = four.w;
+        }
+#pragma unroll
+        for (int e = 0; e < C; ++e) o[e] *= f;
 #pragma unroll
         for (int j = 0; j < kDecKeys; ++j) {
             const int key = i * kDecChunk + 16 * j + vg;
-            union { sqap_v2u v; __half2 h2[2]; } raw;
+            union { piece_t v; __half2 h2[C / 2]; } raw;
             raw.v = rows[j];
-            if (LAST) {                                   // the new token's row, and zeros past it
-                if (key >= past) raw.v = key == past && v_ok ? *reinterpret_cast<const sqap_v2u *>(vnew + vc) : sqap_v2u{0u, 0u};
-            } else {
-                rows[j] = next_value_row();
+            if (LAST && key >= past)                      // the new token's row, and zeros past it
+                raw.v = key == past && v_ok ? *reinterpret_cast<const piece_t *>(vnew + vc) : piece_t{};
+#pragma unroll
+            for (int e = 0; e < C; e += 2) {
+                const float2 v = __half22float2(raw.h2[e / 2]);
+                o[e] = fmaf(p[j], v.x, o[e]);
+                o[e + 1] = fmaf(p[j], v.y, o[e + 1]);
             }
-            const float p = sc[key];
-            const float2 lo = __half22float2(raw.h2[0]), hi = __half22float2(raw.h2[1]);
-            o[0] = fmaf(p, lo.x, o[0]);
-            o[1] = fmaf(p, lo.y, o[1]);
-            o[2] = fmaf(p, hi.x, o[2]);
-            o[3] = fmaf(p, hi.y, o[3]);
         }
+        if (!LAST) load_values(rows, i + kDecLongAhead);
     };
     for (int i0 = 0; i0 < n_chunks; i0 += kDecLongAhead) {
 #pragma unroll
@@ -642,17 +682,17 @@ __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const 
     }
     if (v_ok) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ored[vg * kDecMaxD + vc + e] = o[e];
+        for (int e = 0; e < C; ++e) ored[vg * kDecMaxD + vc + e] = o[e];
     }
     lds_barrier();
-    if (t < d) {
-        float acc = 0.f;
+    float acc = 0.f;
+    const int first = share * (kDecMaxD / SHARES), columns = min(d, kDecMaxD / SHARES);
+    if (t < columns) {
 #pragma unroll
-        for (int g = 0; g < 16; ++g) acc += ored[g * kDecMaxD + t];
-        const float l = (lw[0] + lw[1]) + (lw[2] + lw[3]);
-        O[(int64_t)h * d + t] = __float2half_rn(acc * (1.0f / l));
+        for (int g = 0; g < 16; ++g) acc += ored[g * kDecMaxD + first + t];
     }
-    if (Xq) quantize_by_the_last<kDecLongT>(ored, wave_max, &last_flag, O, width, H, Xq, sx, counter);
+    store_head_output(O + (int64_t)h * d + first, columns, acc * (1.0f / ((lw[0] + lw[1]) + (lw[2] + lw[3]))));
+    if (Xq) quantize_by_the_last<kDecLongT>(ored, wave_max, &last_flag, O, width, H * SHARES, Xq, sx, counter);
 }
 
 sqap_status launch_decode_attention(const __half *QKV, const int32_t *pos, int H, int d, double base, __half *KV,
@@ -661,8 +701,12 @@ sqap_status launch_decode_attention(const __half *QKV, const int32_t *pos, int H
 {
     if (past >= kDecLongMin && past < kDecLongMax && (int64_t)(past + 1024) * ldkv * 2 < (int64_t)1 << 31) {
         const size_t lds = (size_t)(past / kDecChunk + 1) * kDecChunk * sizeof(float);
-        hipLaunchKernelGGL(decode_attention_long_kernel, dim3(H), dim3(kDecLongT), lds, st, QKV, pos, H, d, base, KV, ldkv, past,
-                           O, Xq, sx, counter, rope_frequencies(d, base));
+        const auto launch = [&](auto kernel, int shares) {
+            hipLaunchKernelGGL(kernel, dim3(H, shares), dim3(kDecLongT), lds, st, QKV, pos, H, d, base, KV, ldkv, past, O, Xq, sx, counter,
+                               rope_frequencies(d, base));
+        };
+        if (d == kDecMaxD && 2 * H <= device_cu_count()) launch(decode_attention_long_kernel<2>, 2);
+        else launch(decode_attention_long_kernel<1>, 1);
     } else {
         hipLaunchKernelGGL(decode_attention_kernel, dim3(H), dim3(256), 0, st, QKV, pos, H, d, base, KV, ldkv, past, O, Xq,
                            sx, counter, rope_frequencies(d, base));

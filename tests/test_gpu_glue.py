@@ -388,7 +388,8 @@ def test_attention_batch(G, oracle):
 @pytest.mark.parametrize("H,d,past,quantize", [(32, 128, 148, True), (4, 64, 0, True), (3, 16, 5, True),
                                                 (8, 128, 1100, True), (2, 96, 70, False), (32, 128, 63, False),
                                                 (2, 128, 383, True), (2, 128, 384, True), (3, 96, 575, True), (2, 64, 576, False),
-                                                (1, 8, 577, True), (2, 128, 1535, True)])   # both sides of the form for long caches
+                                                (1, 8, 577, True), (2, 128, 1535, True),    # both sides of the form for long caches
+                                                (130, 128, 385, False), (128, 128, 390, False), (33, 128, 576, True)])   # one and two workgroups per head
 def test_decode_attention_in_one_launch(G, oracle, H, d, past, quantize):
     """Rotation + cache append + attention (+ activation quantizer) of one new token in one launch:
     the cache row against the oracle's rotation, the output against the oracle's attention over the
