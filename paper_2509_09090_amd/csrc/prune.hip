@@ -36,94 +36,65 @@ __device__ __forceinline__ int block_scan_flags(bool flag, int *wave_sums, int *
     return off + before;
 }
 
-constexpr int kTopkSmallMax = 2048;
+constexpr int kTopkWaveMax = 2048;         // tokens that one wavefront holds
 
-// n <= 2048: every element counts how many rank ahead of it (larger key, or the
-// same key at a lower index); it is kept iff that count is below keep_k.
-// With rows_out the same launch also writes the surviving sequence rows (see
-// kept_rows_kernel), saving a dependent launch.
-__global__ __launch_bounds__(256) void topk_rank_kernel(const float *__restrict__ scores, int n,
-                                                        int keep_k, int32_t *__restrict__ idx_out,
-                                                        int seq_len, int vis_begin,
-                                                        int32_t *__restrict__ rows_out)
+// A wavefront's scores as keys, lane l holding tokens l, l + 64, ...; no key past the end.  All loads are on their way before the first is
+// looked at (under a condition each they were four round trips in a row: 256 tokens, whole kernel 5.4 us against 3.6).
+template <int PL>
+__device__ __forceinline__ void load_keys(const float *__restrict__ s, int n, int lane, uint32_t (&key)[PL])
 {
-    __shared__ __attribute__((aligned(16))) uint32_t keys[kTopkSmallMax];
-    __shared__ uint8_t kept[kTopkSmallMax];
-    __shared__ int wave_sums[4];
-    const int t = threadIdx.x;
-    const float *s = scores + (size_t)blockIdx.x * n;
-    int32_t *out = idx_out + (size_t)blockIdx.x * keep_k;
-    const int n4 = (n + 3) & ~3;
-    for (int i = t; i < n4; i += 256) keys[i] = i < n ? score_key(s[i]) : 0u;
-    __syncthreads();
-    int base = 0;
-    for (int c = 0; c < n; c += 256) {
-        const int i = c + t;
-        bool keep = false;
-        if (i < n) {
-            const uint32_t ki = keys[i];
-            int ahead = 0;
-            for (int j = 0; j < n4; j += 4) {
-                uint4 kj = *reinterpret_cast<const uint4 *>(&keys[j]);
-                ahead += (kj.x > ki) || (kj.x == ki && j + 0 < i);
-                ahead += (kj.y > ki) || (kj.y == ki && j + 1 < i);
-                ahead += (kj.z > ki) || (kj.z == ki && j + 2 < i);
-                ahead += (kj.w > ki) || (kj.w == ki && j + 3 < i);
-            }
-            keep = ahead < keep_k;
-            kept[i] = keep;
-        }
-        int total;
-        int pos = block_scan_flags(keep, wave_sums, &total);
-        if (keep) out[base + pos] = i;
-        base += total;
-    }
-    if (rows_out) {
-        int32_t *rows = rows_out + (size_t)blockIdx.x * (seq_len - n + keep_k);
-        __syncthreads();
-        base = 0;
-        for (int c = 0; c < seq_len; c += 256) {
-            const int sq = c + t, v = sq - vis_begin;
-            const bool keep = sq < seq_len && (v < 0 || v >= n || kept[v]);
-            int total;
-            int pos = block_scan_flags(keep, wave_sums, &total);
-            if (keep) rows[base + pos] = blockIdx.x * seq_len + sq;
-            base += total;
-        }
-    }
+    float raw[PL];
+#pragma unroll
+    for (int r = 0; r < PL; ++r) raw[r] = s[min(lane + 64 * r, n - 1)];
+#pragma unroll
+    for (int r = 0; r < PL; ++r) key[r] = lane + 64 * r < n ? score_key(raw[r]) : 0u;
 }
 
-// n <= 1024 and a sequence of at most 2048 positions: one wavefront per observation, no
-// barriers and no LDS traffic in the ranking.  Lane l owns tokens l, l + 64, ...: tokens
-// 64 r .. 64 r + 63 sit in lane order, so "lower index first" is "lower row, then lower lane".
-// The keep_k-th largest key T is built bit by bit from the top (T is the largest value that at
-// least keep_k keys reach) with wave ballots; keys above T are kept, and of the keys equal to T
-// the first ones by index.  Outputs are compacted with ballot prefixes.  PL = tokens per lane.
+// A value that at least k of the wavefront's keys reach, such that k tokens remain if those above it are taken and then the first
+// ones equal to it: bit by bit from the top, up to the first value that exactly k reach (usually after half of the 32 bits), else
+// the k-th largest key.  Keys are compared with values above zero, which keys past the end do not reach.
 template <int PL>
-__global__ __launch_bounds__(64) void topk_wave_kernel(const float *__restrict__ scores, int n, int keep_k,
-                                                       int32_t *__restrict__ idx_out, int seq_len, int vis_begin,
-                                                       int32_t *__restrict__ rows_out)
+__device__ __forceinline__ uint32_t kth_key(const uint32_t (&key)[PL], int k)
 {
-    __shared__ uint8_t keptf[1024];
-    const int lane = threadIdx.x, b = blockIdx.x;
-    const float *s = scores + (size_t)b * n;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    bool valid[PL], kept[PL];
-    uint32_t key[PL];
-#pragma unroll
-    for (int r = 0; r < PL; ++r) {
-        const int i = lane + 64 * r;
-        valid[r] = i < n;
-        key[r] = valid[r] ? score_key(s[i]) : 0u;
-    }
     uint32_t T = 0;
     for (int bit = 31; bit >= 0; --bit) {
         const uint32_t cand = T | (1u << bit);
         int reach = 0;
 #pragma unroll
-        for (int r = 0; r < PL; ++r) reach += __popcll(__ballot(valid[r] && key[r] >= cand));
-        if (reach >= keep_k) T = cand;
+        for (int r = 0; r < PL; ++r) reach += __popcll(__ballot(key[r] >= cand));
+        if (reach >= k) T = cand;
+        if (reach == k) break;
     }
+    return T;
+}
+
+// n <= 2048: one wavefront per observation, no
+// barriers and no LDS traffic in the ranking.  Lane l owns tokens l, l + 64, ...: tokens
+// 64 r .. 64 r + 63 sit in lane order, so "lower index first" is "lower row, then lower lane".
+// Keys above kth_key's T are kept, and of the keys equal to T the first ones by index.  Outputs are compacted with ballot prefixes.
+// PL = tokens per lane.  What bounds it: one trip to memory, the ballot rounds, the stores; us with the row list: 64 tokens 1.9, 3 x 256
+// 3.8, 576 8.6, 4 x 1024 10.2, 2 x 1500 17.3 (loads one after the other, all 32 rounds: 4.4, 5.4, 17.4, 19.4; the last by counting ranks
+// in LDS, 233).
+template <int PL>
+__global__ __launch_bounds__(64) void topk_wave_kernel(const float *__restrict__ scores, int n, int keep_k,
+                                                       int32_t *__restrict__ idx_out, int seq_len, int vis_begin,
+                                                       int32_t *__restrict__ rows_out)
+{
+    __shared__ uint8_t keptf[64 * PL];
+    const int lane = threadIdx.x, b = blockIdx.x;
+    const float *s = scores + (size_t)b * n;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    bool valid[PL], kept[PL];
+    uint32_t key[PL];
+    if (keep_k > 0) {
+        load_keys<PL>(s, n, lane, key);
+    } else {                                                     // (there may be no scores)
+#pragma unroll
+        for (int r = 0; r < PL; ++r) key[r] = 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < PL; ++r) valid[r] = lane + 64 * r < n;
+    const uint32_t T = kth_key<PL>(key, keep_k);
     int above = 0;
 #pragma unroll
     for (int r = 0; r < PL; ++r) above += __popcll(__ballot(valid[r] && key[r] > T));
@@ -146,12 +117,20 @@ __global__ __launch_bounds__(64) void topk_wave_kernel(const float *__restrict__
         __builtin_amdgcn_wave_barrier();
         int32_t *rows = rows_out + (size_t)b * (seq_len - n + keep_k);
         int rbase = 0;
-        for (int c = 0; c < seq_len; c += 64) {
-            const int sq = c + lane, v = sq - vis_begin;
-            const bool keep = sq < seq_len && (v < 0 || v >= n || keptf[v]);
-            const unsigned long long mk = __ballot(keep);
-            if (keep) rows[rbase + __popcll(mk & below)] = b * seq_len + sq;
-            rbase += __popcll(mk);
+        for (int c0 = 0; c0 < seq_len; c0 += 64 * 4) {           // (four flags on their way at a time)
+            bool keep[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int sq = c0 + 64 * u + lane, v = sq - vis_begin;
+                const uint8_t flag = keptf[min(max(v, 0), max(n - 1, 0))];
+                keep[u] = sq < seq_len && (v < 0 || v >= n || flag);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned long long mk = __ballot(keep[u]);
+                if (keep[u]) rows[rbase + __popcll(mk & below)] = b * seq_len + c0 + 64 * u + lane;
+                rbase += __popcll(mk);
+            }
         }
     }
 }
@@ -159,16 +138,15 @@ __global__ __launch_bounds__(64) void topk_wave_kernel(const float *__restrict__
 static bool launch_topk_wave(const float *scores, int batch, int n, int keep_k, int32_t *idx, int seq_len,
                              int vis_begin, int32_t *rows, hipStream_t st)
 {
-    if (n > 1024 || seq_len > 2048) return false;
-    if (n <= 256)
-        hipLaunchKernelGGL(topk_wave_kernel<4>, dim3(batch), dim3(64), 0, st, scores, n, keep_k, idx, seq_len,
-                           vis_begin, rows);
-    else if (n <= 512)
-        hipLaunchKernelGGL(topk_wave_kernel<8>, dim3(batch), dim3(64), 0, st, scores, n, keep_k, idx, seq_len,
-                           vis_begin, rows);
-    else
-        hipLaunchKernelGGL(topk_wave_kernel<16>, dim3(batch), dim3(64), 0, st, scores, n, keep_k, idx, seq_len,
-                           vis_begin, rows);
+    if (n > kTopkWaveMax) return false;
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(batch), dim3(64), 0, st, scores, n, keep_k, idx, seq_len, vis_begin, rows);
+    };
+    if (n <= 64) launch(topk_wave_kernel<1>);
+    else if (n <= 256) launch(topk_wave_kernel<4>);
+    else if (n <= 512) launch(topk_wave_kernel<8>);
+    else if (n <= 1024) launch(topk_wave_kernel<16>);
+    else launch(topk_wave_kernel<32>);
     return true;
 }
 
@@ -227,11 +205,7 @@ __global__ __launch_bounds__(256) void topk_radix_kernel(const float *__restrict
 sqap_status launch_prune_topk(const float *scores, int batch, int n, int keep_k, int32_t *idx,
                               hipStream_t st)
 {
-    if (launch_topk_wave(scores, batch, n, keep_k, idx, 0, 0, nullptr, st)) {
-    } else if (n <= kTopkSmallMax)
-        hipLaunchKernelGGL(topk_rank_kernel, dim3(batch), dim3(256), 0, st, scores, n, keep_k, idx, 0, 0,
-                           (int32_t *)nullptr);
-    else
+    if (!launch_topk_wave(scores, batch, n, keep_k, idx, 0, 0, nullptr, st))
         hipLaunchKernelGGL(topk_radix_kernel, dim3(batch), dim3(256), 0, st, scores, n, keep_k, idx);
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
@@ -240,17 +214,11 @@ sqap_status launch_prune_topk(const float *scores, int batch, int n, int keep_k,
 sqap_status launch_kept_rows(const int32_t *idx, int batch, int keep_k, int seq_len,
                              int vis_begin, int n_vis, int32_t *rows, hipStream_t st);
 
-// top-k and the surviving rows; one launch when the scores fit the rank kernel
+// top-k and the surviving rows; one launch when the scores fit a wavefront
 sqap_status launch_prune_rows(const float *scores, int batch, int n, int keep_k, int seq_len, int vis_begin,
                               int32_t *idx, int32_t *rows, hipStream_t st)
 {
     if (launch_topk_wave(scores, batch, n, keep_k, idx, seq_len, vis_begin, rows, st)) {
-        SQAP_HIP_CHECK(hipGetLastError());
-        return SQAP_OK;
-    }
-    if (n <= kTopkSmallMax) {
-        hipLaunchKernelGGL(topk_rank_kernel, dim3(batch), dim3(256), 0, st, scores, n, keep_k, idx, seq_len,
-                           vis_begin, rows);
         SQAP_HIP_CHECK(hipGetLastError());
         return SQAP_OK;
     }
@@ -266,14 +234,15 @@ sqap_status launch_prune_rows(const float *scores, int batch, int n, int keep_k,
 // are shared out by lane number mod 4; then the first wavefront samples alone (a pick depends on the one before, and a
 // barrier per pick would cost more than the arithmetic it shares out).  Everything after the projection is
 // integer work, so the result is exact.
-// A serial chain bounds it: 32 ballot rounds of the top-k search, one per bit of the key, then the picks; a pick is about
-// 5 instructions per 64 tokens, a wavefront maximum and the decoding of the winner.  A token's state is one word, squared
-// distance * 2048 + inverted index: the largest word is the next pick, a member's distance is zero, which keeps it out without
-// further tests, and (u, v) are packed halves whose squared distance is one subtraction and one dot product.  Measured per
-// call, 16 observations, us (one wavefront, masks and coordinates apart, in brackets): 16 x 16 tokens, 128 kept 15.6 (26.6);
-// 32 x 32, 512 kept 91 (214).
+// A serial chain bounds it: up to 32 ballot rounds of the top-k search, then the picks; a pick is three instructions per 64 tokens, a
+// wavefront maximum and the decoding of the winner.  A token's state is one word, squared distance * 1024 + inverted index: the
+// largest word is the next pick, a member's distance is zero, which keeps it out without further tests.  Coordinates are packed
+// halves, 32 times as large (1023 * 32 fits), so that one subtraction and one dot product, which adds the inverted index, give the
+// state for a new member, and a minimum does the rest.  Measured per call, 16 observations, us (eight instructions per 64 tokens and
+// pick, waits between them, in the first brackets; one wavefront, masks and coordinates apart, in the second): 16 x 16 tokens, 128
+// kept 12.1 (13.7, 26.6); 32 x 32, 512 kept 70 (111, 214).
 constexpr int kSelectCamera = 26;          // doubles per observation: K (9), [R|t] (12), point (3), patch w, h
-constexpr uint32_t kFarAway = 1u << 20;    // above any squared distance on a grid of <= 1024 tokens
+constexpr uint32_t kFarAway = 1u << 30;    // above any state on a grid of <= 1024 tokens: a squared distance is below 2^20
 
 // Eq. 2-3 in binary64, dot products summed left to right, no contraction.
 __device__ __forceinline__ bool project_token(const double *c, int &tu, int &tv)
@@ -316,10 +285,27 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 typedef short v2s __attribute__((ext_vector_type(2)));
 constexpr int kSelectWaves = 4;
 
-__device__ __forceinline__ uint32_t squared_distance(uint32_t a, uint32_t b)        // of packed (u, v)
+// squared distance of packed (32 u, 32 v) * 1024 + the inverted index
+__device__ __forceinline__ uint32_t state_of(uint32_t a, uint32_t b, int inverted)
 {
     const v2s d = __builtin_bit_cast(v2s, a) - __builtin_bit_cast(v2s, b);
-    return (uint32_t)__builtin_amdgcn_sdot2(d, d, 0, false);
+    return (uint32_t)__builtin_amdgcn_sdot2(d, d, inverted, false);
+}
+
+// The states after a new member at `at`.  Four dot products at a time, each in a register of its own: a result can be read three
+// wait states later, and in one register they would wait for each other.
+template <int PL>
+__device__ __forceinline__ void add_member(uint32_t (&state)[PL], const uint32_t (&uv)[PL], const int (&inverted)[PL], uint32_t at)
+{
+#pragma unroll
+    for (int r = 0; r < PL; r += 4) {
+        uint32_t t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = state_of(uv[r + e], at, inverted[r + e]);
+        asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) state[r + e] = min(state[r + e], t[e]);
+    }
 }
 
 template <int PL>     // tokens per lane: at most 64 * PL tokens
@@ -340,31 +326,23 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prune_select_kernel(const f
     // first" is "lower row first, then lower lane".
     bool valid[PL], kept[PL];
     uint32_t key[PL], uv[PL];
+    load_keys<PL>(s, n, lane, key);
 #pragma unroll
     for (int r = 0; r < PL; ++r) {
         const int i = lane + 64 * r;
         valid[r] = i < n;
-        key[r] = valid[r] ? score_key(s[i]) : 0u;
-        uv[r] = valid[r] ? (uint32_t)(i % gw) | ((uint32_t)(i / gw) << 16) : 0u;
+        uv[r] = valid[r] ? ((uint32_t)(i % gw) | ((uint32_t)(i / gw) << 16)) << 5 : 0u;
     }
     int cu = 0, cv = 0;
     bool have_ring = false;
     if (camera) have_ring = project_token(camera + (size_t)b * kSelectCamera, cu, cv);
 
-    // Eq. 1: the k_attn-th largest key T, found bit by bit from the top (T is the largest value
-    // that at least k_attn keys reach), then keys above T and the first tokens equal to T.
-    uint32_t T = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-        const uint32_t cand = T | (1u << bit);
-        int reach = 0;
-#pragma unroll
-        for (int r = 0; r < PL; ++r) reach += __popcll(__ballot(valid[r] && key[r] >= cand));
-        if (reach >= k_attn) T = cand;
-    }
+    // Eq. 1: keys above T and the first tokens equal to T
+    const uint32_t T = kth_key<PL>(key, k_attn);
     int above = 0;
 #pragma unroll
     for (int r = 0; r < PL; ++r) above += __popcll(__ballot(valid[r] && key[r] > T));
-    const int need_eq = k_attn - above;          // (k_attn = 0 ends with T = all ones: nothing above, nothing needed)
+    const int need_eq = k_attn - above;          // (k_attn = 0 ends with a T that no key reaches: nothing above, nothing needed)
     int eq_seen = 0;
 #pragma unroll
     for (int r = 0; r < PL; ++r) {
@@ -374,7 +352,7 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prune_select_kernel(const f
         eq_seen += __popcll(mk);
         // Eq. 4 by the distance itself
         if (have_ring && valid[r]) {
-            const int du = abs((int)(uv[r] & 0xffffu) - cu), dv = abs((int)(uv[r] >> 16) - cv);
+            const int du = abs((int)((uv[r] & 0xffffu) >> 5) - cu), dv = abs((int)(uv[r] >> 21) - cv);
             keep = keep || (du > dv ? du : dv) <= radius;
         }
         kept[r] = keep;
@@ -386,9 +364,14 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prune_select_kernel(const f
     // Eq. 5: distance of every candidate to the set kept so far, then one pick per step
     const int m = keep_total > count ? keep_total - count : 0;
     if (m > 0) {                                             // (the same in all four wavefronts)
-        uint32_t mind[PL];
+        uint32_t state[PL];
+        int inverted[PL];
 #pragma unroll
-        for (int r = 0; r < PL; ++r) mind[r] = valid[r] ? kFarAway : 0u;
+        for (int r = 0; r < PL; ++r) {
+            state[r] = valid[r] ? kFarAway : 0u;
+            inverted[r] = 1023 - (lane + 64 * r);
+            asm volatile("" : "+v"(inverted[r]));            // (a register, not arithmetic on the lane in every pick)
+        }
 #pragma unroll
         for (int rr = 0; rr < PL; ++rr) {
             unsigned long long mk = __ballot(kept[rr]) & (0x1111111111111111ull << wave);      // this wavefront's members
@@ -396,36 +379,33 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prune_select_kernel(const f
                 const int src = __builtin_ctzll(mk);
                 mk &= mk - 1;
                 const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)uv[rr], src);
-#pragma unroll
-                for (int r = 0; r < PL; ++r) mind[r] = min(mind[r], squared_distance(uv[r], at));
+                add_member<PL>(state, uv, inverted, at);
             }
         }
 #pragma unroll
-        for (int r = 0; r < PL; ++r) part[wave][lane + 64 * r] = mind[r];
+        for (int r = 0; r < PL; ++r) part[wave][lane + 64 * r] = state[r];
         __syncthreads();
         if (wave != 0) return;
-        uint32_t state[PL];
 #pragma unroll
         for (int r = 0; r < PL; ++r) {
             const int i = lane + 64 * r;
-            const uint32_t d = min(min(part[0][i], part[1][i]), min(part[2][i], part[3][i]));
-            state[r] = (d << 11) + (uint32_t)(2047 - i);
+            state[r] = min(min(part[0][i], part[1][i]), min(part[2][i], part[3][i]));
+            if (state[r] == kFarAway) state[r] += (uint32_t)inverted[r];                      // (an empty set: token 0 first)
         }
         const uint32_t inv_gw = (1u << 20) / (uint32_t)gw + 1u;      // w / gw = (w * inv_gw) >> 20: w * gw < 2^20
+        const uint32_t row_step = (65536u - (uint32_t)gw) << 5;      // (w - v gw) | v << 16 = w + v (65536 - gw)
         for (int step = 0; step < m; ++step) {
             // largest distance, lowest index among equals: the index is in the state inverted
             uint32_t best = state[0];
 #pragma unroll
             for (int r = 1; r < PL; ++r) best = max(best, state[r]);
             best = wave_max_u32(best);
-            const uint32_t w = 2047u - (best & 2047u);
-            const uint32_t v = (w * inv_gw) >> 20, at = (w - v * (uint32_t)gw) | (v << 16);
-#pragma unroll
-            for (int r = 0; r < PL; ++r)
-                state[r] = min(state[r], (squared_distance(uv[r], at) << 11) + (uint32_t)(2047 - (lane + 64 * r)));
+            const uint32_t w = 1023u & ~best;
+            const uint32_t at = (w << 5) + ((w * inv_gw) >> 20) * row_step;
+            add_member<PL>(state, uv, inverted, at);
         }
 #pragma unroll
-        for (int r = 0; r < PL; ++r) kept[r] = kept[r] || (valid[r] && (state[r] >> 11) == 0u);
+        for (int r = 0; r < PL; ++r) kept[r] = kept[r] || (valid[r] && (state[r] >> 10) == 0u);
     } else if (wave != 0) {
         return;
     }

@@ -29,7 +29,7 @@ def test_topk_random(G, oracle, batch, n, k):
     assert np.array_equal(G.gpu_prune_topk(s, k), oracle.prune_topk(s, k))
 
 
-@pytest.mark.parametrize("n", [64, 256, 4096])
+@pytest.mark.parametrize("n", [64, 256, 512, 1024, 2048, 4096])
 def test_topk_adversarial(G, oracle, n):
     rng = np.random.default_rng(n)
     cases = {
