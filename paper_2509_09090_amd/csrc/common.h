@@ -93,6 +93,12 @@ static inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream
 constexpr int kMaxDeviceSlots = 64;
 static inline int current_device()
 {
+    // a process that sees one device is on it: nothing to ask (the question costs 0.8 us, a fifth of a call)
+    static const bool only_one = [] {
+        int n = 0;
+        return hipGetDeviceCount(&n) == hipSuccess && n == 1;
+    }();
+    if (only_one) return 0;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0) dev = 0;
     return dev;
