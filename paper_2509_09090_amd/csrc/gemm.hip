@@ -495,9 +495,9 @@ __device__ __forceinline__ void epilogue(const GemmParams &p, v16i (&acc)[C::TM]
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             sw4[jn * 4 + q] = *reinterpret_cast<const float4 *>(&sws[wn * WN + jn * 32 + q * 8 + ch4]);
-    // Whole tile inside the matrix and 16-byte stores possible (wave-uniform): no checks per store, and the
+    // Whole tile inside the matrix (wave-uniform): no checks per store, and the
     // four row passes of an accumulator row are read together before they are stored.
-    const bool inside = vec_ok && m0 + C::BM <= p.M && (ng0 << 5) + C::BN <= p.N;
+    const bool inside = m0 + C::BM <= p.M && (ng0 << 5) + C::BN <= p.N;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int row0 = m0 + (i * C::WAVES_M + wm) * 32;
@@ -525,9 +525,17 @@ __device__ __forceinline__ void epilogue(const GemmParams &p, v16i (&acc)[C::TM]
 #pragma unroll
             for (int ps = 0; ps < PASSES; ++ps)
                 v[ps] = *reinterpret_cast<const v4i *>(ep + (ps * ROWS_PER_PASS + rin0) * PITCH + cb);
+            // (Rows that begin inside a cache line share it with the next tile's: not past the L2, which puts the two parts
+            // together.  1630 x 38663 x 512 67 us, 96 with nontemporal stores; 2368 x 12289 x 4096 117 and 124.)
+            if (vec_ok) {
 #pragma unroll
-            for (int ps = 0; ps < PASSES; ++ps)
-                __builtin_nontemporal_store(v[ps], reinterpret_cast<v4i *>(dst + (size_t)ps * ROWS_PER_PASS * p.ldy));
+                for (int ps = 0; ps < PASSES; ++ps)
+                    __builtin_nontemporal_store(v[ps], reinterpret_cast<v4i *>(dst + (size_t)ps * ROWS_PER_PASS * p.ldy));
+            } else {
+#pragma unroll
+                for (int ps = 0; ps < PASSES; ++ps)
+                    *reinterpret_cast<halves8_any *>(dst + (size_t)ps * ROWS_PER_PASS * p.ldy) = v[ps];
+            }
         } else {
 #pragma unroll
             for (int ps = 0; ps < 32 / ROWS_PER_PASS; ++ps) {
@@ -537,8 +545,9 @@ __device__ __forceinline__ void epilogue(const GemmParams &p, v16i (&acc)[C::TM]
                 if (row < p.M && col < p.N) {
                     const v4i v = *reinterpret_cast<const v4i *>(ep + rin * PITCH + cb);
                     __half *dst = p.Y + (size_t)row * p.ldy + col;
-                    if (vec_ok && col + 8 <= p.N) {
-                        __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(dst));
+                    if (col + 8 <= p.N) {
+                        if (vec_ok) __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(dst));
+                        else *reinterpret_cast<halves8_any *>(dst) = v;
                     } else {
                         const __half *h = reinterpret_cast<const __half *>(&v);
 #pragma unroll
@@ -886,7 +895,6 @@ __global__ __launch_bounds__(C::THREADS, 1) void gemm_splitk_kernel(const GemmPa
         // this workgroup's slice of the tile, 16 bytes (4 channels of one token) per thread at a time;
         // partials are read with agent-scope loads (sc1): they bypass this CU's L1
         const int ub = UNITS * rank / nc, ue = UNITS * (rank + 1) / nc;
-        const bool y_vec = (p.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(p.Y) & 7u) == 0;
         constexpr int UPT = 4;                             // units per thread per trip
         for (int u0 = ub + t; u0 < ue; u0 += UPT * C::THREADS) {
             // where each unit goes, and its scales: issued before the partial sums so that the
@@ -949,8 +957,8 @@ __global__ __launch_bounds__(C::THREADS, 1) void gemm_splitk_kernel(const GemmPa
                 pk.x = dequant2(sum.x, sum.y, sxf[x], s01.x, s01.y);
                 pk.y = dequant2(sum.z, sum.w, sxf[x], s23.x, s23.y);
                 __half *dst = p.Y + (size_t)row[x] * p.ldy + col[x];
-                if (y_vec && col[x] + 4 <= p.N) {
-                    *reinterpret_cast<uint2 *>(dst) = pk;
+                if (col[x] + 4 <= p.N) {
+                    *reinterpret_cast<halves4_any *>(dst) = halves4_any{pk.x, pk.y};
                 } else {
                     const __half *h = reinterpret_cast<const __half *>(&pk);
 #pragma unroll

@@ -244,8 +244,8 @@ __global__ __launch_bounds__(kFewThreads, 1) void gemm_few_kernel(const FewParam
         pk.h[0] = __floats2half2_rn(y0, y1);
         pk.h[1] = __floats2half2_rn(y2, y3);
         __half *dst = w.Y + (size_t)o.token * w.ldy + o.col;
-        if (o.col + 4 <= w.N && (w.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(w.Y) & 7u) == 0) {
-            *reinterpret_cast<uint2 *>(dst) = pk.u;
+        if (o.col + 4 <= w.N) {
+            *reinterpret_cast<halves4_any *>(dst) = halves4_any{pk.u.x, pk.u.y};
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)

@@ -273,7 +273,6 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
     lds_barrier();
     const int tok_in = lane & 15, ch4 = (lane >> 4) * 4;
     const RowsWeight &w = p.w;
-    const bool y_vec = (w.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(w.Y) & 7u) == 0;
     const bool a_vec = (w.N & 3) == 0 && w.acc_out && (reinterpret_cast<uintptr_t>(w.acc_out) & 15u) == 0;
     constexpr int OWN = (TG * CB + KS - 1) / KS;
     v4i sums[OWN];
@@ -300,8 +299,8 @@ __device__ __forceinline__ void rows_tile(const RowsParams &p, uint8_t *smem, in
             pk.x = rows_dequant_pair(sum.x, sum.y, sxf, s01.x, s01.y);
             pk.y = rows_dequant_pair(sum.z, sum.w, sxf, s23.x, s23.y);
             __half *dst = w.Y + (size_t)row * w.ldy + col;
-            if (y_vec && col + 4 <= w.N) {
-                *reinterpret_cast<uint2 *>(dst) = pk;
+            if (col + 4 <= w.N) {
+                *reinterpret_cast<halves4_any *>(dst) = halves4_any{pk.x, pk.y};
             } else {
                 const __half *h = reinterpret_cast<const __half *>(&pk);
 #pragma unroll

@@ -253,7 +253,6 @@ __global__ __launch_bounds__(W * 64, 4) void skinny_kernel(const SkinnyArgs a)
         const int xoff = has_row ? (kSkinnyZeroBytes + c0 * 256 + h * 128 + r * 16) : 0;
         const int xstride = has_row ? 256 : 0;
         const float sxf = has_row ? __half2float(e.sx[r]) : 0.f;
-        const bool y_vec = (e.N & 3) == 0 && (e.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(e.Y) & 7u) == 0;
         // 16-byte stores possible: the output goes through the LDS slots (when the launch has any)
         const bool y_late = LATE && a.out_cap > 0 && (e.N & 7) == 0 && (e.ldy & 7) == 0 &&
                             (reinterpret_cast<uintptr_t>(e.Y) & 15u) == 0;
@@ -370,8 +369,8 @@ __global__ __launch_bounds__(W * 64, 4) void skinny_kernel(const SkinnyArgs a)
                         __half *dst = e.Y + (size_t)r * e.ldy + n;
                         if (y_late) {
                             // the halves are in the LDS slot; only the integer accumulators are stored here
-                        } else if (y_vec) {
-                            *reinterpret_cast<uint2 *>(dst) = pk.u;
+                        } else if (n + 4 <= e.N) {
+                            *reinterpret_cast<halves4_any *>(dst) = halves4_any{pk.u.x, pk.u.y};
                         } else {
 #pragma unroll
                             for (int x = 0; x < 4; ++x)

@@ -578,6 +578,33 @@ def test_whole_output_linear_edges(G, oracle, M, N, K):
     assert G.assert_fp16_close(Y, Yo) == 0
 
 
+# output rows at any even address, whole tiles and remainders of every kernel; what lies between the rows stays
+@pytest.mark.parametrize("M,N,K", [(3, 70, 128), (16, 261, 160), (20, 1029, 512), (150, 521, 1024), (84, 24601, 128), (130, 40007, 128), (520, 519, 256),
+                                   (600, 9001, 128), (200, 515, 33 * 32)])
+def test_output_rows_at_any_even_address(G, oracle, M, N, K):
+    import torch
+    from paper_2509_09090_amd import binding as B
+    rng = np.random.default_rng(M + 7 * N + K)
+    Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
+    sx, sw = (rng.random(M) * 2 + 0.01).astype(np.float16), (rng.random(N) * 0.01 + 1e-4).astype(np.float16)
+    Yo, _ = oracle.w4a4_linear(Xq, sx, Wq, sw)
+    W = B.sqap_weight_pack(G.to_dev(Wq), G.to_dev(sw))
+    work = torch.zeros(max(256, B.sqap_workspace_bytes(M, N, K)), dtype=torch.uint8, device="cuda")
+    try:
+        for pitch, start in ((N, 1), (N + 1, 0), (N + 2, 3), (N + 5, 2)):
+            for which in (1, 0):
+                B.sqap_set_mid_m_kernel(which)
+                flat = torch.full((start + M * pitch + 8,), float("nan"), dtype=torch.float16, device="cuda")
+                rows = flat[start:start + M * pitch].view(M, pitch)
+                B.sqap_w4a4_linear(G.to_dev(Xq), G.to_dev(sx), W, rows[:, :N], None, work)
+                assert G.assert_fp16_close(rows[:, :N].cpu().numpy(), Yo) == 0
+                rows[:, :N] = float("nan")
+                assert torch.isnan(flat).all()
+    finally:
+        B.sqap_set_mid_m_kernel(1)
+    W.free()
+
+
 @pytest.mark.parametrize("M,K,Ns", [(1, 64, (1, 1, 1, 1)), (8, 448, (33, 500, 16, 4100)), (4, 4096, (512, 512, 512)), (3, 2112, (9000, 24))])
 def test_group_with_one_input_runs_as_one_product(G, oracle, M, K, Ns):
     import torch
