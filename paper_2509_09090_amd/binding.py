@@ -132,8 +132,6 @@ def _ptr(t):
 # the raw handle: a torch.cuda.Stream object built only to be asked for it costs 2.4 us a call.  (Not part of torch's public
 # interface: without it the object is asked.)
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-# the current device without torch's check that it has been initialised: whoever passes device tensors has
-_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 
 
 def _stream(stream):
@@ -141,7 +139,7 @@ def _stream(stream):
         return ctypes.c_void_p(int(stream))
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(_device())
+    return _raw_stream(torch.cuda.current_device())
 
 
 def sqap_init(stream=None):
