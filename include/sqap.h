@@ -444,7 +444,8 @@ sqap_status sqap_selftest_quotient(uint64_t *mismatches_out, void *stream);
 /*
  * The same for the silu of sqap_swiglu_quantize_act, which is evaluated with an exponential and a
  * reciprocal of the library's own: counts the half values g, all 65536 of them, for which its binary32
- * bits differ from those of (float)(g / (1 + exp(-g))) in binary64 (NaN is NaN).  Expected result: 0.
+ * bits differ from those of (float)(g / (1 + exp(-g))) in binary64 (NaN is NaN), or for which the estimate in
+ * binary32 that goes before it is further from silu than it is taken to be.  Expected result: 0.
  */
 sqap_status sqap_selftest_silu(uint64_t *mismatches_out, void *stream);
 

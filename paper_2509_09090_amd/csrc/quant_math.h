@@ -125,6 +125,46 @@ __device__ __forceinline__ float silu_of(float g)
     return (float)((double)g * r);
 }
 
+// g := the half that silu_of(g) * u rounds to, for eight pairs.  Binary32 and the hardware's exponential and reciprocal give silu with an
+// error of at most kSiluError where g >= kSiluMin, so that where both ends of r (1 +- kSiluReach) round to one half, that half is it:
+// rounding is monotonic, and the reach covers the error, the product's rounding on both ways and the ends' own, 2^-24 each.  Below
+// kSiluMin the estimate is NaN, or -0 (times an infinite u: NaN), or a negative number where silu is one too, so small that its product
+// with any finite u rounds to the zero that silu's does.  Elsewhere (0.2 % of the values, one wavefront in eight; and NaN, which equals
+// nothing) silu_of decides, one element after the other; the estimates of all eight come first, so that none waits for another.
+// None of this is taken from a manual: sqap_selftest_silu looks at all halves.
+constexpr float kSiluMin = -80.f, kSiluError = 5.0e-7f, kSiluReach = 7.0e-7f;
+static_assert(kSiluError + 3.0f / 16777216.0f < kSiluReach, "");
+
+__device__ __forceinline__ float silu_estimate(float g)
+{
+    const float t = g * -1.442695040888963f, power = __builtin_amdgcn_exp2f(t);
+    // what the rounding of t has taken from the exponent, with ln 2 in two parts
+    const float lost = fmaf(t, 0x1.05c610p-29f, fmaf(t, -0x1.62e430p-1f, -g));
+    return g * __builtin_amdgcn_rcpf(1.0f + fmaf(power, lost, power));
+}
+
+__device__ __forceinline__ void swiglu8(float (&g)[8], const float (&u)[8])
+{
+    float h[8];
+    bool open[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float r = silu_estimate(g[e]) * u[e];
+        const __half low = __float2half_rn(fmaf(r, -kSiluReach, r)), high = __float2half_rn(fmaf(r, kSiluReach, r));
+        h[e] = __half2float(high);                         // (of a zero it has the sign, which `low` has not)
+        open[e] = !(__half2float(low) == h[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        if (open[e]) {
+            float exact = silu_of(g[e]) * u[e];
+            asm volatile("" : "+v"(exact));                // two roundings, not one mixed-precision instruction
+            h[e] = __half2float(__float2half_rn(exact));
+        }
+        g[e] = h[e];
+    }
+}
+
 // S / K in binary64.  For a power of two the quotient is S with a smaller exponent (S is zero or at least 2^-48,
 // so nothing underflows): one instruction instead of the division's forty, the same bits.
 __device__ __forceinline__ double mean_of(double S, int K)

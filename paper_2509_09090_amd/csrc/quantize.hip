@@ -248,8 +248,9 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta
 // SwiGLU (Shazeer 2020; the feed-forward of a Llama decoder): v holds the gate row g, pre.U the
 // up row;  v = half(silu(g) * u),  silu(g) = (float)(g / (1 + exp(-g))) evaluated in binary64.
 // silu is a function of a half value: a GPU test walks all 2^16 of them against the host's.
-// At 2368 x 11008 the vector ALU bounds this form (16.5 thousand instructions per SIMD, 42 per element, 25 of them silu's, and issuing
-// in 98 % of the cycles): 40 us against 49.7 with the library's binary64 exponential and division; 117 MB take 23 us.
+// What bounds it at 2368 x 11008 is the vector ALU, then memory (117 MB, 23 us): 30.8 us, whatever the values' spread, against 34.7-38.4
+// with silu_of for every element, 25 instructions in binary64, and 49.7 with the library's exponential and division.  84 rows 6.3-6.6
+// (6.7-7.0), 1000 x 5504 9.2 (10.1).  (With a binary32 estimate good down to g = -8 or -32 only, wider gates took 53 us.)
 // (A per-device table of the 2^16 results was slower than computing: 13 against 10 us at 84 x 11008,
 // 48 scattered 4-byte loads per thread.)
 template <int T, int GPT>
@@ -262,10 +263,7 @@ __device__ __forceinline__ void swiglu_row(float (&v)[GPT][8], const uint4 (&up)
         if (g < groups) {
             float u[8];
             unpack8(up[gi], u);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                v[gi][e] = round_to_half(silu_of(v[gi][e]) * u[e]);
-            }
+            swiglu8(v[gi], u);
             if (pre.y_out) reinterpret_cast<uint4 *>(pre.y_out + (size_t)row * K)[g] = pack8(v[gi]);
         }
     }
@@ -693,6 +691,11 @@ __global__ __launch_bounds__(256) void silu_selftest_kernel(unsigned long long *
     const double gd = (double)g;
     const float want = (float)(gd / (1.0 + exp(-gd))), got = silu_of(g);
     if (__float_as_uint(want) != __float_as_uint(got) && !(want != want && got != got)) atomicAdd(mismatches, 1ull);
+    // what swiglu8 rests on (an estimate that is NaN is left to silu_of)
+    const double silu = gd / (1.0 + exp(-gd)), estimate = (double)silu_estimate(g);
+    const bool good = g < kSiluMin ? signbit(estimate) && estimate > -0x1p-60 && (estimate == 0.0 || want != 0.f)
+                                   : fabs(estimate - silu) <= (double)kSiluError * fabs(silu);
+    if (estimate == estimate && !good) atomicAdd(mismatches, 1ull);
 }
 
 sqap_status launch_silu_selftest(unsigned long long *mismatches, hipStream_t st)

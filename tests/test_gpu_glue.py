@@ -152,6 +152,25 @@ def test_silu_against_many_factors_and_at_the_infinities(G, oracle):
     assert [np.signbit(x) for x in o[3:7]] == [True, True, False, False] and o[3] == 0 and o[4] == 0
 
 
+@pytest.mark.parametrize("spread", [None, 1.0, 30.0])
+def test_swiglu_of_any_pair(G, oracle, spread):
+    """Whichever way a product is found, estimate or binary64: the definition's half.  All bit patterns, infinities and NaN among them,
+    and gates of an ordinary and of a wide spread."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    rng = np.random.default_rng(11)
+    shape = (256, 4096)
+    if spread is None:
+        Gm, Um = (rng.integers(0, 65536, shape, dtype=np.uint16).view(np.float16) for _ in range(2))
+    else:
+        Gm, Um = (rng.standard_normal(shape) * spread).astype(np.float16), rng.standard_normal(shape).astype(np.float16)
+    h = torch.zeros(shape, dtype=torch.float16, device="cuda")
+    B.sqap_swiglu_quantize_act(G.to_dev(Gm), G.to_dev(Um), None, None, h_out=h)
+    want, got = oracle.swiglu(Gm, Um), h.cpu().numpy()
+    nan = np.isnan(want)
+    assert np.array_equal(nan, np.isnan(got)) and np.array_equal(got.view(np.uint16)[~nan], want.view(np.uint16)[~nan])
+
+
 @pytest.mark.parametrize("M", [1, 256, 257, 512, 513])
 @pytest.mark.parametrize("K", [2048, 2064, 4096, 4112, 8192, 8208, 12288, 12304, 16384])
 def test_threads_per_row(G, oracle, M, K):
