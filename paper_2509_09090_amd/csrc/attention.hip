@@ -30,7 +30,7 @@ namespace sqap {
 // 1024 x 2048 50.7 and 51.0; a second time through the keys doubles a workgroup's time).  Heads of 64 are held to the 128 registers that
 // four wavefronts per SIMD leave, which the second time through would pass (16 x 274 x 274, 32 heads 26.6, with 137 registers 28.0).
 // Measured (us; the kernel before, one key tile per wavefront and 2-byte transposing reads, in brackets; heads of 128):
-// 16 x 148 x 148, 32 heads 23.2 (62.8); 1024 x 2048, 32 heads 48.8 (126); 148 x 148, 32 heads 6.5 (8.2); 84 x 84 5.5 (6.2).
+// 16 x 148 x 148, 32 heads 23.2 (62.8); 1024 x 2048, 32 heads 47.5 (126); 148 x 148, 32 heads 6.5 (8.2); 84 x 84 5.5 (6.2).
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -336,17 +336,22 @@ __device__ __forceinline__ bool attend(uint8_t *lds, int l, int wave, int qblock
     return my_q < Sq && (zero[0] + zero[1]) + (zero[2] + zero[3]) != 0.f;
 }
 
-template <int D, int NQ, int NK>
+template <int D, int NQ, int NK, bool ROUNDS>
 __global__ __launch_bounds__(64 * NQ * NK, D == 64 ? 4 : 2) void attention_tiles_kernel(const __half *__restrict__ Q, int64_t ldq,
                                                               const __half *__restrict__ Kc, int64_t ldk,
                                                               const __half *__restrict__ V, int64_t ldv, int Sq, int Sk,
-                                                              __half *__restrict__ O, int64_t ldo)
+                                                              __half *__restrict__ O, int64_t ldo, int round)
 {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     constexpr int OWN = D / 32 / NK;
     const int l = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int qblock = gridDim.y - 1 - blockIdx.y;                    // the longest rows first
+    int rank = blockIdx.y;                                            // 0: the longest rows
+    if (ROUNDS) {                                                     // every other round of the launch the other way about (launch_tiles)
+        const int n = (gridDim.y + round - 1) / round, r = rank / round;
+        if ((n - 1 - r) & 1) rank = (2 * r + 1) * round - 1 - rank;
+    }
+    const int qblock = gridDim.y - 1 - rank;
     Q += (int64_t)blockIdx.z * Sq * ldq + (int64_t)blockIdx.x * D;
     Kc += (int64_t)blockIdx.z * Sk * ldk + (int64_t)blockIdx.x * D;
     V += (int64_t)blockIdx.z * Sk * ldv + (int64_t)blockIdx.x * D;
@@ -382,9 +387,9 @@ __global__ __launch_bounds__(64 * NQ * NK, D == 64 ? 4 : 2) void attention_tiles
     }
 }
 
-template <int D, int NQ, int NK>
+template <int D, int NQ, int NK, bool ROUNDS = false>
 static sqap_status launch_tiles(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
-                                int batch, int Sq, int Sk, int H, __half *O, int64_t ldo, hipStream_t st)
+                                int batch, int Sq, int Sk, int H, __half *O, int64_t ldo, hipStream_t st, int round = 0)
 {
     constexpr int bytes = attention_lds_bytes<D, NQ, NK>();
     static_assert(bytes <= 160 * 1024, "LDS of a compute unit");
@@ -392,13 +397,13 @@ static sqap_status launch_tiles(const __half *Q, int64_t ldq, const __half *Kc, 
         static std::atomic<bool> allowed[kMaxDeviceSlots];
         const int slot = device_slot();
         if (!allowed[slot].load(std::memory_order_acquire)) {
-            SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&attention_tiles_kernel<D, NQ, NK>),
+            SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&attention_tiles_kernel<D, NQ, NK, ROUNDS>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
             allowed[slot].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((attention_tiles_kernel<D, NQ, NK>), dim3(H, (Sq + 32 * NQ - 1) / (32 * NQ), batch),
-                       dim3(64 * NQ * NK), bytes, st, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, O, ldo);
+    hipLaunchKernelGGL((attention_tiles_kernel<D, NQ, NK, ROUNDS>), dim3(H, (Sq + 32 * NQ - 1) / (32 * NQ), batch), dim3(64 * NQ * NK), bytes, st,
+                       Q, ldq, Kc, ldk, V, ldv, Sq, Sk, O, ldo, round);
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }
@@ -420,6 +425,16 @@ sqap_status launch_attention_tiles(const __half *Q, int64_t ldq, const __half *K
     const int64_t groups = (int64_t)batch * H * ((Sq + 31) / 32);
     if (groups <= device_cu_count() && Sk >= 192)
         return launch_tiles<128, 1, 4>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
+    // Later query blocks see more keys.  Where more blocks come than compute units have room for, the longest go first.  Where all
+    // find room at once, one or two per compute unit, their order says which share a unit: the first round of them goes from short to
+    // long, the second from long to short, so that long meets short, and where the second is not full the longest have a unit to
+    // themselves.  32 heads unless said, us, both rounds from long to short in brackets: 1024 x 2048 46.6 (48.1), 1024 x 1024 21.8 (23.2),
+    // 700 x 1500 28.8 (31.2), 600 x 600 13.5 (14.3), 900 x 900, 24 heads 17.7 (19.3).  Heads of 64, four blocks per unit: no gain (520 x
+    // 1024 14.0 (13.5), 700 x 1200 16.0 (16.3)).
+    const int cus = device_cu_count();
+    const int64_t all = (int64_t)H * ((Sq + 63) / 64);
+    if (batch == 1 && H <= cus && all > cus && all <= 2 * (int64_t)cus)
+        return launch_tiles<128, 2, 2, true>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st, cus / H);
     return launch_tiles<128, 2, 2>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
 }
 

@@ -306,7 +306,9 @@ def test_attention(G, oracle, Sq, Sk, H, d):
 
 @pytest.mark.parametrize("batch,Sq,Sk,H,d", [(1, 1, 1, 1, 128), (2, 31, 31, 2, 64), (1, 32, 64, 2, 128), (1, 33, 65, 3, 128), (1, 65, 129, 2, 64),
                                              (1, 20, 191, 2, 128), (1, 20, 192, 2, 128), (2, 70, 193, 2, 128), (1, 3, 640, 1, 128),
-                                             (1, 130, 257, 1, 128), (3, 129, 321, 32, 128), (9, 64, 200, 32, 128)])
+                                             (1, 130, 257, 1, 128), (3, 129, 321, 32, 128), (9, 64, 200, 32, 128),
+                                             # query blocks in two or three rounds, every other one reversed, the last one begun or whole
+                                             (1, 600, 640, 32, 128), (1, 1000, 1100, 30, 128), (1, 1024, 1030, 32, 128), (1, 150, 150, 150, 128)])
 def test_attention_tile_edges(G, oracle, batch, Sq, Sk, H, d):
     """Tile and group edges of both forms of the matrix-core kernel (one or two query groups, two or four key groups),
     against binary64.  Bound: the output's rounding to half (2^-11 of it), and for scores up to 40 in units of ln 2
