@@ -290,7 +290,7 @@ def decode_leg(torch, B, wl, stack, steps_per_m=7):
     # step's dependencies allow.  The roofline object is for the second; the first is kept beside it.
     alg = stack.weight_bytes + stack.scale_bytes
     dep, ceil_ = out["M1"]["per_level"], out["M1"]
-    out["roofline"] = {"bound": "hbm", "kernel": "gemm_rows_kernel and skinny_kernel<S, 8> (129 launches per step, replayed from a HIP graph)",
+    out["roofline"] = {"bound": "hbm", "kernel": "gemm_few_kernel (129 launches per step, replayed from a HIP graph)",
                        "formulation": "dependency-respecting: one launch per group of linears that can run together",
                        "achieved": dep["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": dep["GBps"] / HBM_PEAK_GBS,
                        "target_frac": 0.70, "traffic": None, "algorithmic_bytes_per_step": alg}
