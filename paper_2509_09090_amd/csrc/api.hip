@@ -605,7 +605,8 @@ sqap_status sqap_w4a4_linear(const uint8_t *Xq, const sqap_f16 *sx, int32_t M,
     }
     // (decided once: another thread may turn the switch meanwhile, and what M <= 8 would fall through to asks for a workspace)
     WholePlan plan;
-    const bool whole_outputs = rows_kernel_wanted() && whole_output_plan(M, (w->N + 15) / 16, w->K, device_cu_count(), 1, &plan);
+    const bool whole_outputs = rows_kernel_wanted() &&
+                               whole_output_plan(M, (w->N + 15) / 16, w->K, device_cu_count(), 1, aligned16(Y) && (ldy & 7) == 0, &plan);
     if (M <= kSkinnyMaxM && w->K % 64 == 0 && !whole_outputs) {
         SkinnyArgs a = {};
         a.table = nullptr;
@@ -766,7 +767,7 @@ sqap_status sqap_group_create(const sqap_linear_desc *descs, int32_t count, sqap
 // problems with one input as one product over all their channels, every workgroup with complete outputs
 static bool group_has_whole_outputs(const Group *g, int compute_units, WholePlan *plan)
 {
-    return g->rows_count > 0 && rows_kernel_wanted() && whole_output_plan(g->rows_M, g->rows_groups, g->rows_K, compute_units, g->rows_count, plan);
+    return g->rows_count > 0 && rows_kernel_wanted() && whole_output_plan(g->rows_M, g->rows_groups, g->rows_K, compute_units, g->rows_count, true, plan);
 }
 
 sqap_status sqap_group_run(const sqap_group *g, void *stream)

@@ -202,7 +202,9 @@ struct WholePlan {
     int tblocks, rows_per_block, per_xcd;                          // token blocks, rows of each, workgroups per XCD and block
     int token_groups, channel_groups, k_shares;                    // of a workgroup (16 rows), of a wavefront (16 channels); shares of K
 };
-bool whole_output_plan(int M, int channel_groups, int K, int compute_units, int weights, WholePlan *plan);
+// (y_vectors: output rows begin at multiples of 16 bytes)
+bool whole_output_plan(int M, int channel_groups, int K, int compute_units, int weights, bool y_vectors, WholePlan *plan);
+double tile_kernels_us(int M, int channel_groups, int K, bool y_vectors);        // what the other kernels would take (gemm.hip)
 sqap_status launch_whole_outputs(const WholePlan &plan, const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
                                  unsigned long long *error_word, hipStream_t st);
 bool few_kernel_applies(int M, int channel_groups, int K, int compute_units);

@@ -1448,6 +1448,42 @@ sqap_status plan_linear_shares(int M, int N, int K, int blocks_per_xcd, uint32_t
     return SQAP_OK;
 }
 
+// Microseconds that launch_w4a4_linear takes without whole outputs per workgroup, for the rule that chooses between the two; huge where
+// few tiles are finished jointly (never the faster way).  In closed form what the planner above finds (a plan takes up to five
+// milliseconds of host time): n workgroups per tile, none in two tiles; or all of them, with pieces of two tiles each.  The time of
+// a step and what is outside of the model are fitted to 3200 shapes: nine in ten within 12 %.
+double tile_kernels_us(int M, int channel_groups, int K, bool y_vectors)
+{
+    const bool persistent = K % kBK == 0 && persistent_allowed();
+    const bool big = persistent ? M >= kStreamKMinM : M > CfgMid::BM;
+    const bool mid = !big && (persistent ? narrow_tile_is_mid(M) : M > CfgLow::BM);
+    const int BM = big ? CfgBig::BM : mid ? CfgMid::BM : CfgLow::BM, BN = big ? CfgBig::BN : CfgMid::BN;
+    const int m_tiles = (M + BM - 1) / BM, blocks = persistent_blocks(), nb = blocks / kXcds;
+    const int64_t all = (int64_t)m_tiles * ((channel_groups * 16 + BN - 1) / BN);
+    if (persistent && !big && all * 4 <= kMaxPersistentBlocks) return 1e30;
+    const SplitModel &m = big ? kBigTileModel : kNarrowTileModel;
+    const double steps = (double)K / kBK;
+    const int tiles = (int)((all + kXcds - 1) / kXcds);                        // of an XCD
+    const double one = m.ramp + steps + m.epi;
+    const int rounds = (tiles + nb - 1) / nb;
+    double t = rounds * one;
+    if (!persistent) {
+        // one tile per workgroup, its reduction axis guarded; of the narrow tiles two find room on a compute unit
+        t = big ? 0.93 * t : (1.0 + 0.65 * (rounds - 1)) * one;
+    } else {
+        double share = (double)tiles / nb;                                     // whole tiles' worth of a workgroup
+        if (big) share *= (m_tiles - 1 + kRaggedStep[((M - (m_tiles - 1) * BM + 31) / 32 + 1) / 2 - 1]) / m_tiles;
+        for (int n = 2; n <= nb / tiles; ++n)
+            t = std::min(t, m.ramp + (steps - m.publish) / n + m.publish + m.reduce_fixed + (n - 1) * m.reduce_each + m.epi);
+        const double pieces = steps * share + 2 * m.ramp + m.publish + m.reduce_fixed + ceil(1.0 / share) * m.reduce_each + m.epi +
+                              std::max(0.0, share - 1.0) * (m.ramp + m.epi);
+        t = std::min(t, pieces);
+    }
+    t = big ? 1.1 + 1.43 * t : mid ? 1.1 + 0.67 * t : 0.8 + 0.45 * t;
+    t = std::max(t, 2.0 + channel_groups * 8.0 * K / 3.2e6);                   // weights from memory, with little else to do
+    return t + (y_vectors ? 0.0 : big ? 3.2 : 0.5);                            // (rows at any address: stores that share a line)
+}
+
 sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const Weight &w,
                                __half *Y, int64_t ldy, int32_t *acc_out, void *workspace, const WholePlan *whole_outputs,
                                hipStream_t st)

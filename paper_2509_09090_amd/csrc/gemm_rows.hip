@@ -25,8 +25,9 @@
 // Measured, us, the kernel before (160 rows, quarters of K x halves of the tokens, tokens through registers, three groups) in brackets:
 // 32 x 512 x 512 2.7 (3.1); 84 x 4096 x 4096 6.2 (7.4), 84 x 12288 x 4096 10.4 (12.5), 84 x K = 11008 11.0 (13.3); 148 x 4096 x 4096 8.0
 // (9.8), 148 x 12288 x 4096 13.3 (16.8), 148 x K = 11008 14.5 (16.6); 276 x 4096 x 4096 10.2 (12.5); 300 x 1000 x 1984 4.6 (5.9);
-// 2000 x 700 x 5504 15.7 (18.2).  Against the tiles: 84 x 22016 x 4096 15.9 (21.8), 134 x 13897 x 4096 20.4 (26.8), 451 x 8123 x 4160 35.0
-// (62.1), 679 x 4020 x 2816 19.3 (37.3).
+// 2000 x 700 x 5504 15.7 (18.2).  Against the tiles: 84 x 22016 x 4096 15.6 (20.3), 134 x 13896 x 4096 16.6 (21.7), 148 x 22016 x 4096 23.1
+// (27.6), 276 x 12288 x 4096 22.5 (24.2), 451 x 8123 x 4160 29.6 (52.7), 679 x 4020 x 2816 17.9 (28.8); where they are faster, at
+// whole_output_plan.
 #include <algorithm>
 
 #include "common.h"
@@ -347,16 +348,16 @@ __global__ __launch_bounds__(kRowsThreads, 1) void gemm_rows_kernel(const RowsPa
     }
 }
 
-// Token blocks, channel groups per workgroup and the shares of K: the plan with the lowest cost, in clock cycles.  A step's products
-// and widenings (of which three in ten hide behind products) against the bytes a compute unit loads at 40 per cycle; the start;
-// the reduction; all that once per tile.  Of 29 shapes timed with every possible number of token blocks (20 to 2368 rows, 700 to 22016
-// channels, K of 2048 to 11008) it names the fastest or one within 3 % of it.
-// A second and third tile pay the start again, but even so the tiles of the other kernels lose (148 x 22016 x 4096 24.0 us against 27.8,
-// 276 x 12288 x 4096 23.2 and 24.6, 471 x 5986 x 2048 18.1 and 23.6), except three tiles of a long K (688 x 7772 x 11008 83.2 and 81.3).
-static bool rows_plan(int M, int c16, int K, int cus, WholePlan *plan)
+// Token blocks, channel groups per workgroup and the shares of K: the plan with the lowest cost.  A step's products and widenings
+// against the bytes a compute unit loads, or against what its XCD does (every XCD reads all token rows and an eighth of the weights;
+// workgroups that share token rows are at different places of K, so rows that its L2 of 4 MB does not hold come once for each); the start
+// and the reduction, once per tile.  All numbers are clock cycles but for the microseconds at the end, and fitted to every plan of 2028
+// drawn shapes (17 to 3072 rows, 64 to 45000 channels, K of 384 to 14000, 7432 timings: half of them within 4 %).  The plan named is
+// the fastest or within 3 % of it in 97 of 100 shapes, at worst 10 % off; without the masked steps of a K that ends inside one and without
+// the L2, 22 shapes were 10 to 35 % off (148 x 4096 x 4800 9.0 us against 8.5, 1500 x 768 x 8192 19.8 and 14.9).
+static bool rows_plan(int M, int c16, int K, int cus, WholePlan *plan, int *tiles_out, double *us_out)
 {
     if (K % 32 != 0 || c16 < 1) return false;
-    const int blocks8 = (K / 32 + 31) / 32 * 8, blocks4 = (K / 32 + 15) / 16 * 4;      // of 128 codes, in whole steps of eight and of four shares
     const int max_tiles = K < 1024 && K % 512 != 0 ? 1 : K > 8192 ? kRowsMaxTiles - 1 : kRowsMaxTiles;
     const int tb_min = (M + 16 * kRowsMaxTG - 1) / (16 * kRowsMaxTG), tb_max = std::min(cus / 8, 2 * tb_min + 2);
     double best = 0.0;
@@ -367,16 +368,23 @@ static bool rows_plan(int M, int c16, int K, int cus, WholePlan *plan)
         if (tiles > max_tiles) continue;
         const int n = (n_all + tiles - 1) / tiles;
         for (int ks = n <= kRowsMaxCB ? 8 : 4; ks >= (n < kRowsMaxCB ? 8 : 4); ks -= 4) {
-            const int cb = ks == 8 ? n : (n + 1) / 2, halves = kRowsWaves / ks, blocks = ks == 8 ? blocks8 : blocks4;
-            const double issue = blocks * (17.0 * 2 * tg * cb * halves + 0.7 * 4 * 12 * (tg + cb) * halves) / 4;
-            const double bytes = (rows + 16.0 * n) * 64 * blocks;
-            const double cost = tiles * (std::max(bytes / 40.0, issue) + 3500 + 144.0 * tg * cb);
-            if (best == 0.0 || cost < best) {
-                best = cost;
+            const bool eighths = ks == 8;
+            const int cb = eighths ? n : (n + 1) / 2, halves = kRowsWaves / ks, step = rows_step_chunks(ks);
+            const int steps = (K / 32 + step - 1) / step, blocks = steps * ks;         // of 128 codes
+            const bool masked = K / 32 % step != 0;
+            double issue = blocks * halves * (2.0 * tg * cb + 22.0 * (tg + cb));
+            if (masked) issue += blocks * halves * cb * (eighths ? 17.0 : 6.5);
+            const double bytes = (rows + 16.0 * n) * 64 * blocks / (eighths ? 38.0 : 31.0);
+            const double x = 0.5 * M * K, w = (double)c16 * K / tiles, xcd = (x * (x + w > 4e6 ? per_xcd : 1) + w) / 650;
+            const double us = 2.05 + tiles * (std::max(std::max(bytes, xcd), issue) + 1450 + 258.0 * tg * cb) * 0.00055;
+            if (best == 0.0 || us < best) {
+                best = us;
                 *plan = {false, tb, rows, per_xcd, tg, cb, ks};
+                *tiles_out = tiles;
             }
         }
     }
+    *us_out = best;
     return best > 0.0;
 }
 
@@ -385,13 +393,23 @@ static int rows_cus(int cus) { return cus > 256 ? 256 : cus < 8 ? 8 : cus; }
 // Which of the two kernels with whole outputs per workgroup a shape takes, if any.  (Several weights with one input: few rows only.)
 // At 9 to 16 rows both would do: gemm_few.hip's where a workgroup has few channels (4096 x 4096 4.0 us, 4.2 here, 1024 x 2816 3.3 and
 // 3.5), this one's shorter start from three groups on (12288 x 4096 6.8 here, 7.4 there) and with a long K (11008: 6.9 to 7.1, 7.3 to 8.0).
-bool whole_output_plan(int M, int channel_groups, int K, int compute_units, int weights, WholePlan *plan)
+// One tile per workgroup beats the other kernels' tiles wherever it fits (of 4773 drawn shapes 6 are slower by more than 3 %, none by
+// more than 6 %).  A second and third tile pay start and reduction again, so there the two kernels' times are compared.  Taken always, they were
+// up to 44 % slower than the other kernels (us, those in brackets: 313 x 14832 x 1024 16.1 (12.1), 1500 x 4608 x 512 15.4 (11.8), 148 x
+// 30920 x 1792 23.1 (17.0), 154 x 28768 x 4992 39.9 (33.3), 3072 x 2304 x 8192 64.1 (62.0)) and never, up to 40 % (1024 x 2304 x 1024 9.8
+// (15.5), 700 x 4608 x 2048 15.6 (25.3), 148 x 24576 x 8192 38.7 (45.5), 2048 x 1536 x 512 8.4 (10.7)).  Of 2000 drawn shapes with two or three
+// tiles the comparison takes the faster kernel or one within 5 % of it in 97 of 100, at worst 17 % off.
+bool whole_output_plan(int M, int channel_groups, int K, int compute_units, int weights, bool y_vectors, WholePlan *plan)
 {
     if (M <= kSkinnyMaxM && K % 64 == 0 && K > 32768) return false;         // the streaming kernel's, which says what it refuses
     const int cus = rows_cus(compute_units);
     const bool few = few_kernel_applies(M, channel_groups, K, cus);
     const bool rather_rows = M > kSkinnyMaxM && (K > 8192 || channel_groups > 2 * cus);
-    if ((!few || rather_rows) && weights == 1 && rows_plan(M, channel_groups, K, cus, plan)) return true;
+    int tiles;
+    double us;
+    if ((!few || rather_rows) && weights == 1 && rows_plan(M, channel_groups, K, cus, plan, &tiles, &us) &&
+        (tiles == 1 || M <= 16 || us <= tile_kernels_us(M, channel_groups, K, y_vectors)))
+        return true;
     plan->few = few;
     return few;
 }
