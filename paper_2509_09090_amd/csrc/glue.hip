@@ -705,7 +705,14 @@ sqap_status launch_decode_attention(const __half *QKV, const int32_t *pos, int H
             hipLaunchKernelGGL(kernel, dim3(H, shares), dim3(kDecLongT), lds, st, QKV, pos, H, d, base, KV, ldkv, past, O, Xq, sx, counter,
                                rope_frequencies(d, base));
         };
-        if (d == kDecMaxD && 2 * H <= device_cu_count()) launch(decode_attention_long_kernel<2>, 2);
+        // (Where the output or the cache row lies over the token's own q|k|v: one workgroup reads all of a head's columns before it
+        // writes any, of two one may still have to.)
+        const auto begin = [](const __half *p) { return reinterpret_cast<uintptr_t>(p); };
+        const int64_t width = (int64_t)H * d;
+        const __half *row = KV + (int64_t)past * ldkv;
+        const bool in_place = (begin(O) < begin(QKV + 3 * width) && begin(QKV) < begin(O + width)) ||
+                              (begin(row) < begin(QKV + 3 * width) && begin(QKV) < begin(row + 2 * width));
+        if (d == kDecMaxD && 2 * H <= device_cu_count() && !in_place) launch(decode_attention_long_kernel<2>, 2);
         else launch(decode_attention_long_kernel<1>, 1);
     } else {
         hipLaunchKernelGGL(decode_attention_kernel, dim3(H), dim3(256), 0, st, QKV, pos, H, d, base, KV, ldkv, past, O, Xq,

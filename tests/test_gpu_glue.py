@@ -477,6 +477,26 @@ def test_decode_attention_in_one_launch(G, oracle, H, d, past, quantize):
         assert torch.equal(q2, Xq) and torch.equal(s2.view(torch.int16), sx.view(torch.int16))
 
 
+@pytest.mark.parametrize("past", [5, 383, 384, 600])
+def test_decode_attention_over_its_own_inputs(G, past):
+    """The fused q|k|v rows are the cache: the key is rotated where it lies and the output takes the query's place.  The same bits as
+    from separate buffers, whichever form the cache's length takes."""
+    import torch
+    from paper_2509_09090_amd import binding as B
+    H, d = 32, 128
+    width = H * d
+    rng = np.random.default_rng(past)
+    rows = G.to_dev(rng.standard_normal((past + 1, 3 * width)).astype(np.float16))
+    pos = G.to_dev(np.array([past], dtype=np.int32))
+    cache, O = rows[:, width:].clone(), torch.empty((1, width), dtype=torch.float16, device="cuda")
+    B.sqap_decode_attention(rows[past:].clone(), pos, H, d, cache, past, O)
+    for _ in range(20):
+        mine = rows.clone()
+        B.sqap_decode_attention(mine[past:], pos, H, d, mine[:, width:], past, mine[past:, :width])
+        assert torch.equal(mine[past:, :width].view(torch.int16), O.view(torch.int16))
+        assert torch.equal(mine[:, width:].view(torch.int16), cache.view(torch.int16))
+
+
 def test_decode_attention_replayed_from_a_graph(G, oracle):
     """The folded quantizer's arrival counter is put back to zero by the last workgroup, so a captured
     launch replays: new inputs per replay, an eager call on the same counter in between, each result
