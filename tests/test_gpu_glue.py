@@ -497,13 +497,13 @@ def test_decode_attention_over_its_own_inputs(G, past):
         assert torch.equal(mine[:, width:].view(torch.int16), cache.view(torch.int16))
 
 
-def test_decode_attention_replayed_from_a_graph(G, oracle):
+@pytest.mark.parametrize("H,d,past", [(8, 64, 37), (4, 96, 500), (32, 128, 600)])        # short and long caches, one and two workgroups per head
+def test_decode_attention_replayed_from_a_graph(G, oracle, H, d, past):
     """The folded quantizer's arrival counter is put back to zero by the last workgroup, so a captured
     launch replays: new inputs per replay, an eager call on the same counter in between, each result
-    against the oracle and the counter at zero afterwards."""
+    against the oracle, codes and scale against the quantizer of that result, and the counter at zero afterwards."""
     import torch
     from paper_2509_09090_amd import binding as B
-    H, d, past = 8, 64, 37
     width = H * d
     rng = np.random.default_rng(977)
     prefix = rng.standard_normal((past, 2 * width)).astype(np.float16)

@@ -547,9 +547,11 @@ def test_small_m_linear(G, oracle, M, N, K):
 
 
 # one block of K, fewer blocks than wavefronts, blocks that do not come out even, a last block of one chunk; 8 | 9 and 16 | 17 rows;
-# one and many 16-channel groups per workgroup, the last one of a single channel; more token loads than are staged at once
+# one and many 16-channel groups per workgroup, as many as it can have, the last one of a single channel; up to 2, 4, 8, 12 and more pieces per
+# wavefront; up to 4, 8, 12 and more token loads of it.  (16 rows of 11008 or 16416 codes and few channels are the other kernel's.)
 @pytest.mark.parametrize("M,N,K", [(1, 1, 32), (8, 17, 96), (9, 16, 128), (16, 4097, 160), (17, 4097, 160), (5, 12305, 416), (12, 530, 1056),
-                                   (16, 40, 11008), (16, 48, 16416), (7, 31, 32736), (13, 65537, 64)])
+                                   (16, 40, 11008), (16, 48, 16416), (7, 31, 32736), (13, 65537, 64), (16, 520, 8192), (16, 49200, 8256),
+                                   (8, 131072, 64), (8, 98304, 512)])
 def test_few_rows_linear_edges(G, oracle, M, N, K):
     rng = np.random.default_rng(M * 131 + N + K)
     Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
@@ -565,7 +567,7 @@ def test_few_rows_linear_edges(G, oracle, M, N, K):
 # quarters, an odd one out); two and three tiles per workgroup; several token blocks, the last one short; one, two, three and more steps,
 # whole and begun ones
 @pytest.mark.parametrize("M,N,K", [(17, 16, 32), (33, 4097, 1024), (48, 8200, 2048), (90, 12305, 160), (96, 16400, 1024), (65, 20481, 1536),
-                                   (40, 24593, 1536), (20, 49169, 544), (161, 700, 3072), (97, 33, 4128), (500, 1000, 2080), (2560, 300, 1056),
+                                   (40, 24593, 1536), (17, 57345, 512), (2048, 1537, 512), (33, 33000, 1056), (20, 49169, 544), (161, 700, 3072), (97, 33, 4128), (500, 1000, 2080), (2560, 300, 1056),
                                    (16, 13000, 512), (11, 64, 8224), (1, 16, 65568)])
 def test_whole_output_linear_edges(G, oracle, M, N, K):
     rng = np.random.default_rng(M * 17 + N + K)
@@ -631,7 +633,8 @@ def test_output_rows_at_any_even_address(G, oracle, M, N, K):
     W.free()
 
 
-@pytest.mark.parametrize("M,K,Ns", [(1, 64, (1, 1, 1, 1)), (8, 448, (33, 500, 16, 4100)), (4, 4096, (512, 512, 512)), (3, 2112, (9000, 24))])
+@pytest.mark.parametrize("M,K,Ns", [(1, 64, (1, 1, 1, 1)), (8, 448, (33, 500, 16, 4100)), (4, 4096, (512, 512, 512)), (3, 2112, (9000, 24)),
+                                    (2, 4096, (20000, 11999))])
 def test_group_with_one_input_runs_as_one_product(G, oracle, M, K, Ns):
     import torch
     from paper_2509_09090_amd import binding as B
@@ -764,8 +767,8 @@ def test_small_m_linear_while_another_thread_turns_the_switch(G, oracle):
 
 
 def test_group_info_describes_the_launch(G):
-    """Problems that share their input run as one product of workgroups of eight wavefronts, four along K; with that kernel off,
-    with another input, or with too many channels for the device, the weight-streaming kernel is described."""
+    """Problems that share their input run as one product of workgroups of eight wavefronts, here (four blocks of 128 codes) four along K;
+    with that kernel off, with another input, or with too many channels for the device, the weight-streaming kernel is described."""
     import torch
     from paper_2509_09090_amd import binding as B
     M, N, K = 4, 544, 512
@@ -777,8 +780,16 @@ def test_group_info_describes_the_launch(G):
     streaming = other.info(256)
     assert streaming[:2] == (2, 34) and streaming[2:] != (4, 8, 0)
     assert same.info(256) == (2, 34, 4, 8, 0)
-    few = same.info(8), other.info(8)                # 68 groups of 16 channels over 8 workgroups: nine each, within the limit of twelve
+    few = same.info(8), other.info(8)                # 68 groups of 16 channels over 8 workgroups: nine each, within the limit of 32
     assert few[0] == (2, 34, 4, 8, 0)
+    N2 = 2064                                        # 258 groups: one above 32 each on 8 workgroups, two each on 256
+    W2 = B.sqap_weight_pack(torch.zeros((N2, K // 2), dtype=torch.uint8, device="cuda"), torch.ones((N2,), dtype=torch.float16, device="cuda"))
+    Y2 = torch.zeros((2, M, N2), dtype=torch.float16, device="cuda")
+    many, apart = (B.sqap_group_create([(xq[0], sx, W2, Y2[0]), (xq[i], sx, W2, Y2[1])]) for i in (0, 1))
+    assert many.info(256) == (2, 130, 4, 8, 0) and many.info(8) == apart.info(8) and many.info(8)[3] != 0
+    many.free()
+    apart.free()
+    W2.free()
     B.sqap_set_mid_m_kernel(0)
     try:
         assert same.info(256) == streaming and same.info(8) == few[1]
