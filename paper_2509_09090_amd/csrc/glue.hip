@@ -436,7 +436,7 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(const __half *__r
 {
     __shared__ DecodeAttnLds lds;
     __shared__ int last_flag;
-    decode_attention_head<false>(lds, blockIdx.x, QKV, pos[0], H, d, base, KV, ldkv, past, O, nullptr, freq);
+    decode_attention_head<false>(lds, blockIdx.x, QKV, pos[0], H, d, base, KV, ldkv, past, O, nullptr, freq, nullptr, nullptr, 0, Xq != nullptr);
     if (!Xq) return;
 
     quantize_by_the_last<256>(lds.ored, lds.wred, &last_flag, O, H * d, H, Xq, sx, counter);
@@ -691,7 +691,7 @@ __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const 
 #pragma unroll
         for (int g = 0; g < 16; ++g) acc += ored[g * kDecMaxD + first + t];
     }
-    store_head_output(O + (int64_t)h * d + first, columns, acc * (1.0f / ((lw[0] + lw[1]) + (lw[2] + lw[3]))));
+    store_head_output(O + (int64_t)h * d + first, columns, acc * (1.0f / ((lw[0] + lw[1]) + (lw[2] + lw[3]))), Xq != nullptr);
     if (Xq) quantize_by_the_last<kDecLongT>(ored, wave_max, &last_flag, O, width, H * SHARES, Xq, sx, counter);
 }
 
