@@ -180,6 +180,7 @@ struct PreArgs {
     const __half *U;        // kPreSwiglu: up rows, pitch ldu
     int64_t ldu;
     __half *y_out;          // the half-precision result the quantizer sees, [M, K], nullable
+    bool exact;             // kPreSwiglu: silu in binary64 for every element (set by the launch)
 };
 sqap_status launch_fused_quantize(int pre_op, const __half *X, int64_t ldx, const int32_t *rows, int M, int K,
                                   bool rotate, const __half *col_scales, uint8_t *Xq, __half *sx,

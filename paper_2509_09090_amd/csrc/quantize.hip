@@ -253,6 +253,9 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta
 // (6.7-7.0), 1000 x 5504 9.2 (10.1).  (With a binary32 estimate good down to g = -8 or -32 only, wider gates took 53 us.)
 // (A per-device table of the 2^16 results was slower than computing: 13 against 10 us at 84 x 11008,
 // 48 scattered 4-byte loads per thread.)
+// Rows with at most one group of eight per thread, and few of them, wait for the longest chain of a thread, and with 64 times eight
+// values most wavefronts ask silu_of for one at least: there it works on all at once (pre.exact).
+constexpr int kShortRowT = 256;
 template <int T, int GPT>
 __device__ __forceinline__ void swiglu_row(float (&v)[GPT][8], const uint4 (&up)[GPT], int row, int K, const PreArgs &pre)
 {
@@ -263,7 +266,12 @@ __device__ __forceinline__ void swiglu_row(float (&v)[GPT][8], const uint4 (&up)
         if (g < groups) {
             float u[8];
             unpack8(up[gi], u);
-            swiglu8(v[gi], u);
+            if (GPT == 1 && T == kShortRowT && pre.exact) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[gi][e] = round_to_half(silu_of(v[gi][e]) * u[e]);
+            } else {
+                swiglu8(v[gi], u);
+            }
             if (pre.y_out) reinterpret_cast<uint4 *>(pre.y_out + (size_t)row * K)[g] = pack8(v[gi]);
         }
     }
@@ -618,9 +626,15 @@ sqap_status launch_fused_quantize(int pre_op, const __half *X, int64_t ldx, cons
             return launch_quantize_mode<kChannelwise, kPreNorm>(X, ldx, rows, M, K, rotate, col_scales, Xq, sx, pre, st);
         return launch_quantize_mode<kPerRow, kPreNorm>(X, ldx, rows, M, K, rotate, nullptr, Xq, sx, pre, st);
     }
+    // Estimate first or binary64 at once (us, the other in brackets): 256 x 1024 2.83 (3.04), 84 x 1408 2.97 (3.11), 1000 x 512 3.32 (3.47);
+    // from about 384 groups per compute unit on the arithmetic counts: 600 x 1408 4.20 with the estimate (4.28), 2368 x 1024 6.1 (6.4).  Up to
+    // 32 groups few wavefronts need silu_of: 84 x 56 2.72 with the estimate (2.82).
+    PreArgs swiglu = pre;
+    const int groups = K / 8;
+    swiglu.exact = groups > 32 && groups <= kShortRowT && (int64_t)M * groups <= 384 * (int64_t)device_cu_count();
     if (col_scales)
-        return launch_quantize_mode<kChannelwise, kPreSwiglu>(X, ldx, rows, M, K, rotate, col_scales, Xq, sx, pre, st);
-    return launch_quantize_mode<kPerRow, kPreSwiglu>(X, ldx, rows, M, K, rotate, nullptr, Xq, sx, pre, st);
+        return launch_quantize_mode<kChannelwise, kPreSwiglu>(X, ldx, rows, M, K, rotate, col_scales, Xq, sx, swiglu, st);
+    return launch_quantize_mode<kPerRow, kPreSwiglu>(X, ldx, rows, M, K, rotate, nullptr, Xq, sx, swiglu, st);
 }
 
 template <bool ROTATE>

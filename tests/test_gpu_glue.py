@@ -152,14 +152,14 @@ def test_silu_against_many_factors_and_at_the_infinities(G, oracle):
     assert [np.signbit(x) for x in o[3:7]] == [True, True, False, False] and o[3] == 0 and o[4] == 0
 
 
+@pytest.mark.parametrize("shape", [(256, 4096), (384, 2048), (385, 2048), (300, 264), (300, 256)])        # estimate first, binary64 at once: either side
 @pytest.mark.parametrize("spread", [None, 1.0, 30.0])
-def test_swiglu_of_any_pair(G, oracle, spread):
+def test_swiglu_of_any_pair(G, oracle, spread, shape):
     """Whichever way a product is found, estimate or binary64: the definition's half.  All bit patterns, infinities and NaN among them,
     and gates of an ordinary and of a wide spread."""
     import torch
     from paper_2509_09090_amd import binding as B
     rng = np.random.default_rng(11)
-    shape = (256, 4096)
     if spread is None:
         Gm, Um = (rng.integers(0, 65536, shape, dtype=np.uint16).view(np.float16) for _ in range(2))
     else:
