@@ -472,8 +472,7 @@ sqap_status sqap_weight_pack(const uint8_t *Wq, const sqap_f16 *sw, int32_t N, i
     w->data = nullptr;
     w->scales = nullptr;
     hipError_t e = hipGetDevice(&w->device);
-    // (gemm_few.hip reads K in blocks of four chunks: up to three past the end)
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&w->data), data_bytes + 3 * 512);
+    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&w->data), data_bytes + kWeightTailBytes);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&w->scales), scale_bytes);
     if (e != hipSuccess) {
         if (w->data) (void)hipFree(w->data);

@@ -30,7 +30,7 @@ namespace sqap {
 // 1024 x 2048 50.7 and 51.0; a second time through the keys doubles a workgroup's time).  Heads of 64 are held to the 128 registers that
 // four wavefronts per SIMD leave, which the second time through would pass (16 x 274 x 274, 32 heads 26.6, with 137 registers 28.0).
 // Measured (us; the kernel before, one key tile per wavefront and 2-byte transposing reads, in brackets; heads of 128):
-// 16 x 148 x 148, 32 heads 23.2 (62.8); 1024 x 2048, 32 heads 47.5 (126); 148 x 148, 32 heads 6.5 (8.2); 84 x 84 5.5 (6.2).
+// 16 x 148 x 148, 32 heads 23.2 (62.8); 1024 x 2048, 32 heads 46.6 (126); 148 x 148, 32 heads 6.5 (8.2); 84 x 84 5.5 (6.2).
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));

@@ -36,11 +36,13 @@ struct Weight {
     int32_t N, K;
     int32_t n_groups;   // ceil(N / 256) * 8
     int32_t chunks;     // K / 32
-    uint8_t *data;      // n_groups * chunks * 512 bytes
+    uint8_t *data;      // n_groups * chunks * 512 bytes, and kWeightTailBytes that may be read (times codes of zero)
     __half *scales;     // n_groups * 32 halves (zero padded)
     size_t bytes;
     int device;
 };
+// gemm_few.hip reads K in blocks of four chunks: up to three past the last row group's end.
+constexpr size_t kWeightTailBytes = 3 * 512;
 constexpr uint32_t kWeightMagic = 0x53514150u;  // "SQAP"
 
 // One problem of a small-M launch (see skinny.hip).  rg_begin is the index of the
@@ -80,7 +82,7 @@ constexpr int kRowsMaxWeights = 4;
 // Device-resident table of small-M problems, run by one launch.
 struct Group {
     uint32_t magic;
-    int rows_count;                        // problems, if they share one input and gemm_rows.hip may run them; 0 otherwise
+    int rows_count;                        // problems, if they share one input and can be one product (whole_output_plan); 0 otherwise
     const uint8_t *rows_Xq;
     const __half *rows_sx;
     int rows_M, rows_K, rows_groups;

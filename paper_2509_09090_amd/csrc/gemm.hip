@@ -1517,7 +1517,7 @@ sqap_status launch_w4a4_linear(const uint8_t *Xq, const __half *sx, int M, const
         // three partials to add, which measured faster than the joint finish (23.6 vs 28.6 us at
         // M = 148, N = 11008, K = 4096; the other way round, 21.6 vs 15.2 us, at N = 4096).
         // The joint finish is for devices with fewer than 256 compute units (a partition) and for sqap_set_mid_m_kernel(0): with all
-        // of them, every shape of so few tiles goes to the kernel with whole outputs above (4096 there: 8.0 us).
+        // of them, every shape of so few tiles goes to the kernel with whole outputs above (4096 there: 7.3 us).
         const bool mid = narrow_tile_is_mid(M);
         const int64_t tiles = (int64_t)((M + (mid ? CfgMid::BM : CfgLow::BM) - 1) / (mid ? CfgMid::BM : CfgLow::BM)) *
                               ((w.N + CfgMid::BN - 1) / CfgMid::BN);

@@ -265,7 +265,11 @@ static int few_k_log(int blocks) { return blocks >= 8 ? 3 : blocks >= 4 ? 2 : bl
 int few_k_shares(int K) { return 1 << few_k_log((K / 32 + 3) / 4); }
 
 // R: pieces in flight per wavefront; no more than it has, so that none is asked for twice, twelve where sixteen do not come out even
-// (22016 x 4096: 24 pieces).  Rows staged: 8 or 16, the lanes of a token that is not there read another's.
+// (22016 x 4096: 24 pieces).  The rule was made with weights that the caches held.  With weights from memory (copies of them in turn, 4 rows,
+// us, R as here / 2 / 4 / 8 / 12 / 16) four would do: 512 x 512 3.1 / 3.2 / 3.4 / 3.8 / 4.2 / 4.7, 4096 x 4096 4.3 / 4.0 / 4.3 / 4.6 / 5.0 / 5.3,
+// 12288 x 4096 7.6 / 6.8 / 6.5 / 6.9 / 7.5 / 7.9, 22016 x 4096 10.2 / 10.2 / 9.6 / 9.6 / 10.2 / 11.0, 32000 x 4096 13.4 / 12.7 / 12.1 / 12.5 / 13.2 /
+// 13.2, 4096 x 11008 7.6 / 7.8 / 6.7 / 7.0 / 7.6 / 8.2.
+// Rows staged: 8 or 16, the lanes of a token that is not there read another's.
 static bool few_plan(int M, int c16, int K, int cus, FewParams *p, int *pieces, int *lds)
 {
     if (K % 32 != 0 || c16 < 1 || M < 1 || M > kFewMaxRows) return false;

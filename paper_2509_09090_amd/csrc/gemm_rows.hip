@@ -23,9 +23,10 @@
 // Without any loads after the first two steps the launch is 4 % shorter.  K-steps twice as long for four to six groups: 84 x 22016 x
 // 4096 18.4 us against 15.9, because half of the weights had to arrive before the first product.
 // Measured, us, the kernel before (160 rows, quarters of K x halves of the tokens, tokens through registers, three groups) in brackets:
-// 32 x 512 x 512 2.7 (3.1); 84 x 4096 x 4096 6.2 (7.4), 84 x 12288 x 4096 10.4 (12.5), 84 x K = 11008 11.0 (13.3); 148 x 4096 x 4096 8.0
-// (9.8), 148 x 12288 x 4096 13.3 (16.8), 148 x K = 11008 14.5 (16.6); 276 x 4096 x 4096 10.2 (12.5); 300 x 1000 x 1984 4.6 (5.9);
-// 2000 x 700 x 5504 15.7 (18.2).  Against the tiles: 84 x 22016 x 4096 15.6 (20.3), 134 x 13896 x 4096 16.6 (21.7), 148 x 22016 x 4096 23.1
+// 32 x 512 x 512 3.0 (3.4); 84 x 4096 x 4096 6.0 (7.1), 84 x 12288 x 4096 9.6 (11.0), 84 x K = 11008 10.4 (12.0); 148 x 4096 x 4096 7.3
+// (9.0), 148 x 12288 x 4096 12.4 (14.2), 148 x K = 11008 13.7 (15.4); 276 x 4096 x 4096 9.9 (11.2); 300 x 1000 x 1984 4.8 (6.0);
+// 2000 x 700 x 5504 15.2 (19.1); but tall products of few channels whose K ends inside a step: 263 x 88 x 9728 7.5 (6.4), 433 x 104 x 5888
+// 6.0 (5.4).  Against the tiles: 84 x 22016 x 4096 15.6 (20.3), 134 x 13896 x 4096 16.6 (21.7), 148 x 22016 x 4096 23.1
 // (27.6), 276 x 12288 x 4096 22.5 (24.2), 451 x 8123 x 4160 29.6 (52.7), 679 x 4020 x 2816 17.9 (28.8); where they are faster, at
 // whole_output_plan.
 #include <algorithm>

@@ -451,11 +451,14 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(const __half *__r
 // SHARES: workgroups of a head.  Each works out all scores and takes a share of the value columns, so they need not meet; the first
 // one appends to the cache.
 // What bounds it: a compute unit takes in a cache line of 128 bytes every four cycles or so (65 GB/s, however many rows are on their way:
-// 16 or 24 per lane instead of 8 in the scores gave nothing), and a head's rows go through one unit: with two, keys and half of the values
-// (32 heads of 128, from 1500 to 3000 positions 7.4 ns per position, 8.2 with one).
+// 16 or 24 per lane instead of 8 in the scores gave nothing), and a head's rows go through one unit: 512 bytes per position, with two units
+// keys and half of the values, 384 each (replayed from a graph, from 1500 to 3000 positions: 5.8 ns per position with two, 66 GB/s
+// per unit; 7.5 in the form before, 68 GB/s; heads of 96, one unit and 384 bytes, 6.6, 58 GB/s).  Many heads are bound by memory: 130 heads
+// of 128 16.5 ns, 4 TB/s.
 // Measured with the quantizer folded in (32 heads of 128, us; one workgroup per head; the form before, which also summed key by key and
 // fenced a whole L2 before it arrived): 400 positions 9.5 (10.6; 13.9), 800 11.4 (13.1; 16.5), 1500 13.5 (16.5; 20.7), 3000 24.6 (28.8; 32.3);
-// 64, in the kernel above, 7.5 (8.7).  Without the quantizer the kernel above took 7.5 at 192 positions, 15.9 at 800: this one from two chunks on.
+// 64, in the kernel above, 7.5 (8.7).  As a launch of its own the quantizer takes as long or a little longer (64 positions 7.8 in all, folded in
+// 8.0; 400 9.9 and 10.0; 800 13.1 and 12.8; 3000 25.0 and 24.7; from a graph).  Without the quantizer the kernel above took 7.5 at 192 positions, 15.9 at 800: this one from two chunks on.
 // Two shares where a share of a value row still is whole lines and the heads leave the units for it.
 // Scores wait in LDS, 4 bytes per position: up to kDecLongMax of them (with the rest 52 KiB).
 constexpr int kDecLongMin = 2 * kDecChunk;

@@ -541,11 +541,11 @@ static sqap_status launch_quantize_inst(const __half *X, int64_t ldx, const int3
     return SQAP_OK;
 }
 
-// Threads per row.  With at most two rows per compute unit the longest rows take 1024 (84 x 11008, SwiGLU 6.1 us against 7.1
-// with 512 and 8.8 with 256; plain 3.4 against 3.7 and 5.0).  With more rows 256 are better although the kernel alone is not
-// (2368 x 11008, SwiGLU: 40.6 us, 38.9 with 512, 49.4 with 128): norm, gate|up, SwiGLU and down in a row take 295 us, 315 with
-// 512 and 300 with 128: the linears around it run faster.  Rows of 513 to 1024 groups keep 512 (norm to down at 1100 x 5504
-// 76.6 us, 77.2 with 256).
+// Threads per row.  With at most two rows per compute unit the longest rows take 1024 (84 x 11008, SwiGLU 6.3 us against 6.6
+// with 512 and 7.9 with 256; 512 rows 10.2, 10.7 and 12.1; plain 84 rows 3.4 against 3.7 and 5.0).  With more rows 256, although the SwiGLU
+// kernel alone is not faster (2368 x 11008: 32.7 us, 30.6 with 512, 32.1 with 1024, 38.1 with 128): norm, gate|up, SwiGLU and down in a row
+// take 306.4 us, 308.7 with 512, 307.0 with 1024 and 313.8 with 128.  (At 600 x 11008 the row of four takes 114.9, 113.8 with 512.)  Rows of 513
+// to 1024 groups keep 512 (norm to down at 1100 x 5504 68.6 us, 69.9 with 256 and 69.6 with 1024).
 // The norm's scalar part is repeated by every wavefront, so there fewer are better as soon as rows share compute units (us):
 // up to 512 groups (2368 x 4096 17.2 against 19.8 with 512 threads; 84 x 4096 4.5 against 4.1), above 1024 groups (257 x 8704
 // 6.2 against 9.4 with 1024, 512 x 11008 8.9 against 11.5; 200 x 11008 7.6 against 6.6), and between from two rows per compute unit on
