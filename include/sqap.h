@@ -471,7 +471,7 @@ sqap_status sqap_set_persistent_kernels(int32_t enabled);
 
 /*
  * Which kernel sqap_w4a4_linear uses where the outputs are few enough for every workgroup to own complete
- * ones (any K; M up to 2560 rows, fewer the more channels there are), for M <= 8 too, and for sqap_group_run of up to four
+ * ones (any K; M up to 3072 rows, fewer the more channels there are) and that is the faster way, for M <= 8 too, and for sqap_group_run of up to four
  * problems that share their input: 1, the default, the kernel that does so, in which nothing passes between
  * workgroups (it needs no workspace); 0 the tile kernels that split K between workgroups and exchange
  * partial sums through the workspace, or for M <= 8 the weight-streaming kernel (which other shapes always use).  Same results bit for bit; process

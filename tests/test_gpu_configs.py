@@ -237,9 +237,9 @@ def test_ratio_sweep_and_head_shapes(G, oracle, M, N, K):
         assert G.assert_fp16_close(Y, Yo) == 0, which
 
 
-# The kernel with whole outputs per workgroup at the edges of its range: token counts around the 16-row groups
-# and the 160-row blocks (one, two and four blocks), channel counts that are no multiple of 16 (guarded stores,
-# odd pitches), the shortest K with a whole step for every wavefront and a K with unequal shares for the four of them.
+# The kernels with whole outputs per workgroup at the edges of their range: token counts around the 16-row groups
+# and several blocks of them, channel counts that are no multiple of 16 (guarded stores,
+# odd pitches), the shortest K with a whole step for every wavefront and a K that ends inside a step.
 @pytest.mark.parametrize("M,N,K", [(9, 4096, 4096), (16, 512, 1024), (17, 1000, 2048), (33, 33, 1024), (160, 4096, 4096),
                                    (161, 4096, 4096), (320, 2064, 2048), (321, 4096, 1024), (511, 1536, 2304),
                                    (48, 16, 11008), (100, 12288, 1280), (148, 50, 4096), (640, 256, 1024)])
@@ -255,11 +255,11 @@ def test_whole_output_kernel_edge_shapes(G, oracle, M, N, K):
     assert G.assert_fp16_close(Y, Yo) == 0
 
 
-# K that ends inside a step of 256 codes or is shorter than the four wavefronts' shares (some get no step), up to sixteen
-# blocks of token rows, several tiles per workgroup; the shapes on both sides of every line of the rule.
+# K that ends inside a step (of 512 or 1024 codes) or is shorter than one, up to 32 blocks of token rows and one row more, several tiles
+# per workgroup.
 @pytest.mark.parametrize("M,N,K", [(9, 16, 32), (20, 100, 64), (33, 48, 96), (17, 256, 256), (32, 512, 512), (70, 77, 736), (148, 512, 1408),
                                    (161, 300, 1056), (100, 512, 5504), (300, 33, 4160), (641, 100, 1280), (1300, 64, 288), (2560, 16, 544),
-                                   (2561, 16, 256), (64, 12800, 1024), (65, 12800, 1024), (600, 3100, 1024), (512, 3100, 992), (170, 9000, 2080), (125, 12000, 288)])
+                                   (2561, 16, 256), (3072, 16, 256), (3073, 16, 256), (64, 12800, 1024), (65, 12800, 1024), (600, 3100, 1024), (512, 3100, 992), (170, 9000, 2080), (125, 12000, 288)])
 def test_whole_output_kernel_any_k(G, oracle, M, N, K):
     rng = np.random.default_rng(M + N * 3 + K)
     Xq, Wq = _random_packed(rng, M, K), _random_packed(rng, N, K)
@@ -273,10 +273,10 @@ def test_whole_output_kernel_any_k(G, oracle, M, N, K):
 
 
 @pytest.mark.parametrize("M,K,Ns", [(1, 64, (5,)), (3, 512, (16, 48)), (8, 1408, (1000, 33, 7)), (4, 4096, (512, 512, 512, 100)), (8, 4096, (24576, 24576)),
-                                    (2, 4096, (24576, 24577)), (7, 704, (50, 60, 70, 80, 90))])
+                                    (2, 4096, (24576, 24577)), (2, 64, (70000, 61104)), (7, 704, (50, 60, 70, 80, 90))])
 def test_groups_with_one_input(G, oracle, M, K, Ns):
-    """Groups whose problems share their input are one product over all their channels (up to four problems, up to twelve
-    channel groups per compute unit: the last two are past that), each with its own pitch and accumulators: against the oracle, and
+    """Groups whose problems share their input are one product over all their channels (up to four problems, up to 32 groups of
+    16 channels per compute unit: the last two are past that), each with its own pitch and accumulators: against the oracle, and
     against the weight-streaming kernel."""
     import torch
     from paper_2509_09090_amd import binding as B

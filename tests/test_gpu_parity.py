@@ -320,10 +320,11 @@ def _random_packed(rng, R, K):
                                    # ragged last tile row of the 256-row tiles: 2, 3, 5 and 7 of its 8 row groups hold tokens
                                    (576, 1280, 4096), (608, 512, 2048), (672, 768, 1024), (736, 512, 512),
                                    (2368, 512, 4096),
-                                   # too many channels for whole outputs per workgroup: the other kernels by default, ragged last tile
-                                   # row (3, 5, 7 row groups), narrow tiles of 96 and 160 rows, the same with a guarded K, weight streaming
+                                   # ragged last tile row (3, 5, 7 row groups), narrow tiles of 96 and 160 rows, the same with a guarded K, weight
+                                   # streaming; then shapes that the other kernels have by default too
                                    (608, 4160, 1024), (672, 4160, 1024), (736, 4160, 1024), (84, 12320, 256), (148, 12320, 256),
-                                   (84, 12320, 288), (148, 12320, 288), (300, 12320, 160), (8, 49184, 64)])
+                                   (84, 12320, 288), (148, 12320, 288), (300, 12320, 160), (8, 49184, 64),
+                                   (608, 9280, 1024), (736, 9280, 1024), (84, 24640, 256), (148, 36864, 288), (300, 24640, 160), (8, 131104, 64)])
 def test_linear_random_codes(G, oracle, M, N, K):
     """Uniform random codes (including -8) exercise every tile edge and the exact int32 sum, in the kernel with whole outputs
     per workgroup, where that is the default, and in the one that it stands in for."""
@@ -473,9 +474,10 @@ def test_attn_scores_batch(G, oracle):
 @pytest.mark.parametrize("which,M,N,K", [(0, 600, 768, 1024),     # 3 x 3 tiles of 256 x 256 over 256 workgroups: every tile is shared
                                          (0, 148, 1024, 2048),    # narrow tiles, finished together by their contributors
                                          (0, 84, 512, 11008),
-                                         (1, 600, 4352, 1024),    # stream-K tiles, narrow tiles by default: too many channels for
-                                         (1, 148, 12320, 1024),   # whole outputs per workgroup
-                                         (1, 148, 1024, 2048), (1, 4, 512, 1024)])      # whole outputs per workgroup
+                                         (1, 600, 9344, 1024),    # stream-K tiles, narrow tiles by default
+                                         (1, 148, 30920, 1024),
+                                         (1, 600, 4352, 1024), (1, 148, 12320, 1024),   # whole outputs per workgroup, two tiles
+                                         (1, 148, 1024, 2048), (1, 4, 512, 1024)])      # one tile, few rows
 def test_linear_replayed_from_a_graph(G, oracle, which, M, N, K):
     """A captured launch of the split (persistent) kernels carries the launch epoch it was captured with:
     every replay, with new operands and eager launches on the same workspace in between, must still
