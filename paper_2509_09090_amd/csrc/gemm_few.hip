@@ -264,11 +264,12 @@ static int few_k_log(int blocks) { return blocks >= 8 ? 3 : blocks >= 4 ? 2 : bl
 
 int few_k_shares(int K) { return 1 << few_k_log((K / 32 + 3) / 4); }
 
-// R: pieces in flight per wavefront; no more than it has, so that none is asked for twice, twelve where sixteen do not come out even
-// (22016 x 4096: 24 pieces).  The rule was made with weights that the caches held.  With weights from memory (copies of them in turn, 4 rows,
-// us, R as here / 2 / 4 / 8 / 12 / 16) four would do: 512 x 512 3.1 / 3.2 / 3.4 / 3.8 / 4.2 / 4.7, 4096 x 4096 4.3 / 4.0 / 4.3 / 4.6 / 5.0 / 5.3,
-// 12288 x 4096 7.6 / 6.8 / 6.5 / 6.9 / 7.5 / 7.9, 22016 x 4096 10.2 / 10.2 / 9.6 / 9.6 / 10.2 / 11.0, 32000 x 4096 13.4 / 12.7 / 12.1 / 12.5 / 13.2 /
-// 13.2, 4096 x 11008 7.6 / 7.8 / 6.7 / 7.0 / 7.6 / 8.2.
+// R: pieces in flight per wavefront, no more than it has, so that none is asked for twice: four.  A compute unit takes in 1 KiB per 15 ns, so the
+// 32 KiB of eight wavefronts with four pieces each are half a microsecond of arrivals, and every load in front of the first product is start-up.
+// Measured with up to sixteen in flight in brackets (4 rows, 8 of the last; us, replayed): weights in the caches 12288 x 4096 4.9 (5.1), 22016 x
+// 4096 9.3 (10.0), 4096 x 11008 4.9 (5.1), 32000 x 4096 12.1 (13.5); copies of them in turn, from memory 12288 x 4096 6.9 (7.8), 22016 x 4096 10.6
+// (10.9), 4096 x 11008 7.2 (7.9), 32000 x 4096 13.7 (14.4).  Two, three, five, six and eight: no shape more than 2 % faster than with four but
+// 4096 x 4096 and 4096 x 11008 from memory (two 4.1 against 4.3; six 6.9 against 7.2), others up to 15 % slower.
 // Rows staged: 8 or 16, the lanes of a token that is not there read another's.
 static bool few_plan(int M, int c16, int K, int cus, FewParams *p, int *pieces, int *lds)
 {
@@ -319,10 +320,7 @@ template <bool MULTI>
 static sqap_status launch_few_r(const FewParams &p, int pieces, int lds, hipStream_t st)
 {
     if (pieces <= 2) return launch_few_k<2, MULTI>(p, lds, st);
-    if (pieces <= 4) return launch_few_k<4, MULTI>(p, lds, st);
-    if (pieces <= 8) return launch_few_k<8, MULTI>(p, lds, st);
-    if (pieces <= 12 || (pieces % 12 == 0 && pieces % 16 != 0)) return launch_few_k<12, MULTI>(p, lds, st);
-    return launch_few_k<16, MULTI>(p, lds, st);
+    return launch_few_k<4, MULTI>(p, lds, st);
 }
 
 sqap_status launch_few_linear(const uint8_t *Xq, const __half *sx, int M, int K, const RowsWeight *weights, int count,
