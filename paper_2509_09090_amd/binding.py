@@ -1,9 +1,11 @@
-"""ctypes binding of libsqap.so: argument marshalling only.
+"""Binding of libsqap.so: argument marshalling only.
 
 Every function has the name of the C entry point it wraps (see include/sqap.h)
 and takes torch CUDA tensors, which are used purely as device memory; work is
 enqueued on torch's current stream unless `stream` is given.  Nothing here
 computes: there is no fallback when the library is missing (loading raises).
+The functions that are called once per layer or per token go through _calls.so
+(csrc/calls.cpp), the others through ctypes.
 """
 import ctypes
 import os
@@ -125,6 +127,25 @@ def _check(status):
         raise SqapError(status, lib().sqap_last_error().decode())
 
 
+class _NotLoaded:
+    """Stands for the native calls until the first of them: loads the library then."""
+
+    def __getattr__(self, name):
+        global _native
+        if not isinstance(_native, _NotLoaded):
+            return getattr(_native, name)
+        L = lib()
+        try:
+            from . import _calls
+        except ImportError as e:
+            raise ImportError("_calls.so is not built: run `python -m paper_2509_09090_amd.build`") from e
+        _native = _calls.Calls(lambda entry: ctypes.cast(getattr(L, entry), ctypes.c_void_p).value, _current_stream, _check)
+        return getattr(_native, name)
+
+
+_native = _NotLoaded()
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -140,6 +161,23 @@ def _stream(stream):
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
     return _raw_stream(torch.cuda.current_device())
+
+
+def _current_stream():
+    """The stream of a native call that names none.  With one device, once torch has initialised it (asking for the current device sees
+    to that, and refuses in a forked child), the native calls look in torch's table of current streams by themselves."""
+    handle = int(_stream(None))
+    if torch.cuda.is_initialized() and torch.cuda.device_count() == 1:
+        _native.one_device = True
+    return handle
+
+
+def _forked():
+    if not isinstance(_native, _NotLoaded):
+        _native.one_device = False
+
+
+os.register_at_fork(after_in_child=_forked)
 
 
 def sqap_init(stream=None):
@@ -184,9 +222,7 @@ def sqap_attn_scores(q, k, vis_begin, n_vis, scores_out, workspace=None, stream=
 
 def sqap_attn_scores_batch(q, k, vis_begin, n_vis, scores_out, workspace=None, stream=None):
     """q [batch,H,d] fp16, k [batch,S,H,d] fp16 -> scores_out [batch,n_vis] fp32."""
-    batch, S, H, d = k.shape
-    _check(lib().sqap_attn_scores_batch(_ptr(q), _ptr(k), batch, S, H, d, vis_begin, n_vis, _ptr(scores_out),
-                                        _ptr(workspace), _nbytes(workspace), _stream(stream)))
+    _native.attn_scores_batch(q, k, vis_begin, n_vis, scores_out, workspace, stream)
 
 
 def sqap_attn_scores_noalloc(q, k, vis_begin, n_vis, scores_out, stream=None):
@@ -198,31 +234,24 @@ def sqap_attn_scores_noalloc(q, k, vis_begin, n_vis, scores_out, stream=None):
 
 def sqap_prune_topk(scores, keep_k, idx_out, stream=None):
     """scores [batch, n] fp32 -> idx_out [batch, keep_k] int32 (ascending)."""
-    batch, n = scores.shape
-    _check(lib().sqap_prune_topk(_ptr(scores), batch, n, keep_k, _ptr(idx_out), _stream(stream)))
+    _native.prune_topk(scores, keep_k, idx_out, stream)
 
 
 def sqap_kept_rows(idx, seq_len, vis_begin, n_vis, rows_out, stream=None):
     """idx [batch, keep_k] int32 -> rows_out [batch * (seq_len - n_vis + keep_k)] int32."""
-    batch, keep_k = idx.shape
-    _check(lib().sqap_kept_rows(_ptr(idx), batch, keep_k, seq_len, vis_begin, n_vis, _ptr(rows_out),
-                                _stream(stream)))
+    _native.kept_rows(idx, seq_len, vis_begin, n_vis, rows_out, stream)
 
 
 def sqap_prune_rows(scores, keep_k, seq_len, vis_begin, idx_out, rows_out, stream=None):
     """Fused sqap_prune_topk + sqap_kept_rows."""
-    batch, n = scores.shape
-    _check(lib().sqap_prune_rows(_ptr(scores), batch, n, keep_k, seq_len, vis_begin, _ptr(idx_out),
-                                 _ptr(rows_out), _stream(stream)))
+    _native.prune_rows(scores, keep_k, seq_len, vis_begin, idx_out, rows_out, stream)
 
 
 def sqap_prune_select(scores, grid_w, grid_h, k_attn, keep_total, camera, ring_radius, idx_out, count_out=None,
                       stream=None):
     """K_attn + K_ring + K_fps: scores [batch, grid_w*grid_h] fp32, camera [batch, 26] fp64 or None,
     idx_out [batch, cap] int32 (ascending members, then -1), count_out [batch] int32 or None."""
-    batch = scores.shape[0]
-    _check(lib().sqap_prune_select(_ptr(scores), batch, grid_w, grid_h, k_attn, keep_total, _ptr(camera),
-                                   ring_radius, _ptr(idx_out), idx_out.shape[1], _ptr(count_out), _stream(stream)))
+    _native.prune_select(scores, grid_w, grid_h, k_attn, keep_total, camera, ring_radius, idx_out, count_out, stream)
 
 
 def sqap_gather_rows(X, rows, out, stream=None):
@@ -233,10 +262,7 @@ def sqap_gather_rows(X, rows, out, stream=None):
 
 def sqap_quantize_act(X, rows, Xq, sx, flags=0, stream=None):
     """X [S,K] fp16, rows int32 [M] or None -> Xq [M,K/2] u8, sx [M] fp16."""
-    K = X.shape[1]
-    M = X.shape[0] if rows is None else rows.numel()
-    _check(lib().sqap_quantize_act(_ptr(X), X.stride(0), _ptr(rows), M, K, flags, _ptr(Xq), _ptr(sx),
-                                   _stream(stream)))
+    _native.quantize_act(X, rows, Xq, sx, flags, stream)
 
 
 def sqap_quantize_weight(W, Wq, sw, flags=0, stream=None):
@@ -297,44 +323,34 @@ def sqap_weight_pack(Wq, sw, stream=None):
 def sqap_rmsnorm_quantize_act(X, rows, gamma, eps, Xq, sx, delta=None, flags=0, col_scales=None, xsum_out=None,
                               y_out=None, stream=None):
     """RMSNorm (after an optional residual update) fused into the activation quantizer."""
-    K = X.shape[1]
-    M = X.shape[0] if rows is None else rows.numel()
-    _check(lib().sqap_rmsnorm_quantize_act(_ptr(X), X.stride(0), _ptr(rows), M, K, _ptr(delta), _ptr(gamma), eps,
-                                           flags, _ptr(col_scales), _ptr(xsum_out), _ptr(y_out), _ptr(Xq),
-                                           _ptr(sx), _stream(stream)))
+    _native.rmsnorm_quantize_act(X, rows, gamma, eps, Xq, sx, delta, flags, col_scales, xsum_out, y_out, stream)
 
 
 def sqap_swiglu_quantize_act(G, U, Xq, sx, col_scales=None, h_out=None, stream=None):
     """h = silu(G) * U fused into the activation quantizer; G, U may be column slices of one tensor."""
-    M, F = G.shape
-    _check(lib().sqap_swiglu_quantize_act(_ptr(G), G.stride(0), _ptr(U), U.stride(0), M, F, _ptr(col_scales),
-                                          _ptr(h_out), _ptr(Xq), _ptr(sx), _stream(stream)))
+    _native.swiglu_quantize_act(G, U, Xq, sx, col_scales, h_out, stream)
 
 
 def sqap_rope(X, pos, H, d, base=10000.0, stream=None):
     """X [S, >= H*d] fp16 (row pitch = X.stride(0)), rotated in place at positions pos [S] int32."""
-    _check(lib().sqap_rope(_ptr(X), X.stride(0), _ptr(pos), X.shape[0], H, d, base, _stream(stream)))
+    _native.rope(X, pos, H, d, base, stream)
 
 
 def sqap_rope_append(QKV, pos, H, d, KV, base=10000.0, stream=None):
     """QKV [S, 3*H*d] fused rows: q rotated in place, rotated k | v written to the cache rows KV [S, 2*H*d]."""
-    _check(lib().sqap_rope_append(_ptr(QKV), QKV.stride(0), _ptr(pos), QKV.shape[0], H, d, base, _ptr(KV),
-                                  KV.stride(0), _stream(stream)))
+    _native.rope_append(QKV, pos, H, d, KV, base, stream)
 
 
 def sqap_attention(Q, K, V, H, d, O, batch=1, stream=None):
     """Causal attention; Q, O [batch*Sq, H*d], K, V [batch*Sk, H*d] (row pitches from the strides)."""
-    _check(lib().sqap_attention(_ptr(Q), Q.stride(0), _ptr(K), K.stride(0), _ptr(V), V.stride(0), batch,
-                                Q.shape[0] // batch, K.shape[0] // batch, H, d, _ptr(O), O.stride(0),
-                                _stream(stream)))
+    _native.attention(Q, K, V, H, d, O, batch, stream)
 
 
 def sqap_decode_attention(qkv, pos, H, d, KV, past, O, Xq=None, sx=None, counter=None, base=10000.0, stream=None):
     """One decode step's attention in one launch: qkv [3*H*d] (one token) rotated, key | value appended as
     row `past` of the cache KV [>= past+1, 2*H*d], attention over rows 0..past into O [H*d]; with Xq
     (and sx [1], counter: a zeroed uint32/int32 device word) O is also quantized as by sqap_quantize_act."""
-    _check(lib().sqap_decode_attention(_ptr(qkv), _ptr(pos), H, d, base, _ptr(KV), KV.stride(0), past, _ptr(O),
-                                       _ptr(Xq), _ptr(sx), _ptr(counter), _stream(stream)))
+    _native.decode_attention(qkv, pos, H, d, KV, past, O, Xq, sx, counter, base, stream)
 
 
 def sqap_residual_add(X, delta, stream=None):
@@ -375,10 +391,7 @@ def sqap_workspace_bytes(M, N, K):
 
 def sqap_w4a4_linear(Xq, sx, W, Y, acc_out=None, workspace=None, stream=None):
     """Xq [M,K/2] u8, sx [M] fp16, W: Weight -> Y [M,N] fp16 (+ acc_out [M,N] int32)."""
-    M = Xq.shape[0]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().sqap_w4a4_linear(_ptr(Xq), _ptr(sx), M, W.handle, _ptr(Y), Y.stride(0), _ptr(acc_out),
-                                  _ptr(workspace), ws_bytes, _stream(stream)))
+    _native.w4a4_linear(Xq, sx, W.handle, Y, acc_out, workspace, stream)
 
 
 class Group:
@@ -388,7 +401,7 @@ class Group:
         self.handle, self._keep = handle, keep
 
     def run(self, stream=None):
-        _check(lib().sqap_group_run(self.handle, _stream(stream)))
+        _native.group_run(self.handle, stream)
 
     def info(self, compute_units=0):
         """(problems, row groups, wavefronts per row group, wavefronts per workgroup, LDS output slots) of the launch."""
@@ -435,8 +448,7 @@ class Decoder:
 
     def step(self, x, pos, past, logits, attn_trace=None, stream=None):
         """x [hidden] fp16, pos [1] int32 (device), past: positions already in the caches, logits [vocab] fp16."""
-        _check(lib().sqap_decoder_step(self.handle, _ptr(x), _ptr(pos), past, _ptr(logits), _ptr(attn_trace),
-                                       _stream(stream)))
+        _native.decoder_step(self.handle, x, pos, past, logits, attn_trace, stream)
 
     def status(self, stream=None):
         """Error word of the last step (0: every wait between workgroups ended).  Synchronises the stream."""

@@ -1,11 +1,14 @@
-"""Builds libsqap.so (the gfx950 HIP library) in-tree with hipcc."""
+"""Builds libsqap.so (the gfx950 HIP library) and _calls.so (the binding's argument marshalling) in-tree."""
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libsqap.so")
+CALLS = os.path.join(HERE, "_calls.so")
+CALLS_SOURCE = os.path.join(HERE, "csrc", "calls.cpp")
 SOURCES = sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(HERE, "csrc", "*.h"))) + [os.path.join(ROOT, "include", "sqap.h")]
 
@@ -19,17 +22,31 @@ FLAGS = [
 ]
 
 
+def _older(built, sources):
+    return not os.path.exists(built) or any(os.path.getmtime(f) > os.path.getmtime(built) for f in sources)
+
+
 def is_stale():
-    if not os.path.exists(LIB):
-        return True
-    built = os.path.getmtime(LIB)
-    return any(os.path.getmtime(f) > built for f in SOURCES + HEADERS)
+    return _older(LIB, SOURCES + HEADERS) or _older(CALLS, [CALLS_SOURCE] + HEADERS)
+
+
+def _calls_command():
+    """Host code only: Python's and torch's headers, no kernels."""
+    import torch
+    at = os.path.dirname(torch.__file__)
+    include = [os.path.join(at, "include"), os.path.join(at, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include"]
+    return ([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+            + [f for i in include for f in ("-isystem", i)]
+            + ["-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), CALLS_SOURCE, "-o", CALLS,
+               "-L" + os.path.join(at, "lib"), "-lc10", "-lc10_hip", "-ltorch_python", "-ltorch_cpu"])
 
 
 def build(force=True, verbose=False):
     """Compile every kernel for gfx950.  Returns the library path."""
     if not force and not is_stale():
         return LIB
+    calls = subprocess.Popen(_calls_command())
     objs = []
     procs = []
     for src in SOURCES:
@@ -46,6 +63,8 @@ def build(force=True, verbose=False):
     subprocess.run(cmd, check=True)
     for o in objs:
         os.remove(o)
+    if calls.wait() != 0:
+        raise RuntimeError("the compiler failed on " + CALLS_SOURCE)
     return LIB
 
 
