@@ -179,6 +179,7 @@ struct PreArgs {
     __half *xsum_out;       // kPreNorm: x + delta [M, K], nullable
     const __half *gamma;    // kPreNorm: [K]
     float eps;              // kPreNorm
+    double inv_k;           // kPreNorm: 1 / K (set by the launch)
     const __half *U;        // kPreSwiglu: up rows, pitch ldu
     int64_t ldu;
     __half *y_out;          // the half-precision result the quantizer sees, [M, K], nullable
@@ -319,6 +320,27 @@ __device__ __forceinline__ void wave_sum128(unsigned long long &hi, unsigned lon
     }
     hi = h;
     lo = l;
+}
+
+// the wavefront's sum of a binary64 value, in every lane
+__device__ __forceinline__ double wave_sum(double v)
+{
+    auto step = [&](auto ctrl_c) {
+        constexpr int CTRL = decltype(ctrl_c)::value;
+        const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+        v += __longlong_as_double((long long)((unsigned long long)dpp_move<CTRL>((unsigned)b) |
+                                              ((unsigned long long)dpp_move<CTRL>((unsigned)(b >> 32)) << 32)));
+    };
+    step(std::integral_constant<int, kDppXor1>{});
+    step(std::integral_constant<int, kDppXor2>{});
+    step(std::integral_constant<int, kDppHalfMirror>{});
+    step(std::integral_constant<int, kDppMirror>{});
+    auto row = [&](int l) {
+        const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+        return __longlong_as_double((long long)((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l) |
+                                                ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l) << 32)));
+    };
+    return (row(0) + row(16)) + (row(32) + row(48));
 }
 
 // The sum of an integer over the four rows of 16 lanes (lanes l, l + 16, l + 32, l + 48), in every lane: the

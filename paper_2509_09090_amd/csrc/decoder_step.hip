@@ -104,7 +104,7 @@ struct StepArgs {
     int n_phases, blocks, n_layers;
     int hidden, ffn, H, d;
     float eps;
-    double base;
+    double inv_hidden, base;
     const __half *x_in;     // [hidden] the token's embedding
     const int32_t *pos;     // [1]
     int past;
@@ -124,6 +124,7 @@ struct StepLds {
     __attribute__((aligned(16))) uint8_t xs[kStepMaxK / 2];                       // the linear's input row as int4 codes
     __attribute__((aligned(16))) int partial[kStepMaxGroups][kStepWaves][16];      // per wavefront sums of a group's 16 channels
     __attribute__((aligned(16))) unsigned swl[2][kStepMaxGroups * 8];              // weight scales of the workgroup's channels (pairs), by phase parity
+    double sum[kStepWaves];
     unsigned long long wsum[2 * kStepWaves];
     float wmax[kStepWaves];
     float sx;
@@ -186,12 +187,11 @@ __device__ __forceinline__ void store_tagged_pair(unsigned *row, int n, float y0
 }
 
 // ---- the pieces of the fused quantizer kernels' arithmetic, statement by statement ----
-// RMSNorm:  x' = half(x + delta);  S = sum x'^2 as a 128-bit integer (add_squares8: the sum does not depend on
-// the order);  r = (float)(1 / sqrt(S / K + eps))
-// in binary64;  y = half((x' * r) * gamma).
+// RMSNorm:  x' = half(x + delta);  S = sum x'^2 exactly;  r = (float)(1 / sqrt(S / K + eps)) in binary64 (from a binary64 sum, and the
+// exact one where that leaves r open: norm_factor_of);  y = half((x' * r) * gamma).
 // Quantizer:  scale = half(max|y| / 7) (2^-24 when that is zero), code = clamp(rint(y / scale), -8, 7).
 
-// r from the eight wavefronts' sums (hi, lo pairs)
+// r from the eight wavefronts' exact sums (hi, lo pairs)
 __device__ __forceinline__ float norm_factor(const unsigned long long *wsum, int K, float eps)
 {
     unsigned long long hi = wsum[0], lo = wsum[1];
@@ -201,22 +201,7 @@ __device__ __forceinline__ float norm_factor(const unsigned long long *wsum, int
         lo += olo;
         hi += wsum[2 * w] + (lo < olo ? 1ull : 0ull);
     }
-    double Sd;
-    if (hi == 0) {
-        Sd = (double)lo;
-    } else {
-        const int lz = __clzll((long long)hi);
-        unsigned long long top = lz ? (hi << lz) | (lo >> (64 - lz)) : hi;
-        const unsigned long long rest = lz ? lo << lz : lo;
-        top |= rest != 0 ? 1ull : 0ull;
-        Sd = ldexp((double)top, 64 - lz);
-    }
-    Sd = ldexp(Sd, -48);
-    // (eps widened here: hoisted out of the loop over the phases the double would sit in registers, in practice in
-    // scratch memory, for the whole step)
-    float e = eps;
-    asm volatile("" : "+v"(e));
-    return (float)(1.0 / sqrt(mean_of(Sd, K) + (double)e));
+    return exact_norm_factor(hi, lo, K, eps);
 }
 
 // ---- a workgroup's share of a linear ----
@@ -527,7 +512,7 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
             lds_barrier();
             if (attempt == 0) STEP_STAMP(1);
             unsigned bad = 0;
-            unsigned long long hi = 0, lo = 0;
+            double sum = 0.0;
             float amax = 0.f;
 #pragma unroll
             for (int gi = 0; gi < kStepGpt; ++gi) {
@@ -550,7 +535,8 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
 #pragma unroll
                             for (int e = 0; e < 8; ++e) v[gi][e] = to_half_value(v[gi][e] + in[e]);
                         }
-                        add_squares8(v[gi], hi, lo);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) sum = fma((double)v[gi][e], (double)v[gi][e], sum);
                     } else {                           // the row is the linear's input
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
@@ -561,11 +547,8 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
                 }
             }
             if (P.gamma) {
-                wave_sum128(hi, lo);
-                if (lane == 0) {
-                    lds.wsum[2 * wave] = hi;
-                    lds.wsum[2 * wave + 1] = lo;
-                }
+                sum = wave_sum(sum);
+                if (lane == 0) lds.sum[wave] = sum;
             } else {
                 amax = wavefront_max(amax);
                 if (lane == 0) lds.wmax[wave] = amax;
@@ -581,7 +564,23 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
             if (glue) __builtin_amdgcn_s_sleep(8);
         }
         if (P.gamma) {
-            const float r = norm_factor(lds.wsum, K, a.eps);
+            double sum = lds.sum[0];
+#pragma unroll
+            for (int w = 1; w < kStepWaves; ++w) sum += lds.sum[w];
+            float r;
+            if (__builtin_expect(!norm_factor_of(sum, a.inv_hidden, a.eps, r), 0)) {      // (a row of this kind has `hidden` values)
+                unsigned long long hi = 0, lo = 0;
+#pragma unroll
+                for (int gi = 0; gi < kStepGpt; ++gi)
+                    if (t + gi * kStepThreads < groups) add_squares8(v[gi], hi, lo);
+                wave_sum128(hi, lo);
+                if (lane == 0) {
+                    lds.wsum[2 * wave] = hi;
+                    lds.wsum[2 * wave + 1] = lo;
+                }
+                lds_barrier();
+                r = norm_factor(lds.wsum, K, a.eps);
+            }
             float amax = 0.f;
 #pragma unroll
             for (int gi = 0; gi < kStepGpt; ++gi) {
@@ -619,10 +618,10 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
             for (int gi = 0; gi < kStepGpt; ++gi) {
                 const int g = t + gi * kStepThreads;
                 if (g < groups) {
-                    uint32_t packed = 0;
+                    float q[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) packed |= code4(quotient(v[gi][e], sf, rcp)) << (4 * e);
-                    reinterpret_cast<uint32_t *>(lds.xs)[g] = packed;
+                    for (int e = 0; e < 8; ++e) q[e] = quotient(v[gi][e], sf, rcp);
+                    reinterpret_cast<uint32_t *>(lds.xs)[g] = pack_codes8(q);
                 }
             }
         }
@@ -953,6 +952,7 @@ sqap_status decoder_step(Decoder *d, const sqap_f16 *x, const int32_t *pos, int 
     a.H = d->H;
     a.d = d->d;
     a.eps = d->eps;
+    a.inv_hidden = 1.0 / (double)d->hidden;
     a.base = d->base;
     a.x_in = reinterpret_cast<const __half *>(x);
     a.pos = pos;

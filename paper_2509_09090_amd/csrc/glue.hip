@@ -408,10 +408,9 @@ __device__ __forceinline__ void quantize_by_the_last(float *row_lds, float *wave
     for (int g = t; g < groups; g += T) {
         float f[8];
         unpack_halves(reinterpret_cast<const uint4 *>(row)[g], f);
-        uint32_t packed = 0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) packed |= code4(quotient(f[e], sf, rcp)) << (4 * e);
-        reinterpret_cast<uint32_t *>(Xq)[g] = packed;
+        for (int e = 0; e < 8; ++e) f[e] = quotient(f[e], sf, rcp);
+        reinterpret_cast<uint32_t *>(Xq)[g] = pack_codes8(f);
     }
 }
 

@@ -29,10 +29,21 @@ __device__ __forceinline__ float quotient(float v, float s, float r)
 // bounds are integers and rounding is monotone), and adding 1.5 * 2^23 rounds a value of that size to
 // the nearest integer, ties to even like rint, and leaves it in the low mantissa bits: one addition
 // instead of a rounding and a conversion.  A NaN quotient clamps to -8 either way.
-__device__ __forceinline__ uint32_t code4(float q)
+__device__ __forceinline__ uint32_t code_bits(float q)       // the code in two's complement, added to kCodeBias
 {
-    const float c = fminf(fmaxf(q, -8.f), 7.f);
-    return __float_as_uint(c + 12582912.0f) & 15u;
+    return __float_as_uint(__builtin_amdgcn_fmed3f(q, -8.f, 7.f) + 12582912.0f);
+}
+constexpr uint32_t kCodeBias = 0x4b400000u;                   // the bits of 1.5 * 2^23
+__device__ __forceinline__ uint32_t code4(float q) { return code_bits(q) & 15u; }
+
+// Eight codes in a word, the first in the low bits.  Shifted and added as they come, one instruction each, they and their biases make one
+// sum modulo 2^32; raised by 8 every code is a digit of 0 .. 15 and nothing carries, and the digit's top bit is the code's turned over.
+__device__ __forceinline__ uint32_t pack_codes8(const float (&q)[8])
+{
+    uint32_t sum = code_bits(q[7]);
+#pragma unroll
+    for (int e = 6; e >= 0; --e) sum = (sum << 4) + code_bits(q[e]);
+    return (sum + (0x88888888u - kCodeBias * 0x11111111u)) ^ 0x88888888u;
 }
 
 // scale = half(max|v| / 7), the smallest subnormal when that rounds to zero (an all-zero row)
@@ -44,55 +55,58 @@ __device__ __forceinline__ __half row_scale(float amax)
 }
 
 // Adds the squares of eight half values (held as floats), times 2^48, to the 128-bit integer hi:lo: exactly.
-// A half is an integer m < 2^11 times 2^e, e >= -24, so x^2 * 2^48 is an integer below 2^80.
-// Usual case: binary64.  With E the binary32 exponent field of an element (127 + e + 10 for a normal half; a
-// subnormal half has a smaller field and a coarser unit than that suggests), every square is a multiple of
-// 2^(2 (E_min - 137)) and the sum of eight is below 2^(2 E_max - 249): when the fields of the nonzero elements
-// differ by at most 14 every partial sum has at most 53 significant bits, the binary64 additions are exact, and
-// the sum's significand is shifted into place once.  Otherwise (a group that spans more than 2^14 in magnitude)
-// every square is shifted and added on its own.
+// A half is an integer m < 2^11 times 2^e, e >= -24, so x^2 * 2^48 is an integer below 2^80: m^2 shifted by 2 e + 48.
+// (Asked for by the rare row that norm_factor_of leaves open: few registers, no more, next to a row that is held in them.)
 __device__ __forceinline__ void add_squares8(const float (&v)[8], unsigned long long &hi, unsigned long long &lo)
 {
-    unsigned ex_max = 0u, ex_min = 255u;
-    double sum = 0.0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const unsigned ex = (__float_as_uint(v[e]) >> 23) & 255u;          // 0 for a zero only: halves are not that small
-        ex_max = max(ex_max, ex);
-        ex_min = ex != 0u ? min(ex_min, ex) : ex_min;
-        const double x = (double)v[e];
-        sum = fma(x, x, sum);
-    }
-    const bool narrow = ex_max <= ex_min + 14u;                            // (a group of zeros: 0 <= 269)
-    if (__builtin_expect(narrow, 1)) {
-        if (sum != 0.0) {
-            const unsigned long long bits = (unsigned long long)__double_as_longlong(sum);
-            const unsigned long long mant = (bits & 0xfffffffffffffull) | 0x10000000000000ull;
-            const int s = (int)(bits >> 52) - 1023 - 52 + 48;      // sum * 2^48 = mant * 2^s, an integer
-            unsigned long long add_lo, add_hi = 0ull;
-            if (s >= 0) {
-                add_lo = mant << s;                                // s <= 33 + 25 - 52 + 48 < 64
-                if (s > 11) add_hi = mant >> (64 - s);
-            } else {
-                add_lo = mant >> (-s);                             // the bits shifted out are zero
-            }
-            lo += add_lo;
-            hi += add_hi + (lo < add_lo ? 1ull : 0ull);
-        }
-        return;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const unsigned bits = __half_as_ushort(__float2half_rn(v[e]));      // exact: v is a half value
+        float x = v[e];
+        asm volatile("" : "+v"(x), "+v"(lo));              // (one element after the other)
+        const unsigned bits = __half_as_ushort(__float2half_rn(x));         // exact: v is a half value
         const unsigned exh = (bits >> 10) & 31u, man = bits & 1023u;
-        const unsigned long long m = exh ? man + 1024u : man;
-        const int sh = exh ? 2 * (int)exh - 2 : 0;                          // 2e + 48, at most 58
+        const unsigned m = exh ? man + 1024u : man;
+        const int sh = exh ? 2 * (int)exh - 2 : 0;                          // 2e + 48, at most 60
         const unsigned long long m2 = m * m;                                // below 2^22
         const unsigned long long add_lo = m2 << sh;
         const unsigned long long add_hi = sh > 42 ? m2 >> (64 - sh) : 0ull;
         lo += add_lo;
         hi += add_hi + (lo < add_lo ? 1ull : 0ull);
     }
+}
+
+// (float)(1 / sqrt(S / K + eps)) in binary64 of the exact sum: rounded to binary64 once (its top 64 bits with a sticky last bit, then the
+// hardware's conversion, which rounds to nearest even).
+__device__ __forceinline__ float exact_norm_factor(unsigned long long hi, unsigned long long lo, int K, float eps)
+{
+    double S;
+    if (hi == 0) {
+        S = (double)lo;
+    } else {
+        const int lz = __clzll((long long)hi);
+        unsigned long long top = lz ? (hi << lz) | (lo >> (64 - lz)) : hi;
+        const unsigned long long rest = lz ? lo << lz : lo;
+        top |= rest != 0 ? 1ull : 0ull;
+        S = ldexp((double)top, 64 - lz);
+    }
+    return (float)(1.0 / sqrt(ldexp(S, -48) / (double)K + (double)eps));
+}
+
+// r = (float)(1 / sqrt(S / K + eps)) of the RMSNorm from a sum of squares that is merely close: where everything within kNormReach of the
+// estimate rounds to one binary32 value, that value is r, and true is returned.  `sum`: the squares (exact in binary64) added in binary64
+// in any order.  With K <= 16384 and at least 256 threads a value goes through at most 64 + 7 + 16 additions, so the sum is off by
+// less than 87 * 2^-53 of itself, its half power by half of that; mean, eps, the step below and the definition's own roundings add
+// less than 12 * 2^-53: 55 * 2^-53 < 2^-47 in all.  The step is of third order: an error e of the hardware's estimate (tested: the squared
+// one below 2^-18) leaves 5/16 e^3 < 2^-55.  About one row in 2^18 is open, and one that is not finite or has no norm: the exact sum decides.
+constexpr double kNormReach = 0x1p-44;
+__device__ __forceinline__ bool norm_factor_of(double sum, double inv_k, float eps, float &r)
+{
+    const double a = fma(sum, inv_k, (double)eps);
+    double y = __builtin_amdgcn_rsq(a);
+    const double e = fma(-a * y, y, 1.0);
+    y = fma(y * e, fma(e, 0.375, 0.5), y);
+    r = (float)(y * (1.0 - kNormReach));
+    return r == (float)(y * (1.0 + kNormReach)) && fabs(e) < 0x1p-18;
 }
 
 // silu(g) = (float)(g / (1 + exp(-g))) as the definition evaluates it in binary64, for a half value g: the same binary32
@@ -163,14 +177,6 @@ __device__ __forceinline__ void swiglu8(float (&g)[8], const float (&u)[8])
         }
         g[e] = h[e];
     }
-}
-
-// S / K in binary64.  For a power of two the quotient is S with a smaller exponent (S is zero or at least 2^-48,
-// so nothing underflows): one instruction instead of the division's forty, the same bits.
-__device__ __forceinline__ double mean_of(double S, int K)
-{
-    if ((K & (K - 1)) == 0) return ldexp(S, -__builtin_ctz((unsigned)K));
-    return S / (double)K;
 }
 
 }  // namespace sqap

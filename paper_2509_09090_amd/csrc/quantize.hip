@@ -180,29 +180,17 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8])
 //   v = half((x' * r) * gamma)
 // The sum is exact and therefore independent of the order in which lanes add: a half is an
 // integer m < 2^11 times 2^e, e >= -24, so x^2 * 2^48 is an integer below 2^80; every thread
-// adds its elements into a 128-bit integer, wavefronts and the block add those.  The sum is
-// rounded to binary64 once (top 64 bits with a sticky last bit, then the hardware's u64 -> f64
-// conversion, which rounds to nearest even).  Rows are assumed finite.
+// adds its elements into a 128-bit integer, wavefronts and the block add those.  Rows are assumed finite.
+// That sum is asked for where it matters only: binary64 sums, two instructions per element, nearly always leave one binary32 value for r
+// (norm_factor_of), and the exact sum, six per element and a longer way through the wavefront, decides the rest.
 template <int T, int GPT>
-__device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta)[GPT], const uint4 (&gamma)[GPT], int row,
-                                         int K, const PreArgs &pre, unsigned long long *wsum)
+__device__ __forceinline__ float norm_factor_by_exact_sum(const float (&v)[GPT][8], int K, float eps, unsigned long long *wsum)
 {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, groups = K >> 3;
     unsigned long long hi = 0, lo = 0;
 #pragma unroll
-    for (int gi = 0; gi < GPT; ++gi) {
-        const int g = t + gi * T;
-        if (g < groups) {
-            if (pre.delta) {
-                float d[8];
-                unpack8(delta[gi], d);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[gi][e] = round_to_half(v[gi][e] + d[e]);
-            }
-            if (pre.xsum_out) reinterpret_cast<uint4 *>(pre.xsum_out + (size_t)row * K)[g] = pack8(v[gi]);
-            add_squares8(v[gi], hi, lo);
-        }
-    }
+    for (int gi = 0; gi < GPT; ++gi)
+        if (t + gi * T < groups) add_squares8(v[gi], hi, lo);
     wave_sum128(hi, lo);
     if (lane == 0) {
         wsum[2 * wave] = hi;
@@ -217,18 +205,44 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta
         lo += olo;
         hi += wsum[2 * w] + (lo < olo ? 1ull : 0ull);
     }
-    double Sd;
-    if (hi == 0) {
-        Sd = (double)lo;
-    } else {
-        const int lz = __clzll((long long)hi);
-        unsigned long long top = lz ? (hi << lz) | (lo >> (64 - lz)) : hi;
-        const unsigned long long rest = lz ? lo << lz : lo;
-        top |= rest != 0 ? 1ull : 0ull;
-        Sd = ldexp((double)top, 64 - lz);
+    return exact_norm_factor(hi, lo, K, eps);
+}
+
+template <int T>
+struct NormLds {
+    double sum[T / 64];
+    unsigned long long exact[T / 32];
+};
+
+template <int T, int GPT>
+__device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta)[GPT], const uint4 (&gamma)[GPT], int row,
+                                         int K, const PreArgs &pre, NormLds<T> &lds)
+{
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, groups = K >> 3;
+    double sum = 0.0;
+#pragma unroll
+    for (int gi = 0; gi < GPT; ++gi) {
+        const int g = t + gi * T;
+        if (g < groups) {
+            if (pre.delta) {
+                float d[8];
+                unpack8(delta[gi], d);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[gi][e] = round_to_half(v[gi][e] + d[e]);
+            }
+            if (pre.xsum_out) reinterpret_cast<uint4 *>(pre.xsum_out + (size_t)row * K)[g] = pack8(v[gi]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sum = fma((double)v[gi][e], (double)v[gi][e], sum);
+        }
     }
-    Sd = ldexp(Sd, -48);
-    const float r = (float)(1.0 / sqrt(mean_of(Sd, K) + (double)pre.eps));
+    sum = wave_sum(sum);
+    if (lane == 0) lds.sum[wave] = sum;
+    __syncthreads();
+    sum = lds.sum[0];
+#pragma unroll
+    for (int w = 1; w < T / 64; ++w) sum += lds.sum[w];
+    float r;
+    if (__builtin_expect(!norm_factor_of(sum, pre.inv_k, pre.eps, r), 0)) r = norm_factor_by_exact_sum<T, GPT>(v, K, pre.eps, lds.exact);
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
         const int g = t + gi * T;
@@ -306,7 +320,8 @@ __global__ __launch_bounds__(T, GPT == 6 ? 4 : T / 256) void quantize_rows_kerne
 {
     extern __shared__ __attribute__((aligned(16))) float rot[];       // the padded row when ROTATE
     __shared__ float wave_max[T / 64];
-    __shared__ unsigned long long wave_sum[T / 32];
+    __shared__ NormLds<T> norm_lds;
+    (void)norm_lds;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int row = blockIdx.x;
     const int64_t src = rows ? (int64_t)rows[row] : (int64_t)row;
@@ -323,7 +338,7 @@ __global__ __launch_bounds__(T, GPT == 6 ? 4 : T / 256) void quantize_rows_kerne
         load_raw<T, GPT>(reinterpret_cast<const uint4 *>(PRE == kPreSwiglu ? pre.U + (int64_t)row * pre.ldu : pre.delta + (int64_t)row * K), K, second);
     if (PRE == kPreNorm) load_raw<T, GPT>(reinterpret_cast<const uint4 *>(pre.gamma), K, third);
     load_halves<T, GPT>(xrow, K, v);
-    if (PRE == kPreNorm) norm_row<T, GPT>(v, second, third, row, K, pre, wave_sum);
+    if (PRE == kPreNorm) norm_row<T, GPT>(v, second, third, row, K, pre, norm_lds);
     if (PRE == kPreSwiglu) swiglu_row<T, GPT>(v, second, row, K, pre);
     if (ROTATE) rotate_row<T, GPT>(K, v, rot);
     if (!Xq) return;                     // the caller wanted the half-precision result only (uniform)
@@ -337,12 +352,10 @@ __global__ __launch_bounds__(T, GPT == 6 ? 4 : T / 256) void quantize_rows_kerne
             if (g < groups) {
                 float c[8];
                 load_col_scales(col_scales, g, c);
-                uint32_t packed = 0;
+                float q[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    packed |= code4(v[gi][e] / c[e]) << (4 * e);
-                }
-                qrow[g] = packed;
+                for (int e = 0; e < 8; ++e) q[e] = v[gi][e] / c[e];
+                qrow[g] = pack_codes8(q);
             }
         }
         return;
@@ -383,12 +396,10 @@ __global__ __launch_bounds__(T, GPT == 6 ? 4 : T / 256) void quantize_rows_kerne
     for (int gi = 0; gi < GPT; ++gi) {
         const int g = t + gi * T;
         if (g < groups) {
-            uint32_t packed = 0;
+            float q[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                packed |= code4(divide ? v[gi][e] / sf : quotient(v[gi][e], sf, rcp)) << (4 * e);
-            }
-            qrow[g] = packed;
+            for (int e = 0; e < 8; ++e) q[e] = divide ? v[gi][e] / sf : quotient(v[gi][e], sf, rcp);
+            qrow[g] = pack_codes8(q);
         }
     }
 }
@@ -451,12 +462,10 @@ __global__ __launch_bounds__(256) void quantize_row_pairs_kernel(const __half *_
         for (int gi = 0; gi < GPT; ++gi) {
             const int g = t + gi * 256;
             if (g < groups) {
-                uint32_t packed = 0;
+                float q[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    packed |= code4(quotient(v[gi][e], sf, rcp)) << (4 * e);
-                }
-                qrow[g] = packed;
+                for (int e = 0; e < 8; ++e) q[e] = quotient(v[gi][e], sf, rcp);
+                qrow[g] = pack_codes8(q);
             }
         }
     }
@@ -622,9 +631,11 @@ sqap_status launch_fused_quantize(int pre_op, const __half *X, int64_t ldx, cons
                                   const PreArgs &pre, hipStream_t st)
 {
     if (pre_op == kPreNorm) {
+        PreArgs norm = pre;
+        norm.inv_k = 1.0 / (double)K;
         if (col_scales)
-            return launch_quantize_mode<kChannelwise, kPreNorm>(X, ldx, rows, M, K, rotate, col_scales, Xq, sx, pre, st);
-        return launch_quantize_mode<kPerRow, kPreNorm>(X, ldx, rows, M, K, rotate, nullptr, Xq, sx, pre, st);
+            return launch_quantize_mode<kChannelwise, kPreNorm>(X, ldx, rows, M, K, rotate, col_scales, Xq, sx, norm, st);
+        return launch_quantize_mode<kPerRow, kPreNorm>(X, ldx, rows, M, K, rotate, nullptr, Xq, sx, norm, st);
     }
     // Estimate first or binary64 at once (us, the other in brackets): 256 x 1024 2.83 (3.04), 84 x 1408 2.97 (3.11), 1000 x 512 3.32 (3.47);
     // from about 384 groups per compute unit on the arithmetic counts: 600 x 1408 4.20 with the estimate (4.28), 2368 x 1024 6.1 (6.4).  Up to
