@@ -6,6 +6,7 @@
 // head sizes take binary32 FMAs over LDS tiles with an online softmax, here.
 #include <algorithm>
 
+#include <algorithm>
 #include "common.h"
 #include "quant_math.h"
 #include "decode_attn.h"
@@ -459,12 +460,38 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(const __half *__r
 // 64, in the kernel above, 7.5 (8.7).  As a launch of its own the quantizer takes as long or a little longer (64 positions 7.8 in all, folded in
 // 8.0; 400 9.9 and 10.0; 800 13.1 and 12.8; 3000 25.0 and 24.7; from a graph).  Without the quantizer the kernel above took 7.5 at 192 positions, 15.9 at 800: this one from two chunks on.
 // Two shares where a share of a value row still is whole lines and the heads leave the units for it.
+// What a unit has on its way is limited too (64 KB or so), so that from memory its rate is that over a microsecond's latency.  The units that
+// have no head are near the same memory: two more workgroups per head touch the lines ahead of the two that attend, which then find them
+// in their L2.  Replayed over twelve caches in turn (from memory; without helpers in brackets), us: 32 heads of 128, 800 positions 12.1
+// (12.4), 1500 14.6 (20.4), 3000 24.2 (33.2); 16 heads 1500 13.4 (15.5), 3000 21.8 (33.8); 4 heads 3000 19.1 (23.8); 32 heads of 64 1500 16.6
+// (16.8), 3000 26.1 (35.2).  400 positions 10.2 (9.9): the keys asked for at once are most of them.  One, three, four and six helpers: 0 to 20 % slower
+// at 32 heads (four 2 to 14 %), up to 7 % faster at 16 heads and 3000 positions.
 // Scores wait in LDS, 4 bytes per position: up to kDecLongMax of them (with the rest 52 KiB).
 constexpr int kDecLongMin = 2 * kDecChunk;
 constexpr int kDecLongT = 512, kDecLongMax = 42 * kDecChunk, kDecLongChunks = kDecLongMax / kDecChunk;
 constexpr int kDecLongKeys = 8;            // keys per lane that are summed together, and rows on their way
+constexpr int kDecLongFirst = kDecLongT / 16 * kDecLongKeys;       // keys that a workgroup asks for at once, before anything else
 typedef unsigned int sqap_v2u __attribute__((ext_vector_type(2)));
 constexpr int kDecLongAhead = 2;           // chunks whose value rows are on their way during the output
+constexpr int kDecHelpMin = 3 * kDecChunk;  // cached positions from which on a head gets helpers
+
+// Touches the cache lines of head h that the workgroups attending behind the same L2 are about to read, in the order in which they read them:
+// one word of each, dropped.  `columns` of the values from `first_column` on.  This is helper `index` of `count` >= 1.
+__device__ __forceinline__ void warm_cache(const __half *KV, int64_t ldkv, int past, int h, int H, int d, int first_column, int columns, int index, int count)
+{
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const char *key = reinterpret_cast<const char *>(KV + (int64_t)h * d), *value = reinterpret_cast<const char *>(KV + (int64_t)(H + h) * d + first_column);
+    auto touch = [&](const char *base, int bytes, int first_row) {
+        const int lines = (bytes + 127) >> 7, n = past * lines;
+        for (int i = first_row * lines + (wave * count + index) * 64 + lane; i < n; i += count * kDecLongT) {
+            const int row = i / lines, line = i - row * lines;
+            const unsigned word = *reinterpret_cast<const unsigned *>(base + (int64_t)row * ldkv * 2 + min(line * 128, bytes - 4));
+            asm volatile("" ::"v"(word));
+        }
+    };
+    touch(key, d * 2, kDecLongFirst);
+    touch(value, columns * 2, 0);
+}
 
 template <int SHARES>
 __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const __half *__restrict__ QKV,
@@ -481,6 +508,12 @@ __global__ __launch_bounds__(kDecLongT) void decode_attention_long_kernel(const 
     __shared__ float cmax[kDecLongChunks], mrun[kDecLongChunks], resc[kDecLongChunks], psg[kDecLongChunks * 16], lw[4], wave_max[kDecLongT / 64];
     __shared__ int last_flag;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, h = blockIdx.x, share = SHARES == 1 ? 0 : blockIdx.y;
+    if ((int)blockIdx.y >= SHARES) {                     // (helpers: launch_decode_attention)
+        const int helpers = gridDim.y - SHARES, index = blockIdx.y - SHARES;
+        if (H % 8 == 0) warm_cache(KV, ldkv, past, h, H, d, 0, d, index, helpers);
+        else warm_cache(KV, ldkv, past, h, H, d, (index % SHARES) * (d / SHARES), d / SHARES, index / SHARES, (helpers - index % SHARES + SHARES - 1) / SHARES);
+        return;
+    }
     const int half_d = d >> 1, width = H * d, Sk = past + 1, n_chunks = (Sk + kDecChunk - 1) / kDecChunk;
     const __half *q = QKV + (int64_t)h * d, *k = q + width, *v = k + width;
     __half fresh[6] = {};
@@ -714,8 +747,14 @@ sqap_status launch_decode_attention(const __half *QKV, const int32_t *pos, int H
         const __half *row = KV + (int64_t)past * ldkv;
         const bool in_place = (begin(O) < begin(QKV + 3 * width) && begin(QKV) < begin(O + width)) ||
                               (begin(row) < begin(QKV + 3 * width) && begin(QKV) < begin(row + 2 * width));
-        if (d == kDecMaxD && 2 * H <= device_cu_count() && !in_place) launch(decode_attention_long_kernel<2>, 2);
-        else launch(decode_attention_long_kernel<1>, 1);
+        const int cus = device_cu_count(), shares = d == kDecMaxD && 2 * H <= cus && !in_place ? 2 : 1;
+        // Helpers behind the same L2 as the workgroups that attend (workgroup i of a launch runs on XCD i % 8; were it otherwise, they would
+        // only be of no use): two where all of a head's workgroups are behind one, two for each share otherwise.  Fewer positions are
+        // there as fast without.
+        const int wanted = H % 8 == 0 ? 2 : 2 * shares;
+        const int helpers = H * shares % 8 == 0 && past >= kDecHelpMin ? std::max(0, std::min(wanted, cus / H - shares)) : 0;
+        if (shares == 2) launch(decode_attention_long_kernel<2>, 2 + helpers);
+        else launch(decode_attention_long_kernel<1>, 1 + helpers);
     } else {
         hipLaunchKernelGGL(decode_attention_kernel, dim3(H), dim3(256), 0, st, QKV, pos, H, d, base, KV, ldkv, past, O, Xq,
                            sx, counter, rope_frequencies(d, base));
