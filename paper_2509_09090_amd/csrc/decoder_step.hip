@@ -48,8 +48,8 @@
 //   * Loads of a wavefront return in order, and a store counts as a load: a wavefront with weight loads in
 //     flight would see the rows it polls only after all those loads have landed.  So the eighth wavefront
 //     of the workgroup streams no weights: it polls the flags and reads the rows, the norm gains and the weight
-//     scales into LDS, where all eight work on them (and, in a workgroup with a head, pulls the head's cached
-//     keys and values into L2 ahead of the attention).  The weight stream is read with nontemporal loads, so
+//     scales into LDS, where all eight work on them (and pulls its share of a head's cached keys and values into
+//     the L2 that the workgroup with the head has, ahead of the attention).  The weight stream is read with nontemporal loads, so
 //     that it does not push those lines, the rows and the flags out of the L2 again.
 //   * Barriers inside the workgroup wait for the wavefront's LDS operations only (lds_barrier): __syncthreads()
 //     would also wait for every weight load in flight, several times per phase.  For the same reason LDS is
@@ -81,7 +81,10 @@ constexpr int kStepGpt = 3;                // groups of 8 row elements per threa
 constexpr int kStepMaxK = kStepThreads * 8 * kStepGpt;
 constexpr int kStepMaxHidden = 4096;       // the residual row in LDS; a tagged row and the gains side by side
 constexpr int kStepTagsPerLayer = 5;       // q|k|v, attention, o, h, down
-constexpr int kStepWarmKeys = 2048;         // cached keys whose rows a workgroup warms the L2 cache with before its attention
+constexpr int kStepWarmKeys = 2048;         // cached keys whose rows are pulled into the L2 cache before the attention
+// Words from one workgroup's progress flag to the next: 16 bytes apart.  Flags that share a line hold each other up (7B shape, 148 positions, us per
+// token: 2 bytes apart 1356, 4 bytes 1288, 8 bytes 1254, 16 bytes 1243), and every line more is one more to poll (32 bytes 1249, 128 bytes 1263).
+constexpr int kStepFlagPitch = 2, kStepFlagsAt = 16;      // (the first flag behind the generation, the error word and the count, in a line of its own)
 constexpr long long kStepPollLimit = 200000;      // polls, or repeated reads of a row, before a wait gives up (a few tenths of a second)
 
 enum StepKind { kStepQkv = 0, kStepO = 1, kStepGateUp = 2, kStepDown = 3, kStepHead = 4 };
@@ -313,7 +316,7 @@ __device__ __forceinline__ bool poll_flags(const unsigned long long *flags, int 
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int f = lane + 64 * k;
-            seen[k] = __hip_atomic_load(&flags[f < blocks ? f : blocks - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            seen[k] = __hip_atomic_load(&flags[(f < blocks ? f : blocks - 1) * kStepFlagPitch], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         const int here = (int)(seen[0] >= value) & (int)(seen[1] >= value) & (int)(seen[2] >= value) & (int)(seen[3] >= value);
         if (__all(here)) return true;
@@ -630,19 +633,24 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
         lds_barrier();
         STEP_STAMP(2);
         if (glue) {
-            // A workgroup with a head: the cached keys and values it is about to attend over are known since the
-            // step began.  One word of every 128-byte line of them is asked for now (and dropped), so that the
-            // attention's own loads, which sit in the step's dependency chain, find the lines in the L2 cache.
-            if (P.kind == kStepQkv && block < a.H) {
-                const int lines_per_row = (a.d * 2 + 127) >> 7;                   // of the head's part of a key or value row
-                const int n_lines = min(a.past, kStepWarmKeys) * 2 * lines_per_row;
-                for (int i = lane; i < n_lines; i += 64) {
-                    const int key = i / (2 * lines_per_row), part = i - key * 2 * lines_per_row;
-                    const int kv = part / lines_per_row, line = part - kv * lines_per_row;
-                    const __half *at = P.kv + (size_t)key * P.ldkv + (size_t)kv * a.hidden + (size_t)block * a.d + line * 64;
-                    // (into a corner of LDS that nothing reads: a load into LDS holds no register, so nothing
-                    // has to be kept free until it returns)
-                    fetch_piece<false>(at, lds.stage + kStepStageWarm);
+            // The cached keys and values that the layer's attention is about to read are known since the step began.  One word of every
+            // 128-byte line of a head's is asked for now (and dropped) by the workgroups behind the same L2 as the workgroup that
+            // attends (workgroup i runs on XCD i % 8), so that the attention's own loads, which sit in the step's dependency chain, find
+            // the lines there.
+            if (P.kind == kStepQkv) {
+                const int xcd = block & 7, heads = (a.H - xcd + 7) >> 3, rank = block >> 3;      // of this XCD: heads, and this workgroup's number
+                if (heads > 0) {
+                    const int head = xcd + 8 * (rank % heads), helper = rank / heads, helpers = (kStepBlocks / 8 - rank % heads + heads - 1) / heads;
+                    const int lines_per_row = (a.d * 2 + 127) >> 7;               // of the head's part of a key or value row
+                    const int n_lines = min(a.past, kStepWarmKeys) * 2 * lines_per_row;
+                    for (int i = helper * 64 + lane; i < n_lines; i += helpers * 64) {
+                        const int key = i / (2 * lines_per_row), part = i - key * 2 * lines_per_row;
+                        const int kv = part / lines_per_row, line = part - kv * lines_per_row;
+                        const __half *at = P.kv + (size_t)key * P.ldkv + (size_t)kv * a.hidden + (size_t)head * a.d + line * 64;
+                        // (into a corner of LDS that nothing reads: a load into LDS holds no register, so nothing
+                        // has to be kept free until it returns)
+                        fetch_piece<false>(at, lds.stage + kStepStageWarm);
+                    }
                 }
             }
         } else {
@@ -757,7 +765,7 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
         const bool attends = P.kind == kStepQkv && block < a.H;
         if (P.kind != kStepHead && !attends && t == (n_out * 8 > 64 ? 64 : 0)) {
             const int at = kStepTagsPerLayer * P.layer + (P.kind == kStepQkv ? kTagAttn : P.kind == kStepO ? kTagO : gate_up ? kTagH : kTagDown);
-            __hip_atomic_store(&a.flags[block], gen0 + (unsigned long long)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&a.flags[block * kStepFlagPitch], gen0 + (unsigned long long)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         STEP_STAMP(4);
         if (attends) {
@@ -778,7 +786,7 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
                                         a.attn_trace ? a.attn_trace + (size_t)P.layer * a.hidden : nullptr, a.freq, lds.sincos_tab,
                                         lds.stage + kStepStageNew, tag_of(P.layer, kTagAttn));
             if (t == 64)
-                __hip_atomic_store(&a.flags[block], gen0 + (unsigned long long)(kStepTagsPerLayer * P.layer + kTagAttn), __ATOMIC_RELAXED,
+                __hip_atomic_store(&a.flags[block * kStepFlagPitch], gen0 + (unsigned long long)(kStepTagsPerLayer * P.layer + kTagAttn), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             lds_barrier();                           // its LDS is where the next row lands
             STEP_STAMP(6);
@@ -801,7 +809,7 @@ struct Decoder {
     double base;
     StepPhase *phases;          // device
     unsigned *rows;             // device, tagged words: qkv, attn, o, h, dn
-    unsigned long long *sync;   // device: generation, error word, count of finished workgroups, flags[256]
+    unsigned long long *sync;   // device: generation, error word, count of finished workgroups; flags
     size_t off_attn, off_o, off_h, off_dn, row_stride;
     long long poll_limit;
 };
@@ -919,7 +927,7 @@ sqap_status decoder_create(const sqap_decoder_layer *layers, int n_layers, int n
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&d->phases), sizeof(StepPhase) * ph.size());
     if (e == hipSuccess) e = hipMemcpy(d->phases, ph.data(), sizeof(StepPhase) * ph.size(), hipMemcpyHostToDevice);
     // rows start with tag 0 everywhere, the generation at 1: the first step waits for tags from 2 on
-    std::vector<unsigned long long> sync0(3 + kStepBlocks, 0ull);
+    std::vector<unsigned long long> sync0(kStepFlagsAt + kStepBlocks * kStepFlagPitch, 0ull);
     sync0[0] = 1ull;
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&d->rows), off * sizeof(unsigned));
     if (e == hipSuccess) e = hipMemset(d->rows, 0, off * sizeof(unsigned));
@@ -969,7 +977,7 @@ sqap_status decoder_step(Decoder *d, const sqap_f16 *x, const int32_t *pos, int 
     a.gen = d->sync;
     a.err = d->sync + 1;
     a.done = d->sync + 2;
-    a.flags = d->sync + 3;
+    a.flags = d->sync + kStepFlagsAt;
     a.freq = rope_frequencies(d->d, d->base);
     hipLaunchKernelGGL(decoder_step_kernel, dim3(d->blocks), dim3(kStepThreads), sizeof(StepLds), st, a);
     SQAP_HIP_CHECK(hipGetLastError());
