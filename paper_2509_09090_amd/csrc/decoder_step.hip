@@ -475,6 +475,8 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
         // it uses while it starts on the row.  A word that arrived later than its workgroup's flag is rare: then the
         // row is read again (nothing has been written by then: the residual row is updated after the check).
         float v[kStepGpt][8];
+        double row_sum = 0.0;
+        float row_max = 0.f;
         for (int attempt = 0;; ++attempt) {
             if (glue) {
                 // 1 KiB per instruction, straight into LDS (lane l's 16 bytes land at l * 16: the rows keep their layout)
@@ -559,6 +561,18 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
             if (__any((bad >> 16) != 0) && lane == 0) lds.stale[attempt & 1] = 1;
             lds_barrier();
             if (t == 0) lds.stale[(attempt + 1) & 1] = 0;      // (its last readers have passed the barrier before this one)
+            // what the next steps need is on its way before anything waits for the flags
+            if (P.gamma) {
+                sum = lds.sum[0];
+#pragma unroll
+                for (int w = 1; w < kStepWaves; ++w) sum += lds.sum[w];
+                row_sum = sum;
+            } else {
+                amax = lds.wmax[0];
+#pragma unroll
+                for (int w = 1; w < kStepWaves; ++w) amax = fmaxf(amax, lds.wmax[w]);
+                row_max = amax;
+            }
             if (!row || !lds.stale[attempt & 1] || lds.dead) break;
             if (attempt >= a.poll_limit) {
                 if (glue) give_up(ph, 3);
@@ -567,11 +581,8 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
             if (glue) __builtin_amdgcn_s_sleep(8);
         }
         if (P.gamma) {
-            double sum = lds.sum[0];
-#pragma unroll
-            for (int w = 1; w < kStepWaves; ++w) sum += lds.sum[w];
             float r;
-            if (__builtin_expect(!norm_factor_of(sum, a.inv_hidden, a.eps, r), 0)) {      // (a row of this kind has `hidden` values)
+            if (__builtin_expect(!norm_factor_of(row_sum, a.inv_hidden, a.eps, r), 0)) {      // (a row of this kind has `hidden` values)
                 unsigned long long hi = 0, lo = 0;
 #pragma unroll
                 for (int gi = 0; gi < kStepGpt; ++gi)
@@ -609,13 +620,13 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
             amax = wavefront_max(amax);
             if (lane == 0) lds.wmax[wave] = amax;
             lds_barrier();
+            row_max = lds.wmax[0];
+#pragma unroll
+            for (int w = 1; w < kStepWaves; ++w) row_max = fmaxf(row_max, lds.wmax[w]);
         }
         {
-            float amax = lds.wmax[0];
-#pragma unroll
-            for (int w = 1; w < kStepWaves; ++w) amax = fmaxf(amax, lds.wmax[w]);
-            const float sf = __half2float(row_scale(amax));
-            const float rcp = 1.0f / sf;
+            const float sf = __half2float(row_scale(row_max));
+            const float rcp = scale_reciprocal(sf);
             if (t == 0) lds.sx = sf;
 #pragma unroll
             for (int gi = 0; gi < kStepGpt; ++gi) {

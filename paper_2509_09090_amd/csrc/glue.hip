@@ -401,7 +401,7 @@ __device__ __forceinline__ void quantize_by_the_last(float *row_lds, float *wave
     for (int w = 0; w < T / 64; ++w) amax = fmaxf(amax, wave_max[w]);
     const __half sh = row_scale(amax);
     const float sf = __half2float(sh);
-    const float rcp = 1.0f / sf;
+    const float rcp = scale_reciprocal(sf);
     if (t == 0) {
         sx[0] = sh;
         __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // the next call starts from zero again

@@ -46,12 +46,24 @@ __device__ __forceinline__ uint32_t pack_codes8(const float (&q)[8])
     return (sum + (0x88888888u - kCodeBias * 0x11111111u)) ^ 0x88888888u;
 }
 
-// scale = half(max|v| / 7), the smallest subnormal when that rounds to zero (an all-zero row)
+// scale = half(max|v| / 7), the smallest subnormal when that rounds to zero (an all-zero row).  The division as quotient() does it (7 is a half
+// value): five instructions that wait for each other instead of a dozen.  An infinite maximum stays infinite: what the finite
+// largest value lacks is infinite.
 __device__ __forceinline__ __half row_scale(float amax)
 {
-    __half sh = __float2half_rn(amax / 7.0f);
+    constexpr float seventh = 1.0f / 7.0f;
+    const float q0 = fminf(amax * seventh, 3.402823466e+38f);
+    __half sh = __float2half_rn(fmaf(fmaf(-q0, 7.0f, amax), seventh, q0));
     if (__half_as_ushort(sh) == 0) sh = __ushort_as_half((unsigned short)1);
     return sh;
+}
+
+// RN(1 / s) of a finite half scale s: one Newton step on the hardware's estimate (sqap_selftest_quotient compares all of them with the division
+// operator).  An infinite scale gives NaN, and quotients over it are NaN either way.
+__device__ __forceinline__ float scale_reciprocal(float s)
+{
+    const float y = __builtin_amdgcn_rcpf(s);
+    return fmaf(fmaf(-s, y, 1.0f), y, y);
 }
 
 // Adds the squares of eight half values (held as floats), times 2^48, to the 128-bit integer hi:lo: exactly.

@@ -390,7 +390,7 @@ __global__ __launch_bounds__(T, GPT == 6 ? 4 : T / 256) void quantize_rows_kerne
 
     // The fast quotient is correctly rounded for every finite half scale (quant_math.h).  A rotated row can exceed what a
     // half scale reaches: then the scale is infinite and the division operator says what that gives.
-    const float rcp = 1.0f / sf;
+    const float rcp = scale_reciprocal(sf);
     const bool divide = (ROTATE || MODE == kFolded) && !(sf <= 65504.f);
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void quantize_row_pairs_kernel(const __half *_
         const __half sh = row_scale(amax);
         const float sf = __half2float(sh);
         if (t == 0) scale_out[row] = sh;
-        const float rcp = 1.0f / sf;
+        const float rcp = scale_reciprocal(sf);
         uint32_t *qrow = reinterpret_cast<uint32_t *>(Xq + (size_t)row * (K >> 1));
 #pragma unroll
         for (int gi = 0; gi < GPT; ++gi) {
@@ -688,8 +688,8 @@ __global__ __launch_bounds__(256) void quotient_selftest_kernel(unsigned long lo
 {
     const unsigned s_bits = blockIdx.x + 1;                    // 1 .. 0x7bff
     const float s = __half2float(__ushort_as_half((unsigned short)s_bits));
-    const float r = 1.0f / s;
-    unsigned bad = 0;
+    const float r = scale_reciprocal(s);
+    unsigned bad = threadIdx.x == 0 && __float_as_uint(r) != __float_as_uint(1.0f / s);
     for (unsigned v_bits = threadIdx.x; v_bits < 0x7c00u; v_bits += 256) {
         const float v = __half2float(__ushort_as_half((unsigned short)v_bits));
         const float a = v / s, b = quotient(v, s, r);
