@@ -234,13 +234,13 @@ sqap_status launch_prune_rows(const float *scores, int batch, int n, int keep_k,
 // are shared out by lane number mod 4; then the first wavefront samples alone (a pick depends on the one before, and a
 // barrier per pick would cost more than the arithmetic it shares out).  Everything after the projection is
 // integer work, so the result is exact.
-// A serial chain bounds it: up to 32 ballot rounds of the top-k search, then the picks; a pick is three instructions per 64 tokens, a
+// A serial chain bounds it: up to 32 ballot rounds of the top-k search, then the picks, of which those at squared distances 1 and 2 (four in
+// five where half of the tokens are kept) are made at once, see Words; a pick before them is three instructions per 64 tokens, a
 // wavefront maximum and the decoding of the winner.  A token's state is one word, squared distance * 1024 + inverted index: the
 // largest word is the next pick, a member's distance is zero, which keeps it out without further tests.  Coordinates are packed
 // halves, 32 times as large (1023 * 32 fits), so that one subtraction and one dot product, which adds the inverted index, give the
-// state for a new member, and a minimum does the rest.  Measured per call, 16 observations, us (eight instructions per 64 tokens and
-// pick, waits between them, in the first brackets; one wavefront, masks and coordinates apart, in the second): 16 x 16 tokens, 128
-// kept 12.1 (13.7, 26.6); 32 x 32, 512 kept 70 (111, 214).
+// state for a new member, and a minimum does the rest.  Measured per call, 16 observations, us (every pick by itself in brackets): 16 x 16
+// tokens, 128 kept 8.5 (11.7); 24 x 24, 300 kept 25.2 (46.0); 32 x 32, 512 kept 34.5 (69.5); 12 x 12, 72 kept 7.8 (9.5).
 constexpr int kSelectCamera = 26;          // doubles per observation: K (9), [R|t] (12), point (3), patch w, h
 constexpr uint32_t kFarAway = 1u << 30;    // above any state on a grid of <= 1024 tokens: a squared distance is below 2^20
 
@@ -306,6 +306,59 @@ __device__ __forceinline__ void add_member(uint32_t (&state)[PL], const uint32_t
 #pragma unroll
         for (int e = 0; e < 4; ++e) state[r + e] = min(state[r + e], t[e]);
     }
+}
+
+// The last picks at once.  At squared distance 2 a pick only touches candidates beside, above or below it (theirs becomes 1; the
+// others' stays 2), and nothing new becomes a candidate: taken in order of index, the picks are the candidates that no pick of a lower
+// index lies beside.  All undecided candidates without an undecided one beside them at a lower index are picks, whatever comes later; their
+// neighbours are out; and again until all are decided.  Grids of up to 64 columns, as one word of 64 tokens per lane: word r in lane r.
+struct Words {
+    unsigned long long not_last;               // tokens that are not in the last column
+    int gw;
+    // tokens right of and below those of x
+    __device__ __forceinline__ unsigned long long after(unsigned long long x) const
+    {
+        const unsigned long long r = x & not_last, up = (r >> 63) | (x >> (64 - gw));
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)up, 0x111, 0xf, 0xf, false);         // from the lane before
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(up >> 32), 0x111, 0xf, 0xf, false);
+        return (r << 1) | (gw < 64 ? x << gw : 0ull) | (unsigned long long)hi << 32 | lo;
+    }
+    __device__ __forceinline__ unsigned long long picks(unsigned long long candidates) const
+    {
+        unsigned long long picked = 0;
+        while (__any(candidates != 0ull)) {                                          // (each time round the lowest is decided, at least)
+            const unsigned long long now = candidates & ~after(candidates);
+            picked |= now;
+            candidates &= ~(now | after(now));
+        }
+        return picked;
+    }
+};
+
+// word r of 64 tokens, for lane r
+template <int PL>
+__device__ __forceinline__ unsigned long long to_words(const bool (&is)[PL], int lane)
+{
+    unsigned long long word = 0;
+#pragma unroll
+    for (int r = 0; r < PL; ++r) {
+        const unsigned long long mk = __ballot(is[r]);
+        word = lane == r ? mk : word;
+    }
+    return word;
+}
+
+// Keeps the first `left` of the tokens that `is` says; how many that leaves.
+template <int PL>
+__device__ __forceinline__ int keep_first(const bool (&is)[PL], bool (&kept)[PL], unsigned long long below, int left)
+{
+#pragma unroll
+    for (int r = 0; r < PL; ++r) {
+        const unsigned long long mk = __ballot(is[r]);
+        kept[r] = kept[r] || (is[r] && (int)__popcll(mk & below) < left);
+        left -= (int)__popcll(mk);
+    }
+    return left;
 }
 
 template <int PL>     // tokens per lane: at most 64 * PL tokens
@@ -394,18 +447,44 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prune_select_kernel(const f
         }
         const uint32_t inv_gw = (1u << 20) / (uint32_t)gw + 1u;      // w / gw = (w * inv_gw) >> 20: w * gw < 2^20
         const uint32_t row_step = (65536u - (uint32_t)gw) << 5;      // (w - v gw) | v << 16 = w + v (65536 - gw)
-        for (int step = 0; step < m; ++step) {
+        const uint32_t near = gw <= 64 ? 2u : 1u;
+        int left = m;
+        for (; left > 0; --left) {
             // largest distance, lowest index among equals: the index is in the state inverted
             uint32_t best = state[0];
 #pragma unroll
             for (int r = 1; r < PL; ++r) best = max(best, state[r]);
             best = wave_max_u32(best);
+            if (best >> 10 <= near) break;
             const uint32_t w = 1023u & ~best;
             const uint32_t at = (w << 5) + ((w * inv_gw) >> 20) * row_step;
             add_member<PL>(state, uv, inverted, at);
         }
 #pragma unroll
         for (int r = 0; r < PL; ++r) kept[r] = kept[r] || (valid[r] && (state[r] >> 10) == 0u);
+        if (left > 0) {
+            bool is[PL];
+            if (near == 2u) {
+#pragma unroll
+                for (int r = 0; r < PL; ++r) is[r] = valid[r] && (int)(uv[r] & 0xffffu) >> 5 != gw - 1;
+                const Words words = {to_words<PL>(is, lane), gw};
+#pragma unroll
+                for (int r = 0; r < PL; ++r) is[r] = (state[r] >> 10) == 2u;
+                const unsigned long long picked = words.picks(to_words<PL>(is, lane));
+#pragma unroll
+                for (int r = 0; r < PL; ++r) {
+                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)picked, r);
+                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(picked >> 32), r);
+                    is[r] = ((((unsigned long long)hi << 32) | lo) >> lane & 1ull) != 0ull;
+                }
+                left = keep_first<PL>(is, kept, below, left);
+            }
+            if (left > 0) {                                  // all others lie beside a member: by index
+#pragma unroll
+                for (int r = 0; r < PL; ++r) is[r] = valid[r] && !kept[r];
+                keep_first<PL>(is, kept, below, left);
+            }
+        }
     } else if (wave != 0) {
         return;
     }
@@ -444,7 +523,8 @@ sqap_status launch_prune_select(const float *scores, int batch, int gw, int gh, 
 // One block per observation: walks the sequence in order, keeps every token
 // outside the visual span and the visual tokens listed (ascending) in idx.  The list is read once, into one flag
 // per visual token; spans that do not fit the flags search the list, whose dependent reads took most of the
-// kernel's time (16 x 256 tokens: 3.4 us, with flags 2.6; 16 x 1024: 6.8 and 3.4).
+// kernel's time (16 x 256 tokens: 3.4 us, with flags 2.6; 16 x 1024: 6.8 and 3.4).  A list that is found to be ascending needs neither
+// (one barrier instead of four and two per 256 tokens: 16 x 256 2.43 -> 2.36, 16 x 1024 3.27 -> 2.31).
 constexpr int kRowFlags = 8192;
 __global__ __launch_bounds__(256) void kept_rows_kernel(const int32_t *__restrict__ idx, int keep_k,
                                                         int seq_len, int vis_begin, int n_vis,
@@ -456,6 +536,27 @@ __global__ __launch_bounds__(256) void kept_rows_kernel(const int32_t *__restric
     const int b = blockIdx.x, t = threadIdx.x;
     const int32_t *my = idx + (size_t)b * keep_k;
     int32_t *out = rows + (size_t)b * (seq_len - n_vis + keep_k);
+    // An ascending list of visual tokens says where each goes.  Anything else (a selection of fewer than keep_k ends with -1) takes
+    // the flags, or the search.
+    constexpr int HELD = 4;
+    int held[HELD];
+    bool ascending = keep_k <= 256 * HELD;
+    if (ascending) {
+#pragma unroll
+        for (int j = 0; j < HELD; ++j) {
+            const int i = t + 256 * j;
+            const int v = held[j] = i < keep_k ? my[i] : 0, before = i > 0 && i < keep_k ? my[i - 1] : -1;
+            if (i < keep_k && (v <= before || v < 0 || v >= n_vis)) ascending = false;
+        }
+    }
+    if (__syncthreads_and(ascending)) {
+#pragma unroll
+        for (int j = 0; j < HELD; ++j)
+            if (t + 256 * j < keep_k) out[vis_begin + t + 256 * j] = b * seq_len + vis_begin + held[j];
+        for (int i = t; i < seq_len - n_vis; i += 256)
+            out[i < vis_begin ? i : i + keep_k] = b * seq_len + (i < vis_begin ? i : i + n_vis);
+        return;
+    }
     const bool flagged = n_vis <= kRowFlags;
     if (flagged) {
         for (int i = t; i < (n_vis + 3) / 4; i += 256) flag_words[i] = 0u;
