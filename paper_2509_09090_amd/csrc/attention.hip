@@ -187,19 +187,6 @@ struct Sofar {
     }
 };
 
-// this lane's offsets in a tile's first 16 rows for read_values: lanes 16j .. 16j + 15 read 4 key rows x 16 columns
-template <int D>
-__device__ __forceinline__ void value_offsets(int l, unsigned (&lane_v)[2 * (D / 32)])
-{
-#pragma unroll
-    for (int ct = 0; ct < D / 32; ++ct)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int r = 8 * b + 4 * (l >> 5) + ((l & 15) >> 2), piece = 4 * ct + 2 * ((l >> 4) & 1) + ((l & 3) >> 1);
-            lane_v[2 * ct + b] = r * 2 * D + ((piece ^ swizzle<D>(r)) << 4) + ((l & 1) << 3);
-        }
-}
-
 // The queries of a workgroup over all their keys: this wavefront's column tiles (OWN of them), as pairs of halves.
 // FIRST: the fast way, with two assumptions.  Values are finite: an infinite one times the low half of a probability, which is
 // zero or negative as often as not, is NaN where the probability times the value is infinite.  And scores are below 2^24 in
@@ -484,19 +471,19 @@ constexpr int kWholeTiles = 5;
 // asked for at the start, tile by tile, and a tile is worked on as soon as it is there.
 // What it saves: with a workgroup per 64 queries, 16 x 148 x 148 with 32 heads is three rounds of workgroups that each fetch the keys
 // before their block again; without the loads, reads and softmax of its loop that took 22.8 of 24.4 us, so it was the rounds' starts and ends.
-// Here the 77 MB that go in and out bound it (13 us at the rate of a large copy).  us, replayed from a graph, the kernel above
-// in brackets: 32 heads of 128, 16 x 148 20.2 (24.5), 16 x 100 14.5 (16.8), 16 x 65 10.2 (14.0), 8 x 148 12.1 (14.9), 10 x 148 16.2 (17.0), 6 x 148 10.7 (12.8);
-// 32 heads of 64, 16 x 148 11.3 (13.9), 13 x 148 10.2 (11.5).  No gain: eight wavefronts and 320 keys with a compute unit each (16 x 276 49.3 (45.3),
-// 4 x 276 19.7 (15.9)), every other workgroup's wavefronts the other way about.  (attend's own text stays as it is: taking a tile through Sofar there made
-// heads of 64 2 to 4 % slower.)
-template <int D>
-__global__ __launch_bounds__(256, D == 64 ? 4 : 2) void attention_whole_kernel(const __half *__restrict__ Q, int64_t ldq,
+// Here the 77 MB that go in and out bound it (13 us at the rate of a large copy).  us, replayed from a graph, 32 heads of 128, the kernel above
+// in brackets: 16 x 148 21.6 (24.2), 16 x 100 15.8 (16.7), 16 x 65 11.4 (14.1), 16 x 70 x 150 17.4 (20.5), 8 x 148 13.2 (14.8), 6 x 148 11.9 (12.6).
+// Even and odd tiles go to two sums, which are merged as attend merges its two key groups: the same bits (one sum instead: 16 x 148 20.2, but
+// other roundings).  Two sums of heads of 64 do not fit the registers that four wavefronts per SIMD leave.  No gain: eight wavefronts and 320 keys
+// with a compute unit each (16 x 276 49.3 (45.3), 4 x 276 19.7 (15.9)), every other workgroup's wavefronts the other way about.  (attend's own text
+// stays as it is: taking a tile through Sofar there made heads of 64 2 to 4 % slower.)
+__global__ __launch_bounds__(256, 2) void attention_whole_kernel(const __half *__restrict__ Q, int64_t ldq,
                                                               const __half *__restrict__ Kc, int64_t ldk,
                                                               const __half *__restrict__ V, int64_t ldv, int Sq, int Sk,
                                                               __half *__restrict__ O, int64_t ldo)
 {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];   // keys, then values
-    constexpr int W = 4, T = kWholeTiles, NP = D / 16, CT = D / 32, ROW = 2 * D, PIECES = D / 8, TILE = 32 * ROW, VALUES = T * TILE;
+    constexpr int D = 128, W = 4, T = kWholeTiles, NP = D / 16, CT = D / 32, ROW = 2 * D, PIECES = D / 8, TILE = 32 * ROW, VALUES = T * TILE;
     constexpr int RPI = 1024 / ROW, L = 32 / RPI / W;                 // rows and loads per wavefront and tile
     static_assert(L * RPI * W == 32, "every wavefront asks for the same number of pieces");
     const int l = threadIdx.x & 63, c = l & 31, h = l >> 5;
@@ -514,6 +501,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void attention_whole_kernel(c
         for (int m = 0; m < NP; ++m) qf[m] = *reinterpret_cast<const v8h *>(Q + (int64_t)max(min(my_q, Sq - 1), 0) * ldq + 16 * m + 8 * h);
     };
     load_queries((groups - 1 - wave) * 32 + c);
+    asm volatile("" ::: "memory");                                    // (ahead of the tiles: the waits below count)
     // rows past the end repeat the last one
     const int lr = l / PIECES, lp = ((l % PIECES) ^ swizzle<D>(wave * RPI + lr)) * 8;
 #pragma unroll
@@ -528,37 +516,42 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void attention_whole_kernel(c
                                              (__attribute__((address_space(3))) void *)(lds + VALUES + t * TILE + (wave + i * W) * 1024), 16, 0, 0);
     }
     const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)lds;
-    unsigned lane_v[2 * CT];
-    value_offsets<D>(l, lane_v);
-    int lane_k[NP];
-#pragma unroll
-    for (int m = 0; m < NP; ++m) lane_k[m] = c * ROW + (((2 * m + h) ^ swizzle<D>(c)) << 4);
+    // (a lane's key pieces lie at one offset with another bit or two turned, and so do its value pieces; values: as in attend)
+    const int lane_k = c * ROW + ((h ^ swizzle<D>(c)) << 4);
+    const int vr = 4 * h + ((l & 15) >> 2), lane_v = vr * ROW + (((2 * ((l >> 4) & 1) + ((l & 3) >> 1)) ^ swizzle<D>(vr)) << 4) + ((l & 1) << 3);
 
     auto tile = [&](auto &done, int t, int q0) __attribute__((always_inline)) {
         v8h kf[NP];
+        const int key_at = t * TILE + lane_k;
 #pragma unroll
-        for (int m = 0; m < NP; ++m) kf[m] = *reinterpret_cast<const v8h *>(lds + t * TILE + lane_k[m]);
+        for (int m = 0; m < NP; ++m) kf[m] = *reinterpret_cast<const v8h *>(lds + (key_at ^ (m << 5)));
         __builtin_amdgcn_sched_barrier(0);                            // (all of them in flight before the first product)
         v16f st;
 #pragma unroll
         for (int i = 0; i < 16; ++i) st[i] = 0.f;
 #pragma unroll
         for (int m = 0; m < NP; ++m) st = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[m], qf[m], st, 0, 0, 0);
-        auto read = [&](v8h (&va)[2][CT]) __attribute__((always_inline)) { read_values<D>(lds_base + VALUES + t * TILE, lane_v, va); };
+        auto read = [&](v8h (&va)[2][CT]) __attribute__((always_inline)) {
+            unsigned at[2 * CT];
+#pragma unroll
+            for (int i = 0; i < 2 * CT; ++i) at[i] = (unsigned)lane_v ^ (i >> 1 << 6 | ((i & 1) ? 8 * ROW | 32 : 0));
+            read_values<D>(lds_base + VALUES + t * TILE, at, va);
+        };
         done.add(st, read, 32 * t, q0 + c + shift - 4 * h, 32 * t + 31 > q0 + shift, scale);
     };
+    auto both_halves = [](float sum) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
+        return __uint_as_float(lo[0]) + __uint_as_float(lo[1]);
+    };
     // this lane's 16 CT outputs as pairs of halves; whether one of them is not finite
-    auto outputs = [&](auto &done, bool first, unsigned (&w)[CT][8]) __attribute__((always_inline)) {
-        const auto lo = __builtin_amdgcn_permlane32_swap(__float_as_uint(done.sum), __float_as_uint(done.sum), false, false);
-        const float sum = __uint_as_float(lo[0]) + __uint_as_float(lo[1]);
-        const float inv = !first || sum >= 0.5f ? 1.0f / sum : NAN;
+    auto outputs = [&](auto value, float inv, unsigned (&w)[CT][8]) __attribute__((always_inline)) {
         float zero[4] = {};                                           // NaN with the first output that is not finite
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
             for (int i = 0; i < 16; i += 2) {
                 union { __half2 v; unsigned u; } pk;
-                pk.v = __floats2half2_rn(done.ot[ct][i] * inv, done.ot[ct][i + 1] * inv);
+                pk.v = __floats2half2_rn(value(ct, i) * inv, value(ct, i + 1) * inv);
                 w[ct][i >> 1] = pk.u;
                 zero[(i >> 1) & 3] = __builtin_amdgcn_fdot2(__builtin_bit_cast(v2h, pk.u), v2h{0, 0}, zero[(i >> 1) & 3], false);
             }
@@ -572,8 +565,8 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void attention_whole_kernel(c
             if (g < 0) break;
             load_queries(my_q);
         }
-        Sofar<D, true> done;
-        for (int t = 0; t < (round == 0 ? T : n); ++t) {
+        Sofar<D, true> done[2];                                       // of the even tiles and of the odd ones, as attend's two key groups
+        auto turn = [&](Sofar<D, true> &of, int t) __attribute__((always_inline)) {
             if (round == 0) {
                 switch (T - 1 - t) {                                  // this wavefront's part of the tile has landed
                 case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
@@ -584,11 +577,24 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void attention_whole_kernel(c
                 }
                 lds_barrier();                                        // everybody's has
             }
-            if (t < n) tile(done, t, q0);
+            if (t < n) tile(of, t, q0);
+        };
+        const int turns = round == 0 ? T : n;
+        for (int t = 0; t < turns; t += 2) {
+            turn(done[0], t);
+            if (t + 1 < turns) turn(done[1], t + 1);
         }
         if (g < 0) continue;
+        // the same operations as in attend's merge: the same bits
+        const float m = fmaxf(done[0].m, done[1].m);
+        const float f[2] = {done[0].factor(done[0].m - m), done[1].m == -INFINITY ? 0.f : done[1].factor(done[1].m - m)};
+        const float sum = both_halves(done[0].sum) * f[0] + both_halves(done[1].sum) * f[1];
+        auto merged = [&](int ct, int i) __attribute__((always_inline)) {
+            const int own = ct / (CT / 2);
+            return fmaf(done[1 - own].ot[ct][i], f[1 - own], done[own].ot[ct][i] * f[own]);
+        };
         unsigned w[CT][8];
-        if (__any(outputs(done, true, w) && my_q < Sq)) {
+        if (__any(outputs(merged, sum >= 0.5f ? 1.0f / sum : NAN, w) && my_q < Sq)) {
             // again with one half per probability, see attend; zeros for the values past the last key (whoever reads them meanwhile
             // takes them times zero)
             for (int at = Sk * PIECES + l; at < T * 32 * PIECES; at += 64)
@@ -597,7 +603,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void attention_whole_kernel(c
             Sofar<D, false> again;
             for (int t = 0; t < n; ++t) tile(again, t, q0);
             unsigned w1[CT][8];
-            outputs(again, false, w1);
+            outputs([&](int ct, int i) __attribute__((always_inline)) { return again.ot[ct][i]; }, 1.0f / both_halves(again.sum), w1);
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -628,13 +634,12 @@ static hipError_t allow_lds(int bytes)
     return e;
 }
 
-template <int D>
 static sqap_status launch_whole(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
                                 int batch, int Sq, int Sk, int H, __half *O, int64_t ldo, hipStream_t st)
 {
-    constexpr int bytes = 2 * kWholeTiles * 32 * 2 * D;
-    if constexpr (bytes > 48 * 1024) SQAP_HIP_CHECK((allow_lds<attention_whole_kernel<D>>(bytes)));
-    hipLaunchKernelGGL((attention_whole_kernel<D>), dim3(H, 1, batch), dim3(256), bytes, st, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, O, ldo);
+    constexpr int bytes = 2 * kWholeTiles * 32 * 2 * 128;
+    SQAP_HIP_CHECK(allow_lds<attention_whole_kernel>(bytes));
+    hipLaunchKernelGGL(attention_whole_kernel, dim3(H, 1, batch), dim3(256), bytes, st, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, O, ldo);
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }
@@ -665,15 +670,16 @@ static sqap_status launch_tiles(const __half *Q, int64_t ldq, const __half *Kc, 
 sqap_status launch_attention_tiles(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
                                    int batch, int Sq, int Sk, int H, int d, __half *O, int64_t ldo, hipStream_t st)
 {
-    // Where blocks of 64 queries would not all find room at once (two per compute unit, four with heads of 64) and five tiles hold
-    // all keys: a workgroup per sequence and head.  Below that the blocks are the better split (us, by blocks / by sequences:
-    // 4 x 148, 32 heads of 128 9.4 / 10.0, of 64 6.5 / 7.4; 1 x 148, 32 heads 6.6 / 9.4; 8 x 97, 32 heads 8.8 / 9.0); figures above it are at the kernel.
     const int cus = device_cu_count();
-    if (Sk <= 32 * kWholeTiles && (int64_t)batch * H * ((Sq + 63) / 64) > (int64_t)cus * (d == 64 ? 4 : 2)) {
-        if (d == 64) return launch_whole<64>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
-        return launch_whole<128>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
-    }
     if (d == 64) return launch_tiles<64, 2, 2>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
+    // Where blocks of 64 queries would not all find room at once (two per compute unit) and five tiles hold all keys: a workgroup
+    // per sequence and head.  Below that the blocks are the better split (32 heads, us, by blocks / by sequences: 4 x 148 9.4 / 10.0, 1 x 148
+    // 6.6 / 9.4, 8 x 97 8.8 / 9.0), and where the blocks' last round is nearly full and the sequences' is not (10 x 148 16.9 / 17.5, but
+    // 9 x 148 16.8 / 16.0, 11 x 148 18.3 / 18.2, 20 x 148 29.9 / 29.2); figures above it are at the kernel.
+    const int64_t sequences = (int64_t)batch * H, blocks = sequences * ((Sq + 63) / 64), room = 2 * (int64_t)cus;
+    const bool blocks_fill = (blocks - 1) % room >= room * 7 / 8 - 1 && sequences > cus && (sequences - 1) % room < room * 3 / 4;
+    if (Sk <= 32 * kWholeTiles && blocks > room && !blocks_fill)
+        return launch_whole(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
     const int64_t groups = (int64_t)batch * H * ((Sq + 31) / 32);
     if (groups <= cus && Sk >= 192)
         return launch_tiles<128, 1, 4>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
