@@ -626,7 +626,7 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
         }
         {
             const float sf = __half2float(row_scale(row_max));
-            const float rcp = scale_reciprocal(sf);
+            const Reciprocal rcp = scale_reciprocal(sf);
             if (t == 0) lds.sx = sf;
 #pragma unroll
             for (int gi = 0; gi < kStepGpt; ++gi) {
@@ -634,7 +634,7 @@ __global__ __launch_bounds__(kStepThreads, 1) void decoder_step_kernel(const Ste
                 if (g < groups) {
                     float q[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) q[e] = quotient(v[gi][e], sf, rcp);
+                    for (int e = 0; e < 8; ++e) q[e] = quotient(v[gi][e], rcp);
                     reinterpret_cast<uint32_t *>(lds.xs)[g] = pack_codes8(q);
                 }
             }

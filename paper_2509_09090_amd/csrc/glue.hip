@@ -401,7 +401,7 @@ __device__ __forceinline__ void quantize_by_the_last(float *row_lds, float *wave
     for (int w = 0; w < T / 64; ++w) amax = fmaxf(amax, wave_max[w]);
     const __half sh = row_scale(amax);
     const float sf = __half2float(sh);
-    const float rcp = scale_reciprocal(sf);
+    const Reciprocal rcp = scale_reciprocal(sf);
     if (t == 0) {
         sx[0] = sh;
         __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // the next call starts from zero again
@@ -410,7 +410,7 @@ __device__ __forceinline__ void quantize_by_the_last(float *row_lds, float *wave
         float f[8];
         unpack_halves(reinterpret_cast<const uint4 *>(row)[g], f);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = quotient(f[e], sf, rcp);
+        for (int e = 0; e < 8; ++e) f[e] = quotient(f[e], rcp);
         reinterpret_cast<uint32_t *>(Xq)[g] = pack_codes8(f);
     }
 }

@@ -7,23 +7,16 @@
 
 namespace sqap {
 
-// Correctly rounded binary32 quotient v / s for a divisor whose reciprocal r = RN(1/s)
-// was formed once per row (IEEE division).  q0 = RN(v r) is within one ulp of v/s, the
-// FMA gives the exact remainder, and the second FMA rounds q0 + rem * r to the
-// correctly rounded quotient (Markstein's correction; it can fail only for divisors whose
-// significand is all ones, which a half-precision scale widened to binary32 never is).
-// Three instructions instead of the ~15 of a full IEEE division per element; every
-// half / half pair is compared against the division operator by sqap_selftest_quotient.
-// It holds for any binary32 v over a half scale: q0 is within two ulps, so the remainder is exact and the corrected sum
-// is off by less than 2^-22 ulp before its one rounding; v / s is never that close to a midpoint of binary32: it is not
-// one (25 odd bits times s would not fit v's 24), and v minus the midpoint times s is a whole number of units, which
-// leaves at least 2^-12 ulp.  (Quotients so small that the remainder underflows are code 0 either way.)
-__device__ __forceinline__ float quotient(float v, float s, float r)
-{
-    const float q0 = v * r;
-    const float rem = fmaf(-q0, s, v);
-    return fmaf(rem, r, q0);
-}
+// Correctly rounded binary32 quotient v / s (IEEE division) for a half scale s and any binary32 v, with 1 / s in two parts formed
+// once per row: hi = RN(1 / s), lo what that lacks.  hi + lo is within 2^-47 of 1 / s, and so is the sum that the multiply-add
+// rounds, once; v / s is never that close to a midpoint of binary32: it is not one (25 odd bits times s would not fit v's
+// 24), and v minus the midpoint times s is a whole number of units, which leaves at least 2^-12 ulp, 2^-36 of v / s.  Two instructions instead of the
+// ~15 of a full IEEE division per element, or three with the remainder; every half / half pair is compared against the division operator by
+// sqap_selftest_quotient.  (Quotients so small that v * lo underflows are code 0 either way.)
+struct Reciprocal {
+    float hi, lo;
+};
+__device__ __forceinline__ float quotient(float v, const Reciprocal &r) { return fmaf(v, r.hi, v * r.lo); }
 
 // clamp(rint(q), -8, 7) as a 4-bit two's complement code.  Clamping first gives the same integer (both
 // bounds are integers and rounding is monotone), and adding 1.5 * 2^23 rounds a value of that size to
@@ -46,7 +39,7 @@ __device__ __forceinline__ uint32_t pack_codes8(const float (&q)[8])
     return (sum + (0x88888888u - kCodeBias * 0x11111111u)) ^ 0x88888888u;
 }
 
-// scale = half(max|v| / 7), the smallest subnormal when that rounds to zero (an all-zero row).  The division as quotient() does it (7 is a half
+// scale = half(max|v| / 7), the smallest subnormal when that rounds to zero (an all-zero row).  The division by the remainder of an estimate (7 is a half
 // value): five instructions that wait for each other instead of a dozen.  An infinite maximum stays infinite: what the finite
 // largest value lacks is infinite.
 __device__ __forceinline__ __half row_scale(float amax)
@@ -58,12 +51,12 @@ __device__ __forceinline__ __half row_scale(float amax)
     return sh;
 }
 
-// RN(1 / s) of a finite half scale s: one Newton step on the hardware's estimate (sqap_selftest_quotient compares all of them with the division
-// operator).  An infinite scale gives NaN, and quotients over it are NaN either way.
-__device__ __forceinline__ float scale_reciprocal(float s)
+// 1 / s of a finite half scale s: RN(1 / s) by one Newton step on the hardware's estimate (sqap_selftest_quotient compares all of them with the
+// division operator), and the rest.  An infinite scale gives NaN, and quotients over it are NaN either way.
+__device__ __forceinline__ Reciprocal scale_reciprocal(float s)
 {
-    const float y = __builtin_amdgcn_rcpf(s);
-    return fmaf(fmaf(-s, y, 1.0f), y, y);
+    const float y = __builtin_amdgcn_rcpf(s), hi = fmaf(fmaf(-s, y, 1.0f), y, y);
+    return {hi, fmaf(-s, hi, 1.0f) * hi};
 }
 
 // Adds the squares of eight half values (held as floats), times 2^48, to the 128-bit integer hi:lo: exactly.
@@ -152,42 +145,51 @@ __device__ __forceinline__ float silu_of(float g)
 }
 
 // g := the half that silu_of(g) * u rounds to, for eight pairs.  Binary32 and the hardware's exponential and reciprocal give silu with an
-// error of at most kSiluError where g >= kSiluMin, so that where both ends of r (1 +- kSiluReach) round to one half, that half is it:
-// rounding is monotonic, and the reach covers the error, the product's rounding on both ways and the ends' own, 2^-24 each.  Below
-// kSiluMin the estimate is NaN, or -0 (times an infinite u: NaN), or a negative number where silu is one too, so small that its product
-// with any finite u rounds to the zero that silu's does.  Elsewhere (0.2 % of the values, one wavefront in eight; and NaN, which equals
-// nothing) silu_of decides, one element after the other; the estimates of all eight come first, so that none waits for another.
+// error of at most kSiluError where |g| <= kSiluMax, so that where both ends of r (1 +- kSiluReach) round to one half, that half is it:
+// rounding is monotonic, and the reach covers the error, the product's rounding on both ways and the ends' own, 2^-24 each.  The exponent
+// stops at kSiluMax: above it silu is g itself, and so is the estimate; below, the estimate is a negative number (zero for none) so small
+// that its product with any finite u rounds to the zero that silu's does.  Two halves that differ in more than the sign (a low end
+// of -0 comes out as +0) are open (0.2 % of the values, one wavefront in eight; an infinite r, whose low end is NaN), and silu_of decides; NaN is
+// NaN by the definition too.  The estimates of all eight come first, so that none waits for another.
 // None of this is taken from a manual: sqap_selftest_silu looks at all halves.
-constexpr float kSiluMin = -80.f, kSiluError = 5.0e-7f, kSiluReach = 7.0e-7f;
+constexpr float kSiluMax = 80.f, kSiluError = 5.0e-7f, kSiluReach = 7.0e-7f;
 static_assert(kSiluError + 3.0f / 16777216.0f < kSiluReach, "");
 
 __device__ __forceinline__ float silu_estimate(float g)
 {
-    const float t = g * -1.442695040888963f, power = __builtin_amdgcn_exp2f(t);
+    const float x = __builtin_amdgcn_fmed3f(g, -kSiluMax, kSiluMax), t = x * -1.442695040888963f, power = __builtin_amdgcn_exp2f(t);
     // what the rounding of t has taken from the exponent, with ln 2 in two parts
-    const float lost = fmaf(t, 0x1.05c610p-29f, fmaf(t, -0x1.62e430p-1f, -g));
+    const float lost = fmaf(t, 0x1.05c610p-29f, fmaf(t, -0x1.62e430p-1f, -x));
     return g * __builtin_amdgcn_rcpf(1.0f + fmaf(power, lost, power));
 }
 
 __device__ __forceinline__ void swiglu8(float (&g)[8], const float (&u)[8])
 {
-    float h[8];
-    bool open[8];
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+    union Pair { v2h h; uint32_t bits; } low[4], high[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float r = silu_estimate(g[e]) * u[e];
-        const __half low = __float2half_rn(fmaf(r, -kSiluReach, r)), high = __float2half_rn(fmaf(r, kSiluReach, r));
-        h[e] = __half2float(high);                         // (of a zero it has the sign, which `low` has not)
-        open[e] = !(__half2float(low) == h[e]);
+    for (int p = 0; p < 4; ++p) {
+        const float a = silu_estimate(g[2 * p]) * u[2 * p], b = silu_estimate(g[2 * p + 1]) * u[2 * p + 1];
+        low[p].h = __builtin_convertvector((v2f{fmaf(a, -kSiluReach, a), fmaf(b, -kSiluReach, b)}), v2h);
+        high[p].h = __builtin_convertvector((v2f{fmaf(a, kSiluReach, a), fmaf(b, kSiluReach, b)}), v2h);
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        if (open[e]) {
-            float exact = silu_of(g[e]) * u[e];
+    for (int p = 0; p < 4; ++p) {
+        float a = (float)high[p].h[0], b = (float)high[p].h[1];
+        const uint32_t open = low[p].bits ^ high[p].bits;
+        if (open & 0x7fffu) {                              // (not the sign: that of a zero's low end is lost)
+            float exact = silu_of(g[2 * p]) * u[2 * p];
             asm volatile("" : "+v"(exact));                // two roundings, not one mixed-precision instruction
-            h[e] = __half2float(__float2half_rn(exact));
+            a = __half2float(__float2half_rn(exact));
         }
-        g[e] = h[e];
+        if (open & 0x7fff0000u) {
+            float exact = silu_of(g[2 * p + 1]) * u[2 * p + 1];
+            asm volatile("" : "+v"(exact));
+            b = __half2float(__float2half_rn(exact));
+        }
+        g[2 * p] = a;
+        g[2 * p + 1] = b;
     }
 }
 

@@ -262,9 +262,11 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta
 // SwiGLU (Shazeer 2020; the feed-forward of a Llama decoder): v holds the gate row g, pre.U the
 // up row;  v = half(silu(g) * u),  silu(g) = (float)(g / (1 + exp(-g))) evaluated in binary64.
 // silu is a function of a half value: a GPU test walks all 2^16 of them against the host's.
-// What bounds it at 2368 x 11008 is the vector ALU, then memory (117 MB, 23 us): 30.8 us, whatever the values' spread, against 34.7-38.4
-// with silu_of for every element, 25 instructions in binary64, and 49.7 with the library's exponential and division.  84 rows 6.3-6.6
-// (6.7-7.0), 1000 x 5504 9.2 (10.1).  (With a binary32 estimate good down to g = -8 or -32 only, wider gates took 53 us.)
+// What bounds it at 2368 x 11008 is memory (117 MB, 23 us), with the vector ALU close behind: 29.5 us, whatever the values' spread, 31.9 with halves
+// compared one by one and three instructions per quotient (32 instructions per value, 27 now), 38 with silu_of for every element, 25 instructions in
+// binary64, and 49.7 with the library's exponential and division.  84 rows 5.36 (5.46), 1000 x 5504 8.3 (8.6), one row 4.55 (4.71).  (With a
+// binary32 estimate good down to g = -8 or -32 only, wider gates took 53 us; where a product of -0 is left to silu_of, the zeros that quantized
+// products are full of cost 5 %.)
 // (A per-device table of the 2^16 results was slower than computing: 13 against 10 us at 84 x 11008,
 // 48 scattered 4-byte loads per thread.)
 // Rows with at most one group of eight per thread, and few of them, wait for the longest chain of a thread, and with 64 times eight
@@ -390,7 +392,7 @@ __global__ __launch_bounds__(T, GPT == 6 ? 4 : T / 256) void quantize_rows_kerne
 
     // The fast quotient is correctly rounded for every finite half scale (quant_math.h).  A rotated row can exceed what a
     // half scale reaches: then the scale is infinite and the division operator says what that gives.
-    const float rcp = scale_reciprocal(sf);
+    const Reciprocal rcp = scale_reciprocal(sf);
     const bool divide = (ROTATE || MODE == kFolded) && !(sf <= 65504.f);
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
@@ -398,7 +400,7 @@ __global__ __launch_bounds__(T, GPT == 6 ? 4 : T / 256) void quantize_rows_kerne
         if (g < groups) {
             float q[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) q[e] = divide ? v[gi][e] / sf : quotient(v[gi][e], sf, rcp);
+            for (int e = 0; e < 8; ++e) q[e] = divide ? v[gi][e] / sf : quotient(v[gi][e], rcp);
             qrow[g] = pack_codes8(q);
         }
     }
@@ -456,7 +458,7 @@ __global__ __launch_bounds__(256) void quantize_row_pairs_kernel(const __half *_
         const __half sh = row_scale(amax);
         const float sf = __half2float(sh);
         if (t == 0) scale_out[row] = sh;
-        const float rcp = scale_reciprocal(sf);
+        const Reciprocal rcp = scale_reciprocal(sf);
         uint32_t *qrow = reinterpret_cast<uint32_t *>(Xq + (size_t)row * (K >> 1));
 #pragma unroll
         for (int gi = 0; gi < GPT; ++gi) {
@@ -464,7 +466,7 @@ __global__ __launch_bounds__(256) void quantize_row_pairs_kernel(const __half *_
             if (g < groups) {
                 float q[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) q[e] = quotient(v[gi][e], sf, rcp);
+                for (int e = 0; e < 8; ++e) q[e] = quotient(v[gi][e], rcp);
                 qrow[g] = pack_codes8(q);
             }
         }
@@ -551,9 +553,8 @@ static sqap_status launch_quantize_inst(const __half *X, int64_t ldx, const int3
 }
 
 // Threads per row.  With at most two rows per compute unit the longest rows take 1024 (84 x 11008, SwiGLU 6.3 us against 6.6
-// with 512 and 7.9 with 256; 512 rows 10.2, 10.7 and 12.1; plain 84 rows 3.4 against 3.7 and 5.0).  With more rows 256, although the SwiGLU
-// kernel alone is not faster (2368 x 11008: 32.7 us, 30.6 with 512, 32.1 with 1024, 38.1 with 128): norm, gate|up, SwiGLU and down in a row
-// take 306.4 us, 308.7 with 512, 307.0 with 1024 and 313.8 with 128.  (At 600 x 11008 the row of four takes 114.9, 113.8 with 512.)  Rows of 513
+// with 512 and 7.9 with 256; 512 rows 10.2, 10.7 and 12.1; plain 84 rows 3.4 against 3.7 and 5.0).  With more rows 512 for SwiGLU (2368 x
+// 11008 29.5 us, 31.1 with 256, 30.9 with 1024; norm, gate|up, SwiGLU and down in a row 284.2, 287.2 and 284.7), else 256.  Rows of 513
 // to 1024 groups keep 512 (norm to down at 1100 x 5504 68.6 us, 69.9 with 256 and 69.6 with 1024).
 // The norm's scalar part is repeated by every wavefront, so there fewer are better as soon as rows share compute units (us):
 // up to 512 groups (2368 x 4096 17.2 against 19.8 with 512 threads; 84 x 4096 4.5 against 4.1), above 1024 groups (257 x 8704
@@ -568,6 +569,9 @@ static sqap_status launch_quantize_gpt(const __half *X, int64_t ldx, const int32
 #define SQAP_Q(T, G) launch_quantize_inst<ROTATE, T, G, MODE, PRE>(X, ldx, rows, M, K, col_scales, Xq, sx, pre, st)
     if (groups > 1024) {
         if (M <= (PRE == kPreNorm ? cus : 2 * cus)) return SQAP_Q(1024, 2);
+        if constexpr (PRE == kPreSwiglu) {
+            if (groups <= 1536) return SQAP_Q(512, 3);
+        }
         return groups <= 1536 ? SQAP_Q(256, 6) : SQAP_Q(256, 8);
     }
     if (groups > 512) {
@@ -688,12 +692,12 @@ __global__ __launch_bounds__(256) void quotient_selftest_kernel(unsigned long lo
 {
     const unsigned s_bits = blockIdx.x + 1;                    // 1 .. 0x7bff
     const float s = __half2float(__ushort_as_half((unsigned short)s_bits));
-    const float r = scale_reciprocal(s);
-    unsigned bad = threadIdx.x == 0 && __float_as_uint(r) != __float_as_uint(1.0f / s);
+    const Reciprocal r = scale_reciprocal(s);
+    unsigned bad = threadIdx.x == 0 && __float_as_uint(r.hi) != __float_as_uint(1.0f / s);
     for (unsigned v_bits = threadIdx.x; v_bits < 0x7c00u; v_bits += 256) {
         const float v = __half2float(__ushort_as_half((unsigned short)v_bits));
-        const float a = v / s, b = quotient(v, s, r);
-        const float an = (-v) / s, bn = quotient(-v, s, r);
+        const float a = v / s, b = quotient(v, r);
+        const float an = (-v) / s, bn = quotient(-v, r);
         // (a zero quotient may differ in sign: -0 / s is -0, the corrected form gives +0;
         // both become code 0)
         bad += (__float_as_uint(a) != __float_as_uint(b) && !(a == 0.f && b == 0.f)) +
@@ -716,11 +720,13 @@ __global__ __launch_bounds__(256) void silu_selftest_kernel(unsigned long long *
     const double gd = (double)g;
     const float want = (float)(gd / (1.0 + exp(-gd))), got = silu_of(g);
     if (__float_as_uint(want) != __float_as_uint(got) && !(want != want && got != got)) atomicAdd(mismatches, 1ull);
-    // what swiglu8 rests on (an estimate that is NaN is left to silu_of)
+    // what swiglu8 rests on: NaN only where silu is
     const double silu = gd / (1.0 + exp(-gd)), estimate = (double)silu_estimate(g);
-    const bool good = g < kSiluMin ? signbit(estimate) && estimate > -0x1p-60 && (estimate == 0.0 || want != 0.f)
-                                   : fabs(estimate - silu) <= (double)kSiluError * fabs(silu);
-    if (estimate == estimate && !good) atomicAdd(mismatches, 1ull);
+    const bool good = want != want ? !(fabs(estimate) < INFINITY)
+                      : fabsf(g) == INFINITY ? estimate == silu
+                      : g < -kSiluMax ? signbit(estimate) && estimate > -0x1p-90 && signbit(want) && want > -0x1p-90f
+                                      : fabs(estimate - silu) <= (double)kSiluError * fabs(silu);
+    if (!good) atomicAdd(mismatches, 1ull);
 }
 
 sqap_status launch_silu_selftest(unsigned long long *mismatches, hipStream_t st)
