@@ -262,9 +262,9 @@ __device__ __forceinline__ void norm_row(float (&v)[GPT][8], const uint4 (&delta
 // SwiGLU (Shazeer 2020; the feed-forward of a Llama decoder): v holds the gate row g, pre.U the
 // up row;  v = half(silu(g) * u),  silu(g) = (float)(g / (1 + exp(-g))) evaluated in binary64.
 // silu is a function of a half value: a GPU test walks all 2^16 of them against the host's.
-// What bounds it at 2368 x 11008 is memory (117 MB, 23 us), with the vector ALU close behind: 29.5 us, whatever the values' spread, 31.9 with halves
-// compared one by one and three instructions per quotient (32 instructions per value, 27 now), 38 with silu_of for every element, 25 instructions in
-// binary64, and 49.7 with the library's exponential and division.  84 rows 5.36 (5.46), 1000 x 5504 8.3 (8.6), one row 4.55 (4.71).  (With a
+// What bounds it at 2368 x 11008 is the vector ALU, which issues in every cycle in which a compute unit has work (counters: 36 instructions per 64 values,
+// a tenth of them lanes past the row's end), then memory (117 MB, 23 us): 29.5 us, whatever the values' spread, 31.9 with 256 threads, halves compared one by one
+// and three instructions per quotient, 38 with silu_of for every element, 25 instructions in binary64, and 49.7 with the library's exponential and division.  84 rows 5.36 (5.46), 1000 x 5504 8.3 (8.6), one row 4.55 (4.71).  (With a
 // binary32 estimate good down to g = -8 or -32 only, wider gates took 53 us; where a product of -0 is left to silu_of, the zeros that quantized
 // products are full of cost 5 %.)
 // (A per-device table of the 2^16 results was slower than computing: 13 against 10 us at 84 x 11008,
