@@ -432,10 +432,12 @@ sqap_status sqap_residual_add(sqap_f16 *X, int64_t ldx, const sqap_f16 *delta, i
 
 /*
  * Self-test of the quantizer's arithmetic.  The quantizer divides every element
- * of a row by the same scale; it does so with a reciprocal and two fused
- * corrections that give the correctly rounded binary32 quotient.  This call
- * checks that claim on the device for every pair (v, s) of finite half values,
- * s > 0, both signs of v, against the division operator, and ADDS the number of
+ * of a row by the same scale; it does so with the reciprocal in two parts and
+ * one fused multiply-add, which gives the correctly rounded binary32 quotient.
+ * This call checks that claim on the device for every pair (v, s) of finite half
+ * values, s > 0, both signs of v, against the division operator, and the scale
+ * of a row against the division by 7 and its conversion to half for every
+ * binary32 maximum from zero to infinity; it ADDS the number of
  * differing bit patterns to *mismatches_out (a device uint64 the caller has
  * zeroed).  Expected result: 0.  EINVAL: null pointer.
  */

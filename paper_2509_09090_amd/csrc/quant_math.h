@@ -39,14 +39,18 @@ __device__ __forceinline__ uint32_t pack_codes8(const float (&q)[8])
     return (sum + (0x88888888u - kCodeBias * 0x11111111u)) ^ 0x88888888u;
 }
 
-// scale = half(max|v| / 7), the smallest subnormal when that rounds to zero (an all-zero row).  The division by the remainder of an estimate (7 is a half
-// value): five instructions that wait for each other instead of a dozen.  An infinite maximum stays infinite: what the finite
-// largest value lacks is infinite.
+// scale = half(float(max|v| / 7)), the smallest subnormal when that rounds to zero (an all-zero row).  The division by the remainder of an estimate (7 is
+// a half value): five instructions that wait for each other instead of a dozen.  An infinite maximum stays infinite: what the finite
+// largest value lacks is infinite.  Two roundings, of which the first decides at ties between two halves: without the empty asm the last
+// multiply-add and the conversion become one instruction that rounds once.  sqap_selftest_quotient compares all binary32 maxima with the division
+// operator.
 __device__ __forceinline__ __half row_scale(float amax)
 {
     constexpr float seventh = 1.0f / 7.0f;
     const float q0 = fminf(amax * seventh, 3.402823466e+38f);
-    __half sh = __float2half_rn(fmaf(fmaf(-q0, 7.0f, amax), seventh, q0));
+    float q = fmaf(fmaf(-q0, 7.0f, amax), seventh, q0);
+    asm volatile("" : "+v"(q));
+    __half sh = __float2half_rn(q);
     if (__half_as_ushort(sh) == 0) sh = __ushort_as_half((unsigned short)1);
     return sh;
 }

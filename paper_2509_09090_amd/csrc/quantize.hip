@@ -687,7 +687,8 @@ sqap_status launch_channel_scales(const __half *X, int64_t ldx, const int32_t *r
 }
 
 // Self-test: for every pair (v, s) of finite half values with s > 0, compares the fast
-// quotient with the division operator, bit for bit.  Counts the differences.
+// quotient with the division operator, bit for bit; and row_scale with the division and the conversion of its result, for every
+// largest value that is not negative.  Counts the differences.
 __global__ __launch_bounds__(256) void quotient_selftest_kernel(unsigned long long *mismatches)
 {
     const unsigned s_bits = blockIdx.x + 1;                    // 1 .. 0x7bff
@@ -706,9 +707,24 @@ __global__ __launch_bounds__(256) void quotient_selftest_kernel(unsigned long lo
     if (bad) atomicAdd(mismatches, (unsigned long long)bad);
 }
 
+__global__ __launch_bounds__(256) void scale_selftest_kernel(unsigned long long *mismatches)
+{
+    unsigned bad = 0;
+    for (unsigned bits = blockIdx.x * 256 + threadIdx.x; bits <= 0x7f800000u; bits += gridDim.x * 256) {
+        const float amax = __uint_as_float(bits);
+        float q = amax / 7.0f;
+        asm volatile("" : "+v"(q));
+        const unsigned want = __half_as_ushort(__float2half_rn(q));
+        bad += __half_as_ushort(row_scale(amax)) != (want ? want : 1u);
+    }
+    if (bad) atomicAdd(mismatches, (unsigned long long)bad);
+}
+
 sqap_status launch_quotient_selftest(unsigned long long *mismatches, hipStream_t st)
 {
     hipLaunchKernelGGL(quotient_selftest_kernel, dim3(0x7bff), dim3(256), 0, st, mismatches);
+    SQAP_HIP_CHECK(hipGetLastError());
+    hipLaunchKernelGGL(scale_selftest_kernel, dim3(4096), dim3(256), 0, st, mismatches);
     SQAP_HIP_CHECK(hipGetLastError());
     return SQAP_OK;
 }
