@@ -110,83 +110,6 @@ __device__ __forceinline__ void read_values(unsigned at, const unsigned (&lane_v
         for (int ct = 0; ct < D / 32; ++ct) va[n][ct] = r[n][ct].v;
 }
 
-// What a lane has of its query so far, and a tile of 32 keys added to it (FIRST: see attend).
-template <int D, bool FIRST>
-struct Sofar {
-    static constexpr int CT = D / 32;
-    v16f ot[CT];                                                      // 16 of 32 columns' weighted sums per column tile
-    float m, sum;                                                     // maximum; sum: this lane half's keys only
-
-    __device__ __forceinline__ Sofar() : m(-INFINITY), sum(0.f)
-    {
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) ot[ct][i] = 0.f;
-    }
-    static __device__ __forceinline__ float factor(float x)
-    {
-        const float f = __builtin_amdgcn_exp2f(x);
-        return !FIRST && f < 0x1p-100f ? 0x1p-100f : f;               // (NaN stays)
-    }
-    static __device__ __forceinline__ float probability(float s, float scale, float m)
-    {
-        if (FIRST) return __builtin_amdgcn_exp2f(fmaf(s, scale, -m));
-        const float p = __builtin_amdgcn_exp2f((s * scale - m) + 9.f);
-        return p < 0x1p-24f && s > -INFINITY ? 0x1p-24f : p;
-    }
-    // read: the tile's values, which arrive while the scores' products are worked on (not FIRST: once there is room for them);
-    // key0: the tile's first; last: the last that the query sees, counted from the first of this lane half; diagonal: some query of the
-    // wavefront does not see all
-    template <class READ>
-    __device__ __forceinline__ void add(v16f &st, READ read, int key0, int last, bool diagonal, float scale)
-    {
-        v8h va[2][CT];
-        if (FIRST) read(va);
-        if (diagonal) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (key0 + 8 * (i >> 2) + (i & 3) > last) st[i] = -INFINITY;
-        }
-        float tmax = st[0];
-#pragma unroll
-        for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, st[i]);
-        const auto other = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax), __float_as_uint(tmax), false, false);
-        tmax = fmaxf(__uint_as_float(other[0]), __uint_as_float(other[1])) * scale;
-        if (__any(tmax > m + kRaiseBy)) {
-            const float m_new = fmaxf(m, tmax);
-            const float f = m_new == -INFINITY ? 1.f : factor(m - m_new);
-            m = m_new;
-            sum *= f;
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) ot[ct][i] *= f;
-        }
-        const float m_sub = m == -INFINITY ? 0.f : m;                 // (a query that sees none of these keys so far)
-        v8h ph[2], pl[2];
-#pragma unroll
-        for (int i = 0; i < 16; i += 2) {
-            const float p0 = probability(st[i], scale, m_sub), p1 = probability(st[i + 1], scale, m_sub);
-            sum += p0 + p1;
-            const v2h pk = {(_Float16)p0, (_Float16)p1};
-            const v2h pr = {(_Float16)remainder_of<0>(pk, p0), (_Float16)remainder_of<1>(pk, p1)};
-            ph[i >> 3][i & 7] = pk[0];
-            ph[i >> 3][(i & 7) + 1] = pk[1];
-            pl[i >> 3][i & 7] = pr[0];
-            pl[i >> 3][(i & 7) + 1] = pr[1];
-        }
-        if (!FIRST) read(va);
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                ot[ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[n][ct], ph[n], ot[ct], 0, 0, 0);
-                if (FIRST) ot[ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[n][ct], pl[n], ot[ct], 0, 0, 0);
-            }
-    }
-};
-
 // The queries of a workgroup over all their keys: this wavefront's column tiles (OWN of them), as pairs of halves.
 // FIRST: the fast way, with two assumptions.  Values are finite: an infinite one times the low half of a probability, which is
 // zero or negative as often as not, is NaN where the probability times the value is infinite.  And scores are below 2^24 in
@@ -464,193 +387,21 @@ __global__ __launch_bounds__(64 * NQ * NK, D == 64 ? 4 : 2) void attention_tiles
     }
 }
 
-constexpr int kWholeTiles = 5;
-
-// Sequences whose keys and values all fit into LDS: one workgroup per sequence and head, a wavefront per query group of 32 (the longest
-// groups first; a fifth group is short and falls to the last wavefront), no key groups and nothing to merge.  All loads are
-// asked for at the start, tile by tile, and a tile is worked on as soon as it is there.
-// What it saves: with a workgroup per 64 queries, 16 x 148 x 148 with 32 heads is three rounds of workgroups that each fetch the keys
-// before their block again; without the loads, reads and softmax of its loop that took 22.8 of 24.4 us, so it was the rounds' starts and ends.
-// Here the 77 MB that go in and out bound it (13 us at the rate of a large copy).  us, replayed from a graph, 32 heads of 128, the kernel above
-// in brackets: 16 x 148 21.6 (24.2), 16 x 100 15.8 (16.7), 16 x 65 11.4 (14.1), 16 x 70 x 150 17.4 (20.5), 8 x 148 13.2 (14.8), 6 x 148 11.9 (12.6).
-// Even and odd tiles go to two sums, which are merged as attend merges its two key groups: the same bits (one sum instead: 16 x 148 20.2, but
-// other roundings).  Two sums of heads of 64 do not fit the registers that four wavefronts per SIMD leave.  No gain: eight wavefronts and 320 keys
-// with a compute unit each (16 x 276 49.3 (45.3), 4 x 276 19.7 (15.9)), every other workgroup's wavefronts the other way about.  (attend's own text
-// stays as it is: taking a tile through Sofar there made heads of 64 2 to 4 % slower.)
-__global__ __launch_bounds__(256, 2) void attention_whole_kernel(const __half *__restrict__ Q, int64_t ldq,
-                                                              const __half *__restrict__ Kc, int64_t ldk,
-                                                              const __half *__restrict__ V, int64_t ldv, int Sq, int Sk,
-                                                              __half *__restrict__ O, int64_t ldo)
-{
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];   // keys, then values
-    constexpr int D = 128, W = 4, T = kWholeTiles, NP = D / 16, CT = D / 32, ROW = 2 * D, PIECES = D / 8, TILE = 32 * ROW, VALUES = T * TILE;
-    constexpr int RPI = 1024 / ROW, L = 32 / RPI / W;                 // rows and loads per wavefront and tile
-    static_assert(L * RPI * W == 32, "every wavefront asks for the same number of pieces");
-    const int l = threadIdx.x & 63, c = l & 31, h = l >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    Q += (int64_t)blockIdx.z * Sq * ldq + (int64_t)blockIdx.x * D;
-    Kc += (int64_t)blockIdx.z * Sk * ldk + (int64_t)blockIdx.x * D;
-    V += (int64_t)blockIdx.z * Sk * ldv + (int64_t)blockIdx.x * D;
-    O += (int64_t)blockIdx.z * Sq * ldo + (int64_t)blockIdx.x * D;
-    const int shift = Sk - Sq, groups = (Sq + 31) / 32;
-    const float scale = 1.4426950408889634f / sqrtf((float)D);
-
-    v8h qf[NP];
-    auto load_queries = [&](int my_q) __attribute__((always_inline)) {
-#pragma unroll
-        for (int m = 0; m < NP; ++m) qf[m] = *reinterpret_cast<const v8h *>(Q + (int64_t)max(min(my_q, Sq - 1), 0) * ldq + 16 * m + 8 * h);
-    };
-    load_queries((groups - 1 - wave) * 32 + c);
-    asm volatile("" ::: "memory");                                    // (ahead of the tiles: the waits below count)
-    // rows past the end repeat the last one
-    const int lr = l / PIECES, lp = ((l % PIECES) ^ swizzle<D>(wave * RPI + lr)) * 8;
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-#pragma unroll
-        for (int i = 0; i < L; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) v4i *)(Kc + (int64_t)min(t * 32 + (wave + i * W) * RPI + lr, Sk - 1) * ldk + lp),
-                                             (__attribute__((address_space(3))) void *)(lds + t * TILE + (wave + i * W) * 1024), 16, 0, 0);
-#pragma unroll
-        for (int i = 0; i < L; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) v4i *)(V + (int64_t)min(t * 32 + (wave + i * W) * RPI + lr, Sk - 1) * ldv + lp),
-                                             (__attribute__((address_space(3))) void *)(lds + VALUES + t * TILE + (wave + i * W) * 1024), 16, 0, 0);
-    }
-    const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)lds;
-    // (a lane's key pieces lie at one offset with another bit or two turned, and so do its value pieces; values: as in attend)
-    const int lane_k = c * ROW + ((h ^ swizzle<D>(c)) << 4);
-    const int vr = 4 * h + ((l & 15) >> 2), lane_v = vr * ROW + (((2 * ((l >> 4) & 1) + ((l & 3) >> 1)) ^ swizzle<D>(vr)) << 4) + ((l & 1) << 3);
-
-    auto tile = [&](auto &done, int t, int q0) __attribute__((always_inline)) {
-        v8h kf[NP];
-        const int key_at = t * TILE + lane_k;
-#pragma unroll
-        for (int m = 0; m < NP; ++m) kf[m] = *reinterpret_cast<const v8h *>(lds + (key_at ^ (m << 5)));
-        __builtin_amdgcn_sched_barrier(0);                            // (all of them in flight before the first product)
-        v16f st;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) st[i] = 0.f;
-#pragma unroll
-        for (int m = 0; m < NP; ++m) st = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[m], qf[m], st, 0, 0, 0);
-        auto read = [&](v8h (&va)[2][CT]) __attribute__((always_inline)) {
-            unsigned at[2 * CT];
-#pragma unroll
-            for (int i = 0; i < 2 * CT; ++i) at[i] = (unsigned)lane_v ^ (i >> 1 << 6 | ((i & 1) ? 8 * ROW | 32 : 0));
-            read_values<D>(lds_base + VALUES + t * TILE, at, va);
-        };
-        done.add(st, read, 32 * t, q0 + c + shift - 4 * h, 32 * t + 31 > q0 + shift, scale);
-    };
-    auto both_halves = [](float sum) {
-        const auto lo = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
-        return __uint_as_float(lo[0]) + __uint_as_float(lo[1]);
-    };
-    // this lane's 16 CT outputs as pairs of halves; whether one of them is not finite
-    auto outputs = [&](auto value, float inv, unsigned (&w)[CT][8]) __attribute__((always_inline)) {
-        float zero[4] = {};                                           // NaN with the first output that is not finite
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int i = 0; i < 16; i += 2) {
-                union { __half2 v; unsigned u; } pk;
-                pk.v = __floats2half2_rn(value(ct, i) * inv, value(ct, i + 1) * inv);
-                w[ct][i >> 1] = pk.u;
-                zero[(i >> 1) & 3] = __builtin_amdgcn_fdot2(__builtin_bit_cast(v2h, pk.u), v2h{0, 0}, zero[(i >> 1) & 3], false);
-            }
-        return (zero[0] + zero[1]) + (zero[2] + zero[3]) != 0.f;
-    };
-
-    for (int round = 0; round < 2; ++round) {
-        const int g = groups - 1 - (round == 0 ? wave : 7 - wave), q0 = 32 * g, my_q = q0 + c;
-        const int n = g < 0 ? 0 : (min(q0 + 31, Sq - 1) + shift) / 32 + 1;      // tiles of which the group sees keys
-        if (round == 1) {
-            if (g < 0) break;
-            load_queries(my_q);
-        }
-        Sofar<D, true> done[2];                                       // of the even tiles and of the odd ones, as attend's two key groups
-        auto turn = [&](Sofar<D, true> &of, int t) __attribute__((always_inline)) {
-            if (round == 0) {
-                switch (T - 1 - t) {                                  // this wavefront's part of the tile has landed
-                case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
-                case 1: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * L) : "memory"); break;
-                case 2: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * L) : "memory"); break;
-                case 3: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(6 * L) : "memory"); break;
-                default: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * L) : "memory"); break;       // (T - 1 = 4)
-                }
-                lds_barrier();                                        // everybody's has
-            }
-            if (t < n) tile(of, t, q0);
-        };
-        const int turns = round == 0 ? T : n;
-        for (int t = 0; t < turns; t += 2) {
-            turn(done[0], t);
-            if (t + 1 < turns) turn(done[1], t + 1);
-        }
-        if (g < 0) continue;
-        // the same operations as in attend's merge: the same bits
-        const float m = fmaxf(done[0].m, done[1].m);
-        const float f[2] = {done[0].factor(done[0].m - m), done[1].m == -INFINITY ? 0.f : done[1].factor(done[1].m - m)};
-        const float sum = both_halves(done[0].sum) * f[0] + both_halves(done[1].sum) * f[1];
-        auto merged = [&](int ct, int i) __attribute__((always_inline)) {
-            const int own = ct / (CT / 2);
-            return fmaf(done[1 - own].ot[ct][i], f[1 - own], done[own].ot[ct][i] * f[own]);
-        };
-        unsigned w[CT][8];
-        if (__any(outputs(merged, sum >= 0.5f ? 1.0f / sum : NAN, w) && my_q < Sq)) {
-            // again with one half per probability, see attend; zeros for the values past the last key (whoever reads them meanwhile
-            // takes them times zero)
-            for (int at = Sk * PIECES + l; at < T * 32 * PIECES; at += 64)
-                *reinterpret_cast<uint4 *>(lds + VALUES + 16 * at) = make_uint4(0u, 0u, 0u, 0u);
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-            Sofar<D, false> again;
-            for (int t = 0; t < n; ++t) tile(again, t, q0);
-            unsigned w1[CT][8];
-            outputs([&](int ct, int i) __attribute__((always_inline)) { return again.ot[ct][i]; }, 1.0f / both_halves(again.sum), w1);
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) w[ct][i] = where_not_finite(w[ct][i], w1[ct][i]);
-        }
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            // four consecutive columns per register quad; two quads make 16 bytes once the lane halves have exchanged
-#pragma unroll
-            for (int k = 0; k < 4; k += 2) {
-                const auto a = __builtin_amdgcn_permlane32_swap(w[ct][2 * k], w[ct][2 * k + 2], false, false);
-                const auto b = __builtin_amdgcn_permlane32_swap(w[ct][2 * k + 1], w[ct][2 * k + 3], false, false);
-                if (my_q < Sq) *reinterpret_cast<uint4 *>(O + (int64_t)my_q * ldo + 32 * ct + 8 * k + 8 * h) = make_uint4(a[0], b[0], a[1], b[1]);
-            }
-        }
-    }
-}
-
-// more than 48 KiB of LDS has to be asked for, once per device
-template <auto KERNEL>
-static hipError_t allow_lds(int bytes)
-{
-    static std::atomic<bool> allowed[kMaxDeviceSlots];
-    const int slot = device_slot();
-    if (allowed[slot].load(std::memory_order_acquire)) return hipSuccess;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess) allowed[slot].store(true, std::memory_order_release);
-    return e;
-}
-
-static sqap_status launch_whole(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
-                                int batch, int Sq, int Sk, int H, __half *O, int64_t ldo, hipStream_t st)
-{
-    constexpr int bytes = 2 * kWholeTiles * 32 * 2 * 128;
-    SQAP_HIP_CHECK(allow_lds<attention_whole_kernel>(bytes));
-    hipLaunchKernelGGL(attention_whole_kernel, dim3(H, 1, batch), dim3(256), bytes, st, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, O, ldo);
-    SQAP_HIP_CHECK(hipGetLastError());
-    return SQAP_OK;
-}
-
 template <int D, int NQ, int NK, bool ROUNDS = false>
 static sqap_status launch_tiles(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
                                 int batch, int Sq, int Sk, int H, __half *O, int64_t ldo, hipStream_t st, int round = 0)
 {
     constexpr int bytes = attention_lds_bytes<D, NQ, NK>();
     static_assert(bytes <= 160 * 1024, "LDS of a compute unit");
-    if constexpr (bytes > 48 * 1024) SQAP_HIP_CHECK((allow_lds<attention_tiles_kernel<D, NQ, NK, ROUNDS>>(bytes)));
+    if constexpr (bytes > 48 * 1024) {
+        static std::atomic<bool> allowed[kMaxDeviceSlots];
+        const int slot = device_slot();
+        if (!allowed[slot].load(std::memory_order_acquire)) {
+            SQAP_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&attention_tiles_kernel<D, NQ, NK, ROUNDS>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+            allowed[slot].store(true, std::memory_order_release);
+        }
+    }
     hipLaunchKernelGGL((attention_tiles_kernel<D, NQ, NK, ROUNDS>), dim3(H, (Sq + 32 * NQ - 1) / (32 * NQ), batch), dim3(64 * NQ * NK), bytes, st,
                        Q, ldq, Kc, ldk, V, ldv, Sq, Sk, O, ldo, round);
     SQAP_HIP_CHECK(hipGetLastError());
@@ -670,18 +421,9 @@ static sqap_status launch_tiles(const __half *Q, int64_t ldq, const __half *Kc, 
 sqap_status launch_attention_tiles(const __half *Q, int64_t ldq, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
                                    int batch, int Sq, int Sk, int H, int d, __half *O, int64_t ldo, hipStream_t st)
 {
-    const int cus = device_cu_count();
     if (d == 64) return launch_tiles<64, 2, 2>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
-    // Where blocks of 64 queries would not all find room at once (two per compute unit) and five tiles hold all keys: a workgroup
-    // per sequence and head.  Below that the blocks are the better split (32 heads, us, by blocks / by sequences: 4 x 148 9.4 / 10.0, 1 x 148
-    // 6.6 / 9.4, 8 x 97 8.8 / 9.0), and where the blocks' last round is nearly full and the sequences' is not (10 x 148 16.9 / 17.5, but
-    // 9 x 148 16.8 / 16.0, 11 x 148 18.3 / 18.2, 20 x 148 29.9 / 29.2); figures above it are at the kernel.
-    const int64_t sequences = (int64_t)batch * H, blocks = sequences * ((Sq + 63) / 64), room = 2 * (int64_t)cus;
-    const bool blocks_fill = (blocks - 1) % room >= room * 7 / 8 - 1 && sequences > cus && (sequences - 1) % room < room * 3 / 4;
-    if (Sk <= 32 * kWholeTiles && blocks > room && !blocks_fill)
-        return launch_whole(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
     const int64_t groups = (int64_t)batch * H * ((Sq + 31) / 32);
-    if (groups <= cus && Sk >= 192)
+    if (groups <= device_cu_count() && Sk >= 192)
         return launch_tiles<128, 1, 4>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st);
     // Later query blocks see more keys.  Where more blocks come than compute units have room for, the longest go first.  Where all
     // find room at once, one or two per compute unit, their order says which share a unit: the first round of them goes from short to
@@ -689,6 +431,7 @@ sqap_status launch_attention_tiles(const __half *Q, int64_t ldq, const __half *K
     // themselves.  32 heads unless said, us, both rounds from long to short in brackets: 1024 x 2048 46.6 (48.1), 1024 x 1024 21.8 (23.2),
     // 700 x 1500 28.8 (31.2), 600 x 600 13.5 (14.3), 900 x 900, 24 heads 17.7 (19.3).  Heads of 64, four blocks per unit: no gain (520 x
     // 1024 14.0 (13.5), 700 x 1200 16.0 (16.3)).
+    const int cus = device_cu_count();
     const int64_t all = (int64_t)H * ((Sq + 63) / 64);
     if (batch == 1 && H <= cus && all > cus && all <= 2 * (int64_t)cus)
         return launch_tiles<128, 2, 2, true>(Q, ldq, Kc, ldk, V, ldv, batch, Sq, Sk, H, O, ldo, st, cus / H);

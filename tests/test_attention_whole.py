@@ -1,11 +1,11 @@
-"""Attention with a workgroup per sequence and head (five tiles of 32 keys hold all of them, and there are more sequences than blocks of 64
-queries would find room for at once): edges of query groups and key tiles, a fifth query group, fewer queries than keys, infinite values, huge scores."""
+"""Attention over batches of short whole sequences, more than the device has room for at once: edges of query groups and key tiles, fewer queries
+than keys, infinite values, huge scores."""
 import pytest
 
 from tests import test_gpu_glue as glue
 
 pytestmark = pytest.mark.gpu
-# batch, queries, keys, heads, head size: more than two blocks per compute unit, for 256 of them
+# batch, queries, keys, heads, head size: more than two blocks of 64 queries per compute unit, for 256 of them
 SHAPES = [(17, 1, 160, 32, 128), (17, 33, 33, 32, 128), (9, 65, 65, 32, 128), (9, 96, 97, 32, 128), (9, 97, 128, 32, 128), (7, 128, 129, 40, 128),
           (6, 129, 129, 32, 128), (6, 148, 148, 32, 128), (5, 160, 160, 40, 128), (300, 64, 160, 2, 128), (520, 20, 31, 1, 128)]
 
@@ -28,7 +28,7 @@ def test_huge_scores(batch, Sq, Sk, H, d):
 
 @pytest.mark.parametrize("Sq,Sk", [(148, 148), (65, 97), (160, 160), (129, 130)])
 def test_the_bits_of_single_calls(Sq, Sk):
-    """A sequence of a batch gets what it gets alone, from the kernel with a workgroup per block of queries."""
+    """A sequence of a batch gets what it gets alone, to the bit."""
     import torch
     from paper_2509_09090_amd import binding as B
     g = torch.Generator().manual_seed(Sq + Sk)
