@@ -118,7 +118,8 @@ __device__ __forceinline__ void read_values(unsigned at, const unsigned (&lane_v
 // a probability overflows.  Where an assumption fails outputs are not finite, and the result is true (for a lane of them).  Not FIRST:
 // one half per probability, rounded products, and zeros for the values past the last key, for which neither matters; no
 // probability of a key that is seen, and no factor, is zero there, so that an infinite value stays one however small its weight
-// (probabilities are 2^9 times as large: the smallest half adds 2^-33 of the largest).
+// (probabilities are 2^9 times as large: the smallest half adds 2^-33 of the largest).  In a tile of which some query does not see every
+// key, values that are not finite take no part in the products, where they would be NaN times that query's zero (add_not_finite).
 template <int D, int NQ, int NK, bool FIRST>
 __device__ __forceinline__ bool attend(uint8_t *lds, int l, int wave, int qblock, const __half *__restrict__ Q, int64_t ldq,
                                         const __half *__restrict__ Kc, int64_t ldk, const __half *__restrict__ V, int64_t ldv,
@@ -227,6 +228,18 @@ __device__ __forceinline__ bool attend(uint8_t *lds, int l, int wave, int qblock
 #pragma unroll
             for (int i = 0; i < 16; ++i)
                 if (k0 + 8 * (i >> 2) + 4 * h + (i & 3) > my_q + shift) st[i] = -INFINITY;
+            if (!FIRST) {
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) {
+                        union { v8h v; unsigned u[4]; } x;
+                        x.v = va[n][ct];
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) x.u[p] = where_not_finite(x.u[p], 0u);
+                        va[n][ct] = x.v;
+                    }
+            }
         }
         float tmax = st[0];
 #pragma unroll
@@ -336,6 +349,39 @@ __device__ __forceinline__ bool attend(uint8_t *lds, int l, int wave, int qblock
     return my_q < Sq && (zero[0] + zero[1]) + (zero[2] + zero[3]) != 0.f;
 }
 
+// The infinities and NaN that attend<.., false> leaves out, to the outputs of the queries that see them: values at keys `from` .. `to`, of which
+// this lane's query (its row Q) sees those up to `sees`.  V: this wavefront's columns.  A key whose score is -infinity has no weight: NaN.
+template <int D, int OWN>
+__device__ __forceinline__ void add_not_finite(unsigned (&w)[OWN][8], const __half *Q, const __half *Kc, int64_t ldk, const __half *V, int64_t ldv,
+                                            int from, int to, int sees, int h)
+{
+    for (int key = from; key <= to; ++key) {
+        unsigned x[OWN * 8];
+        bool any = false;
+#pragma unroll
+        for (int i = 0; i < OWN * 4; ++i) {                           // columns 8 i + 4 h ..: register quad i % 4 of column tile i / 4
+            const uint2 four = *reinterpret_cast<const uint2 *>(V + key * ldv + 8 * i + 4 * h);
+            x[2 * i] = four.x;
+            x[2 * i + 1] = four.y;
+            any = any || where_not_finite(four.x, 0u) != four.x || where_not_finite(four.y, 0u) != four.y;
+        }
+        if (!any || key > sees) continue;
+        float score = 0.f;
+        for (int i = 0; i < D; ++i) score = fmaf(__half2float(Q[i]), __half2float(Kc[key * ldk + i]), score);
+        const float weight = score == -INFINITY ? 0.f : 1.f;
+#pragma unroll
+        for (int i = 0; i < OWN * 8; ++i) {
+            union { unsigned u; _Float16 f[2]; } value, out;
+            value.u = x[i];
+            out.u = w[i >> 3][i & 7];
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                if (!(fabsf((float)value.f[e]) < INFINITY)) out.f[e] = (_Float16)((float)out.f[e] + (float)value.f[e] * weight);
+            w[i >> 3][i & 7] = out.u;
+        }
+    }
+}
+
 template <int D, int NQ, int NK, bool ROUNDS>
 __global__ __launch_bounds__(64 * NQ * NK, D == 64 ? 4 : 2) void attention_tiles_kernel(const __half *__restrict__ Q, int64_t ldq,
                                                               const __half *__restrict__ Kc, int64_t ldk,
@@ -368,6 +414,10 @@ __global__ __launch_bounds__(64 * NQ * NK, D == 64 ? 4 : 2) void attention_tiles
         lds_barrier();                                                // everybody has read it: the tiles come back
         unsigned w1[OWN][8];
         attend<D, NQ, NK, false>(lds, l1, wave, qblock, Q, ldq, Kc, ldk, V, ldv, Sq, Sk, w1);
+        const int q0 = (qblock * NQ + wave % NQ) * 32, q = q0 + (l1 & 31), shift = Sk - Sq;
+        add_not_finite<D, OWN>(w1, Q + (int64_t)min(q, Sq - 1) * ldq, Kc, ldk, V + 32 * (wave / NQ) * OWN, ldv, (q0 + shift + 1) / 32 * 32,
+                               min(q0 + 31, Sq - 1) + shift, q < Sq ? q + shift : -1, l1 >> 5);
+        lds_barrier();                                                // (before anybody stores over queries that others read there)
 #pragma unroll
         for (int t = 0; t < OWN; ++t)
 #pragma unroll

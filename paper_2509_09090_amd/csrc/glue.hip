@@ -6,7 +6,6 @@
 // head sizes take binary32 FMAs over LDS tiles with an online softmax, here.
 #include <algorithm>
 
-#include <algorithm>
 #include "common.h"
 #include "quant_math.h"
 #include "decode_attn.h"
@@ -324,7 +323,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const __half *__restrict
         __syncthreads();                                                        // ps complete
 #pragma unroll
         for (int c = 0; c < CPT; ++c) o[c] *= rescale;
-        const int kmax = min(kAttK, Sk - k0);
+        const int kmax = min(min(kAttK, Sk - k0), my_q + shift - k0 + 1);      // (no infinite value times the zero of a query that does not see it)
         for (int j = 0; j < kmax; ++j) {
             const float pj = ps[qi * (kAttK + 1) + j];
             const __half *vrow = vs + j * PITCH + sub * CPT;
