@@ -182,17 +182,15 @@ PyObject *call(const Calls *c, Py_ssize_t n, Py_ssize_t want, Body body)
     return nullptr;
 }
 
-struct Unlocked {
-    PyThreadState *state;
-    Unlocked() : state(PyEval_SaveThread()) {}
-    ~Unlocked() { PyEval_RestoreThread(state); }
-};
-// (the arguments are evaluated before the lock is given up)
+// (The arguments are evaluated before the lock is given up.  It is taken again outside of any destructor: where the interpreter has ended
+// meanwhile, as for a daemon thread, that ends the thread by unwinding its stack, which a destructor would turn into an abort.)
 template <class F, class... A>
 long run(F f, A... a)
 {
-    const Unlocked unlocked;
-    return f(a...);
+    PyThreadState *const state = PyEval_SaveThread();
+    const long status = f(a...);
+    PyEval_RestoreThread(state);
+    return status;
 }
 
 #define SQAP_METHOD(NAME, N, BODY)                                                       \

@@ -151,6 +151,32 @@ def test_current_stream_is_asked_for_until_one_device_is_known(recorded, monkeyp
     assert B._native.one_device is False
 
 
+def test_a_call_that_outlasts_the_interpreter():
+    """A daemon thread still in a call when the program ends: the program ends as ever, without an abort."""
+    import os
+    import subprocess
+    import sys
+    program = """
+import ctypes, sys, threading, time
+from paper_2509_09090_amd import binding as B
+B.lib()
+from paper_2509_09090_amd import _calls
+libc = ctypes.CDLL(None)
+sleep = ctypes.cast(libc.usleep, ctypes.c_void_p).value
+calls = _calls.Calls(lambda name: sleep, lambda: 0, B._check)          # (the handle is how long)
+threading.Thread(target=calls.group_run, args=(ctypes.c_void_p(900000), 0), daemon=True).start()
+time.sleep(0.2)
+class Late:
+    def __del__(self):
+        libc.usleep(1500000)                                           # without the interpreter's lock, while it ends
+sys.modules["late"] = Late()
+print("done", flush=True)
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", program], cwd=root, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout == "done\n", (r.returncode, r.stderr)
+
+
 @pytest.mark.gpu
 def test_native_calls_follow_the_current_stream():
     x, u8, s1 = (_half(6, 64).cuda(), torch.zeros(6, 32, dtype=torch.uint8, device="cuda"), _half(6).cuda())
