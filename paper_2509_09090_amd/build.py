@@ -13,6 +13,7 @@ SOURCES = sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(HERE, "csrc", "*.h"))) + [os.path.join(ROOT, "include", "sqap.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "/opt/rocm/bin/amdclang++")       # comes with hipcc
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt",
@@ -27,7 +28,18 @@ def _older(built, sources):
 
 
 def is_stale():
-    return _older(LIB, SOURCES + HEADERS) or _older(CALLS, [CALLS_SOURCE] + HEADERS)
+    return _older(LIB, SOURCES + HEADERS) or _older(CALLS, [CALLS_SOURCE] + HEADERS) or not _built_for_this_torch()
+
+
+def _torch_mark():
+    import torch
+    return "sqap: built for torch " + torch.__version__
+
+
+def _built_for_this_torch():
+    """_calls.so holds torch's internal layouts, of the version that its mark names."""
+    with open(CALLS, "rb") as f:
+        return _torch_mark().encode() + b"\0" in f.read()
 
 
 def _calls_command():
@@ -35,8 +47,8 @@ def _calls_command():
     import torch
     at = os.path.dirname(torch.__file__)
     include = [os.path.join(at, "include"), os.path.join(at, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include"]
-    return ([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    return ([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DSQAP_TORCH_MARK="%s"' % _torch_mark()]
             + [f for i in include for f in ("-isystem", i)]
             + ["-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), CALLS_SOURCE, "-o", CALLS,
                "-L" + os.path.join(at, "lib"), "-lc10", "-lc10_hip", "-ltorch_python", "-ltorch_cpu"])
@@ -46,9 +58,8 @@ def build(force=True, verbose=False):
     """Compile every kernel for gfx950.  Returns the library path."""
     if not force and not is_stale():
         return LIB
-    calls = subprocess.Popen(_calls_command())
+    procs = [(CALLS_SOURCE, subprocess.Popen(_calls_command()))]
     objs = []
-    procs = []
     for src in SOURCES:
         obj = src[:-4] + ".o"
         cmd = [HIPCC] + [f for f in FLAGS if f != "-shared"] + ["-c", src, "-o", obj]
@@ -56,15 +67,13 @@ def build(force=True, verbose=False):
             print(" ".join(cmd))
         procs.append((src, subprocess.Popen(cmd)))
         objs.append(obj)
-    for src, pr in procs:
-        if pr.wait() != 0:
-            raise RuntimeError("hipcc failed on " + src)
+    failed = [src for src, pr in procs if pr.wait() != 0]          # (all of them are waited for)
+    if failed:
+        raise RuntimeError("the compiler failed on " + ", ".join(failed))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
     for o in objs:
         os.remove(o)
-    if calls.wait() != 0:
-        raise RuntimeError("the compiler failed on " + CALLS_SOURCE)
     return LIB
 
 

@@ -325,6 +325,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, nullptr, nul
 
 PyMODINIT_FUNC PyInit__calls()
 {
+    static const char *const volatile mark = SQAP_TORCH_MARK;       // (which torch's headers these were: build.py looks for it)
+    (void)mark;
     calls_type.tp_name = "_calls.Calls";
     calls_type.tp_basicsize = sizeof(Calls);
     calls_type.tp_flags = Py_TPFLAGS_DEFAULT;
