@@ -82,8 +82,8 @@ constexpr int kStepMaxK = kStepThreads * 8 * kStepGpt;
 constexpr int kStepMaxHidden = 4096;       // the residual row in LDS; a tagged row and the gains side by side
 constexpr int kStepTagsPerLayer = 5;       // q|k|v, attention, o, h, down
 constexpr int kStepWarmKeys = 2048;         // cached keys whose rows are pulled into the L2 cache before the attention
-// Words from one workgroup's progress flag to the next: 16 bytes apart.  Flags that share a line hold each other up (7B shape, 148 positions, us per
-// token: 2 bytes apart 1356, 4 bytes 1288, 8 bytes 1254, 16 bytes 1243), and every line more is one more to poll (32 bytes 1249, 128 bytes 1263).
+// Words of 8 bytes from one workgroup's progress flag to the next: 16 bytes apart.  Flags that share a line hold each other up, and every line more is
+// one more to poll (7B shape, 148 positions, us per token: 8 bytes apart 1231, 16 and 32 bytes 1222, 128 bytes 1235).
 constexpr int kStepFlagPitch = 2, kStepFlagsAt = 16;      // (the first flag behind the generation, the error word and the count, in a line of its own)
 constexpr long long kStepPollLimit = 200000;      // polls, or repeated reads of a row, before a wait gives up (a few tenths of a second)
 

@@ -18,7 +18,7 @@ struct Reciprocal {
 };
 __device__ __forceinline__ float quotient(float v, const Reciprocal &r) { return fmaf(v, r.hi, v * r.lo); }
 
-// clamp(rint(q), -8, 7) as a 4-bit two's complement code.  Clamping first gives the same integer (both
+// clamp(rint(q), -8, 7) as a 4-bit two's complement code, the low bits of the result.  Clamping first gives the same integer (both
 // bounds are integers and rounding is monotone), and adding 1.5 * 2^23 rounds a value of that size to
 // the nearest integer, ties to even like rint, and leaves it in the low mantissa bits: one addition
 // instead of a rounding and a conversion.  A NaN quotient clamps to -8 either way.
@@ -27,7 +27,6 @@ __device__ __forceinline__ uint32_t code_bits(float q)       // the code in two'
     return __float_as_uint(__builtin_amdgcn_fmed3f(q, -8.f, 7.f) + 12582912.0f);
 }
 constexpr uint32_t kCodeBias = 0x4b400000u;                   // the bits of 1.5 * 2^23
-__device__ __forceinline__ uint32_t code4(float q) { return code_bits(q) & 15u; }
 
 // Eight codes in a word, the first in the low bits.  Shifted and added as they come, one instruction each, they and their biases make one
 // sum modulo 2^32; raised by 8 every code is a digit of 0 .. 15 and nothing carries, and the digit's top bit is the code's turned over.

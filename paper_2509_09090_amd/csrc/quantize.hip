@@ -311,10 +311,8 @@ __device__ __forceinline__ void load_col_scales(const __half *col_scales, int g,
 //   scale = half(max|v| / 7), 2^-24 if that is zero;  code = clamp(rint(v / scale), -8, 7)
 // GPT = groups per thread the instance is compiled for (registers, hence occupancy).
 // PRE selects an operation applied to the row between its read and the quantizer (see above).
-// Six groups per thread are held to the 128 registers that four wavefronts per SIMD leave: the norm takes 129 otherwise, and
-// 1000 rotated rows of 8704, four per compute unit, then take two rounds (21.4 us, 19.7 in one).
 template <bool ROTATE, int T, int GPT, int MODE, int PRE>
-__global__ __launch_bounds__(T, GPT == 6 ? 4 : T / 256) void quantize_rows_kernel(const __half *X, int64_t ldx,      // may alias pre.xsum_out
+__global__ __launch_bounds__(T, T / 256) void quantize_rows_kernel(const __half *X, int64_t ldx,      // may alias pre.xsum_out
                                                             const int32_t *__restrict__ rows, int K,
                                                             const __half *__restrict__ col_scales,
                                                             uint8_t *__restrict__ Xq,
@@ -556,11 +554,12 @@ static sqap_status launch_quantize_inst(const __half *X, int64_t ldx, const int3
 // with 512 and 7.9 with 256; 512 rows 10.2, 10.7 and 12.1; plain 84 rows 3.4 against 3.7 and 5.0).  With more rows 512 for SwiGLU (2368 x
 // 11008 29.5 us, 31.1 with 256, 30.9 with 1024; norm, gate|up, SwiGLU and down in a row 284.2, 287.2 and 284.7), else 256.  Rows of 513
 // to 1024 groups keep 512 (norm to down at 1100 x 5504 68.6 us, 69.9 with 256 and 69.6 with 1024).
-// The norm's scalar part is repeated by every wavefront, so there fewer are better as soon as rows share compute units (us):
-// up to 512 groups (2368 x 4096 17.2 against 19.8 with 512 threads; 84 x 4096 4.5 against 4.1), above 1024 groups (257 x 8704
-// 6.2 against 9.4 with 1024, 512 x 11008 8.9 against 11.5; 200 x 11008 7.6 against 6.6), and between from two rows per compute unit on
-// (2000 x 5504 13.7 against 16.0 with 512, 513 x 8192 7.2 and 7.7; 355 x 5504 6.0 and 5.9); rotated rows only up to 768
-// groups there (2000 x 4608 21.2 against 23.2, 2000 x 6144 28.1 and 29.6; 513 x 8192 18.9 against 16.9).
+// The norm's scalar part is repeated by every wavefront, so there fewer are better once rows share compute units (us, with the residual, from a
+// graph over four inputs; more threads, then fewer): up to 512 groups from more than one row per unit on (256 x 4096 3.30, 3.45; 400 x 4096
+// 4.65, 4.50; 2368 x 4096 13.7, 12.6), above 1024 groups likewise (256 x 11008 6.35, 6.79; 257 x 8704 6.83, 6.57; 400 x 11008 9.2, 9.4, 512 x 11008
+// 9.7, 10.2 the other way), and between from two rows per unit on (2000 x 5504 14.6, 14.4; 355 x 5504 5.4, 5.5; 1000 x 5504 9.2, 9.5 and
+// 513 x 8192 8.1, 8.6 the other way); rotated rows only up to 768 groups there (2000 x 4608 20.1, 19.9; 2000 x 6144 26.3, 26.7; 513 x 8192
+// 16.8, 18.7).
 template <bool ROTATE, int MODE, int PRE>
 static sqap_status launch_quantize_gpt(const __half *X, int64_t ldx, const int32_t *rows, int M, int K,
                                        const __half *col_scales, uint8_t *Xq, __half *sx, const PreArgs &pre, hipStream_t st)
@@ -569,10 +568,9 @@ static sqap_status launch_quantize_gpt(const __half *X, int64_t ldx, const int32
 #define SQAP_Q(T, G) launch_quantize_inst<ROTATE, T, G, MODE, PRE>(X, ldx, rows, M, K, col_scales, Xq, sx, pre, st)
     if (groups > 1024) {
         if (M <= (PRE == kPreNorm ? cus : 2 * cus)) return SQAP_Q(1024, 2);
-        if constexpr (PRE == kPreSwiglu) {
-            if (groups <= 1536) return SQAP_Q(512, 3);
-        }
-        return groups <= 1536 ? SQAP_Q(256, 6) : SQAP_Q(256, 8);
+        if (groups > 1536) return SQAP_Q(256, 8);
+        if constexpr (PRE == kPreSwiglu) return SQAP_Q(512, 3);
+        else return SQAP_Q(256, 6);
     }
     if (groups > 512) {
         if constexpr (PRE == kPreNorm) {
